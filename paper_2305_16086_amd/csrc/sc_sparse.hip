@@ -480,7 +480,10 @@ Layout g_scratch_last[kMaxDevices];
 size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 
 // Carve the buffers of a run with W slots from base (null: only measure).
-// Returns the bytes used.
+// Returns the bytes used.  The columns (Q, S) come before every buffer whose size
+// depends on P, the largest wave's half-edges: two graphs with the same n, slot
+// count and W differ in P, and their columns must still be the same memory (the
+// record of the last run knows them to be zero by these three numbers only).
 size_t carve(unsigned char* base, int64_t n, int64_t S2, int W, int64_t P, SrcBufs* B) {
   size_t off = 0;
   auto take = [&](auto** p, size_t bytes) {
@@ -497,13 +500,13 @@ size_t carve(unsigned char* base, int64_t n, int64_t S2, int W, int64_t P, SrcBu
   take(&b.totals, sizeof(unsigned long long) * kTotals);
   take(&b.ctl, sizeof(int64_t) * 2);
   take(&b.slot_ctl, sizeof(int32_t) * 2 * W);
+  take(&b.Q, sizeof(uint64_t) * 2 * static_cast<size_t>(W) * n);
+  take(&b.S, sizeof(int32_t) * 2 * static_cast<size_t>(W) * n);
   take(&b.pos_slot, sizeof(int32_t) * std::max<int64_t>(P, 1));
   take(&b.pos_w, sizeof(int32_t) * std::max<int64_t>(P, 1));
   take(&b.nr_pos, sizeof(int64_t) * std::max<int64_t>(P, 1));
   take(&b.chunk_off, sizeof(int64_t) * (P + 1));
   take(&b.part, sizeof(double) * kStaticPartCapacity);
-  take(&b.Q, sizeof(uint64_t) * 2 * static_cast<size_t>(W) * n);
-  take(&b.S, sizeof(int32_t) * 2 * static_cast<size_t>(W) * n);
   b.part_capacity = kStaticPartCapacity;
   if (const char* c = std::getenv("SC_SOURCE_PART_CAPACITY"))   // smaller buffer (tests)
     b.part_capacity = std::max<int64_t>(1, std::min<int64_t>(kStaticPartCapacity, std::atoll(c)));
