@@ -10,8 +10,9 @@
 //
 // Network 16 -> 64 -> 64 -> 1 with silu activations.  Parameters are one flat
 // float vector: W1[64][16], b1[64], W2[64][64], b2[64], W3[64], b3.
-// Training (FP32): per-workgroup forward/backward on 64-sample tiles, partial
-// gradients reduced in a fixed order, Adam.  Inference: BF16 MFMA
+// Training (FP32): forward/backward of 16-sample tiles on the FP32 matrix
+// instruction (v_mfma_f32_16x16x4_f32), partial gradients reduced in a fixed
+// order by the kernel that also takes the Adam step.  Inference: BF16 MFMA
 // (gfx950's v_mfma_f32_16x16x32_bf16) with FP32 accumulation.
 #include "sc_internal.hpp"
 
@@ -208,140 +209,210 @@ __global__ __launch_bounds__(256) void k_norm_stats(const float* __restrict__ X,
 }
 
 // ------------------------------------------------------------------ training: forward + backward
-// One workgroup of 64 threads per tile of 64 samples (thread = sample).
-// grads: [tiles][kNParam] partial sums; lossp: [tiles] partial loss sums.
-__global__ __launch_bounds__(64) void k_mlp_train_tile(const float* __restrict__ theta,
-                                                       const float* __restrict__ norm,
-                                                       const float* __restrict__ X,
-                                                       const float* __restrict__ z,
-                                                       const float* __restrict__ w,
-                                                       const int64_t* __restrict__ idx,
-                                                       int64_t nbatch, float inv_count,
-                                                       float* __restrict__ grads,
-                                                       float* __restrict__ lossp) {
-  // weights are read with wave-uniform addresses straight from global memory
-  const float* __restrict__ P = theta;
-  __shared__ float sX[64][kIn + 1];
-  __shared__ float sH1[64][kHid + 1];
-  __shared__ float sD2[64][kHid + 1];
-  __shared__ float sD1[64][kHid + 1];
-  __shared__ float sdy[64];
-  __shared__ float sl[64];
-  const int t = threadIdx.x;
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 64 + t;
-  const bool live = i < nbatch;
-  const int64_t row = live ? idx[i] : 0;
-  float x[kIn];
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// One workgroup of four waves per tile of 16 samples (tiles b, b + gridDim.x, ...),
+// all five layer products on v_mfma_f32_16x16x4_f32 with the operand layout
+//   A (16 x 4, i,k): lane l supplies A[l%16][l/16]
+//   B (4 x 16, k,j): lane l supplies B[l/16][l%16]
+//   D (16 x 16):     lane l holds D[4*(l/16) .. +3][l%16]
+// Wave w owns hidden units 16w .. 16w+15: its columns of W1, W2 and W2^T stay in
+// registers, its rows of the weight gradients accumulate in MFMA registers over
+// the tiles, and activations cross waves through LDS (row stride 68 / 20 floats:
+// the 16 rows x 4 columns of an A operand fall on 64 different banks).
+//
+// A step of 4,096 samples is 130 MFLOP and is bound by the chain of dependent
+// phases, not by bytes or operations: 16-sample tiles give 256 workgroups, one per
+// CU, where a thread per sample (64 waves in all) left three quarters of the chip
+// idle and kept its 128 activations in scratch memory.
+// grads: [gridDim.x][kNParam] partial sums; lossp: [gridDim.x] partial loss sums.
+constexpr int kTile = 16;
+constexpr int kMaxTrainBlocks = 512;
+constexpr int kSH = 68, kSX = 20;   // LDS row strides
+
+__device__ inline f32x4_t mfma4(float a, float b, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+__global__ __launch_bounds__(256) void k_mlp_train_tile(const float* __restrict__ theta,
+                                                        const float* __restrict__ norm,
+                                                        const float* __restrict__ X,
+                                                        const float* __restrict__ z,
+                                                        const float* __restrict__ w,
+                                                        const int64_t* __restrict__ idx,
+                                                        int64_t nbatch, float inv_count,
+                                                        float* __restrict__ grads,
+                                                        float* __restrict__ lossp) {
+  __shared__ float sX[kTile][kSX];
+  __shared__ float sH1[kTile][kSH], sD2[kTile][kSH], sD1[kTile][kSH];
+  __shared__ float sY[kWavesPerBlock][kTile];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wv = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  const int u = 16 * wv + li;   // this lane's hidden unit (column of D)
+  float w1[4], w2[16], w2t[16];
 #pragma unroll
-  for (int f = 0; f < kIn; ++f) {
-    x[f] = live ? (X[row * kIn + f] - norm[f]) * norm[kIn + f] : 0.0f;
-    sX[t][f] = x[f];
-  }
-  __syncthreads();
-  // forward
-  float a1[kHid], a2[kHid];
-  for (int o = 0; o < kHid; ++o) {
-    float acc = P[oB1 + o];
+  for (int k = 0; k < 4; ++k) w1[k] = theta[oW1 + u * kIn + 4 * k + lk];
 #pragma unroll
-    for (int f = 0; f < kIn; ++f) acc += P[oW1 + o * kIn + f] * x[f];
-    a1[o] = acc;
-    sH1[t][o] = silu_f(acc);
+  for (int k = 0; k < 16; ++k) {
+    w2[k] = theta[oW2 + u * kHid + 4 * k + lk];
+    w2t[k] = theta[oW2 + (4 * k + lk) * kHid + u];
   }
-  float y = P[oB3];
-  for (int o = 0; o < kHid; ++o) {
-    float acc = P[oB2 + o];
-    for (int q = 0; q < kHid; ++q) acc += P[oW2 + o * kHid + q] * sH1[t][q];
-    a2[o] = acc;
-    y += P[oW3 + o] * silu_f(acc);
+  const float b1 = theta[oB1 + u], b2 = theta[oB2 + u], w3 = theta[oW3 + u], b3 = theta[oB3];
+  const float mean = norm[tid & 15], isd = norm[kIn + (tid & 15)];
+  const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4_t g1 = zero, g2[4] = {zero, zero, zero, zero};
+  float gb1 = 0.f, gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, loss = 0.f;
+  for (int64_t base = static_cast<int64_t>(blockIdx.x) * kTile; base < nbatch;
+       base += static_cast<int64_t>(gridDim.x) * kTile) {
+    {
+      // thread = (sample, feature)
+      const int64_t i = base + (tid >> 4);
+      float x = 0.f;
+      if (i < nbatch) x = (X[idx[i] * kIn + (tid & 15)] - mean) * isd;
+      sX[tid >> 4][tid & 15] = x;
+    }
+    // target and weight of the lane's four samples (rows 4 lk .. 4 lk + 3 of D)
+    float zt[4], wt[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t i = base + 4 * lk + r;
+      const int64_t row = i < nbatch ? idx[i] : 0;
+      zt[r] = i < nbatch ? z[row] : 0.f;
+      wt[r] = i < nbatch ? (w ? w[row] : 1.f) : 0.f;
+    }
+    __syncthreads();
+    // layer 1
+    f32x4_t a1 = {b1, b1, b1, b1};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) a1 = mfma4(sX[li][4 * k + lk], w1[k], a1);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sH1[4 * lk + r][u] = silu_f(a1[r]);
+    __syncthreads();
+    // layer 2 and the output
+    f32x4_t a2 = {b2, b2, b2, b2};
+#pragma unroll
+    for (int k = 0; k < 16; ++k) a2 = mfma4(sH1[li][4 * k + lk], w2[k], a2);
+    float h2[4], yp[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      h2[r] = silu_f(a2[r]);
+      yp[r] = w3 * h2[r];
+#pragma unroll
+      for (int off = 8; off >= 1; off >>= 1) yp[r] += __shfl_xor(yp[r], off, 64);
+    }
+    if (li == 0) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sY[wv][4 * lk + r] = yp[r];
+    }
+    __syncthreads();
+    // output error; layer 2 and 3 gradients of the lane's unit over its four samples
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int s = 4 * lk + r;
+      const float y = b3 + sY[0][s] + sY[1][s] + sY[2][s] + sY[3][s];
+      const float e = base + s < nbatch ? y - zt[r] : 0.f;
+      const float dy = 2.0f * wt[r] * e * inv_count;
+      const float d2 = dy * w3 * silu_grad_f(a2[r]);
+      sD2[s][u] = d2;
+      gb2 += d2;
+      gw3 += dy * h2[r];
+      gb3 += dy;
+      loss += wt[r] * e * e;
+    }
+    __syncthreads();
+    // dH1 = dA2 W2, dA1 = dH1 silu'(A1)
+    f32x4_t d1 = zero;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) d1 = mfma4(sD2[li][4 * k + lk], w2t[k], d1);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float v = d1[r] * silu_grad_f(a1[r]);
+      sD1[4 * lk + r][u] = v;
+      gb1 += v;
+    }
+    __syncthreads();
+    // weight gradients: rows = this wave's units, contraction over the 16 samples
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int s = 4 * k + lk;
+      const float ad2 = sD2[s][u];
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb) g2[nb] = mfma4(ad2, sH1[s][16 * nb + li], g2[nb]);
+      g1 = mfma4(sD1[s][u], sX[s][li], g1);
+    }
+    __syncthreads();   // the next tile overwrites sX and the activations
   }
-  const float wt = live ? (w ? w[row] : 1.0f) : 0.0f;
-  const float r = live ? y - z[row] : 0.0f;
-  sl[t] = wt * r * r;
-  const float dy = 2.0f * wt * r * inv_count;
-  sdy[t] = dy;
-  // backward through layer 3 and silu 2
-  for (int o = 0; o < kHid; ++o) sD2[t][o] = dy * P[oW3 + o] * silu_grad_f(a2[o]);
-  __syncthreads();
-  // dA1 = (W2^T dA2) * silu'(a1)
-  for (int q = 0; q < kHid; ++q) {
-    float acc = 0.0f;
-    for (int o = 0; o < kHid; ++o) acc += P[oW2 + o * kHid + q] * sD2[t][o];
-    sD1[t][q] = acc * silu_grad_f(a1[q]);
-  }
-  __syncthreads();
-  // weight gradients for this tile: thread t owns hidden unit t (fixed sample order)
   float* g = grads + static_cast<size_t>(blockIdx.x) * kNParam;
-  {
-    const int o = t;
-    float gb1 = 0.0f, gb2 = 0.0f;
-    float gw1[kIn];
 #pragma unroll
-    for (int f = 0; f < kIn; ++f) gw1[f] = 0.0f;
-    for (int s = 0; s < 64; ++s) {
-      const float d1 = sD1[s][o];
-      gb1 += d1;
+  for (int r = 0; r < 4; ++r) {
+    const int o = 16 * wv + 4 * lk + r;   // row of D
+    g[oW1 + o * kIn + li] = g1[r];
 #pragma unroll
-      for (int f = 0; f < kIn; ++f) gw1[f] += d1 * sX[s][f];
-      gb2 += sD2[s][o];
-    }
-#pragma unroll
-    for (int f = 0; f < kIn; ++f) g[oW1 + o * kIn + f] = gw1[f];
-    g[oB1 + o] = gb1;
-    g[oB2 + o] = gb2;
-    for (int q = 0; q < kHid; ++q) {
-      float acc = 0.0f;
-      for (int s = 0; s < 64; ++s) acc += sD2[s][o] * sH1[s][q];
-      g[oW2 + o * kHid + q] = acc;
-    }
+    for (int nb = 0; nb < 4; ++nb) g[oW2 + o * kHid + 16 * nb + li] = g2[nb][r];
   }
-  // layer-3 gradients need h2 = silu(a2) per sample: recompute into sD1 (no longer needed)
-  __syncthreads();
-  for (int o = 0; o < kHid; ++o) sD1[t][o] = silu_f(a2[o]);
-  __syncthreads();
-  {
-    float acc = 0.0f;
-    for (int s = 0; s < 64; ++s) acc += sdy[s] * sD1[s][t];
-    g[oW3 + t] = acc;
+#pragma unroll
+  for (int off = 16; off < 64; off <<= 1) {   // the four sample groups of a unit
+    gb1 += __shfl_xor(gb1, off, 64);
+    gb2 += __shfl_xor(gb2, off, 64);
+    gw3 += __shfl_xor(gw3, off, 64);
+    gb3 += __shfl_xor(gb3, off, 64);
+    loss += __shfl_xor(loss, off, 64);
   }
-  if (t == 0) {
-    float gb3 = 0.0f, ls = 0.0f;
-    for (int s = 0; s < 64; ++s) {
-      gb3 += sdy[s];
-      ls += sl[s];
-    }
+  if (lk == 0) {
+    g[oB1 + u] = gb1;
+    g[oB2 + u] = gb2;
+    g[oW3 + u] = gw3;
+  }
+  if (tid == 0) {
     g[oB3] = gb3;
-    lossp[blockIdx.x] = ls;
+    lossp[blockIdx.x] = loss;
   }
 }
 
-// grad[p] = sum over tiles in order; loss = sum of tile losses * inv_count
-__global__ void k_grad_reduce(const float* __restrict__ grads, int tiles,
-                              const float* __restrict__ lossp, float inv_count,
-                              float* __restrict__ grad, float* __restrict__ loss_out) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+// Parameters p0 .. p0 + 63 of the gradient: sixteen waves sum contiguous sixteenths
+// of the tiles' partial gradients, wave 0 adds the sixteen in order and, with theta,
+// takes the Adam step of those parameters (one launch for the reduction and the
+// step; the chain of loads per lane is blocks / 16).  loss = sum of the tile
+// losses * inv_count.
+constexpr int kReduceWaves = 16;
+
+__global__ __launch_bounds__(64 * kReduceWaves) void k_grad_reduce(
+    const float* __restrict__ grads, int blocks, const float* __restrict__ lossp, float inv_count,
+    float* __restrict__ grad, float* __restrict__ loss_out, float* __restrict__ theta,
+    float* __restrict__ m1, float* __restrict__ m2, AdamStep ad) {
+  __shared__ float s_part[kReduceWaves][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int p = blockIdx.x * 64 + lane;
+  const int per = (blocks + kReduceWaves - 1) / kReduceWaves;
+  const int t0 = wv * per, t1 = min(blocks, t0 + per);
+  float acc = 0.f;
   if (p < kNParam) {
-    float acc = 0.0f;
-    for (int b = 0; b < tiles; ++b) acc += grads[static_cast<size_t>(b) * kNParam + p];
-    grad[p] = acc;
+#pragma unroll 16
+    for (int t = t0; t < t1; ++t) acc += grads[static_cast<size_t>(t) * kNParam + p];
   }
-  if (p == 0 && loss_out) {
-    float l = 0.0f;
-    for (int b = 0; b < tiles; ++b) l += lossp[b];
-    *loss_out = l * inv_count;
+  s_part[wv][lane] = acc;
+  __syncthreads();
+  if (wv == 0 && p < kNParam) {
+    float g = s_part[0][lane];
+#pragma unroll
+    for (int q = 1; q < kReduceWaves; ++q) g += s_part[q][lane];
+    if (grad) grad[p] = g;
+    if (theta) {
+      const float a = ad.b1 * m1[p] + (1.0f - ad.b1) * g;
+      const float b = ad.b2 * m2[p] + (1.0f - ad.b2) * g * g;
+      m1[p] = a;
+      m2[p] = b;
+      theta[p] -= ad.lr * (a / ad.bc1) / (sqrtf(b / ad.bc2) + ad.eps);
+    }
   }
-}
-
-__global__ void k_adam(float* __restrict__ theta, const float* __restrict__ grad,
-                       float* __restrict__ m1, float* __restrict__ m2, float lr, float b1,
-                       float b2, float eps, float bc1, float bc2) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= kNParam) return;
-  const float g = grad[p];
-  const float a = b1 * m1[p] + (1.0f - b1) * g;
-  const float b = b2 * m2[p] + (1.0f - b2) * g * g;
-  m1[p] = a;
-  m2[p] = b;
-  theta[p] -= lr * (a / bc1) / (sqrtf(b / bc2) + eps);
+  if (blockIdx.x == 0 && wv == 1 && loss_out) {
+    float l = 0.f;
+    for (int t = lane; t < blocks; t += 64) l += lossp[t];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) l += __shfl_xor(l, off, 64);
+    if (lane == 0) *loss_out = l * inv_count;
+  }
 }
 
 // ------------------------------------------------------------------ inference
@@ -374,7 +445,6 @@ __global__ __launch_bounds__(256) void k_mlp_infer_f32(const float* __restrict__
 }
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // LDS hand-off between lanes of one wave (no workgroup barrier: waves iterate independently)
 __device__ inline void wave_sync() {
@@ -640,25 +710,23 @@ hipError_t launch_feature_range(const float* X, int64_t N, float* fmin, float* f
   return hipGetLastError();
 }
 
-hipError_t launch_mlp_train_step(const float* theta, const float* norm, const float* X,
-                                 const float* z, const float* w, const int64_t* idx,
-                                 int64_t nbatch, float inv_count, float* grads, float* lossp,
-                                 float* grad, float* loss_out, hipStream_t st) {
-  const int tiles = static_cast<int>((nbatch + 63) / 64);
-  k_mlp_train_tile<<<tiles, 64, 0, st>>>(theta, norm, X, z, w, idx, nbatch, inv_count, grads,
-                                         lossp);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  k_grad_reduce<<<grid_for(kNParam, 256), 256, 0, st>>>(grads, tiles, lossp, inv_count, grad,
-                                                        loss_out);
-  return hipGetLastError();
+int mlp_train_blocks(int64_t nbatch) {
+  return static_cast<int>(std::min<int64_t>((nbatch + kTile - 1) / kTile, kMaxTrainBlocks));
 }
 
-hipError_t launch_adam(float* theta, const float* grad, float* m1, float* m2, float lr,
-                       float b1, float b2, float eps, int step, hipStream_t st) {
-  const float bc1 = 1.0f - powf(b1, static_cast<float>(step));
-  const float bc2 = 1.0f - powf(b2, static_cast<float>(step));
-  k_adam<<<grid_for(kNParam, 256), 256, 0, st>>>(theta, grad, m1, m2, lr, b1, b2, eps, bc1, bc2);
+hipError_t launch_mlp_train_step(float* theta, const float* norm, const float* X, const float* z,
+                                 const float* w, const int64_t* idx, int64_t nbatch,
+                                 float inv_count, float* grads, float* lossp, float* grad,
+                                 float* loss_out, float* m1, float* m2, const AdamStep* adam,
+                                 hipStream_t st) {
+  const int blocks = mlp_train_blocks(nbatch);
+  k_mlp_train_tile<<<blocks, 256, 0, st>>>(theta, norm, X, z, w, idx, nbatch, inv_count, grads,
+                                           lossp);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  k_grad_reduce<<<grid_for(kNParam, 64), 64 * kReduceWaves, 0, st>>>(
+      grads, blocks, lossp, inv_count, grad, loss_out, adam ? theta : nullptr, m1, m2,
+      adam ? *adam : AdamStep{});
   return hipGetLastError();
 }
 

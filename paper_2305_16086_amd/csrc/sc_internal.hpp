@@ -382,12 +382,19 @@ hipError_t launch_targets(int64_t m, const double* s_ref, const double* s0, cons
 hipError_t launch_norm_stats(const float* X, int64_t N, float* norm, hipStream_t st);
 hipError_t launch_feature_range(const float* X, int64_t N, float* fmin, float* fmax,
                                 hipStream_t st);
-hipError_t launch_mlp_train_step(const float* theta, const float* norm, const float* X,
-                                 const float* z, const float* w, const int64_t* idx,
-                                 int64_t nbatch, float inv_count, float* grads, float* lossp,
-                                 float* grad, float* loss_out, hipStream_t st);
-hipError_t launch_adam(float* theta, const float* grad, float* m1, float* m2, float lr,
-                       float b1, float b2, float eps, int step, hipStream_t st);
+// Adam's constants for one step: rate, decay rates, epsilon, bias corrections 1 - b^step.
+struct AdamStep {
+  float lr = 0.f, b1 = 0.f, b2 = 0.f, eps = 0.f, bc1 = 1.f, bc2 = 1.f;
+};
+// Partial-gradient rows (and partial losses) launch_mlp_train_step writes for nbatch samples.
+int mlp_train_blocks(int64_t nbatch);
+// Gradient of the weighted squared error over samples idx[0 .. nbatch) into grad (may be
+// null) and, with adam, the Adam step on theta, m1, m2.
+hipError_t launch_mlp_train_step(float* theta, const float* norm, const float* X, const float* z,
+                                 const float* w, const int64_t* idx, int64_t nbatch,
+                                 float inv_count, float* grads, float* lossp, float* grad,
+                                 float* loss_out, float* m1, float* m2, const AdamStep* adam,
+                                 hipStream_t st);
 hipError_t launch_mlp_infer(const float* theta, const float* norm, const float* X, int64_t N,
                             int bf16, float* y, hipStream_t st);
 hipError_t launch_closure_apply(const DeviceGraph& g, const float* zpred, const double* s0,

@@ -24,9 +24,9 @@ struct sc_mlp {
   bool has_norm = false;
   bool has_range = false;
   int step = 0;
-  float* grads = nullptr;  // [tiles][5313]
-  size_t grads_tiles = 0;
-  float* lossp = nullptr;  // [tiles]
+  float* grads = nullptr;  // [workgroups][5313]
+  size_t grads_blocks = 0;
+  float* lossp = nullptr;  // [workgroups]
   float* grad = nullptr;   // [5313]
   float* losses = nullptr; // [steps of an epoch]
   size_t losses_cap = 0;
@@ -61,13 +61,14 @@ uint64_t splitmix64(uint64_t& x) {
 double uniform01(uint64_t& x) { return static_cast<double>(splitmix64(x) >> 11) * (1.0 / 9007199254740992.0); }
 
 int ensure_train_scratch(sc_mlp* net, int64_t batch, int64_t n) {
-  const size_t tiles = static_cast<size_t>((batch + 63) / 64);
-  if (tiles > net->grads_tiles) {
+  const size_t blocks = static_cast<size_t>(sc::mlp_train_blocks(batch));
+  if (blocks > net->grads_blocks) {
     dev_free(net->grads);
     dev_free(net->lossp);
-    HIP_TRY(dev_alloc(&net->grads, tiles * kP));
-    HIP_TRY(dev_alloc(&net->lossp, tiles));
-    net->grads_tiles = tiles;
+    net->grads_blocks = 0;
+    HIP_TRY(dev_alloc(&net->grads, blocks * kP));
+    HIP_TRY(dev_alloc(&net->lossp, blocks));
+    net->grads_blocks = blocks;
   }
   if (static_cast<size_t>(n) > net->idx_cap) {
     dev_free(net->idx);
@@ -185,7 +186,7 @@ extern "C" int sc_mlp_grad(sc_mlp* net, const float* X, const float* z, const fl
   HIP_TRY(hipMemcpyAsync(net->idx, id.data(), N * sizeof(int64_t), hipMemcpyHostToDevice, st));
   HIP_TRY(sc::launch_mlp_train_step(net->theta, net->norm, X, z, w, net->idx, N,
                                     1.0f / static_cast<float>(N), net->grads, net->lossp,
-                                    net->grad, net->losses, st));
+                                    net->grad, net->losses, nullptr, nullptr, nullptr, st));
   if (grad_host) HIP_TRY(hipMemcpyAsync(grad_host, net->grad, kP * sizeof(float), hipMemcpyDeviceToHost, st));
   if (loss_host) HIP_TRY(hipMemcpyAsync(loss_host, net->losses, sizeof(float), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
@@ -225,12 +226,13 @@ extern "C" int sc_mlp_train(sc_mlp* net, const float* X, const float* z, const f
     HIP_TRY(hipMemcpyAsync(net->idx, perm.data(), N * sizeof(int64_t), hipMemcpyHostToDevice, st));
     for (int64_t b = 0; b < steps; ++b) {
       const int64_t nb = std::min<int64_t>(t.batch, N - b * t.batch);
+      ++net->step;
+      sc::AdamStep ad{t.lr, 0.9f, 0.999f, 1e-8f, 1.f, 1.f};
+      ad.bc1 = 1.0f - powf(ad.b1, static_cast<float>(net->step));
+      ad.bc2 = 1.0f - powf(ad.b2, static_cast<float>(net->step));
       HIP_TRY(sc::launch_mlp_train_step(net->theta, net->norm, X, z, w, net->idx + b * t.batch, nb,
                                         1.0f / static_cast<float>(nb), net->grads, net->lossp,
-                                        net->grad, net->losses + b, st));
-      ++net->step;
-      HIP_TRY(sc::launch_adam(net->theta, net->grad, net->m1, net->m2, t.lr, 0.9f, 0.999f, 1e-8f,
-                              net->step, st));
+                                        nullptr, net->losses + b, net->m1, net->m2, &ad, st));
     }
     HIP_TRY(hipMemcpyAsync(losses.data(), net->losses, steps * sizeof(float), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
