@@ -18,6 +18,8 @@
 
 #include <hip/hip_bf16.h>
 
+#include <algorithm>
+
 namespace sc {
 
 namespace {
@@ -53,18 +55,6 @@ __global__ void k_record_init(int64_t nslots, const int32_t* __restrict__ col,
   roff[k * kRec + 1] = inv_deg[col[k]];
 }
 
-template <typename T, int B>
-__global__ void k_record(int kbeg, int kend, int s0, int ell, const int32_t* __restrict__ slot_row,
-                         const int32_t* __restrict__ col, const T* __restrict__ Y,
-                         T* __restrict__ rdiag, T* __restrict__ roff) {
-  const int k = kbeg + blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= kend) return;
-  const int s = slot_row[k];
-  const int c = s - s0;
-  rdiag[static_cast<int64_t>(k) * kRec + ell] = Y[static_cast<size_t>(s) * B + c];
-  roff[static_cast<int64_t>(k) * kRec + ell] = Y[static_cast<size_t>(col[k]) * B + c];
-}
-
 // The last recorded step without a full dense step: only p_L(s,s) and p_L(j,s)
 // of the block's slots are read, so each is summed from the neighbour rows of
 // Y = the state at L - 1 directly (Algorithm 2 lines 6-9 restricted to those
@@ -80,10 +70,14 @@ __device__ inline T wave_sum_t(T v) {
 
 template <typename T, int B>
 __global__ __launch_bounds__(kThreads) void k_record_last(
-    int kbeg, int kend, int s0, int nsrc, int ell, const int32_t* __restrict__ rowptr,
+    BlockList blocks, int n, int ell, const int32_t* __restrict__ rowptr,
     const int32_t* __restrict__ col, const int32_t* __restrict__ slot_row,
-    const T* __restrict__ inv_deg, const T* __restrict__ Y, T* __restrict__ rdiag,
-    T* __restrict__ roff) {
+    const T* __restrict__ inv_deg, const T* __restrict__ Yg, int64_t ystride,
+    T* __restrict__ rdiag, T* __restrict__ roff) {
+  const BlockRef br = blocks.b[blockIdx.y];
+  const int kbeg = br.kbeg, kend = br.kend, s0 = br.s0;
+  const int nsrc = min(B, n - s0);
+  const T* __restrict__ Y = Yg + br.buf * ystride;
   const int lane = threadIdx.x & 63;
   const int w = static_cast<int>(blockIdx.x) * kWavesPerBlock + static_cast<int>(threadIdx.x >> 6);
   if (w < nsrc) {
@@ -662,24 +656,17 @@ hipError_t launch_record_init(const DeviceGraph& g, T* rdiag, T* roff, hipStream
 }
 
 template <typename T>
-hipError_t launch_record(const DeviceGraph& g, int kbeg, int kend, int s0, int B, int ell,
-                         const T* Y, T* rdiag, T* roff, hipStream_t st) {
-  if (kend <= kbeg) return hipSuccess;
-  SC_DISPATCH_B(B, (k_record<T, kB><<<grid_for(kend - kbeg, 256), 256, 0, st>>>(
-                        kbeg, kend, s0, ell, g.slot_row, g.col, Y, rdiag, roff)));
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_record_last(const DeviceGraph& g, int kbeg, int kend, int s0, int B, int ell,
-                              const T* Y, T* rdiag, T* roff, hipStream_t st) {
-  if (kend <= kbeg || ell < 3 || ell >= kRec) return hipErrorInvalidValue;
-  const int nsrc = static_cast<int>(std::min<int64_t>(B, static_cast<int64_t>(g.n) - s0));
-  if (nsrc <= 0) return hipErrorInvalidValue;
-  const int waves = nsrc + (kend - kbeg);
-  SC_DISPATCH_B(B, (k_record_last<T, kB><<<grid_for(waves, kWavesPerBlock), kThreads, 0, st>>>(
-                        kbeg, kend, s0, nsrc, ell, g.rowptr, g.col, g.slot_row, inv_deg_sel<T>(g),
-                        Y, rdiag, roff)));
+hipError_t launch_record_last(const DeviceGraph& g, const BlockList& blocks, int B, int ell,
+                              const T* Y, int64_t ystride, T* rdiag, T* roff, hipStream_t st) {
+  if (blocks.nb == 0) return hipSuccess;
+  if (ell < 3 || ell >= kRec) return hipErrorInvalidValue;
+  int waves = 0;
+  for (int i = 0; i < blocks.nb; ++i)
+    waves = std::max(waves, B + blocks.b[i].kend - blocks.b[i].kbeg);
+  const dim3 grid(grid_for(waves, kWavesPerBlock), blocks.nb);
+  SC_DISPATCH_B(B, (k_record_last<T, kB><<<grid, kThreads, 0, st>>>(
+                        blocks, g.n, ell, g.rowptr, g.col, g.slot_row, inv_deg_sel<T>(g), Y,
+                        ystride, rdiag, roff)));
   return hipGetLastError();
 }
 
@@ -763,14 +750,11 @@ hipError_t launch_combine_masked(const DeviceGraph& g, const double* gacc,
 
 template hipError_t launch_record_init<float>(const DeviceGraph&, float*, float*, hipStream_t);
 template hipError_t launch_record_init<double>(const DeviceGraph&, double*, double*, hipStream_t);
-template hipError_t launch_record<float>(const DeviceGraph&, int, int, int, int, int, const float*,
-                                         float*, float*, hipStream_t);
-template hipError_t launch_record<double>(const DeviceGraph&, int, int, int, int, int,
-                                          const double*, double*, double*, hipStream_t);
-template hipError_t launch_record_last<float>(const DeviceGraph&, int, int, int, int, int,
-                                              const float*, float*, float*, hipStream_t);
-template hipError_t launch_record_last<double>(const DeviceGraph&, int, int, int, int, int,
-                                               const double*, double*, double*, hipStream_t);
+template hipError_t launch_record_last<float>(const DeviceGraph&, const BlockList&, int, int,
+                                              const float*, int64_t, float*, float*, hipStream_t);
+template hipError_t launch_record_last<double>(const DeviceGraph&, const BlockList&, int, int,
+                                               const double*, int64_t, double*, double*,
+                                               hipStream_t);
 template hipError_t launch_features<float>(const DeviceGraph&, const float*, const float*, double,
                                            float*, double*, double*, double*, double*,
                                            hipStream_t);

@@ -8,6 +8,7 @@
 #include "sc_internal.hpp"
 #include "accumulate.hpp"
 
+#include <algorithm>
 #include <cfloat>
 #include <climits>
 
@@ -72,8 +73,9 @@ __device__ inline void list_last(const double (&lv)[kMaxGamma], const int (&li)[
     }
 }
 
-// The per-column summary of Algorithm 3 runs in four passes over the block
-// state Y (lanes are columns, rows are cut into kColParts chunks):
+// The per-column summary of Algorithm 3 runs in four passes over the block states Y
+// (lanes are columns, rows are cut into nparts chunks; every pass takes all blocks
+// of a group, blockIdx.y the block):
 //  A  chunk maxima and minima (one coalesced read of Y);
 //  B  per column: overall extremes and theta = the gamma-th largest chunk
 //     maximum.  The gamma largest chunk maxima are gamma distinct entries, so
@@ -82,41 +84,53 @@ __device__ inline void list_last(const double (&lv)[kMaxGamma], const int (&li)[
 //     and register themselves with the column;
 //  D  per column: merge the registered lists, test candidate pairs for edges
 //     (Algorithm 3 lines 3-5, safe reading), extremes over N(s).
-// Chunk p of column c: pmx/pmn[c*kColParts + p], lists pv/pi[(p*B + c)*gamma + r].
+// Chunk p of column c: pmx/pmn[c*nparts + p], lists pv/pi[(p*B + c)*gamma + r].
+struct ColScratch {
+  char* base;
+  size_t bytes;    // per block
+  int nparts;
+  __device__ char* of(int i) const { return base + static_cast<size_t>(i) * bytes; }
+  template <typename T>
+  __device__ T* pv(int i) const { return reinterpret_cast<T*>(of(i)); }
+  __device__ size_t cells() const { return static_cast<size_t>(nparts) * 64; }
+  __device__ int* pi(int i) const {
+    return reinterpret_cast<int*>(of(i) + cells() * kMaxGamma * sizeof(double));
+  }
+  template <typename T>
+  __device__ T* pmx(int i) const {
+    return reinterpret_cast<T*>(of(i) + cells() * kMaxGamma * (sizeof(double) + sizeof(int)));
+  }
+  template <typename T>
+  __device__ T* pmn(int i) const { return pmx<T>(i) + cells(); }
+  template <typename T>
+  __device__ int* act(int i) const { return reinterpret_cast<int*>(pmn<T>(i) + cells()); }
+  template <typename T>
+  __device__ int* nact(int i) const { return act<T>(i) + cells(); }
+  template <typename T>
+  __device__ T* thr(int i) const { return reinterpret_cast<T*>(nact<T>(i) + 64); }
+};
 
-// Slot kbeg + i of a finished block: add its chunk sums in chunk order, divided
-// by n_r (nothing when the block walked one slot per wave: ctl[1] == 0).
-__device__ inline void walk_finish_slot(const FinishJob& f, int i) {
-  if (f.ctl[1] == 0 || i >= f.kend - f.kbeg) return;
-  const long long n_r = f.nr[f.kbeg + i];
-  if (n_r <= 0) return;
-  double acc = 0.0;
-  for (long long c = f.chunk_off[i]; c < f.chunk_off[i + 1]; ++c) acc += f.part[c];
-  f.gacc[f.kbeg + i] += acc / static_cast<double>(n_r);
-}
-
-// Workgroups after col_blocks carry the accumulation of the step held in Y
-// (acc; Algorithm 2 lines 10-11) and then a previous block's walk finish (fin),
-// saving launches.
+// Workgroups after col_blocks carry the accumulation of the block's state (Algorithm
+// 2 lines 10-11), saving a launch.
 template <typename T, int B>
-__global__ __launch_bounds__(kThreads) void k_colmax(int n, int rows_per_part, int nparts,
-                                                     const T* __restrict__ Y,
-                                                     T* __restrict__ pmx, T* __restrict__ pmn,
-                                                     int col_blocks, AccJob acc, int acc_blocks,
-                                                     FinishJob fin,
+__global__ __launch_bounds__(kThreads) void k_colmax(int n, int rows_per_part, ColScratch sc,
+                                                     BlockList blocks, const T* __restrict__ Yg,
+                                                     int64_t ystride, int col_blocks, AccJob acc,
                                                      const int32_t* __restrict__ slot_row,
                                                      const int32_t* __restrict__ col,
                                                      const double* __restrict__ inv_deg_d) {
+  const int bi = static_cast<int>(blockIdx.y);
+  const BlockRef br = blocks.b[bi];
+  const T* __restrict__ Y = Yg + br.buf * ystride;
   if (static_cast<int>(blockIdx.x) >= col_blocks) {
     const int t = static_cast<int>(blockIdx.x) - col_blocks;
-    if (t < acc_blocks) {
-      const int k = acc.kbeg + t * kThreads + threadIdx.x;
-      accumulate_half<T, B>(acc, slot_row, col, inv_deg_d, Y, k);
-    } else {
-      walk_finish_slot(fin, (t - acc_blocks) * kThreads + static_cast<int>(threadIdx.x));
-    }
+    const int k = br.kbeg + t * kThreads + static_cast<int>(threadIdx.x);
+    if (k < br.kend) accumulate_half<T, B>(acc, br.s0, slot_row, col, inv_deg_d, Y, k);
     return;
   }
+  const int nparts = sc.nparts;
+  T* __restrict__ pmx = sc.pmx<T>(bi);
+  T* __restrict__ pmn = sc.pmn<T>(bi);
   constexpr int G = 64 / B;
   __shared__ T smx[kThreads], smn[kThreads];
   const int lane = threadIdx.x & 63;
@@ -176,8 +190,16 @@ constexpr int kThreshWaves = 4;
 
 template <typename T, int B>
 __global__ __launch_bounds__(64 * kThreshWaves) void k_colthresh(
-    int gamma, int nparts, const T* __restrict__ pmx, const T* __restrict__ pmn,
-    T* __restrict__ thr, int* __restrict__ nact, int* __restrict__ act, ColStats* __restrict__ cs) {
+    int gamma, int n, ColScratch sc, BlockList blocks, ColStats* __restrict__ csg) {
+  const int bi = static_cast<int>(blockIdx.y);
+  if (blocks.b[bi].s0 + static_cast<int>(blockIdx.x) >= n) return;   // uniform per workgroup
+  const int nparts = sc.nparts;
+  const T* __restrict__ pmx = sc.pmx<T>(bi);
+  const T* __restrict__ pmn = sc.pmn<T>(bi);
+  T* __restrict__ thr = sc.thr<T>(bi);
+  int* __restrict__ nact = sc.nact<T>(bi);
+  int* __restrict__ act = sc.act<T>(bi);
+  ColStats* __restrict__ cs = csg + bi * 64;
   constexpr int kPer = kColParts / (64 * kThreshWaves);
   __shared__ double s_top[kThreshWaves][kMaxGamma];
   __shared__ double s_mx[kThreshWaves], s_mn[kThreshWaves];
@@ -303,7 +325,7 @@ __global__ __launch_bounds__(64 * kThreshWaves) void k_colthresh(
   for (int k = 0; k < kPer; ++k) {
     if ((bal[k] >> lane) & 1ull) {
       const int idx = base + __popcll(bal[k] & ((1ull << lane) - 1ull));
-      act[static_cast<size_t>(c) * kColParts + idx] = wave * (kPer * 64) + k * 64 + lane;
+      act[static_cast<size_t>(c) * nparts + idx] = wave * (kPer * 64) + k * 64 + lane;
     }
     base += __popcll(bal[k]);
   }
@@ -317,19 +339,25 @@ constexpr int kScanWaves = 16;
 
 template <typename T, int B>
 __global__ __launch_bounds__(kThreads) void k_colscan(int n, int rows_per_part, int gamma,
-                                                      const T* __restrict__ Y,
-                                                      const T* __restrict__ thr,
-                                                      T* __restrict__ pv, int* __restrict__ pi,
-                                                      const int* __restrict__ nact,
-                                                      const int* __restrict__ act) {
+                                                      ColScratch sc, BlockList blocks,
+                                                      const T* __restrict__ Yg, int64_t ystride) {
+  const int bi = static_cast<int>(blockIdx.y);
+  const BlockRef br = blocks.b[bi];
+  const T* __restrict__ Y = Yg + br.buf * ystride;
+  const T* __restrict__ thr = sc.thr<T>(bi);
+  T* __restrict__ pv = sc.pv<T>(bi);
+  int* __restrict__ pi = sc.pi(bi);
+  const int* __restrict__ nact = sc.nact<T>(bi);
+  const int* __restrict__ act = sc.act<T>(bi);
   const int lane = threadIdx.x & 63;
   const int gw = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   const int c = gw / kScanWaves;
   const int wc = gw % kScanWaves;
+  if (br.s0 + c >= n) return;   // uniform per wave
   const int na = nact[c];
   const T th = thr[c];
   for (int k = wc; k < na; k += kScanWaves) {
-    const int part = act[static_cast<size_t>(c) * kColParts + k];
+    const int part = act[static_cast<size_t>(c) * sc.nparts + k];
     const int x0 = part * rows_per_part;
     const int x1 = min(n, x0 + rows_per_part);
     double lv = -DBL_MAX;   // list entry r sits in lane r (r < gamma)
@@ -384,17 +412,23 @@ __global__ __launch_bounds__(kThreads) void k_colscan(int n, int rows_per_part, 
 // one wave per column; the registered chunk order is arbitrary but the
 // selection uses the total order (value desc, id asc), so the result is not
 template <typename T, int B>
-__global__ __launch_bounds__(64) void k_colmerge(int n, int s0, int gamma,
+__global__ __launch_bounds__(64) void k_colmerge(int n, int gamma, ColScratch sc,
+                                                 BlockList blocks,
                                                  const int32_t* __restrict__ rowptr,
                                                  const int32_t* __restrict__ col,
-                                                 const T* __restrict__ Y,
-                                                 const T* __restrict__ pv,
-                                                 const int* __restrict__ pi,
-                                                 const int* __restrict__ nact,
-                                                 const int* __restrict__ act,
-                                                 ColStats* __restrict__ cs) {
+                                                 const T* __restrict__ Yg, int64_t ystride,
+                                                 ColStats* __restrict__ csg) {
+  const int bi = static_cast<int>(blockIdx.y);
+  const BlockRef br = blocks.b[bi];
+  const T* __restrict__ Y = Yg + br.buf * ystride;
+  const T* __restrict__ pv = sc.pv<T>(bi);
+  const int* __restrict__ pi = sc.pi(bi);
+  const int* __restrict__ nact = sc.nact<T>(bi);
+  const int* __restrict__ act = sc.act<T>(bi);
+  ColStats* __restrict__ cs = csg + bi * 64;
   const int c = blockIdx.x;
-  const int s = s0 + c;
+  const int s = br.s0 + c;
+  if (s >= n) return;   // uniform per workgroup
   const int lane = threadIdx.x;
   double lv[kMaxGamma];
   int li[kMaxGamma];
@@ -407,7 +441,7 @@ __global__ __launch_bounds__(64) void k_colmerge(int n, int s0, int gamma,
   int lasti = INT_MAX;
   const int na = nact[c];
   for (int k = lane; k < na; k += 64) {
-    const size_t o = static_cast<size_t>(act[static_cast<size_t>(c) * kColParts + k]) * B + c;
+    const size_t o = static_cast<size_t>(act[static_cast<size_t>(c) * sc.nparts + k]) * B + c;
     for (int r = 0; r < gamma; ++r) {
       const int id = pi[o * gamma + r];
       if (id == INT_MAX) break;
@@ -507,13 +541,19 @@ __device__ inline double wave_sum(double v) {
 constexpr int kWcBatch = 3;
 template <typename T, int B>
 __global__ __launch_bounds__(kThreads) void k_walk_counts(
-    int kbeg, int kend, int s0, int tilde, int gamma, double coef, long long nr_cap,
+    BlockList blocks, int tilde, int gamma, double coef, long long nr_cap,
     const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
-    const int32_t* __restrict__ slot_row, const int32_t* __restrict__ deg, const T* __restrict__ Y,
-    const ColStats* __restrict__ cs, const int32_t* __restrict__ tau, long long* __restrict__ nr) {
+    const int32_t* __restrict__ slot_row, const int32_t* __restrict__ deg,
+    const T* __restrict__ Yg, int64_t ystride, const ColStats* __restrict__ csg,
+    const int32_t* __restrict__ tau, long long* __restrict__ nr) {
+  const int bi = static_cast<int>(blockIdx.y);
+  const BlockRef br = blocks.b[bi];
+  const T* __restrict__ Y = Yg + br.buf * ystride;
+  const ColStats* __restrict__ cs = csg + bi * 64;
+  const int s0 = br.s0;
   const int lane = threadIdx.x & 63;
-  const int k = kbeg + blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-  if (k >= kend) return;
+  const int k = br.kbeg + blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+  if (k >= br.kend) return;
   const int len = tau[k] - tilde;
   if (len <= 0) {
     if (lane == 0) nr[k] = 0;
@@ -562,12 +602,16 @@ __global__ __launch_bounds__(kThreads) void k_walk_counts(
   nr[k] = w;
 }
 
-// walk pairs and single-walk steps of slots [kbeg, kend): one atomic pair per
-// workgroup (integer sums, so the totals do not depend on the order)
-__global__ __launch_bounds__(256) void k_work_totals(int kbeg, int kend, int tilde,
+// walk pairs and single-walk steps of each block's slots into work[stride * block]:
+// one atomic pair per workgroup (integer sums, so the totals do not depend on the
+// order)
+__global__ __launch_bounds__(256) void k_work_totals(BlockList blocks, int tilde,
                                                      const int32_t* __restrict__ tau,
                                                      const long long* __restrict__ nr,
-                                                     unsigned long long* __restrict__ work) {
+                                                     unsigned long long* __restrict__ work_g,
+                                                     int stride) {
+  const int kbeg = blocks.b[blockIdx.y].kbeg, kend = blocks.b[blockIdx.y].kend;
+  unsigned long long* __restrict__ work = work_g + static_cast<size_t>(blockIdx.y) * stride;
   __shared__ unsigned long long s0[256], s1[256];
   unsigned long long a = 0, b = 0;
   for (int k = kbeg + blockIdx.x * 256 + threadIdx.x; k < kend; k += gridDim.x * 256) {
@@ -647,11 +691,16 @@ __device__ inline void slot_walks(int k, int lane, int s0, int tilde, unsigned k
 constexpr int kScanThreads = 256;   // one small workgroup: schedules beside the traversal kernels
 constexpr int kScanPer = 8;
 
-__global__ __launch_bounds__(kScanThreads) void k_walk_scan(int kbeg, int kend,
+template <int B>
+__global__ __launch_bounds__(kScanThreads) void k_walk_scan(BlockList blocks,
                                                             const long long* __restrict__ nr,
-                                                            long long* __restrict__ chunk_off,
+                                                            long long* __restrict__ chunk_off_g,
                                                             long long capacity,
-                                                            long long* __restrict__ ctl) {
+                                                            long long* __restrict__ ctl_g) {
+  const BlockRef br = blocks.b[blockIdx.x];
+  const int kbeg = br.kbeg, kend = br.kend;
+  long long* __restrict__ chunk_off = chunk_off_g + kbeg + br.s0 / B;
+  long long* __restrict__ ctl = ctl_g + 2 * blockIdx.x;
   __shared__ long long wsum[kScanThreads / 64];
   __shared__ long long carry_s;
   const int tid = threadIdx.x;
@@ -701,12 +750,19 @@ __global__ __launch_bounds__(kScanThreads) void k_walk_scan(int kbeg, int kend,
 
 template <typename T, int B>
 __global__ __launch_bounds__(kThreads) void k_walks_flat(
-    int kbeg, int kend, int s0, int tilde, unsigned k0, unsigned k1,
-    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
-    const int32_t* __restrict__ slot_row, const double* __restrict__ inv_deg,
-    const T* __restrict__ Y, const int32_t* __restrict__ tau, const long long* __restrict__ nr,
-    const long long* __restrict__ chunk_off, const long long* __restrict__ ctl,
-    double* __restrict__ part, double* __restrict__ gacc) {
+    BlockList blocks, int tilde, unsigned k0, unsigned k1, const int32_t* __restrict__ rowptr,
+    const int32_t* __restrict__ col, const int32_t* __restrict__ slot_row,
+    const double* __restrict__ inv_deg, const T* __restrict__ Yg, int64_t ystride,
+    const int32_t* __restrict__ tau, const long long* __restrict__ nr,
+    const long long* __restrict__ chunk_off_g, const long long* __restrict__ ctl_g,
+    double* __restrict__ part_g, long long capacity, double* __restrict__ gacc) {
+  const int bi = static_cast<int>(blockIdx.y);
+  const BlockRef br = blocks.b[bi];
+  const int kbeg = br.kbeg, kend = br.kend, s0 = br.s0;
+  const T* __restrict__ Y = Yg + br.buf * ystride;
+  const long long* __restrict__ chunk_off = chunk_off_g + kbeg + s0 / B;
+  const long long* __restrict__ ctl = ctl_g + 2 * bi;
+  double* __restrict__ part = part_g + bi * capacity;
   const int lane = threadIdx.x & 63;
   const long long nwaves = static_cast<long long>(gridDim.x) * kWavesPerBlock;
   const long long w = static_cast<long long>(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
@@ -775,8 +831,27 @@ __global__ __launch_bounds__(kThreads) void k_walks_flat(
   }
 }
 
-__global__ void k_walk_finish(FinishJob f) {
-  walk_finish_slot(f, static_cast<int>(blockIdx.x * blockDim.x + threadIdx.x));
+// gacc[k] += (slot k's chunk sums in chunk order) / n_r (nothing for a block that
+// walked one slot per wave: ctl[1] == 0).
+template <int B>
+__global__ __launch_bounds__(256) void k_walk_finish(BlockList blocks,
+                                                     const long long* __restrict__ nr,
+                                                     const long long* __restrict__ chunk_off_g,
+                                                     const long long* __restrict__ ctl_g,
+                                                     const double* __restrict__ part_g,
+                                                     long long capacity,
+                                                     double* __restrict__ gacc) {
+  const int bi = static_cast<int>(blockIdx.y);
+  const BlockRef br = blocks.b[bi];
+  const int i = static_cast<int>(blockIdx.x * 256 + threadIdx.x);
+  if (ctl_g[2 * bi + 1] == 0 || i >= br.kend - br.kbeg) return;
+  const long long n_r = nr[br.kbeg + i];
+  if (n_r <= 0) return;
+  const long long* __restrict__ off = chunk_off_g + br.kbeg + br.s0 / B;
+  const double* __restrict__ part = part_g + bi * capacity;
+  double acc = 0.0;
+  for (long long c = off[i]; c < off[i + 1]; ++c) acc += part[c];
+  gacc[br.kbeg + i] += acc / static_cast<double>(n_r);
 }
 
 }  // namespace
@@ -789,114 +864,116 @@ __global__ void k_walk_finish(FinishJob f) {
     default: return hipErrorInvalidValue;             \
   }
 
+int col_parts(int64_t n) {
+  // about 48 rows per chunk: enough chunks to spread a column over the chip, few
+  // enough that a small graph's summary stays small
+  int p = 64;
+  while (p < kColParts && static_cast<int64_t>(p) * 48 < n) p *= 2;
+  return p;
+}
+
+size_t col_scratch_bytes(int nparts) {
+  return (static_cast<size_t>(nparts) * 64 *
+              (kMaxGamma * (sizeof(double) + sizeof(int)) + 2 * sizeof(double) + sizeof(int)) +
+          64 * (sizeof(int) + sizeof(double)) + 255) / 256 * 256;
+}
+
+namespace {
+int max_slots(const BlockList& blocks) {
+  int m = 0;
+  for (int i = 0; i < blocks.nb; ++i) m = std::max(m, blocks.b[i].kend - blocks.b[i].kbeg);
+  return m;
+}
+}  // namespace
+
 template <typename T>
-hipError_t launch_colstats(const DeviceGraph& g, int s0, int B, int gamma, const T* Y,
-                           ColStats* cs, void* scratch, hipStream_t st, const AccJob* acc,
-                           const FinishJob* fin) {
-  int ncols = B;
-  if (s0 + ncols > g.n) ncols = g.n - s0;
-  if (ncols <= 0) return fin ? launch_walk_finish(*fin, st) : hipSuccess;
+hipError_t launch_colstats(const DeviceGraph& g, const BlockList& blocks, int B, int gamma,
+                           const T* Y, int64_t ystride, const TailScratch& ts, hipStream_t st,
+                           const AccJob* acc) {
+  if (blocks.nb == 0) return hipSuccess;
   if (gamma > kMaxGamma || gamma < 0) return hipErrorInvalidValue;
   const int G = 64 / B;
-  const int nparts = kColParts;
-  const int waves = nparts / G;
+  const int nparts = ts.nparts;
   const int rows = (g.n + nparts - 1) / nparts;
-  // scratch layout (see kColScratchBytes)
-  char* base = static_cast<char*>(scratch);
-  const size_t cells = static_cast<size_t>(nparts) * 64;
-  T* pv = reinterpret_cast<T*>(base);
-  int* pi = reinterpret_cast<int*>(base + cells * kMaxGamma * sizeof(double));
-  T* pmx = reinterpret_cast<T*>(base + cells * kMaxGamma * (sizeof(double) + sizeof(int)));
-  T* pmn = pmx + cells;
-  int* act = reinterpret_cast<int*>(pmn + cells);             // [64][kColParts]
-  int* nact = act + cells;                                     // [64]
-  T* thr = reinterpret_cast<T*>(nact + 64);                    // [64]
-  const int col_blocks = waves / kWavesPerBlock;
-  const AccJob job = acc ? *acc : AccJob{};
-  const int acc_blocks =
-      acc_job_set(job) ? static_cast<int>(grid_for(job.kend - job.kbeg, kThreads)) : 0;
-  const FinishJob fj = fin ? *fin : FinishJob{};
-  const int fin_blocks =
-      fj.gacc && fj.kend > fj.kbeg ? static_cast<int>(grid_for(fj.kend - fj.kbeg, kThreads)) : 0;
-  SC_DISPATCH_B(B, (k_colmax<T, kB><<<col_blocks + acc_blocks + fin_blocks, kThreads, 0, st>>>(
-                        g.n, rows, nparts, Y, pmx, pmn, col_blocks, job, acc_blocks, fj,
+  const ColScratch sc{ts.col, ts.col_bytes, nparts};
+  const int col_blocks = nparts / G / kWavesPerBlock;
+  if (col_blocks < 1 || nparts > kColParts) return hipErrorInvalidValue;
+  const int acc_blocks = acc ? static_cast<int>(grid_for(max_slots(blocks), kThreads)) : 0;
+  const unsigned nb = static_cast<unsigned>(blocks.nb);
+  SC_DISPATCH_B(B, (k_colmax<T, kB><<<dim3(col_blocks + acc_blocks, nb), kThreads, 0, st>>>(
+                        g.n, rows, sc, blocks, Y, ystride, col_blocks, acc ? *acc : AccJob{},
                         g.slot_row, g.col, g.inv_deg_d)));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  SC_DISPATCH_B(B, (k_colthresh<T, kB><<<ncols, 64 * kThreshWaves, 0, st>>>(
-                        gamma, nparts, pmx, pmn, thr, nact, act, cs)));
+  SC_DISPATCH_B(B, (k_colthresh<T, kB><<<dim3(B, nb), 64 * kThreshWaves, 0, st>>>(
+                        gamma, g.n, sc, blocks, ts.cs)));
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (gamma > 0) {
-    SC_DISPATCH_B(B, (k_colscan<T, kB><<<grid_for(static_cast<int64_t>(ncols) * kScanWaves,
-                                                  kWavesPerBlock), kThreads, 0, st>>>(
-                          g.n, rows, gamma, Y, thr, pv, pi, nact, act)));
+    SC_DISPATCH_B(B, (k_colscan<T, kB><<<dim3(grid_for(static_cast<int64_t>(B) * kScanWaves,
+                                                       kWavesPerBlock), nb), kThreads, 0, st>>>(
+                          g.n, rows, gamma, sc, blocks, Y, ystride)));
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  SC_DISPATCH_B(B, (k_colmerge<T, kB><<<ncols, 64, 0, st>>>(g.n, s0, gamma, g.rowptr, g.col, Y,
-                                                             pv, pi, nact, act, cs)));
+  SC_DISPATCH_B(B, (k_colmerge<T, kB><<<dim3(B, nb), 64, 0, st>>>(
+                        g.n, gamma, sc, blocks, g.rowptr, g.col, Y, ystride, ts.cs)));
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_walk_counts(const DeviceGraph& g, int kbeg, int kend, int s0, int B, int tilde,
-                              int gamma, double coef, int64_t nr_cap, const T* Y,
-                              const ColStats* cs, const int32_t* tau_slot, int64_t* nr_slot,
+hipError_t launch_walk_counts(const DeviceGraph& g, const BlockList& blocks, int B, int tilde,
+                              int gamma, double coef, int64_t nr_cap, const T* Y, int64_t ystride,
+                              const TailScratch& ts, const int32_t* tau_slot, int64_t* nr_slot,
                               hipStream_t st) {
-  if (kend <= kbeg) return hipSuccess;
-  SC_DISPATCH_B(B, (k_walk_counts<T, kB><<<grid_for(kend - kbeg, kWavesPerBlock), kThreads, 0,
-                                          st>>>(
-                        kbeg, kend, s0, tilde, gamma, coef, static_cast<long long>(nr_cap),
-                        g.rowptr, g.col, g.slot_row, g.deg, Y, cs, tau_slot,
+  const int slots = max_slots(blocks);
+  if (slots == 0) return hipSuccess;
+  const dim3 grid(grid_for(slots, kWavesPerBlock), blocks.nb);
+  SC_DISPATCH_B(B, (k_walk_counts<T, kB><<<grid, kThreads, 0, st>>>(
+                        blocks, tilde, gamma, coef, static_cast<long long>(nr_cap), g.rowptr,
+                        g.col, g.slot_row, g.deg, Y, ystride, ts.cs, tau_slot,
                         reinterpret_cast<long long*>(nr_slot))));
   return hipGetLastError();
 }
 
-hipError_t launch_work_totals(int kbeg, int kend, int tilde, const int32_t* tau_slot,
-                              const int64_t* nr_slot, unsigned long long* work, hipStream_t st) {
-  if (kend <= kbeg) return hipSuccess;
-  unsigned blocks = grid_for(kend - kbeg, 256);
-  if (blocks > 256) blocks = 256;
-  k_work_totals<<<blocks, 256, 0, st>>>(kbeg, kend, tilde, tau_slot,
-                                        reinterpret_cast<const long long*>(nr_slot), work);
+hipError_t launch_work_totals(const BlockList& blocks, int tilde, const int32_t* tau_slot,
+                              const int64_t* nr_slot, unsigned long long* work, int stride,
+                              hipStream_t st) {
+  const int slots = max_slots(blocks);
+  if (slots == 0) return hipSuccess;
+  const dim3 grid(std::min<unsigned>(256, grid_for(slots, 256)), blocks.nb);
+  k_work_totals<<<grid, 256, 0, st>>>(blocks, tilde, tau_slot,
+                                      reinterpret_cast<const long long*>(nr_slot), work, stride);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_walks(const DeviceGraph& g, int kbeg, int kend, int s0, int B, int tilde,
-                        uint64_t seed, const T* Y, const int32_t* tau_slot,
-                        const int64_t* nr_slot, double* gacc, const WalkScratch& ws,
-                        hipStream_t st, FinishJob* defer) {
-  if (defer) *defer = FinishJob{};
-  if (kend <= kbeg) return hipSuccess;
+hipError_t launch_walks(const DeviceGraph& g, const BlockList& blocks, int B, int tilde,
+                        uint64_t seed, const T* Y, int64_t ystride, const int32_t* tau_slot,
+                        const int64_t* nr_slot, double* gacc, const TailScratch& ts,
+                        hipStream_t st) {
+  const int slots = max_slots(blocks);
+  if (slots == 0) return hipSuccess;
   const unsigned k0 = static_cast<unsigned>(seed & 0xFFFFFFFFull);
   const unsigned k1 = static_cast<unsigned>(seed >> 32);
   const long long* nr = reinterpret_cast<const long long*>(nr_slot);
-  long long* off = reinterpret_cast<long long*>(ws.chunk_off);
-  long long* ctl = reinterpret_cast<long long*>(ws.ctl);
-  if (!ws.chunk_off || !ws.part || !ws.ctl) return hipErrorInvalidValue;   // scratch required
-  k_walk_scan<<<1, kScanThreads, 0, st>>>(kbeg, kend, nr, off, ws.capacity, ctl);
+  long long* off = reinterpret_cast<long long*>(ts.chunk_off);
+  long long* ctl = reinterpret_cast<long long*>(ts.ctl);
+  if (!ts.chunk_off || !ts.part || !ts.ctl) return hipErrorInvalidValue;   // scratch required
+  const unsigned nb = static_cast<unsigned>(blocks.nb);
+  SC_DISPATCH_B(B, (k_walk_scan<kB><<<nb, kScanThreads, 0, st>>>(blocks, nr, off, ts.capacity, ctl)));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  SC_DISPATCH_B(B, (k_walks_flat<T, kB><<<kWalkBlocks, kThreads, 0, st>>>(
-                        kbeg, kend, s0, tilde, k0, k1, g.rowptr, g.col, g.slot_row, g.inv_deg_d,
-                        Y, tau_slot, nr, off, ctl, ws.part, gacc)));
+  // kWalkBlocks workgroups in all, at least 128 per block
+  const dim3 grid(std::max<unsigned>(128, kWalkBlocks / nb), nb);
+  SC_DISPATCH_B(B, (k_walks_flat<T, kB><<<grid, kThreads, 0, st>>>(
+                        blocks, tilde, k0, k1, g.rowptr, g.col, g.slot_row, g.inv_deg_d, Y,
+                        ystride, tau_slot, nr, off, ctl, ts.part, ts.capacity, gacc)));
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  FinishJob f;
-  f.kbeg = kbeg;
-  f.kend = kend;
-  f.nr = nr_slot;
-  f.chunk_off = ws.chunk_off;
-  f.ctl = ws.ctl;
-  f.part = ws.part;
-  f.gacc = gacc;
-  if (defer) {
-    *defer = f;
-    return hipSuccess;
-  }
-  return launch_walk_finish(f, st);
+  SC_DISPATCH_B(B, (k_walk_finish<kB><<<dim3(grid_for(slots, 256), nb), 256, 0, st>>>(
+                        blocks, nr, off, ctl, ts.part, ts.capacity, gacc)));
+  return hipGetLastError();
 }
 
 // The nodes visited by walk pair r of half-edge (i, j): thread 0 walks from i
@@ -929,29 +1006,19 @@ hipError_t launch_walk_trace(const DeviceGraph& g, int i, int j, uint32_t r, int
   return hipGetLastError();
 }
 
-hipError_t launch_walk_finish(const FinishJob& f, hipStream_t st) {
-  if (!f.gacc || f.kend <= f.kbeg) return hipSuccess;
-  k_walk_finish<<<grid_for(f.kend - f.kbeg, 256), 256, 0, st>>>(f);
-  return hipGetLastError();
-}
-
-template hipError_t launch_colstats<float>(const DeviceGraph&, int, int, int, const float*,
-                                           ColStats*, void*, hipStream_t, const AccJob*,
-                                           const FinishJob*);
-template hipError_t launch_colstats<double>(const DeviceGraph&, int, int, int, const double*,
-                                            ColStats*, void*, hipStream_t, const AccJob*,
-                                            const FinishJob*);
-template hipError_t launch_walk_counts<float>(const DeviceGraph&, int, int, int, int, int, int,
-                                              double, int64_t, const float*, const ColStats*,
-                                              const int32_t*, int64_t*, hipStream_t);
-template hipError_t launch_walk_counts<double>(const DeviceGraph&, int, int, int, int, int, int,
-                                               double, int64_t, const double*, const ColStats*,
-                                               const int32_t*, int64_t*, hipStream_t);
-template hipError_t launch_walks<float>(const DeviceGraph&, int, int, int, int, int, uint64_t,
-                                        const float*, const int32_t*, const int64_t*, double*,
-                                        const WalkScratch&, hipStream_t, FinishJob*);
-template hipError_t launch_walks<double>(const DeviceGraph&, int, int, int, int, int, uint64_t,
-                                         const double*, const int32_t*, const int64_t*, double*,
-                                         const WalkScratch&, hipStream_t, FinishJob*);
+#define SC_INSTANTIATE(T)                                                                       \
+  template hipError_t launch_colstats<T>(const DeviceGraph&, const BlockList&, int, int,        \
+                                         const T*, int64_t, const TailScratch&, hipStream_t,    \
+                                         const AccJob*);                                        \
+  template hipError_t launch_walk_counts<T>(const DeviceGraph&, const BlockList&, int, int,     \
+                                            int, double, int64_t, const T*, int64_t,            \
+                                            const TailScratch&, const int32_t*, int64_t*,       \
+                                            hipStream_t);                                       \
+  template hipError_t launch_walks<T>(const DeviceGraph&, const BlockList&, int, int, uint64_t, \
+                                      const T*, int64_t, const int32_t*, const int64_t*,        \
+                                      double*, const TailScratch&, hipStream_t);
+SC_INSTANTIATE(float)
+SC_INSTANTIATE(double)
+#undef SC_INSTANTIATE
 
 }  // namespace sc

@@ -1,18 +1,22 @@
-// Deterministic traversal kernels (Algorithm 2) for a block of B sources.
+// Deterministic traversal kernels (Algorithm 2) for blocks of B sources.
 //
-// Layout: the block state Y is node-major, Y[x * B + c] = p_l(x, s0 + c), so
+// Layout: a block's state Y is node-major, Y[x * B + c] = p_l(x, s0 + c), so
 // gathering a neighbour row reads B contiguous values.  Every floating-point
 // reduction has a fixed order (no floating-point atomics), so results are
-// bit-reproducible.  A row with at most kChunk neighbours is one wave's task;
-// a heavier row is one workgroup's task (its four waves take interleaved
+// bit-reproducible: a row with at most kChunk neighbours adds them in slot
+// order; a heavier row is one workgroup's task (its four waves take interleaved
 // 64-slot pieces and add their sums in wave order through LDS); a row above
 // kGiant neighbours is cut into workgroup chunks whose partial sums a fix-up
 // pass adds in chunk order.
+//
+// B = 64 runs a group of blocks per launch (k_step).  B = 16 and 32 run one
+// block per launch (k_twohop, k_propagate).
 #include "sc_internal.hpp"
 #include "accumulate.hpp"
 #include <hip/hip_ext.h>
 #include "tau.hpp"
 
+#include <algorithm>
 #include <cfloat>
 #include <climits>
 
@@ -191,22 +195,24 @@ __global__ __launch_bounds__(256) void k_ritz(int64_t n, int64_t ld, const doubl
 }
 
 // ------------------------------------------------------------------ indicator masks
-// Waves [0, B) mark bit c of mask[u] (and the node's bit in anymask) for every
-// u in N(s_set + c) in buffer `buf`; waves [B, 2B) clear what block s_clear
-// marked in the other buffer.  Each buffer only ever holds one block's bits,
-// so clearing may zero whole words.
-__device__ inline void mask_update_wave(int w, int lane, int n, const MaskJob& mj,
+// Wave w of the set part marks bit c of mask[u] (and the node's bit in the
+// filter) for every u in N(s0 + c), c = w mod B, of block w / B of `set` in mask
+// set `buf`; the waves after them zero what the blocks of `clear` marked in the
+// other set.  A block's words only ever hold that block's bits, so clearing may
+// zero whole words.
+__device__ inline void mask_update_wave(int w, int lane, int n, int B, const MaskJob& mj,
                                         const int32_t* __restrict__ rowptr,
                                         const int32_t* __restrict__ col) {
-  if (w >= 2 * mj.B) return;
-  const bool set = w < mj.B;
-  const int c = set ? w : w - mj.B;
-  const int sb = set ? mj.s_set : mj.s_clear;
-  const int s = sb + c;
-  if (sb < 0 || s >= n) return;
-  const int b = set ? mj.buf : 1 - mj.buf;
-  unsigned long long* mk = mj.mask + static_cast<size_t>(b) * mj.mwords;
-  unsigned* am = mj.anymask + static_cast<size_t>(b) * mj.awords;
+  const bool set = w < mj.set.nb * B;
+  if (!set) w -= mj.set.nb * B;
+  const BlockList& bl = set ? mj.set : mj.clear;
+  const int i = w / B, c = w % B;
+  if (i >= bl.nb) return;
+  const int s = bl.b[i].s0 + c;
+  if (s >= n) return;
+  const int64_t at = static_cast<int64_t>(set ? mj.buf : 1 - mj.buf) * mj.slots + i;
+  unsigned long long* mk = mj.mask + at * n;
+  unsigned* am = mj.anymask + at * mj.awords;
   const unsigned long long bit = 1ull << c;
   for (int k = rowptr[s] + lane; k < rowptr[s + 1]; k += 64) {
     const int u = col[k];
@@ -220,9 +226,9 @@ __device__ inline void mask_update_wave(int w, int lane, int n, const MaskJob& m
   }
 }
 
-__global__ void k_mask_update(int n, MaskJob mj, const int32_t* __restrict__ rowptr,
+__global__ void k_mask_update(int n, int B, MaskJob mj, const int32_t* __restrict__ rowptr,
                               const int32_t* __restrict__ col) {
-  mask_update_wave(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6), threadIdx.x & 63, n, mj,
+  mask_update_wave(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6), threadIdx.x & 63, n, B, mj,
                    rowptr, col);
 }
 
@@ -250,43 +256,41 @@ __device__ inline double bcast(double v, int jj) {
 // Pointers the row kernels need (passed by value).
 template <typename T>
 struct RowArgs {
-  const Task* tasks;          // wave tasks: one light row each (used when B < 64)
+  const Task* tasks;          // wave tasks: one light row each (B < 64)
   int ntasks;
-  const Task* ptasks;         // wave tasks: runs of consecutive light rows (B = 64)
-  int nptasks;
-  const int32_t* rowptr;
   const Task* wg_tasks;       // workgroup tasks (heavy rows, giant-row chunks)
   int nwg;
-  int row_blocks;             // nwg + workgroups of wave tasks
   const int32_t* col;
   const T* inv_deg;
   T* partials;
-  // fused accumulation of the previous step (workgroups after row_blocks)
-  const int32_t* slot_row;
-  const double* inv_deg_d;
-  AccJob acc;
-  // rows known to be zero in Yp (nz[u] == 0, B = 64 only)
-  const uint8_t* nz;
-  // the next block's mask update (workgroups after the accumulation)
-  int acc_blocks;
-  MaskJob mj;
-  int n;
 };
 
-// gacc[k] += (Y[s][c] - Y[j][c]) / d_s for slot k = (s -> j), l <= tau_k (Eq. 9)
+// Workgroup a of the accumulation of the blocks in `list`: block by the prefix
+// of their workgroup counts, one slot per thread.
 template <typename T, int B>
-__device__ inline void accumulate_slot(const RowArgs<T>& a, const T* Y, int k) {
-  accumulate_half<T, B>(a.acc, a.slot_row, a.col, a.inv_deg_d, Y, k);
+__device__ inline void accumulate_group(const AccJob& acc, const int32_t* __restrict__ slot_row,
+                                        const int32_t* __restrict__ col,
+                                        const double* __restrict__ inv_deg_d, const T* Y,
+                                        int64_t ystride, int a) {
+  int i = 0;
+  while (i + 1 < acc.list.nb && a >= acc.wg0[i + 1]) ++i;   // uniform per workgroup
+  const BlockRef br = acc.list.b[i];
+  const int k = br.kbeg + (a - acc.wg0[i]) * kThreads + static_cast<int>(threadIdx.x);
+  if (k < br.kend)
+    accumulate_half<T, B>(acc, br.s0, slot_row, col, inv_deg_d, Y + br.buf * ystride, k);
 }
 
 // Sum over the 64-slot pieces first, first + step, ... of [beg, end) of the
 // neighbour rows of Yp (column c); lanes c, c+B, ... share a column and are
-// combined at the end.
+// combined at the end.  kSkip (B = 64): rows whose flags in nz (nslices arrays of
+// n bytes) are all zero are exact zeros in Yp and are not gathered.
 template <typename T, int B, bool kSkip = false>
 __device__ inline T gather_pieces(const RowArgs<T>& a, const T* __restrict__ Yp, int beg, int end,
-                                  int first, int step, int lane, int c, int gq) {
+                                  int first, int step, int lane, int c, int gq,
+                                  const uint8_t* nz = nullptr, int n = 0) {
   constexpr int G = 64 / B;
   constexpr int kBatch = sizeof(T) == 4 ? 32 : 16;   // gathers in flight per lane
+  constexpr int kSlices = static_cast<int>(sizeof(T)) / 2;   // of 128 bytes per 64-column row
   static_assert(!kSkip || G == 1, "zero-row skipping needs one column per lane");
   T acc = T(0);
   for (int base = beg + 64 * first; base < end; base += 64 * step) {
@@ -295,7 +299,12 @@ __device__ inline T gather_pieces(const RowArgs<T>& a, const T* __restrict__ Yp,
     if (kSkip) {
       // gather only the slots whose row is nonzero, in slot order: the skipped
       // rows are exact zeros, so the sum is that of the full slot loop
-      unsigned long long rem = __ballot(lane < cnt && a.nz[myu]);
+      unsigned any = 0;
+      if (lane < cnt) {
+#pragma unroll
+        for (int q = 0; q < kSlices; ++q) any |= nz[static_cast<size_t>(q) * n + myu];
+      }
+      unsigned long long rem = __ballot(any != 0);
       while (rem) {
         T v[kBatch];
 #pragma unroll
@@ -376,86 +385,6 @@ __device__ inline T twohop_pieces(const RowArgs<T>& a, const unsigned long long*
   return reduce_groups<T, B>(acc);
 }
 
-// A run of consecutive light rows with at most 64 slots in total (B = 64):
-// one coalesced load of their neighbour lists, all gathers in flight, and the
-// row sums closed in slot order (the same order as the one-row path).
-template <typename T, int B>
-__device__ inline void gather_run(const RowArgs<T>& a, const T* __restrict__ Yp, const Task& tk,
-                                  int lane, T* __restrict__ Yn) {
-  constexpr int kBatch = sizeof(T) == 4 ? 32 : 16;
-  const int nrows = tk.part;
-  const int cnt = tk.end - tk.beg;
-  const int myu = lane < cnt ? a.col[tk.beg + lane] : 0;
-  const int myend = lane < nrows ? a.rowptr[tk.row + lane + 1] - tk.beg : 0;
-  const T myinv = lane < nrows ? a.inv_deg[tk.row + lane] : T(0);
-  T acc = T(0);
-  int ri = 0;
-  int bnd = __builtin_amdgcn_readlane(myend, 0);
-  for (int jj = 0; jj < cnt; jj += kBatch) {
-    T v[kBatch];
-#pragma unroll
-    for (int q = 0; q < kBatch; ++q) {
-      const int l = jj + q;
-      const int u = __builtin_amdgcn_readlane(myu, l & 63);
-      v[q] = l < cnt ? Yp[static_cast<size_t>(u) * B + lane] : T(0);
-    }
-#pragma unroll
-    for (int q = 0; q < kBatch; ++q) {
-      const int l = jj + q;
-      if (l < cnt) {
-        acc += v[q];
-        if (l + 1 == bnd) {
-          Yn[static_cast<size_t>(tk.row + ri) * B + lane] = acc * bcast(myinv, ri);
-          acc = T(0);
-          ++ri;
-          bnd = __builtin_amdgcn_readlane(myend, ri & 63);
-        }
-      }
-    }
-  }
-}
-
-template <typename T, int B>
-__device__ inline void twohop_run(const RowArgs<T>& a, const unsigned long long* __restrict__ mask,
-                                  const unsigned* __restrict__ anymask, const Task& tk, int lane,
-                                  T* __restrict__ Y, uint8_t* __restrict__ nzw) {
-  const int nrows = tk.part;
-  const int cnt = tk.end - tk.beg;
-  const int myu = lane < cnt ? a.col[tk.beg + lane] : 0;
-  const int myend = lane < nrows ? a.rowptr[tk.row + lane + 1] - tk.beg : 0;
-  const T myinv = lane < nrows ? a.inv_deg[tk.row + lane] : T(0);
-  const bool hit = lane < cnt && ((anymask[myu >> 5] >> (myu & 31)) & 1u);
-  const unsigned long long mym = hit ? mask[myu] : 0ull;
-  const T myw = hit ? a.inv_deg[myu] : T(0);
-  const unsigned long long hits = __ballot(hit);
-  const int mlo = static_cast<int>(mym & 0xFFFFFFFFull);
-  const int mhi = static_cast<int>(mym >> 32);
-  // row by row, visiting only the slots some column marks (in slot order, so
-  // the sums are those of the full slot loop: the other slots add nothing)
-  int rbeg = 0;
-  for (int ri = 0; ri < nrows; ++ri) {
-    const int rend = __builtin_amdgcn_readlane(myend, ri);
-    const unsigned long long below_end = rend >= 64 ? ~0ull : ((1ull << rend) - 1ull);
-    const unsigned long long below_beg = (1ull << rbeg) - 1ull;   // rbeg < 64
-    unsigned long long rh = hits & below_end & ~below_beg;
-    T acc = T(0);
-    while (rh) {
-      const int l = __builtin_ctzll(rh);
-      rh &= rh - 1ull;
-      const unsigned long long mk =
-          (static_cast<unsigned long long>(static_cast<unsigned>(__builtin_amdgcn_readlane(mhi, l))) << 32) |
-          static_cast<unsigned>(__builtin_amdgcn_readlane(mlo, l));
-      if ((mk >> lane) & 1ull) acc += bcast(myw, l);
-    }
-    Y[static_cast<size_t>(tk.row + ri) * B + lane] = acc * bcast(myinv, ri);
-    if (nzw) {
-      const bool any = __ballot(acc != T(0)) != 0ull;
-      if (lane == 0) nzw[tk.row + ri] = any ? 1 : 0;
-    }
-    rbeg = rend;
-  }
-}
-
 // Workgroup task: the four waves' sums are added in wave order; a whole row
 // is scaled by 1/d and stored, a giant-row chunk goes to its partial row.
 template <typename T, int B>
@@ -475,12 +404,283 @@ __device__ inline void wg_finish(const RowArgs<T>& a, const Task& tk, T sum, int
   }
 }
 
-// ------------------------------------------------------------------ Y2 from masks
+// ------------------------------------------------------------------ one step of a group, B = 64
+// A block's state is cut into slices of 128 bytes per row (32 FP32 or 16 FP64
+// columns: one cache line), and a slice's light rows are one XCD's work: workgroup
+// w runs on XCD w mod 8 and takes slice w mod 8 (+ 8, 16, ...) of the launch, so
+// each XCD's 4 MB L2 holds one slice of one block at a time instead of parts of
+// whole rows of the same block in all eight.  BA, n = 34,401, 12 edges per node
+// (a slice is 4.4 MB): 25 -> 9 us per step and block; n = 100,000 (12.8 MB): 63 ->
+// 45 us, where the bound stays the rate of rows fetched past L2.
+//
+// Light rows are read through the sliced lists of DeviceGraph (rows sorted by
+// degree in groups of 8): a wave takes a group, 8 lanes x 16 bytes per row, so one
+// load instruction fetches the neighbours of 8 rows; the ids of 8 rows x 8 slots
+// are one coalesced load, spread within each row's lanes by ds_swizzle.  Padding
+// (id n) and, in kSkip, rows the two-hop step flagged zero issue no load.
+//
+// A launch covers every block of a group (up to kMaxGroup): the launch and drain of
+// a step and its longest row's chain of dependent loads are paid once per group.
+enum StepMode { kFull, kSkip, kTwoHop };
+
+template <typename T>
+struct StepArgs {
+  int n;
+  int nslices;                 // slices of the launch: blocks.nb * slices per block
+  int slice_wgs;               // workgroups per slice
+  int heavy_wgs;               // workgroups of the heavy tasks (multiple of 8, before the slices)
+  int light_wgs;               // workgroups of the slices
+  int acc_wgs;                 // workgroups of the accumulation, then the mask update
+  const int2* grp;             // [ngrp] (first id word, padded width)
+  int ngrp;
+  const int32_t* grow;         // [ngrp * 8] rows (n: none)
+  const T* ginv;               // [ngrp * 8] 1/degree
+  const int32_t* gnb;          // ids
+  const T* Yp;                 // state at l - 1 / at l, block buf at buf * ystride
+  T* Yn;
+  int64_t ystride;
+  uint8_t* nz;                 // [buf][slice][n]: row flags of the two-hop state
+  const unsigned long long* mask;   // [i][n], i = position of the block in the group
+  const unsigned* anymask;
+  int64_t awords;
+  const T* inv;                // [n] 1/degree by node
+  int part_rows;               // partial-sum rows per block
+  RowArgs<T> row;
+  BlockList blocks;
+  AccJob acc;                  // accumulation of the states in Yp (list.nb == 0: none)
+  const int32_t* slot_row;
+  const double* inv_deg_d;
+  const int32_t* rowptr;
+  MaskJob mj;
+};
+
+// lane of row r (8 lanes), step k: the value the row's lane k holds
+template <int k>
+__device__ inline int row_lane(int v) {
+  return __builtin_amdgcn_ds_swizzle(v, 0x18 | (k << 5));
+}
+template <int k>
+__device__ inline float row_lane_f(float v) {
+  return __int_as_float(row_lane<k>(__float_as_int(v)));
+}
+template <int k>
+__device__ inline double row_lane_f(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = row_lane<k>(static_cast<int>(b & 0xFFFFFFFFll));
+  const int hi = row_lane<k>(static_cast<int>(b >> 32));
+  return __longlong_as_double((static_cast<long long>(hi) << 32) |
+                              static_cast<long long>(static_cast<unsigned>(lo)));
+}
+
+template <typename T>
+struct alignas(16) Vec16 {
+  T v[16 / sizeof(T)];
+};
+
+// Loads of one chunk: the rows of ids (8 per row group lane set) in flight at once.
+template <typename T, int k>
+__device__ inline void load_step(const char* Yp, int ids, int n, uint32_t coff, Vec16<T>& out) {
+  constexpr uint32_t kRow = 64 * sizeof(T);
+  const int u = row_lane<k>(ids);
+  if (u < n) {
+    out = *reinterpret_cast<const Vec16<T>*>(Yp + (static_cast<size_t>(static_cast<uint32_t>(u)) * kRow + coff));
+  } else {
+#pragma unroll
+    for (int e = 0; e < static_cast<int>(16 / sizeof(T)); ++e) out.v[e] = T(0);
+  }
+}
+
+template <typename T>
+__device__ inline void load_chunk(const char* Yp, int ids, int n, uint32_t coff, Vec16<T> (&v)[8]) {
+  load_step<T, 0>(Yp, ids, n, coff, v[0]);
+  load_step<T, 1>(Yp, ids, n, coff, v[1]);
+  load_step<T, 2>(Yp, ids, n, coff, v[2]);
+  load_step<T, 3>(Yp, ids, n, coff, v[3]);
+  load_step<T, 4>(Yp, ids, n, coff, v[4]);
+  load_step<T, 5>(Yp, ids, n, coff, v[5]);
+  load_step<T, 6>(Yp, ids, n, coff, v[6]);
+  load_step<T, 7>(Yp, ids, n, coff, v[7]);
+}
+
+template <typename T>
+__device__ inline void add_chunk(const Vec16<T> (&v)[8], T (&acc)[16 / sizeof(T)]) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+#pragma unroll
+    for (int e = 0; e < static_cast<int>(16 / sizeof(T)); ++e) acc[e] += v[k].v[e];
+}
+
+// two-hop: neighbour u adds 1/d_u to the columns whose source it is joined to
+template <typename T, int k>
+__device__ inline void twohop_step(unsigned m, T w, int c, T (&acc)[16 / sizeof(T)]) {
+  constexpr int V = 16 / sizeof(T);
+  const unsigned mk = static_cast<unsigned>(row_lane<k>(static_cast<int>(m))) >> (c * V);
+  const T wk = row_lane_f<k>(w);
+#pragma unroll
+  for (int e = 0; e < V; ++e) acc[e] += ((mk >> e) & 1u) ? wk : T(0);
+}
+
+template <typename T, int MODE>
+__device__ inline void light_rows(const StepArgs<T>& a, int sl, int wg, int lane, int wave) {
+  constexpr int V = 16 / sizeof(T);        // columns per lane
+  constexpr int C = 8 * V;                 // columns per slice
+  constexpr int kSlices = 64 / C;          // slices per block
+  const int gi = wg * kWavesPerBlock + wave;
+  if (gi >= a.ngrp) return;
+  const int i = sl / kSlices, h = sl % kSlices;
+  const int buf = a.blocks.b[i].buf;
+  const int n = a.n;
+  const int2 g = a.grp[gi];
+  const int r = lane >> 3, c = lane & 7;
+  const int row = a.grow[gi * 8 + r];
+  const T iv = a.ginv[gi * 8 + r];
+  const int32_t* __restrict__ p = a.gnb + g.x + lane;
+  const int nch = g.y >> 3;
+  T acc[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) acc[e] = T(0);
+  const uint32_t coff = static_cast<uint32_t>(h * 128 + c * 16);
+  if constexpr (MODE == kTwoHop) {
+    const unsigned long long* __restrict__ mask = a.mask + static_cast<size_t>(i) * n;
+    const unsigned* __restrict__ am = a.anymask + static_cast<size_t>(i) * a.awords;
+    for (int ch = 0; ch < nch; ++ch) {
+      const int u = p[ch * 64];
+      // the small bitmap filters out the neighbours no column marks
+      const bool hit = u < n && ((am[u >> 5] >> (u & 31)) & 1u);
+      unsigned m = 0;
+      if (hit) m = static_cast<unsigned>(mask[u] >> (h * C)) & (C == 32 ? 0xFFFFFFFFu : ((1u << (C & 31)) - 1u));
+      if (__ballot(m != 0) == 0ull) continue;
+      const T w = m ? a.inv[u] : T(0);
+      twohop_step<T, 0>(m, w, c, acc);
+      twohop_step<T, 1>(m, w, c, acc);
+      twohop_step<T, 2>(m, w, c, acc);
+      twohop_step<T, 3>(m, w, c, acc);
+      twohop_step<T, 4>(m, w, c, acc);
+      twohop_step<T, 5>(m, w, c, acc);
+      twohop_step<T, 6>(m, w, c, acc);
+      twohop_step<T, 7>(m, w, c, acc);
+    }
+  } else {
+    const char* Yp = reinterpret_cast<const char*>(a.Yp + buf * a.ystride);
+    const uint8_t* __restrict__ nz =
+        MODE == kSkip ? a.nz + (static_cast<size_t>(buf) * kSlices + h) * n : nullptr;
+    // two chunks (16 slots of each row) in flight; sums in slot order
+    int ch = 0;
+    for (; ch + 1 < nch; ch += 2) {
+      int i0 = p[ch * 64], i1 = p[ch * 64 + 64];
+      if (MODE == kSkip) {
+        if (i0 < n && !nz[i0]) i0 = n;
+        if (i1 < n && !nz[i1]) i1 = n;
+      }
+      Vec16<T> v0[8], v1[8];
+      load_chunk<T>(Yp, i0, n, coff, v0);
+      load_chunk<T>(Yp, i1, n, coff, v1);
+      add_chunk<T>(v0, acc);
+      add_chunk<T>(v1, acc);
+    }
+    if (ch < nch) {
+      int i0 = p[ch * 64];
+      if (MODE == kSkip && i0 < n && !nz[i0]) i0 = n;
+      Vec16<T> v0[8];
+      load_chunk<T>(Yp, i0, n, coff, v0);
+      add_chunk<T>(v0, acc);
+    }
+  }
+  if (MODE == kTwoHop) {
+    bool any = false;
+#pragma unroll
+    for (int e = 0; e < V; ++e) any |= acc[e] != T(0);
+    const unsigned long long b = __ballot(any);
+    if (c == 0 && row < n)
+      a.nz[(static_cast<size_t>(buf) * kSlices + h) * n + row] = (b >> (8 * r)) & 0xFFull ? 1 : 0;
+  }
+  if (row < n) {
+    Vec16<T> o;
+#pragma unroll
+    for (int e = 0; e < V; ++e) o.v[e] = acc[e] * iv;
+    char* Yn = reinterpret_cast<char*>(a.Yn + buf * a.ystride);
+    *reinterpret_cast<Vec16<T>*>(Yn + (static_cast<size_t>(row) * (64 * sizeof(T)) + coff)) = o;
+  }
+}
+
+// Heavy task of one block: the four waves take interleaved 64-slot pieces, lane =
+// column.
+template <typename T, int MODE>
+__device__ inline void heavy_rows(const StepArgs<T>& a, int i, int t, int lane, int wave) {
+  constexpr int kSlices = static_cast<int>(sizeof(T)) / 2;
+  const int buf = a.blocks.b[i].buf;
+  const Task tk = a.row.wg_tasks[t];
+  uint8_t* nz = a.nz + static_cast<size_t>(buf) * kSlices * a.n;
+  RowArgs<T> ra = a.row;
+  ra.partials += static_cast<size_t>(buf) * a.part_rows * 64;
+  T sum;
+  if constexpr (MODE == kTwoHop) {
+    sum = twohop_pieces<T, 64>(ra, a.mask + static_cast<size_t>(i) * a.n,
+                               a.anymask + static_cast<size_t>(i) * a.awords, tk.beg, tk.end, wave,
+                               kWavesPerBlock, lane, lane, 0);
+    if (static_cast<int>(threadIdx.x) < kSlices)   // heavy rows count as nonzero
+      nz[static_cast<size_t>(threadIdx.x) * a.n + tk.row] = 1;
+  } else {
+    sum = gather_pieces<T, 64, MODE == kSkip>(ra, a.Yp + buf * a.ystride, tk.beg, tk.end, wave,
+                                              kWavesPerBlock, lane, lane, 0, nz, a.n);
+  }
+  wg_finish<T, 64>(ra, tk, sum, wave, lane, a.Yn + buf * a.ystride);
+}
+
+template <typename T, int MODE>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_step(StepArgs<T> a) {
+  constexpr int kSlices = static_cast<int>(sizeof(T)) / 2;
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  int w = static_cast<int>(blockIdx.x);
+  const int nb = a.blocks.nb;
+  if (w < a.heavy_wgs) {
+    // a block's heavy tasks on the XCDs that take its slices, where the counts divide
+    int i, t;
+    if (nb <= 8 && 8 % nb == 0) {
+      const int k = 8 / nb;
+      i = (w & 7) / k;
+      t = (w >> 3) * k + (w & 7) % k;
+    } else {
+      i = w % nb;
+      t = w / nb;
+    }
+    if (t < a.row.nwg) heavy_rows<T, MODE>(a, i, t, lane, wave);
+    return;
+  }
+  w -= a.heavy_wgs;
+  if (w < a.light_wgs) {
+    const int x = w & 7, j = w >> 3;
+    const int rounds = a.nslices >> 3, rem = a.nslices & 7;
+    int sl, wg;
+    if (j < rounds * a.slice_wgs) {
+      sl = x + 8 * (j / a.slice_wgs);
+      wg = j % a.slice_wgs;
+    } else {   // the last rem < 8 slices, each on 8, 4, 2 or 1 XCDs
+      const int k = rem > 4 ? 1 : rem > 2 ? 2 : rem > 1 ? 4 : 8;
+      if (x / k >= rem) return;
+      sl = 8 * rounds + x / k;
+      wg = (j - rounds * a.slice_wgs) * k + x % k;
+    }
+    light_rows<T, MODE>(a, sl, wg, lane, wave);
+    return;
+  }
+  w -= a.light_wgs;
+  if (w < a.acc_wgs) {
+    accumulate_group<T, 64>(a.acc, a.slot_row, a.row.col, a.inv_deg_d, a.Yp, a.ystride, w);
+    return;
+  }
+  mask_update_wave((w - a.acc_wgs) * kWavesPerBlock + wave, lane, a.n, 64, a.mj, a.rowptr,
+                   a.row.col);
+  (void)kSlices;
+}
+
+// ------------------------------------------------------------------ one step of a block, B < 64
 template <typename T, int B>
 __global__ __launch_bounds__(kThreads) void k_twohop(RowArgs<T> a,
                                                      const unsigned long long* __restrict__ mask,
                                                      const unsigned* __restrict__ anymask,
-                                                     T* __restrict__ Y, uint8_t* __restrict__ nzw) {
+                                                     T* __restrict__ Y) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int c = lane % B;
@@ -488,151 +688,84 @@ __global__ __launch_bounds__(kThreads) void k_twohop(RowArgs<T> a,
   if (static_cast<int>(blockIdx.x) < a.nwg) {
     const Task tk = a.wg_tasks[blockIdx.x];
     const T sum = twohop_pieces<T, B>(a, mask, anymask, tk.beg, tk.end, wave, kWavesPerBlock, lane, c, gq);
-    wg_finish<T, B>(a, tk, sum, wave, lane, Y);   // heavy rows keep their flag (1)
+    wg_finish<T, B>(a, tk, sum, wave, lane, Y);
     return;
   }
   const int t = (blockIdx.x - a.nwg) * kWavesPerBlock + wave;
-  if (B == 64) {
-    if (t >= a.nptasks) return;
-    const Task tk = a.ptasks[t];
-    if (tk.end - tk.beg <= 64) {
-      twohop_run<T, B>(a, mask, anymask, tk, lane, Y, nzw);
-      return;
-    }
-    const T sum = twohop_pieces<T, B>(a, mask, anymask, tk.beg, tk.end, 0, 1, lane, c, gq);
-    Y[static_cast<size_t>(tk.row) * B + c] = sum * a.inv_deg[tk.row];
-    if (nzw) {
-      const bool any = __ballot(sum != T(0)) != 0ull;
-      if (lane == 0) nzw[tk.row] = any ? 1 : 0;
-    }
-    return;
-  }
   if (t >= a.ntasks) return;
   const Task tk = a.tasks[t];
   const T sum = twohop_pieces<T, B>(a, mask, anymask, tk.beg, tk.end, 0, 1, lane, c, gq);
   if (gq == 0) Y[static_cast<size_t>(tk.row) * B + c] = sum * a.inv_deg[tk.row];
 }
 
-// gather_run when the rows flagged zero in nz are exact zeros: only the slots
-// of nonzero rows are gathered; each row's sum still closes in slot order and
-// rows whose slots are all skipped are written as zeros.
+// Workgroups [0, nwg): heavy rows and giant-row chunks; then wave tasks.
 template <typename T, int B>
-__device__ inline void gather_run_skip(const RowArgs<T>& a, const T* __restrict__ Yp,
-                                       const Task& tk, int lane, T* __restrict__ Yn) {
-  constexpr int kBatch = sizeof(T) == 4 ? 32 : 16;
-  const int nrows = tk.part;
-  const int cnt = tk.end - tk.beg;
-  const int myu = lane < cnt ? a.col[tk.beg + lane] : 0;
-  const int myend = lane < nrows ? a.rowptr[tk.row + lane + 1] - tk.beg : 0;
-  const T myinv = lane < nrows ? a.inv_deg[tk.row + lane] : T(0);
-  unsigned long long rem = __ballot(lane < cnt && a.nz[myu]);
-  T acc = T(0);
-  int ri = 0;
-  int bnd = __builtin_amdgcn_readlane(myend, 0);
-  while (rem) {
-    T v[kBatch];
-    int sl[kBatch];   // wave-uniform slot of each gather, 64 = none
-#pragma unroll
-    for (int q = 0; q < kBatch; ++q) {
-      v[q] = T(0);
-      sl[q] = 64;
-      if (rem) {
-        const int l = __builtin_ctzll(rem);
-        rem &= rem - 1ull;
-        const int u = __builtin_amdgcn_readlane(myu, l);
-        v[q] = Yp[static_cast<size_t>(u) * B + lane];
-        sl[q] = l;
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < kBatch; ++q) {
-      if (sl[q] < 64) {
-        while (bnd <= sl[q]) {   // close the rows that end before this slot
-          Yn[static_cast<size_t>(tk.row + ri) * B + lane] = acc * bcast(myinv, ri);
-          acc = T(0);
-          ++ri;
-          bnd = __builtin_amdgcn_readlane(myend, ri & 63);
-        }
-        acc += v[q];
-      }
-    }
-  }
-  for (; ri < nrows; ++ri) {
-    Yn[static_cast<size_t>(tk.row + ri) * B + lane] = acc * bcast(myinv, ri);
-    acc = T(0);
-  }
-}
-
-// ------------------------------------------------------------------ dense propagation
-// Workgroups [0, nwg): heavy rows and giant-row chunks; then wave tasks; then
-// the accumulation of the step held in Yp (fused, saves a launch).  Register
-// use is held to 6 waves per SIMD: more waves with shallower gather batches run
-// the kernel faster alone but slow the concurrent tail of the block pipeline.
-// kSkip (B = 64): rows with nz[u] == 0 are exact zeros in Yp and are not gathered.
-template <typename T, int B, bool kSkip>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_propagate(RowArgs<T> a, const T* __restrict__ Yp,
                                                         T* __restrict__ Yn) {
-  if (static_cast<int>(blockIdx.x) >= a.row_blocks) {
-    const int t = blockIdx.x - a.row_blocks;
-    if (t < a.acc_blocks) {
-      accumulate_slot<T, B>(a, Yp, a.acc.kbeg + t * kThreads + threadIdx.x);
-    } else {
-      mask_update_wave((t - a.acc_blocks) * kWavesPerBlock + (threadIdx.x >> 6),
-                       threadIdx.x & 63, a.n, a.mj, a.rowptr, a.col);
-    }
-    return;
-  }
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int c = lane % B;
   const int gq = lane / B;
   if (static_cast<int>(blockIdx.x) < a.nwg) {
     const Task tk = a.wg_tasks[blockIdx.x];
-    const T sum =
-        gather_pieces<T, B, kSkip>(a, Yp, tk.beg, tk.end, wave, kWavesPerBlock, lane, c, gq);
+    const T sum = gather_pieces<T, B>(a, Yp, tk.beg, tk.end, wave, kWavesPerBlock, lane, c, gq);
     wg_finish<T, B>(a, tk, sum, wave, lane, Yn);
     return;
   }
   const int t = (blockIdx.x - a.nwg) * kWavesPerBlock + wave;
-  if (B == 64) {
-    if (t >= a.nptasks) return;
-    const Task tk = a.ptasks[t];
-    if (tk.end - tk.beg <= 64) {
-      if (kSkip)
-        gather_run_skip<T, B>(a, Yp, tk, lane, Yn);
-      else
-        gather_run<T, B>(a, Yp, tk, lane, Yn);
-      return;
-    }
-    const T sum = gather_pieces<T, B, kSkip>(a, Yp, tk.beg, tk.end, 0, 1, lane, c, gq);
-    Yn[static_cast<size_t>(tk.row) * B + c] = sum * a.inv_deg[tk.row];
-    return;
-  }
   if (t >= a.ntasks) return;
   const Task tk = a.tasks[t];
   const T sum = gather_pieces<T, B>(a, Yp, tk.beg, tk.end, 0, 1, lane, c, gq);
   if (gq == 0) Yn[static_cast<size_t>(tk.row) * B + c] = sum * a.inv_deg[tk.row];
 }
 
-// Giant rows: Y[row] = inv_deg[row] * (sum of the chunk partials in chunk order).
+// Giant rows: Y[row] = inv_deg[row] * (sum of the chunk partials in chunk order),
+// for block blockIdx.y of the list.
 template <typename T, int B>
 __global__ __launch_bounds__(kThreads) void k_fixup(const HeavyRow* __restrict__ giant, int ngiant,
                                                     const T* __restrict__ inv_deg,
-                                                    const T* __restrict__ partials,
-                                                    T* __restrict__ Y) {
+                                                    const T* __restrict__ partials, int part_rows,
+                                                    T* __restrict__ Y, int64_t ystride,
+                                                    BlockList blocks) {
   const int lane = threadIdx.x & 63;
   const int h = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   if (h >= ngiant || lane >= B) return;
+  const int buf = blocks.b[blockIdx.y].buf;
+  const T* pp = partials + static_cast<size_t>(buf) * part_rows * B;
   const HeavyRow hr = giant[h];
   T acc = T(0);
-  for (int p = 0; p < hr.nparts; ++p) acc += partials[static_cast<size_t>(hr.part0 + p) * B + lane];
-  Y[static_cast<size_t>(hr.row) * B + lane] = acc * inv_deg[hr.row];
+  for (int p = 0; p < hr.nparts; ++p) acc += pp[static_cast<size_t>(hr.part0 + p) * B + lane];
+  Y[buf * ystride + static_cast<size_t>(hr.row) * B + lane] = acc * inv_deg[hr.row];
 }
 
-// standalone accumulation (the last step of a block)
+// standalone accumulation (the last step of a group)
 template <typename T, int B>
-__global__ void k_accumulate(RowArgs<T> a, const T* __restrict__ Y) {
-  accumulate_slot<T, B>(a, Y, a.acc.kbeg + blockIdx.x * blockDim.x + threadIdx.x);
+__global__ __launch_bounds__(kThreads) void k_accumulate(AccJob acc, const int32_t* __restrict__ slot_row,
+                                                         const int32_t* __restrict__ col,
+                                                         const double* __restrict__ inv_deg_d,
+                                                         const T* __restrict__ Y, int64_t ystride) {
+  accumulate_group<T, B>(acc, slot_row, col, inv_deg_d, Y, ystride, static_cast<int>(blockIdx.x));
+}
+
+// ------------------------------------------------------------------ sliced lists (B = 64)
+// Word (group g, chunk q, row r, k) of the lists: neighbour 8 q + k of the group's
+// row r, or n past its degree.
+__global__ __launch_bounds__(256) void k_fill_slices(int n, int ngrp, const int2* __restrict__ grp,
+                                                     const int32_t* __restrict__ grow,
+                                                     const int32_t* __restrict__ rowptr,
+                                                     const int32_t* __restrict__ col,
+                                                     int32_t* __restrict__ gnb) {
+  const int gi = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (gi >= ngrp) return;
+  const int2 g = grp[gi];
+  const int row = grow[gi * 8 + (lane >> 3)];
+  const int beg = row < n ? rowptr[row] : 0;
+  const int end = row < n ? rowptr[row + 1] : 0;
+  for (int q = 0; q < (g.y >> 3); ++q) {
+    const int k = beg + 8 * q + (lane & 7);
+    gnb[g.x + q * 64 + lane] = k < end ? col[k] : n;
+  }
 }
 
 // ------------------------------------------------------------------ combine and traces
@@ -735,30 +868,22 @@ hipError_t launch_ritz(int64_t n, int64_t ld, const double* V, int steps, const 
   return hipGetLastError();
 }
 
-MaskJob mask_job(const DeviceGraph& g, int s_set, int s_clear, int B, int buf,
-                 unsigned long long* mask, unsigned* anymask) {
-  MaskJob mj;
-  mj.s_set = s_set;
-  mj.s_clear = s_clear;
-  mj.B = B;
-  mj.buf = buf;
-  mj.mwords = g.n;
-  mj.awords = (g.n + 31) / 32;
-  mj.mask = mask;
-  mj.anymask = anymask;
-  return mj;
-}
-
-hipError_t launch_mask_update(const DeviceGraph& g, int s_set, int s_clear, int B, int buf,
-                              unsigned long long* mask, unsigned* anymask, hipStream_t st) {
-  k_mask_update<<<grid_for(2 * B, kWavesPerBlock), kThreads, 0, st>>>(
-      g.n, mask_job(g, s_set, s_clear, B, buf, mask, anymask), g.rowptr, g.col);
+hipError_t launch_mask_update(const DeviceGraph& g, int B, const MaskJob& mj, hipStream_t st) {
+  const int waves = (mj.set.nb + mj.clear.nb) * B;
+  if (waves == 0) return hipSuccess;
+  k_mask_update<<<grid_for(waves, kWavesPerBlock), kThreads, 0, st>>>(g.n, B, mj, g.rowptr, g.col);
   return hipGetLastError();
 }
 
 #define SC_DISPATCH_B(B, CALL)                        \
   switch (B) {                                        \
     case 64: { constexpr int kB = 64; CALL; } break;  \
+    case 32: { constexpr int kB = 32; CALL; } break;  \
+    case 16: { constexpr int kB = 16; CALL; } break;  \
+    default: return hipErrorInvalidValue;             \
+  }
+#define SC_DISPATCH_B_NARROW(B, CALL)                 \
+  switch (B) {                                        \
     case 32: { constexpr int kB = 32; CALL; } break;  \
     case 16: { constexpr int kB = 16; CALL; } break;  \
     default: return hipErrorInvalidValue;             \
@@ -772,92 +897,137 @@ template <>
 const double* inv_deg_of<double>(const DeviceGraph& g) { return g.inv_deg_d; }
 
 template <typename T>
-RowArgs<T> row_args(const DeviceGraph& g, int B, T* partials, const AccJob& acc) {
+const T* slice_inv_of(const DeviceGraph& g);
+template <>
+const float* slice_inv_of<float>(const DeviceGraph& g) { return g.slice_inv_f; }
+template <>
+const double* slice_inv_of<double>(const DeviceGraph& g) { return g.slice_inv_d; }
+
+template <typename T>
+RowArgs<T> row_args(const DeviceGraph& g, T* partials) {
   RowArgs<T> a;
   a.tasks = g.tasks;
   a.ntasks = g.ntasks;
-  a.ptasks = g.ptasks;
-  a.nptasks = g.nptasks;
-  a.rowptr = g.rowptr;
   a.wg_tasks = g.wg_tasks;
   a.nwg = g.nwg;
-  a.row_blocks = g.nwg + static_cast<int>(grid_for(B == 64 ? g.nptasks : g.ntasks, kWavesPerBlock));
   a.col = g.col;
   a.inv_deg = inv_deg_of<T>(g);
   a.partials = partials;
-  a.slot_row = g.slot_row;
-  a.inv_deg_d = g.inv_deg_d;
-  a.acc = acc;
-  a.nz = nullptr;
-  a.acc_blocks = 0;
-  a.mj = MaskJob{};
-  a.n = g.n;
   return a;
 }
 
-inline int acc_blocks(const AccJob& acc) {
-  return acc_job_set(acc) ? static_cast<int>(grid_for(acc.kend - acc.kbeg, kThreads))
-                                          : 0;
+// fills the prefix of workgroup counts of an accumulation; returns their total
+int plan_acc(AccJob& acc) {
+  int wgs = 0;
+  for (int i = 0; i < acc.list.nb; ++i) {
+    acc.wg0[i] = wgs;
+    wgs += static_cast<int>(grid_for(acc.list.b[i].kend - acc.list.b[i].kbeg, kThreads));
+  }
+  return wgs;
 }
 
-template <typename T>
-hipError_t launch_fixup(const DeviceGraph& g, int B, const T* partials, T* Y, hipStream_t st) {
-  if (g.ngiant == 0) return hipSuccess;
-  SC_DISPATCH_B(B, (k_fixup<T, kB><<<grid_for(g.ngiant, kWavesPerBlock), kThreads, 0, st>>>(
-                        g.giant, g.ngiant, inv_deg_of<T>(g), partials, Y)));
+hipError_t launch_fill_slices(const DeviceGraph& g, hipStream_t st) {
+  if (g.nslice_grp == 0) return hipSuccess;
+  k_fill_slices<<<grid_for(g.nslice_grp, 4), 256, 0, st>>>(g.n, g.nslice_grp, g.slice_grp,
+                                                           g.slice_row, g.rowptr, g.col,
+                                                           g.slice_nb);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_twohop(const DeviceGraph& g, int B, const unsigned long long* mask,
-                         const unsigned* anymask, T* Y, T* partials, uint8_t* nz, hipStream_t st) {
-  const RowArgs<T> a = row_args<T>(g, B, partials, AccJob{});
-  SC_DISPATCH_B(B, (k_twohop<T, kB><<<a.row_blocks, kThreads, 0, st>>>(a, mask, anymask, Y,
-                                                                        B == 64 ? nz : nullptr)));
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_fixup<T>(g, B, partials, Y, st);
-}
-
-template <typename T>
-hipError_t launch_propagate_rows(const DeviceGraph& g, int B, const T* Yp, T* Yn, T* partials,
-                                 const AccJob& acc, hipStream_t st, const uint8_t* nz,
-                                 hipEvent_t ev_start, hipEvent_t ev_stop, const MaskJob* mj) {
-  RowArgs<T> a = row_args<T>(g, B, partials, acc);
-  a.acc_blocks = acc_blocks(acc);
-  int mask_blocks = 0;
-  if (mj && mj->B > 0) {
-    a.mj = *mj;
-    mask_blocks = static_cast<int>(grid_for(2 * mj->B, kWavesPerBlock));
-  }
-  const int blocks = a.row_blocks + a.acc_blocks + mask_blocks;
-  if (B == 64 && nz) {
-    a.nz = nz;
-    hipExtLaunchKernelGGL(k_propagate<T, 64, true>, dim3(blocks), dim3(kThreads), 0, st,
-                          ev_start, ev_stop, 0, a, Yp, Yn);
-  } else {
-    SC_DISPATCH_B(B, (hipExtLaunchKernelGGL(k_propagate<T, kB, false>, dim3(blocks),
-                                            dim3(kThreads), 0, st, ev_start, ev_stop, 0, a, Yp,
-                                            Yn)));
-  }
+hipError_t launch_fixup(const DeviceGraph& g, int B, const BlockList& blocks, const T* partials,
+                        T* Y, int64_t ystride, hipStream_t st) {
+  if (g.ngiant == 0 || blocks.nb == 0) return hipSuccess;
+  const dim3 grid(grid_for(g.ngiant, kWavesPerBlock), blocks.nb);
+  SC_DISPATCH_B(B, (k_fixup<T, kB><<<grid, kThreads, 0, st>>>(g.giant, g.ngiant, inv_deg_of<T>(g),
+                                                              partials, std::max(g.nparts, 1), Y,
+                                                              ystride, blocks)));
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_propagate(const DeviceGraph& g, int B, const T* Yp, T* Yn, T* partials,
-                            const AccJob& acc, hipStream_t st) {
-  const hipError_t e = launch_propagate_rows<T>(g, B, Yp, Yn, partials, acc, st, nullptr);
+hipError_t launch_step(const DeviceGraph& g, int B, const StepJob<T>& job, hipStream_t st) {
+  const bool twohop = job.mask != nullptr;
+  const int64_t awords = (static_cast<int64_t>(g.n) + 31) / 32;
+  const int nb = job.blocks.nb;
+  if (B != 64) {   // one launch per block; accumulation and masks in launches of their own
+    for (int i = 0; i < nb; ++i) {
+      const int64_t off = job.blocks.b[i].buf * job.ystride;
+      const RowArgs<T> a = row_args<T>(
+          g, job.partials + static_cast<size_t>(job.blocks.b[i].buf) * std::max(g.nparts, 1) * B);
+      const unsigned grid = g.nwg + grid_for(g.ntasks, kWavesPerBlock);
+      if (twohop) {
+        SC_DISPATCH_B_NARROW(B, (k_twohop<T, kB><<<grid, kThreads, 0, st>>>(
+                                    a, job.mask + static_cast<size_t>(i) * g.n,
+                                    job.anymask + i * awords, job.Yn + off)));
+      } else {
+        SC_DISPATCH_B_NARROW(B, (hipExtLaunchKernelGGL(k_propagate<T, kB>, dim3(grid),
+                                                       dim3(kThreads), 0, st, job.ev_start,
+                                                       job.ev_stop, 0, a, job.Yp + off,
+                                                       job.Yn + off)));
+      }
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    hipError_t e = launch_accumulate<T>(g, B, job.acc, job.Yp, job.ystride, st);
+    if (e == hipSuccess) e = launch_mask_update(g, B, job.mj, st);
+    if (e == hipSuccess) e = launch_fixup<T>(g, B, job.blocks, job.partials, job.Yn, job.ystride, st);
+    return e;
+  }
+  StepArgs<T> a;
+  a.n = g.n;
+  a.nslices = nb * static_cast<int>(sizeof(T) / 2);
+  a.slice_wgs = static_cast<int>(grid_for(g.nslice_grp, kWavesPerBlock));
+  a.heavy_wgs = (nb * g.nwg + 7) / 8 * 8;
+  const int rem = a.nslices & 7;
+  const int k = rem > 4 ? 1 : rem > 2 ? 2 : rem > 1 ? 4 : 8;
+  a.light_wgs = 8 * (a.nslices >> 3) * a.slice_wgs + (rem ? 8 * ((a.slice_wgs + k - 1) / k) : 0);
+  a.grp = g.slice_grp;
+  a.ngrp = g.nslice_grp;
+  a.grow = g.slice_row;
+  a.ginv = slice_inv_of<T>(g);
+  a.gnb = g.slice_nb;
+  a.Yp = job.Yp;
+  a.Yn = job.Yn;
+  a.ystride = job.ystride;
+  a.nz = job.nz;
+  a.mask = job.mask;
+  a.anymask = job.anymask;
+  a.awords = awords;
+  a.inv = inv_deg_of<T>(g);
+  a.part_rows = std::max(g.nparts, 1);
+  a.row = row_args<T>(g, job.partials);
+  a.blocks = job.blocks;
+  a.acc = job.acc;
+  a.acc_wgs = plan_acc(a.acc);
+  a.slot_row = g.slot_row;
+  a.inv_deg_d = g.inv_deg_d;
+  a.rowptr = g.rowptr;
+  a.mj = job.mj;
+  const int mask_wgs =
+      static_cast<int>(grid_for((job.mj.set.nb + job.mj.clear.nb) * B, kWavesPerBlock));
+  const int64_t grid = static_cast<int64_t>(a.heavy_wgs) + a.light_wgs + a.acc_wgs + mask_wgs;
+  if (grid <= 0 || grid > INT_MAX) return hipErrorInvalidValue;
+  const dim3 gd(static_cast<unsigned>(grid)), bd(kThreads);
+  if (twohop)
+    k_step<T, kTwoHop><<<gd, bd, 0, st>>>(a);
+  else if (job.skip)
+    k_step<T, kSkip><<<gd, bd, 0, st>>>(a);
+  else
+    hipExtLaunchKernelGGL((k_step<T, kFull>), gd, bd, 0, st, job.ev_start, job.ev_stop, 0, a);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_fixup<T>(g, B, partials, Yn, st);
+  return launch_fixup<T>(g, B, job.blocks, job.partials, job.Yn, job.ystride, st);
 }
 
 template <typename T>
-hipError_t launch_accumulate(const DeviceGraph& g, int B, const T* Y, const AccJob& acc,
-                             hipStream_t st) {
-  const int blocks = acc_blocks(acc);
-  if (blocks == 0) return hipSuccess;
-  const RowArgs<T> a = row_args<T>(g, B, nullptr, acc);
-  SC_DISPATCH_B(B, (k_accumulate<T, kB><<<blocks, kThreads, 0, st>>>(a, Y)));
+hipError_t launch_accumulate(const DeviceGraph& g, int B, const AccJob& acc, const T* Y,
+                             int64_t ystride, hipStream_t st) {
+  AccJob job = acc;
+  const int wgs = plan_acc(job);
+  if (wgs == 0) return hipSuccess;
+  SC_DISPATCH_B(B, (k_accumulate<T, kB><<<wgs, kThreads, 0, st>>>(job, g.slot_row, g.col,
+                                                                  g.inv_deg_d, Y, ystride)));
   return hipGetLastError();
 }
 
@@ -895,26 +1065,11 @@ hipError_t launch_multi_axpy(const double* V, int ncols, int64_t ld, const doubl
   return hipGetLastError();
 }
 
-template hipError_t launch_twohop<float>(const DeviceGraph&, int, const unsigned long long*,
-                                         const unsigned*, float*, float*, uint8_t*, hipStream_t);
-template hipError_t launch_twohop<double>(const DeviceGraph&, int, const unsigned long long*,
-                                          const unsigned*, double*, double*, uint8_t*, hipStream_t);
-template hipError_t launch_propagate_rows<float>(const DeviceGraph&, int, const float*, float*,
-                                                float*, const AccJob&, hipStream_t, const uint8_t*,
-                                                hipEvent_t, hipEvent_t, const MaskJob*);
-template hipError_t launch_propagate_rows<double>(const DeviceGraph&, int, const double*, double*,
-                                                 double*, const AccJob&, hipStream_t,
-                                                 const uint8_t*, hipEvent_t, hipEvent_t,
-                                                 const MaskJob*);
-template hipError_t launch_fixup<float>(const DeviceGraph&, int, const float*, float*, hipStream_t);
-template hipError_t launch_fixup<double>(const DeviceGraph&, int, const double*, double*, hipStream_t);
-template hipError_t launch_propagate<float>(const DeviceGraph&, int, const float*, float*,
-                                            float*, const AccJob&, hipStream_t);
-template hipError_t launch_propagate<double>(const DeviceGraph&, int, const double*, double*,
-                                             double*, const AccJob&, hipStream_t);
-template hipError_t launch_accumulate<float>(const DeviceGraph&, int, const float*,
-                                             const AccJob&, hipStream_t);
-template hipError_t launch_accumulate<double>(const DeviceGraph&, int, const double*,
-                                              const AccJob&, hipStream_t);
+template hipError_t launch_step<float>(const DeviceGraph&, int, const StepJob<float>&, hipStream_t);
+template hipError_t launch_step<double>(const DeviceGraph&, int, const StepJob<double>&, hipStream_t);
+template hipError_t launch_accumulate<float>(const DeviceGraph&, int, const AccJob&, const float*,
+                                             int64_t, hipStream_t);
+template hipError_t launch_accumulate<double>(const DeviceGraph&, int, const AccJob&,
+                                              const double*, int64_t, hipStream_t);
 
 }  // namespace sc

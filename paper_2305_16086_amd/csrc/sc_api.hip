@@ -91,12 +91,20 @@ void sc_graph::release() {
   dev_free(d.inv_deg_d);
   dev_free(d.tasks);
   dev_free(d.wg_tasks);
-  dev_free(d.ptasks);
+  dev_free(d.slice_grp);
+  dev_free(d.slice_row);
+  dev_free(d.slice_nb);
+  dev_free(d.slice_inv_f);
+  dev_free(d.slice_inv_d);
   dev_free(d.giant);
   dev_free(rank_d);
-  for (auto& y : Y) {
-    if (y) (void)sc::tracked_free(y);
-    y = nullptr;
+  if (Y) (void)sc::tracked_free(Y);
+  Y = nullptr;
+  if (tau_host) (void)hipHostFree(tau_host);
+  tau_host = nullptr;
+  for (auto& e : call_ev) {
+    if (e) (void)hipEventDestroy(e);
+    e = nullptr;
   }
   if (tail_stream) (void)hipStreamDestroy(tail_stream);
   tail_stream = nullptr;
@@ -114,16 +122,16 @@ void sc_graph::release() {
   dev_free(nr_slot);
   dev_free(spec_lam);
   dev_free(spec_phi);
-  dev_free(cs);
-  if (colscratch) (void)sc::tracked_free(colscratch);
-  colscratch = nullptr;
+  dev_free(tail.cs);
+  dev_free(tail.col);
+  dev_free(tail.chunk_off);
+  dev_free(tail.part);
+  dev_free(tail.ctl);
+  tail = sc::TailScratch{};
+  tail_blocks = tail_walk_blocks = 0;
   dev_free(work);
   dev_free(plan_work);
   dev_free(nz);
-  dev_free(walk.chunk_off);
-  dev_free(walk.part);
-  dev_free(walk.ctl);
-  walk.capacity = 0;
   dev_free(out_dev);
   dev_free(tau_out_dev);
   dev_free(nr_out_dev);
@@ -273,21 +281,6 @@ int sc::build_host_csr(int64_t n, int64_t m, const int64_t* u, const int64_t* v,
       tasks.push_back({x, rowptr[x], rowptr[x + 1], -1});
     }
   }
-  // runs of consecutive light rows, at most 64 slots per run (rows with more
-  // than 64 slots stay alone)
-  std::vector<sc::Task> ptasks;
-  for (int32_t x = 0; x < N;) {
-    if (deg[x] > sc::kChunk) {
-      ++x;
-      continue;
-    }
-    int32_t y = x + 1;
-    if (deg[x] <= 64)
-      while (y < N && deg[y] <= sc::kChunk && rowptr[y + 1] - rowptr[x] <= 64) ++y;
-    ptasks.push_back({x, rowptr[x], rowptr[y], y - x});
-    x = y;
-  }
-
   std::vector<float> inv_f(N);
   std::vector<double> inv_d(N);
   for (int32_t x = 0; x < N; ++x) {
@@ -304,7 +297,6 @@ int sc::build_host_csr(int64_t n, int64_t m, const int64_t* u, const int64_t* v,
   out.slot_half = std::move(slot_half);
   out.half_slot = std::move(half_slot);
   out.tasks = std::move(tasks);
-  out.ptasks = std::move(ptasks);
   out.wg_tasks = std::move(wg_tasks);
   out.giant = std::move(giant);
   out.nparts = nparts;
@@ -318,7 +310,6 @@ int sc::upload_csr(const HostCSR& h, DeviceGraph& d) {
   d.m = h.m;
   d.nslots = h.nslots;
   d.ntasks = static_cast<int32_t>(h.tasks.size());
-  d.nptasks = static_cast<int32_t>(h.ptasks.size());
   d.nwg = static_cast<int32_t>(h.wg_tasks.size());
   d.ngiant = static_cast<int32_t>(h.giant.size());
   d.nparts = h.nparts;
@@ -339,7 +330,6 @@ int sc::upload_csr(const HostCSR& h, DeviceGraph& d) {
   if (e == hipSuccess) e = up(&d.inv_deg_d, h.inv_d);
   if (e == hipSuccess) e = up(&d.tasks, h.tasks);
   if (e == hipSuccess) e = up(&d.wg_tasks, h.wg_tasks);
-  if (e == hipSuccess) e = up(&d.ptasks, h.ptasks);
   if (e == hipSuccess) e = up(&d.giant, h.giant);
   if (e != hipSuccess)
     return fail(e == hipErrorOutOfMemory ? SC_ENOMEM : SC_EHIP,
@@ -1046,31 +1036,126 @@ extern "C" void sc_default_options(sc_options* o) {
 
 namespace sc {
 
-int ensure_buffers(sc_graph* g, int B, size_t tsize) {
+PipeLayout pipe_layout(const sc_graph* g, int B, size_t tsize) {
+  PipeLayout l;
+  const int64_t n = g->d.n;
+  l.ystride = (n * B + 63) / 64 * 64;
+  const size_t yb = static_cast<size_t>(l.ystride) * tsize;
+  const int64_t nblocks = (n + B - 1) / B;
+  int64_t group = static_cast<int64_t>(kGroupBytes / (2 * yb));
+  group = std::max<int64_t>(group, kMinGroup);
+  while (group > 1 && 2 * kPipeSets * group * yb > kPipeBudgetBytes) --group;
+  group = std::min<int64_t>({group, nblocks, kMaxGroup});
+  // whole rounds of the 8 XCDs (a block is tsize / 2 slices when B = 64)
+  const int64_t unit = std::max<int64_t>(1, 16 / static_cast<int64_t>(tsize));
+  if (group > unit && group < nblocks) group = group / unit * unit;
+  l.group = static_cast<int>(group);
+  const size_t tail = col_scratch_bytes(col_parts(n)) +
+                      8 * static_cast<size_t>(std::min<int64_t>(int64_t(1) << 22,
+                                                                4 * g->d.nslots + 65536));
+  l.tail_group = static_cast<int>(
+      std::min<int64_t>(group, std::max<int64_t>(1, static_cast<int64_t>(kTailBytes / tail))));
+  return l;
+}
+
+namespace {
+
+template <typename P>
+hipError_t grow_zeroed(P** p, size_t* have, size_t want, hipStream_t st) {
+  if (*p && *have >= want) return hipSuccess;
+  dev_free(*p);
+  *have = 0;
+  hipError_t e = dev_alloc(p, want);
+  if (e == hipSuccess) e = hipMemsetAsync(*p, 0, want * sizeof(P), st);
+  if (e == hipSuccess) *have = want;
+  return e;
+}
+
+// The sliced lists of DeviceGraph: rows of at most kChunk slots by degree
+// (descending, ties by id), groups of 8.
+int build_slice_lists(sc_graph* g, hipStream_t st) {
+  DeviceGraph& d = g->d;
+  if (d.slice_nb) return SC_OK;
+  const int32_t n = d.n;
+  std::vector<int32_t> first(kChunk + 2, 0), rows;
+  std::vector<int2> grp;
+  try {
+    for (int32_t x = 0; x < n; ++x)
+      if (g->deg_h[x] <= kChunk) ++first[kChunk - g->deg_h[x] + 1];
+    for (int k = 0; k <= kChunk; ++k) first[k + 1] += first[k];
+    const int32_t light = first[kChunk + 1];
+    const int32_t ngrp = (light + 7) / 8;
+    rows.assign(static_cast<size_t>(ngrp) * 8, n);
+    for (int32_t x = 0; x < n; ++x)
+      if (g->deg_h[x] <= kChunk) rows[first[kChunk - g->deg_h[x]]++] = x;
+    grp.resize(ngrp);
+    int64_t off = 0;
+    for (int32_t k = 0; k < ngrp; ++k) {
+      const int32_t width = (g->deg_h[rows[8 * k]] + 7) / 8 * 8;
+      grp[k] = make_int2(static_cast<int>(off), width);
+      off += 8 * static_cast<int64_t>(width);
+      if (off > std::numeric_limits<int32_t>::max() - 64)
+        return fail(SC_EINVAL, "graph too large for the block path's neighbour lists");
+    }
+    std::vector<float> invf(rows.size(), 0.0f);
+    std::vector<double> invd(rows.size(), 0.0);
+    for (size_t r = 0; r < rows.size(); ++r)
+      if (rows[r] < n) {
+        invf[r] = 1.0f / static_cast<float>(g->deg_h[rows[r]]);
+        invd[r] = 1.0 / static_cast<double>(g->deg_h[rows[r]]);
+      }
+    d.nslice_grp = ngrp;
+    auto up = [&](auto** dst, const auto& src) -> hipError_t {
+      if (*dst) return hipSuccess;
+      hipError_t e = dev_alloc(dst, src.size());
+      if (e == hipSuccess && !src.empty())
+        e = hipMemcpyAsync(*dst, src.data(), src.size() * sizeof(src[0]), hipMemcpyHostToDevice, st);
+      return e;
+    };
+    hipError_t e = up(&d.slice_grp, grp);
+    if (e == hipSuccess) e = up(&d.slice_row, rows);
+    if (e == hipSuccess) e = up(&d.slice_inv_f, invf);
+    if (e == hipSuccess) e = up(&d.slice_inv_d, invd);
+    int32_t* nb = nullptr;
+    if (e == hipSuccess) e = dev_alloc(&nb, static_cast<size_t>(off));
+    if (e == hipSuccess) {
+      d.slice_nb = nb;
+      e = launch_fill_slices(d, st);
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(st);   // the host arrays end here
+    if (e != hipSuccess) {
+      dev_free(d.slice_nb);
+      return fail(e == hipErrorOutOfMemory ? SC_ENOMEM : SC_EHIP,
+                  std::string("neighbour lists: ") + hipGetErrorString(e));
+    }
+  } catch (const std::bad_alloc&) {
+    return fail(SC_ENOMEM, "host allocation failed");
+  }
+  return SC_OK;
+}
+
+}  // namespace
+
+int ensure_buffers(sc_graph* g, int B, size_t tsize, hipStream_t st) {
   using namespace sc;
   const int64_t n = g->d.n;
   const int64_t S = static_cast<int64_t>(g->rowptr_h[n]);
-  const size_t yb = static_cast<size_t>(n) * B * tsize;
-  // blocks per pipeline group: as many as the budget allows (at least one)
-  int group = sc::kMaxGroupBlocks;
-  while (group > 1 && 2 * sc::kPipeGroups * group * yb > sc::kPipeBudgetBytes) group /= 2;
-  const int pairs = sc::kPipeGroups * group;
-  if (yb > g->ybytes || pairs != g->ypairs) {
-    for (auto& y : g->Y) {
-      if (y) (void)sc::tracked_free(y);
-      y = nullptr;
-    }
+  const PipeLayout lay = pipe_layout(g, B, tsize);
+  const size_t yb = 2 * static_cast<size_t>(lay.bufs()) * lay.ystride * tsize;
+  if (yb > g->ybytes) {
+    if (g->Y) (void)sc::tracked_free(g->Y);
+    g->Y = nullptr;
     g->ybytes = 0;
-    g->ypairs = 0;
-    for (int i = 0; i < 2 * pairs; ++i) HIP_TRY(sc::tracked_malloc(&g->Y[i], yb));
+    HIP_TRY(sc::tracked_malloc(&g->Y, yb));
     g->ybytes = yb;
-    g->ypairs = pairs;
   }
-  if (!g->nz) {
-    HIP_TRY(dev_alloc(&g->nz, n));
-    HIP_TRY(hipMemset(g->nz, 1, n));
+  if (B == 64) {
+    const int rc = build_slice_lists(g, st);
+    if (rc) return rc;
+    const size_t nzb = static_cast<size_t>(lay.bufs()) * (tsize / 2) * n;
+    HIP_TRY(grow_zeroed(&g->nz, &g->nz_bytes, nzb, st));
   }
-  const size_t pb = static_cast<size_t>(std::max(g->d.nparts, 1)) * B * tsize;
+  const size_t pb = static_cast<size_t>(lay.bufs()) * std::max(g->d.nparts, 1) * B * tsize;
   if (pb > g->pbytes) {
     if (g->partials) (void)sc::tracked_free(g->partials);
     g->partials = nullptr;
@@ -1078,22 +1163,72 @@ int ensure_buffers(sc_graph* g, int B, size_t tsize) {
     HIP_TRY(sc::tracked_malloc(&g->partials, pb));
     g->pbytes = pb;
   }
-  if (!g->mask) {
-    HIP_TRY(dev_alloc(&g->mask, 2 * n));
-    HIP_TRY(hipMemset(g->mask, 0, 2 * n * sizeof(unsigned long long)));
-    HIP_TRY(dev_alloc(&g->anymask, 2 * ((n + 31) / 32)));
-    HIP_TRY(hipMemset(g->anymask, 0, 2 * ((n + 31) / 32) * sizeof(unsigned)));
-    g->mask_pending_s0 = -1;
+  const size_t mw = 2 * static_cast<size_t>(lay.group) * n;
+  const size_t aw = 2 * static_cast<size_t>(lay.group) * ((n + 31) / 32);
+  if (!g->mask_clean || mw > g->mask_words || aw > g->anymask_words) {
+    // new words, or a call that failed between setting bits and clearing them
+    g->mask_clean = false;
+    g->mask_pending = BlockList{};
+    if (mw > g->mask_words) {
+      dev_free(g->mask);
+      g->mask_words = 0;
+      HIP_TRY(dev_alloc(&g->mask, mw));
+      g->mask_words = mw;
+    }
+    if (aw > g->anymask_words) {
+      dev_free(g->anymask);
+      g->anymask_words = 0;
+      HIP_TRY(dev_alloc(&g->anymask, aw));
+      g->anymask_words = aw;
+    }
+    HIP_TRY(launch_fill_u64(reinterpret_cast<uint64_t*>(g->mask),
+                            static_cast<int64_t>(g->mask_words), 0, st));
+    HIP_TRY(launch_fill_u32(g->anymask, static_cast<int64_t>(g->anymask_words), 0, st));
+    g->mask_clean = true;
   }
   if (!g->gacc) HIP_TRY(dev_alloc(&g->gacc, S));
   if (!g->tau_slot) HIP_TRY(dev_alloc(&g->tau_slot, S));
   if (!g->tau_row) HIP_TRY(dev_alloc(&g->tau_row, n));
   if (!g->nr_slot) HIP_TRY(dev_alloc(&g->nr_slot, S));
-  if (!g->cs) HIP_TRY(dev_alloc(&g->cs, 64));
-  if (!g->colscratch) HIP_TRY(sc::tracked_malloc(&g->colscratch, sc::kColScratchBytes));
   if (!g->work) HIP_TRY(dev_alloc(&g->work, 4));   // [0..1] walk totals, [2] capped halves
-  if (!g->plan_work) HIP_TRY(dev_alloc(&g->plan_work, 2 * 64));
+  if (!g->plan_work) HIP_TRY(dev_alloc(&g->plan_work, 4 * 2 * 64));
   if (!g->out_dev) HIP_TRY(dev_alloc(&g->out_dev, g->d.m));
+  if (!g->tau_host)
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&g->tau_host),
+                          (static_cast<size_t>(n) + 8) * sizeof(int32_t)));
+  for (auto& e : g->call_ev)
+    if (!e) HIP_TRY(hipEventCreate(&e));
+  return SC_OK;
+}
+
+int ensure_tail(sc_graph* g, int blocks, bool walks) {
+  const int64_t n = g->d.n, S = g->d.nslots;
+  TailScratch& t = g->tail;
+  if (!t.ctl) {
+    t.nparts = col_parts(n);
+    t.col_bytes = col_scratch_bytes(t.nparts);
+    // flattened walks: a block whose chunks do not fit walks one slot per wave
+    t.capacity = std::min<int64_t>(int64_t(1) << 22, 4 * S + 65536);
+    if (const char* cap = std::getenv("SC_WALK_CHUNK_CAPACITY"))   // smaller buffer (tests)
+      t.capacity = std::max<int64_t>(1, std::min<int64_t>(t.capacity, std::atoll(cap)));
+    HIP_TRY(dev_alloc(&t.ctl, 2 * static_cast<size_t>(kMaxGroup)));
+  }
+  if (!t.cs) HIP_TRY(dev_alloc(&t.cs, static_cast<size_t>(kMaxGroup) * 64));
+  if (static_cast<size_t>(blocks) > g->tail_blocks) {
+    dev_free(t.col);
+    g->tail_blocks = 0;
+    HIP_TRY(dev_alloc(&t.col, t.col_bytes * blocks));
+    g->tail_blocks = blocks;
+  }
+  if (walks) {
+    if (!t.chunk_off) HIP_TRY(dev_alloc(&t.chunk_off, S + n / 16 + 2));
+    if (static_cast<size_t>(blocks) > g->tail_walk_blocks) {
+      dev_free(t.part);
+      g->tail_walk_blocks = 0;
+      HIP_TRY(dev_alloc(&t.part, static_cast<size_t>(t.capacity) * blocks));
+      g->tail_walk_blocks = blocks;
+    }
+  }
   return SC_OK;
 }
 
@@ -1139,6 +1274,96 @@ CostModel cost_model() {
   return c;
 }
 
+// The switch step by the cost model: walk steps at every candidate, sampled on up to
+// four blocks (traversed as one group).
+template <typename T>
+int plan_switch(sc_graph* g, Runner<T>& R, const int32_t* tau_row, int Lmax, int gamma,
+                double coef, int64_t nr_cap, int* tilde_out) {
+  const int B = R.B;
+  const int64_t n = g->d.n;
+  hipStream_t st = R.st;
+  const int nblocks = static_cast<int>((n + B - 1) / B);
+  const CostModel cm = cost_model();
+  const double dense = cm.step_fixed + static_cast<double>(g->d.nslots) * B * sizeof(T) / cm.gather_bw;
+  const double tail0 = cm.tail_fixed + cm.tail_per_node * static_cast<double>(n);
+  const int nsamp = std::min(nblocks, 4);
+  constexpr int kSlots = 2 * 64;   // counters of a sample
+  std::vector<double> cost(Lmax + 1, 0.0);
+  std::vector<unsigned long long> wk(static_cast<size_t>(nsamp) * kSlots, 0ull);
+  std::vector<int> tmaxs(nsamp, 0);
+  HIP_TRY(hipMemsetAsync(g->plan_work, 0, nsamp * kSlots * sizeof(unsigned long long), st));
+  const int step = std::min({nsamp, R.lay.bufs(), R.lay.group, R.lay.tail_group});
+  int rc = sc::ensure_tail(g, step, false);
+  if (rc) return rc;
+  for (int s = 0; s < nsamp; s += step) {
+    sc::BlockList list;
+    int tmax_of[sc::kMaxGroup], sample_of[sc::kMaxGroup], to2[sc::kMaxGroup];
+    int tmax_all = 0;
+    for (int si = s; si < std::min(nsamp, s + step); ++si) {
+      sc::BlockRef r = R.block_ref(static_cast<int>((si + 0.5) * nblocks / nsamp), tau_row, &tmaxs[si]);
+      if (tmaxs[si] < 3) continue;
+      r.buf = list.nb;
+      tmax_of[list.nb] = tmaxs[si];
+      sample_of[list.nb] = si;
+      to2[list.nb] = 2;
+      tmax_all = std::max(tmax_all, tmaxs[si]);
+      list.b[list.nb++] = r;
+    }
+    if (list.nb == 0) continue;
+    rc = R.traverse(list, to2, false, nullptr);
+    if (rc) return rc;
+    for (int ell = 2; ell < tmax_all && ell <= Lmax && ell < 64; ++ell) {
+      sc::BlockList on;   // the samples that have a step beyond ell
+      int on_sample[sc::kMaxGroup];
+      for (int i = 0; i < list.nb; ++i)
+        if (ell < tmax_of[i]) {
+          on_sample[on.nb] = sample_of[i];
+          on.b[on.nb++] = list.b[i];
+        }
+      if (ell > 2) {
+        rc = R.advance(on);
+        if (rc) return rc;
+      }
+      HIP_TRY(sc::launch_colstats<T>(g->d, on, B, gamma, R.Y(R.par), R.lay.ystride, g->tail, st));
+      HIP_TRY(sc::launch_walk_counts<T>(g->d, on, B, ell, gamma, coef, nr_cap, R.Y(R.par),
+                                        R.lay.ystride, g->tail, g->tau_slot, g->nr_slot, st));
+      for (int i = 0; i < on.nb; ++i) {
+        sc::BlockList one;
+        one.nb = 1;
+        one.b[0] = on.b[i];
+        HIP_TRY(sc::launch_work_totals(one, ell, g->tau_slot, g->nr_slot,
+                                       g->plan_work + on_sample[i] * kSlots + 2 * ell, 0, st));
+      }
+    }
+  }
+  HIP_TRY(hipMemcpyAsync(wk.data(), g->plan_work, wk.size() * sizeof(unsigned long long),
+                         hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipStreamSynchronize(st));
+  for (int si = 0; si < nsamp; ++si) {
+    const int tmax = tmaxs[si];
+    for (int ell = 2; ell <= Lmax; ++ell) {
+      const int steps = std::min(ell, tmax);
+      const double first = B == 64 ? cm.skip_frac : 1.0;   // l = 3
+      const double trav =
+          steps >= 2 ? cm.step_fixed +
+                           dense * (cm.twohop_frac + (steps >= 3 ? first + (steps - 3) : 0.0))
+                     : 0.0;
+      // switch points beyond the 64 counter slots are not candidates
+      const double tail =
+          ell < tmax
+              ? (ell < 64 ? tail0 + static_cast<double>(wk[si * kSlots + 2 * ell + 1]) * cm.walk_step
+                          : 1e30)
+              : cm.step_fixed;
+      cost[ell] += std::max(trav, tail) + cm.overlap * std::min(trav, tail);
+    }
+  }
+  int tilde = Lmax;
+  for (int ell = 2; ell <= Lmax; ++ell)
+    if (cost[ell] < cost[tilde]) tilde = ell;
+  *tilde_out = tilde;
+  return SC_OK;
+}
+
 template <typename T>
 int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_user,
                sc_stats* st_user) {
@@ -1151,25 +1376,19 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
   if (gamma > sc::kMaxGamma) return fail(SC_EINVAL, "gamma above 16 is not supported");
   int max_L = o.max_L > 0 ? o.max_L : 255;
   if (max_L % 2 == 0) --max_L;
-  int rc = sc::ensure_buffers(g, B, sizeof(T));
+  int rc = sc::ensure_buffers(g, B, sizeof(T), st);
   if (rc) return rc;
   const bool dev_ptrs = (o.flags & SC_DEVICE_PTRS) != 0;
 
+  g->mask_clean = false;   // set again once the call's last clear is enqueued
   Runner<T> R{g, B, st, (o.flags & SC_TIME_KERNELS) != 0};
+  const sc::PipeLayout& lay = R.lay;
   R.stats.block = B;
   R.stats.tilde_tau = -1;
   R.stats.tilde_min = -1;
   R.stats.tilde_max = -1;
   R.stats.lambda_converged = -1;
-  hipEvent_t t0 = nullptr, t1 = nullptr;
-  auto destroy_events = [&]() {
-    if (t0) (void)hipEventDestroy(t0);
-    if (t1) (void)hipEventDestroy(t1);
-  };
-  const sc::ScopeExit<decltype(destroy_events)> ev_guard{destroy_events};   // every return path
-  HIP_TRY(hipEventCreate(&t0));
-  HIP_TRY(hipEventCreate(&t1));
-  HIP_TRY(hipEventRecord(t0, st));
+  HIP_TRY(hipEventRecord(g->call_ev[0], st));
 
   // truncation policy: uniform L, CalTau with the graph's spectrum (Algorithm 1),
   // or the lambda*-bound (Algorithm 1 line 1)
@@ -1195,50 +1414,43 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
   R.stats.lambda_star = lam;
   const double eps_tau = plus ? eps / 2.0 : eps;
   unsigned long long* capped = g->work + 2;
-  HIP_TRY(hipMemsetAsync(capped, 0, sizeof(unsigned long long), st));
-  if (spectral)
-    HIP_TRY(sc::launch_caltau(g->d, g->spec_lam, g->spec_phi, g->spec_omega, eps_tau, max_L,
-                              g->tau_slot, g->tau_row, st, capped));
-  else
-    HIP_TRY(sc::launch_tau(g->d, Lodd, eps_tau, lam, max_L, g->tau_slot, g->tau_row, st, capped));
-  std::vector<int32_t> tau_row(n);
-  unsigned long long capped_h = 0;
-  HIP_TRY(hipMemcpyAsync(tau_row.data(), g->tau_row, n * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(&capped_h, capped, sizeof(capped_h), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
-  R.stats.L_capped = static_cast<int64_t>(capped_h / 2);   // both halves of an edge share tau
-  int Lmax = 0, Lmin = 1 << 30;
-  for (int64_t x = 0; x < n; ++x) {
-    Lmax = std::max(Lmax, tau_row[x]);
-    Lmin = std::min(Lmin, tau_row[x]);
+  int32_t* const tau_row = g->tau_host;   // pinned: [n] row truncations, then the capped count
+  if (L > 0) {
+    // every edge has tau = Lodd: nothing to read back
+    HIP_TRY(sc::launch_tau(g->d, Lodd, eps_tau, lam, max_L, g->tau_slot, g->tau_row, st, nullptr));
+    std::fill(tau_row, tau_row + n, Lodd);
+    R.stats.L_used = R.stats.L_min = Lodd;
+  } else {
+    HIP_TRY(sc::launch_fill_u64(reinterpret_cast<uint64_t*>(capped), 1, 0, st));
+    if (spectral)
+      HIP_TRY(sc::launch_caltau(g->d, g->spec_lam, g->spec_phi, g->spec_omega, eps_tau, max_L,
+                                g->tau_slot, g->tau_row, st, capped));
+    else
+      HIP_TRY(sc::launch_tau(g->d, Lodd, eps_tau, lam, max_L, g->tau_slot, g->tau_row, st, capped));
+    unsigned long long* capped_h =
+        reinterpret_cast<unsigned long long*>(tau_row + (n + 1) / 2 * 2);
+    HIP_TRY(hipMemcpyAsync(tau_row, g->tau_row, n * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(capped_h, capped, sizeof(*capped_h), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    R.stats.L_capped = static_cast<int64_t>(*capped_h / 2);   // both halves of an edge share tau
+    int Lmax = 0, Lmin = 1 << 30;
+    for (int64_t x = 0; x < n; ++x) {
+      Lmax = std::max(Lmax, tau_row[x]);
+      Lmin = std::min(Lmin, tau_row[x]);
+    }
+    R.stats.L_used = Lmax;
+    R.stats.L_min = Lmin;
   }
-  R.stats.L_used = Lmax;
-  R.stats.L_min = Lmin;
-
+  const int Lmax = R.stats.L_used;
   const int nblocks = static_cast<int>((n + B - 1) / B);
-  auto block_range = [&](int b, int* s0, int* kbeg, int* kend, int* tmax) {
-    R.block_range(b, tau_row, s0, kbeg, kend, tmax);
-  };
 
   int tilde = Lmax;
   double coef = 0.0;
   const int64_t nr_cap = (1ll << 31) - 1;
-  if (plus && !g->walk.chunk_off) {
-    // flattened walks: chunk offsets per slot, chunk sums (a block whose chunks
-    // do not fit runs the per-slot kernel instead)
-    const int64_t S = g->rowptr_h[n];
-    HIP_TRY(sc::dev_alloc(&g->walk.chunk_off, S + 1));
-    HIP_TRY(sc::dev_alloc(&g->walk.ctl, 2));
-    g->walk.capacity = std::min<int64_t>(int64_t(1) << 22, 4 * S + 65536);
-    if (const char* cap = std::getenv("SC_WALK_CHUNK_CAPACITY"))   // smaller buffer (tests)
-      g->walk.capacity = std::max<int64_t>(1, std::min<int64_t>(g->walk.capacity, std::atoll(cap)));
-    HIP_TRY(sc::dev_alloc(&g->walk.part, g->walk.capacity));
-  }
   if (plus) {
     const double delta = o.delta > 0.0 ? o.delta : 1.0 / static_cast<double>(n);
     // Eq. 13 constant; m counts distinct edges
     coef = 8.0 * std::log(static_cast<double>(g->d.nslots) / delta) / (eps * eps);
-    HIP_TRY(hipMemsetAsync(g->nr_slot, 0, g->rowptr_h[n] * sizeof(int64_t), st));
     const sc_graph::PlanKey key{eps,  L,     max_L, lam, B, static_cast<int>(sizeof(T)), gamma,
                                 delta, spectral ? g->spec_version : 0};
     if (o.tilde_tau >= 0) {
@@ -1246,60 +1458,13 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
     } else if (g->plan_valid && g->plan_key == key) {
       tilde = g->plan_tilde;   // the switch step depends only on the graph and these options
     } else {
-      // sample blocks: walk steps at every candidate switch point
-      const CostModel cm = cost_model();
-      const double dense = cm.step_fixed + static_cast<double>(g->d.nslots) * B * sizeof(T) / cm.gather_bw;
-      const double tail0 = cm.tail_fixed + cm.tail_per_node * static_cast<double>(n);
-      const int nsamp = std::min(nblocks, 4);
-      std::vector<double> cost(Lmax + 1, 0.0);
-      for (int si = 0; si < nsamp; ++si) {
-        const int b = static_cast<int>((si + 0.5) * nblocks / nsamp);
-        int s0, kbeg, kend, tmax;
-        block_range(b, &s0, &kbeg, &kend, &tmax);
-        std::vector<unsigned long long> wk(2 * (Lmax + 1), 0ull);
-        HIP_TRY(hipMemsetAsync(g->plan_work, 0, 2 * 64 * sizeof(unsigned long long), st));
-        if (tmax >= 3) {
-          rc = R.traverse(s0, kbeg, kend, 2, false, nullptr);
-          if (rc) return rc;
-          for (int ell = 2; ell < tmax && ell <= Lmax && ell < 64; ++ell) {
-            if (ell > 2) {
-              rc = R.advance();
-              if (rc) return rc;
-            }
-            HIP_TRY(sc::launch_colstats<T>(g->d, s0, B, gamma, R.Yb(R.cur), g->cs, g->colscratch, st));
-            HIP_TRY(sc::launch_walk_counts<T>(g->d, kbeg, kend, s0, B, ell, gamma, coef, nr_cap,
-                                              R.Yb(R.cur), g->cs, g->tau_slot, g->nr_slot, st));
-            HIP_TRY(sc::launch_work_totals(kbeg, kend, ell, g->tau_slot, g->nr_slot,
-                                           g->plan_work + 2 * ell, st));
-          }
-          HIP_TRY(hipMemcpyAsync(wk.data(), g->plan_work,
-                                 std::min<size_t>(wk.size(), 2 * 64) * sizeof(unsigned long long),
-                                 hipMemcpyDeviceToHost, st));
-          HIP_TRY(hipStreamSynchronize(st));
-        }
-        for (int ell = 2; ell <= Lmax; ++ell) {
-          const int steps = std::min(ell, tmax);
-          const double first = B == 64 ? cm.skip_frac : 1.0;   // l = 3
-          const double trav =
-              steps >= 2 ? cm.step_fixed +
-                               dense * (cm.twohop_frac + (steps >= 3 ? first + (steps - 3) : 0.0))
-                         : 0.0;
-          // switch points beyond the 64 counter slots are not candidates
-          const double tail =
-              ell < tmax ? (ell < 64 ? tail0 + static_cast<double>(wk[2 * ell + 1]) * cm.walk_step
-                                     : 1e30)
-                         : cm.step_fixed;
-          cost[ell] += std::max(trav, tail) + cm.overlap * std::min(trav, tail);
-        }
-      }
-      tilde = Lmax;
-      for (int ell = 2; ell <= Lmax; ++ell)
-        if (cost[ell] < cost[tilde]) tilde = ell;
-      HIP_TRY(hipMemsetAsync(g->nr_slot, 0, g->rowptr_h[n] * sizeof(int64_t), st));
+      rc = plan_switch<T>(g, R, tau_row, Lmax, gamma, coef, nr_cap, &tilde);
+      if (rc) return rc;
       g->plan_key = key;
       g->plan_tilde = tilde;
       g->plan_valid = true;
     }
+    HIP_TRY(sc::launch_fill_u64(reinterpret_cast<uint64_t*>(g->nr_slot), g->rowptr_h[n], 0, st));
     R.stats.tilde_tau = tilde;
     R.stats.tilde_min = tilde;
     R.stats.tilde_max = tilde;
@@ -1309,113 +1474,111 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
   R.stats.prop_launches = 0;
   R.stats.prop_bytes = 0.0;
 
-  unsigned long long* work = g->work;
-  HIP_TRY(hipMemsetAsync(work, 0, 2 * sizeof(unsigned long long), st));
-  // Block pipeline: the traversal of block b runs on the caller's stream, its
-  // tail (last accumulation, candidate summary, walk counts, walks) on the
-  // tail stream, overlapping the traversals of the next blocks.  The streams
-  // meet once per group of G blocks: the tails of a group wait for the whole
-  // group's traversal, and the traversal of group q waits for the tails of
-  // group q - kPipeGroups, whose Y pairs it reuses (block i of the launched
-  // sequence takes pair i mod (kPipeGroups G)).  Blocks touch disjoint slots
-  // of gacc and nr_slot.
-  rc = sc::ensure_pipeline(g);
-  if (rc) return rc;
-  hipStream_t sb = g->tail_stream;
-  HIP_TRY(hipEventRecord(g->pipe_ev[0], st));
-  HIP_TRY(hipStreamWaitEvent(sb, g->pipe_ev[0], 0));
-  const auto host0 = std::chrono::steady_clock::now();
-  constexpr int Q = sc::kPipeGroups;
-  const int D = g->ypairs;
-  const int G = D / Q;
-  bool tail_recorded[Q] = {};
-  // the last pass of a block's walks rides on the next candidate summary's
-  // first launch (same stream, before the next walks reuse the chunk buffers)
-  sc::FinishJob fin;
-  // a traversed block whose tail is not yet enqueued
-  struct TailJob {
-    int s0, kbeg, kend, tmax, pair, cur;
-    sc::AccJob acc;
+  // Groups of blocks in source order.  A block whose edges all stop at tau <= 1 has
+  // only the l = 0, 1 terms, which the accumulator initialisation already holds, and
+  // is in no group.
+  struct Group {
+    sc::BlockList all, trav, tail;   // tail: blocks with edges beyond the switch step
+    int lend[sc::kMaxGroup];         // last traversal step per block of trav
   };
-  std::vector<TailJob> group_jobs;
-  group_jobs.reserve(G);
-  auto enqueue_tails = [&](int qset) -> int {
+  std::vector<Group> groups;
+  bool any_tail = false;
+  int max_tail = 0;
+  for (int b = 0; b < nblocks; ++b) {
+    int tmax;
+    sc::BlockRef r = R.block_ref(b, tau_row, &tmax);
+    const int lend = plus ? std::min(tmax, tilde) : tmax;
+    const bool tail = plus && tmax > tilde;
+    if (lend < 2 && !tail) continue;
+    if (groups.empty() || groups.back().all.nb == lay.group) groups.emplace_back();
+    Group& gr = groups.back();
+    r.buf = static_cast<int>((groups.size() - 1) % sc::kPipeSets) * lay.group + gr.all.nb;
+    gr.all.b[gr.all.nb++] = r;
+    if (lend >= 2) {
+      gr.lend[gr.trav.nb] = lend;
+      gr.trav.b[gr.trav.nb++] = r;
+    }
+    if (tail) {
+      gr.tail.b[gr.tail.nb++] = r;
+      any_tail = true;
+      max_tail = std::max(max_tail, gr.tail.nb);
+    }
+  }
+  if (any_tail) {
+    rc = sc::ensure_tail(g, std::min(max_tail, lay.tail_group), true);
+    if (rc) return rc;
+  }
+  // Pipeline: the traversals run on the caller's stream, a group's tails (candidate
+  // summary, walk counts, walks) on the tail stream beside the next group's traversal.
+  // The tails of a group wait for its traversal, and the traversal of group q waits
+  // for the tails of group q - kPipeSets, whose states it reuses.  Blocks touch
+  // disjoint slots of gacc and nr_slot.
+  hipStream_t sb = st;
+  if (any_tail) {
+    rc = sc::ensure_pipeline(g);
+    if (rc) return rc;
+    sb = g->tail_stream;
+    HIP_TRY(hipEventRecord(g->pipe_ev[0], st));
+    HIP_TRY(hipStreamWaitEvent(sb, g->pipe_ev[0], 0));
+  }
+  const auto host0 = std::chrono::steady_clock::now();
+  bool tail_recorded[sc::kPipeSets] = {};
+  for (size_t q = 0; q < groups.size(); ++q) {
+    const Group& gr = groups[q];
+    const int qset = static_cast<int>(q % sc::kPipeSets);
+    if (tail_recorded[qset])
+      HIP_TRY(hipStreamWaitEvent(st, g->pipe_ev[1 + sc::kPipeSets + qset], 0));
+    R.st = st;
+    rc = R.traverse(gr.trav, gr.lend, true, g->gacc, q + 1 < groups.size() ? &groups[q + 1].trav : nullptr);
+    if (rc) return rc;
+    if (gr.tail.nb == 0) {
+      rc = R.flush_acc();
+      if (rc) return rc;
+      continue;
+    }
+    // the last step's accumulation rides on the candidate summary's first launch when
+    // every block of the group that still has it pending is summarised there
+    const bool fuse_acc = R.pending.list.nb == gr.tail.nb;
+    if (!fuse_acc) {
+      rc = R.flush_acc();
+      if (rc) return rc;
+    }
+    const sc::AccJob last = R.pending;
+    R.pending = sc::AccJob{};
     HIP_TRY(hipEventRecord(g->pipe_ev[1 + qset], st));
     HIP_TRY(hipStreamWaitEvent(sb, g->pipe_ev[1 + qset], 0));
     R.st = sb;
-    for (const TailJob& tj : group_jobs) {
-      R.po = 2 * tj.pair;
-      R.cur = tj.cur;
-      R.pending_acc = tj.acc;
-      // the last step's accumulation rides on the candidate summary's first
-      // launch when there is one (same state, same stream)
-      const bool fuse_acc = plus && tj.tmax > tilde && tilde >= 2;
-      if (!fuse_acc) {
-        const int rc1 = R.flush_acc();
-        if (rc1) return rc1;
-      }
-      if (plus && tj.tmax > tilde) {
-        if (tilde < 2) {
-          const int rc1 = R.init_low(tj.s0, tilde);
-          if (rc1) return rc1;
-        }
-        HIP_TRY(sc::launch_colstats<T>(g->d, tj.s0, B, gamma, R.Yb(R.cur), g->cs, g->colscratch,
-                                       sb, fuse_acc ? &R.pending_acc : nullptr, &fin));
-        R.pending_acc = sc::AccJob{};
-        fin = sc::FinishJob{};
-        HIP_TRY(sc::launch_walk_counts<T>(g->d, tj.kbeg, tj.kend, tj.s0, B, tilde, gamma, coef,
-                                          nr_cap, R.Yb(R.cur), g->cs, g->tau_slot, g->nr_slot,
-                                          sb));
-        HIP_TRY(sc::launch_walks<T>(g->d, tj.kbeg, tj.kend, tj.s0, B, tilde, o.seed,
-                                    R.Yb(R.cur), g->tau_slot, g->nr_slot, g->gacc, g->walk, sb,
-                                    &fin));
-      }
-    }
-    group_jobs.clear();
-    HIP_TRY(hipEventRecord(g->pipe_ev[1 + Q + qset], sb));
-    tail_recorded[qset] = true;
-    R.st = st;
-    return SC_OK;
-  };
-  int launched = 0;   // blocks traversed so far
-  for (int b = 0; b < nblocks; ++b) {
-    int s0, kbeg, kend, tmax;
-    block_range(b, &s0, &kbeg, &kend, &tmax);
-    const int lend = plus ? std::min(tmax, tilde) : tmax;
-    // a block whose edges all stop at tau <= 1 has only the l = 0, 1 terms,
-    // which the accumulator initialisation already holds: no launch, no events
-    if (lend < 2 && !(plus && tmax > tilde)) continue;
-    const int pair = launched % D;
-    const int qset = (launched / G) % Q;
-    if (launched % G == 0 && tail_recorded[qset])
-      HIP_TRY(hipStreamWaitEvent(st, g->pipe_ev[1 + Q + qset], 0));
-    R.st = st;
-    R.po = 2 * pair;
-    rc = R.traverse(s0, kbeg, kend, lend, true, g->gacc, b + 1 < nblocks ? s0 + B : -1);
-    if (rc) return rc;
-    group_jobs.push_back(TailJob{s0, kbeg, kend, tmax, pair, R.cur, R.pending_acc});
-    R.pending_acc = sc::AccJob{};
-    ++launched;
-    if (launched % G == 0) {
-      rc = enqueue_tails(qset);
+    if (tilde < 2) {
+      rc = R.init_low(gr.tail, tilde);
       if (rc) return rc;
     }
+    for (int t = 0; t < gr.tail.nb; t += lay.tail_group) {
+      sc::BlockList part;
+      for (int i = t; i < std::min(gr.tail.nb, t + lay.tail_group); ++i) part.b[part.nb++] = gr.tail.b[i];
+      HIP_TRY(sc::launch_colstats<T>(g->d, part, B, gamma, R.Y(R.par), lay.ystride, g->tail, sb,
+                                     fuse_acc ? &last : nullptr));
+      HIP_TRY(sc::launch_walk_counts<T>(g->d, part, B, tilde, gamma, coef, nr_cap, R.Y(R.par),
+                                        lay.ystride, g->tail, g->tau_slot, g->nr_slot, sb));
+      HIP_TRY(sc::launch_walks<T>(g->d, part, B, tilde, o.seed, R.Y(R.par), lay.ystride,
+                                  g->tau_slot, g->nr_slot, g->gacc, g->tail, sb));
+    }
+    HIP_TRY(hipEventRecord(g->pipe_ev[1 + sc::kPipeSets + qset], sb));
+    tail_recorded[qset] = true;
+    R.st = st;
   }
-  if (!group_jobs.empty()) {
-    rc = enqueue_tails(((launched - 1) / G) % Q);
-    if (rc) return rc;
-  }
+  R.st = st;
   R.stats.host_ms =
       std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - host0).count();
-  HIP_TRY(sc::launch_walk_finish(fin, sb));
-  HIP_TRY(hipEventRecord(g->pipe_ev[0], sb));
-  HIP_TRY(hipStreamWaitEvent(st, g->pipe_ev[0], 0));
-  R.po = 0;
+  if (any_tail) {
+    HIP_TRY(hipEventRecord(g->pipe_ev[0], sb));
+    HIP_TRY(hipStreamWaitEvent(st, g->pipe_ev[0], 0));
+  }
   rc = R.flush_masks();
   if (rc) return rc;
+  g->mask_clean = true;
   double* out_dev = dev_ptrs ? out_user : g->out_dev;
   HIP_TRY(sc::launch_combine(g->d, g->gacc, out_dev, st));
-  HIP_TRY(hipEventRecord(t1, st));
+  HIP_TRY(hipEventRecord(g->call_ev[1], st));
 
   // traces
   int32_t* tau_o = nullptr;
@@ -1441,9 +1604,13 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
       std::memcpy(o.tilde_tau_out, tilde_h.data(), n * sizeof(int32_t));
   }
   unsigned long long wk[2] = {0, 0};
-  if (plus) {
-    HIP_TRY(sc::launch_work_totals(0, static_cast<int>(g->d.nslots), tilde, g->tau_slot,
-                                   g->nr_slot, work, st));
+  if (any_tail) {
+    unsigned long long* work = g->work;
+    HIP_TRY(sc::launch_fill_u64(reinterpret_cast<uint64_t*>(work), 2, 0, st));
+    sc::BlockList whole;
+    whole.nb = 1;
+    whole.b[0].kend = static_cast<int>(g->d.nslots);
+    HIP_TRY(sc::launch_work_totals(whole, tilde, g->tau_slot, g->nr_slot, work, 0, st));
     HIP_TRY(hipMemcpyAsync(wk, work, sizeof(wk), hipMemcpyDeviceToHost, st));
   }
   if (!dev_ptrs) {
@@ -1455,7 +1622,7 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
   }
   HIP_TRY(hipStreamSynchronize(st));
   float ms = 0.0f;
-  HIP_TRY(hipEventElapsedTime(&ms, t0, t1));
+  HIP_TRY(hipEventElapsedTime(&ms, g->call_ev[0], g->call_ev[1]));
   R.stats.total_ms = ms;
   R.stats.walks = plus ? static_cast<int64_t>(wk[0]) : 0;
   R.stats.walk_steps = plus ? static_cast<int64_t>(wk[1]) : 0;

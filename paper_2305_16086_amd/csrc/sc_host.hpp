@@ -4,6 +4,7 @@
 
 #include "sc_internal.hpp"
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -42,15 +43,26 @@ void dev_free(P*& p) {
   p = nullptr;
 }
 
-// The per-graph block pipeline synchronises its two streams once per group of
-// blocks; groups cycle through kPipeGroups sets of Y pairs, so the traversal of
-// group q reuses the pairs of group q - kPipeGroups once that group's tails are
-// done.  A group holds up to kMaxGroupBlocks blocks (fewer when the Y pairs of
-// the larger pipeline would not fit kPipeBudgetBytes).
-constexpr int kPipeGroups = 3;
-constexpr int kMaxGroupBlocks = 4;
-constexpr int kMaxPipe = kPipeGroups * kMaxGroupBlocks;   // Y pairs at most
+// Source blocks run in groups of up to kMaxGroup, one launch per step and group (see
+// k_step).  TGT+ overlaps the tails of a group with the traversal of the next on a
+// second stream, the groups alternating between kPipeSets sets of states.  A group is
+// as large as keeps its states (two per block) within kGroupBytes, which leaves them
+// in the 256 MB last-level cache together with what the tails read; but at least 4
+// blocks (8 slices of FP32 states: one per XCD) where the states of all sets fit
+// kPipeBudgetBytes.
+constexpr int kPipeSets = 2;
+constexpr int kMinGroup = 4;
+constexpr size_t kGroupBytes = size_t(160) << 20;
 constexpr size_t kPipeBudgetBytes = size_t(2) << 30;
+constexpr size_t kTailBytes = size_t(256) << 20;   // candidate-summary and walk scratch
+
+// Blocks per group and the layout of the state arrays for block width B.
+struct PipeLayout {
+  int group = 1;          // blocks per group
+  int tail_group = 1;     // blocks per tail launch
+  int64_t ystride = 0;    // elements per block state
+  int bufs() const { return kPipeSets * group; }
+};
 
 // runs f when the scope ends (releases buffers on every return path)
 template <typename F>
@@ -91,30 +103,35 @@ struct sc_graph {
   std::vector<double> spec_lam_h;
 
   // work buffers, grown on demand
-  void* Y[2 * sc::kMaxPipe] = {};          // one ping-pong pair per block in flight
+  void* Y = nullptr;                    // [2 parities][bufs][ystride] block states
   size_t ybytes = 0;
-  int ypairs = 0;                          // pairs allocated (kPipeGroups x group size)
-  hipStream_t tail_stream = nullptr;   // per-block tails overlap the next traversal
+  hipStream_t tail_stream = nullptr;    // a group's tails overlap the next traversal
   // [0] stream joins, [1 + q] traversal of the group in set q done,
-  // [1 + kPipeGroups + q] its tails done
-  hipEvent_t pipe_ev[1 + 2 * sc::kPipeGroups] = {};
-  void* partials = nullptr;
+  // [1 + kPipeSets + q] its tails done
+  hipEvent_t pipe_ev[1 + 2 * sc::kPipeSets] = {};
+  hipEvent_t call_ev[2] = {};           // start and end of a call (timing)
+  void* partials = nullptr;             // [bufs][nparts][B] giant-row chunk sums
   size_t pbytes = 0;
-  unsigned long long* mask = nullptr;   // 2 x n words (two alternating buffers)
-  uint8_t* nz = nullptr;                // [n] nonzero rows of the two-hop state (1: unknown)
-  unsigned* anymask = nullptr;          // 2 x ceil(n/32) words, one bit per node
-  int mask_pending_s0 = -1;             // block whose bits are still set
-  int mask_pending_buf = 0;
+  unsigned long long* mask = nullptr;   // [2][group][n] neighbour bits
+  size_t mask_words = 0;
+  uint8_t* nz = nullptr;                // [bufs][slices][n] nonzero rows of the two-hop state
+  size_t nz_bytes = 0;
+  unsigned* anymask = nullptr;          // [2][group][ceil(n/32)], one bit per node
+  size_t anymask_words = 0;
+  bool mask_clean = false;              // every mask word is zero but mask_pending's bits
+  sc::BlockList mask_pending;           // blocks whose bits are set (nb == 0: none), in
+  int mask_pending_buf = 0;             // this mask set
   int mask_pending_B = 0;
   double* gacc = nullptr;
   int32_t* tau_slot = nullptr;
   int32_t* tau_row = nullptr;
   int64_t* nr_slot = nullptr;
-  sc::ColStats* cs = nullptr;
-  void* colscratch = nullptr;  // sc::kColScratchBytes
+  int32_t* tau_host = nullptr;          // pinned [n + 2]: tau_row, then the capped count
   unsigned long long* work = nullptr;
-  unsigned long long* plan_work = nullptr;   // [2 x 64] walk totals per candidate switch step
-  sc::WalkScratch walk;                      // flattened walks (chunk offsets, chunk sums)
+  unsigned long long* plan_work = nullptr;   // [4][2 x 64] walk totals per candidate switch step
+  sc::TailScratch tail;                      // candidate summaries and flattened walks
+  size_t tail_blocks = 0;                    // blocks the tail buffers hold
+  size_t tail_walk_blocks = 0;
   // cached switch-step plan (the cost model depends only on these inputs)
   struct PlanKey {
     double eps;
@@ -186,7 +203,7 @@ struct HostCSR {
   int32_t n = 0;
   int64_t m = 0, nslots = 0;
   std::vector<int32_t> rowptr, col, deg, slot_row, slot_half, half_slot;
-  std::vector<Task> tasks, ptasks, wg_tasks;
+  std::vector<Task> tasks, wg_tasks;
   std::vector<HeavyRow> giant;
   int32_t nparts = 0;
   std::vector<float> inv_f;
@@ -211,7 +228,11 @@ int lanczos_lambda_star(const DeviceGraph& d, const int32_t* deg_host, hipStream
 int lanczos_spectrum(sc_graph* g, int omega, int max_iter, double tol, hipStream_t st, int* kept,
                      double* worst);
 
-int ensure_buffers(sc_graph* g, int B, size_t tsize);
+PipeLayout pipe_layout(const sc_graph* g, int B, size_t tsize);
+// work buffers of the traversal (and the sliced lists for B = 64)
+int ensure_buffers(sc_graph* g, int B, size_t tsize, hipStream_t st);
+// buffers of `blocks` tails; walks: also the chunk sums
+int ensure_tail(sc_graph* g, int blocks, bool walks);
 int ensure_pipeline(sc_graph* g);
 int ensure_closure_buffers(sc_graph* g, size_t tsize);
 int compute_lambda_star(sc_graph* g, hipStream_t st, double* out);
@@ -241,25 +262,30 @@ inline const float* inv_deg_host_sel<float>(const DeviceGraph& g) { return g.inv
 template <>
 inline const double* inv_deg_host_sel<double>(const DeviceGraph& g) { return g.inv_deg_d; }
 
-// Drives the launches of one source block [s0, s0+B).
+// Drives the launches of groups of source blocks.
 template <typename T>
 struct Runner {
   sc_graph* g;
   int B;
   hipStream_t st;
   bool timing;
+  PipeLayout lay;
   sc_stats stats{};
   size_t ev_used = 0;
-  int cur = 0;            // index of the Y buffer holding the latest step
-  int po = 0;             // first buffer of the Y pair in use (2 * pair)
+  int par = 0;            // parity of the states of the latest step
   T* rdiag = nullptr;     // optional per-slot recordings of p_l(s,s), p_l(j,s)
   T* roff = nullptr;
   int record_to = -1;     // record steps 2..record_to
 
-  T* Yb(int i) { return static_cast<T*>(g->Y[po + i]); }
+  Runner(sc_graph* g_, int B_, hipStream_t st_, bool timing_)
+      : g(g_), B(B_), st(st_), timing(timing_), lay(pipe_layout(g_, B_, sizeof(T))) {}
+
+  T* Y(int parity) {
+    return static_cast<T*>(g->Y) + static_cast<int64_t>(parity) * lay.bufs() * lay.ystride;
+  }
   T* parts() { return static_cast<T*>(g->partials); }
 
-  // odd: the sampled launches cycle through the dense steps of a block
+  // odd: the sampled launches cycle through the dense steps of a group
   static constexpr int64_t kTimeEvery = 15;
 
   // timing-only events: no system-scope fence (a fence writes back and
@@ -276,153 +302,180 @@ struct Runner {
     return SC_OK;
   }
 
-  // algorithmic bytes of one dense propagation launch: the state read once and
+  // algorithmic bytes of one dense step of one block: the state read once and
   // written once, the CSR column array, the task list and the degree vector
   double step_bytes() const {
     const double n = g->d.n, S = static_cast<double>(g->rowptr_h[g->d.n]);
     return 2.0 * n * B * sizeof(T) + 4.0 * S + 16.0 * (g->d.ntasks + g->d.nwg) + sizeof(T) * n;
   }
 
-  AccJob pending_acc;     // accumulation of the latest step, not yet launched
-
-  // recordings of step ell next to an accumulation (without one, the
-  // recording is the pending job itself and rides on the next launch)
-  int record_step(int s0, int kbeg, int kend, int ell, bool acc) {
-    if (acc && rdiag && ell <= record_to)
-      HIP_TRY(launch_record<T>(g->d, kbeg, kend, s0, B, ell, Yb(cur), rdiag, roff, st));
-    return SC_OK;
-  }
+  AccJob pending;         // accumulation of the latest step, not yet launched
 
   // launches the pending accumulation on its own
   int flush_acc() {
-    if (acc_job_set(pending_acc))
-      HIP_TRY(launch_accumulate<T>(g->d, B, Yb(cur), pending_acc, st));
-    pending_acc = AccJob{};
+    HIP_TRY(launch_accumulate<T>(g->d, B, pending, Y(par), lay.ystride, st));
+    pending = AccJob{};
     return SC_OK;
+  }
+
+  MaskJob mask_job(const BlockList& set, const BlockList& clear, int buf) {
+    MaskJob mj;
+    mj.set = set;
+    mj.clear = clear;
+    mj.buf = buf;
+    mj.slots = lay.group;
+    mj.awords = (g->d.n + 31) / 32;
+    mj.mask = g->mask;
+    mj.anymask = g->anymask;
+    return mj;
   }
 
   // clears the neighbour bits a traversal left set
   int flush_masks() {
-    if (g->mask_pending_s0 >= 0) {
-      HIP_TRY(launch_mask_update(g->d, -1, g->mask_pending_s0, g->mask_pending_B,
-                                 1 - g->mask_pending_buf, g->mask, g->anymask, st));
-      g->mask_pending_s0 = -1;
+    if (g->mask_pending.nb > 0) {
+      HIP_TRY(launch_mask_update(g->d, g->mask_pending_B,
+                                 mask_job(BlockList{}, g->mask_pending, 1 - g->mask_pending_buf),
+                                 st));
+      g->mask_pending = BlockList{};
     }
     return SC_OK;
   }
 
-  // traverse the block from l = 2 up to l = lend (l = 0, 1 are closed form);
-  // the accumulation of step l rides on the launch of step l + 1, the last one
-  // stays pending (flush_acc or a fused consumer launches it).  With next_s0 >= 0
-  // the first dense step also sets the masks of block next_s0 and clears this
-  // block's (the two-hop step, the only reader, is done by then).
-  int traverse(int s0, int kbeg, int kend, int lend, bool acc, double* gacc, int next_s0 = -1) {
-    pending_acc = AccJob{};
-    if (lend < 2) return SC_OK;
-    int buf;
-    if (g->mask_pending_s0 == s0 && g->mask_pending_B == B) {
-      buf = g->mask_pending_buf;   // a buffer only ever holds one block's bits: these are s0's
-    } else {
-      buf = g->mask_pending_s0 >= 0 ? 1 - g->mask_pending_buf : 0;
-      if (g->mask_pending_s0 >= 0 && g->mask_pending_B != B) {
-        int rc0 = flush_masks();
-        if (rc0) return rc0;
-      }
-      HIP_TRY(launch_mask_update(g->d, s0, g->mask_pending_s0, B, buf, g->mask, g->anymask, st));
-      g->mask_pending_s0 = s0;
-      g->mask_pending_buf = buf;
+  // Traverses the blocks from l = 2 (l = 0, 1 are closed form) to their own last
+  // steps lend[i] >= 2; the accumulation of step l rides on the launch of step
+  // l + 1, that of the last step stays pending (flush_acc or a fused consumer
+  // launches it).  The first dense step also sets the masks of the blocks of
+  // `next` (may be null) and clears these blocks' (the two-hop step, the only
+  // reader, is done by then).
+  int traverse(const BlockList& blocks, const int* lend, bool acc, double* gacc,
+               const BlockList* next = nullptr) {
+    pending = AccJob{};
+    if (blocks.nb == 0) return SC_OK;
+    int L = 2;
+    for (int i = 0; i < blocks.nb; ++i) L = std::max(L, lend[i]);
+    bool ready = g->mask_pending.nb == blocks.nb && g->mask_pending_B == B;
+    for (int i = 0; ready && i < blocks.nb; ++i) ready = g->mask_pending.b[i].s0 == blocks.b[i].s0;
+    if (!ready) {
+      const int rc = flush_masks();
+      if (rc) return rc;
+      HIP_TRY(launch_mask_update(g->d, B, mask_job(blocks, BlockList{}, 0), st));
+      g->mask_pending = blocks;
+      g->mask_pending_buf = 0;
       g->mask_pending_B = B;
     }
-    unsigned long long* mk = g->mask + static_cast<size_t>(buf) * g->d.n;
-    unsigned* am = g->anymask + static_cast<size_t>(buf) * ((g->d.n + 31) / 32);
-    cur = 0;
-    HIP_TRY(launch_twohop<T>(g->d, B, mk, am, Yb(cur), parts(), g->nz, st));
+    const int mbuf = g->mask_pending_buf;
+    const int64_t awords = (g->d.n + 31) / 32;
+    // blocks that have a step l, and the accumulation (or recording) of step l
+    auto having = [&](int ell) {
+      BlockList bl;
+      for (int i = 0; i < blocks.nb; ++i)
+        if (lend[i] >= ell) bl.b[bl.nb++] = blocks.b[i];
+      return bl;
+    };
     auto job = [&](int ell) {
       AccJob j;
+      j.ell = ell;
       if (acc) {
-        j.kbeg = kbeg;
-        j.kend = kend;
-        j.s0 = s0;
-        j.ell = ell;
+        j.list = having(ell);
         j.tau = g->tau_slot;
         j.gacc = gacc;
       } else if (rdiag && ell <= record_to) {
-        j.kbeg = kbeg;
-        j.kend = kend;
-        j.s0 = s0;
-        j.ell = ell;
+        j.list = having(ell);
         j.rdiag = rdiag;
         j.roff = roff;
       }
       return j;
     };
-    pending_acc = job(2);
-    int rc = record_step(s0, kbeg, kend, 2, acc);
-    if (rc) return rc;
-    for (int ell = 3; ell <= lend; ++ell) {
-      hipEvent_t a = nullptr, b = nullptr;
+    StepJob<T> s;
+    s.ystride = lay.ystride;
+    s.partials = parts();
+    s.nz = g->nz;
+    par = 0;
+    s.blocks = blocks;
+    s.Yp = Y(1);   // not read
+    s.Yn = Y(0);
+    s.mask = g->mask + static_cast<int64_t>(mbuf) * lay.group * g->d.n;
+    s.anymask = g->anymask + static_cast<int64_t>(mbuf) * lay.group * awords;
+    HIP_TRY(launch_step<T>(g->d, B, s, st));
+    s.mask = nullptr;
+    s.anymask = nullptr;
+    auto next_masks = [&]() {
+      const MaskJob mj = mask_job(next ? *next : BlockList{}, blocks, 1 - mbuf);
+      g->mask_pending = mj.set;
+      g->mask_pending_buf = 1 - mbuf;
+      return mj;
+    };
+    pending = job(2);
+    for (int ell = 3; ell <= L; ++ell) {
       // the first dense step skips the rows the two-hop step left at zero (B = 64);
       // the later ones gather every neighbour row and are the launches the stats
-      // count.  Every kTimeEvery-th of those is timed by events that take the
-      // row-gather kernel's own start and end (the kernel the roofline is taken
-      // on); the others run without events.
-      const bool skip = ell == 3 && B == 64;
-      const bool timed = timing && !skip && stats.prop_launches % kTimeEvery == 0;
+      // count.  Every kTimeEvery-th of those is timed by events that take the row
+      // kernel's own start and end; the others run without events.
+      s.skip = ell == 3 && B == 64;
+      const bool timed = timing && !s.skip && stats.prop_launches % kTimeEvery == 0;
+      s.ev_start = s.ev_stop = nullptr;
       if (timed) {
-        rc = event_pair(&a, &b);
+        const int rc = event_pair(&s.ev_start, &s.ev_stop);
         if (rc) return rc;
       }
-      MaskJob mj;
-      const bool carry = ell == 3 && next_s0 >= 0;
-      if (carry) mj = mask_job(g->d, next_s0, s0, B, 1 - buf, g->mask, g->anymask);
-      // a and b (when timed) take the kernel's own start and end times
-      HIP_TRY(launch_propagate_rows<T>(g->d, B, Yb(cur), Yb(1 - cur), parts(), pending_acc, st,
-                                       skip ? g->nz : nullptr, a, b, carry ? &mj : nullptr));
-      if (carry) {
-        g->mask_pending_s0 = next_s0;
-        g->mask_pending_buf = 1 - buf;
-      }
-      HIP_TRY(launch_fixup<T>(g->d, B, parts(), Yb(1 - cur), st));
-      if (!skip) {
+      s.blocks = having(ell);
+      s.Yp = Y(par);
+      s.Yn = Y(1 - par);
+      s.acc = pending;
+      s.mj = ell == 3 ? next_masks() : MaskJob{};
+      HIP_TRY(launch_step<T>(g->d, B, s, st));
+      if (!s.skip) {
         ++stats.prop_launches;
-        stats.prop_bytes += step_bytes();
+        stats.prop_bytes += step_bytes() * s.blocks.nb;
       }
-      cur = 1 - cur;
-      pending_acc = job(ell);
-      rc = record_step(s0, kbeg, kend, ell, acc);
-      if (rc) return rc;
+      par = 1 - par;
+      pending = job(ell);
     }
+    if (L == 2) HIP_TRY(launch_mask_update(g->d, B, next_masks(), st));
     return SC_OK;
   }
 
   // one more dense step without accumulation (switch-step planning)
-  int advance() {
-    HIP_TRY(launch_propagate<T>(g->d, B, Yb(cur), Yb(1 - cur), parts(), AccJob{}, st));
-    cur = 1 - cur;
+  int advance(const BlockList& blocks) {
+    StepJob<T> s;
+    s.blocks = blocks;
+    s.Yp = Y(par);
+    s.Yn = Y(1 - par);
+    s.ystride = lay.ystride;
+    s.partials = parts();
+    s.nz = g->nz;
+    HIP_TRY(launch_step<T>(g->d, B, s, st));
+    par = 1 - par;
     return SC_OK;
   }
 
-  // state at l = 0 (indicators) or l = 1 (one hop) when the walk tail starts that early
-  int init_low(int s0, int ell) {
-    HIP_TRY(hipMemsetAsync(Yb(0), 0, g->ybytes, st));
-    cur = 0;
-    k_init_low<T><<<B, 64, 0, st>>>(g->d.n, s0, B, ell, g->d.rowptr, g->d.col,
-                                    inv_deg_host_sel<T>(g->d), Yb(0));
-    HIP_TRY(hipGetLastError());
+  // states at l = 0 (indicators) or l = 1 (one hop) when the walk tail starts that early
+  int init_low(const BlockList& blocks, int ell) {
+    par = 0;
+    for (int i = 0; i < blocks.nb; ++i) {
+      T* y = Y(0) + blocks.b[i].buf * lay.ystride;
+      HIP_TRY(hipMemsetAsync(y, 0, static_cast<size_t>(g->d.n) * B * sizeof(T), st));
+      k_init_low<T><<<B, 64, 0, st>>>(g->d.n, blocks.b[i].s0, B, ell, g->d.rowptr, g->d.col,
+                                      inv_deg_host_sel<T>(g->d), y);
+      HIP_TRY(hipGetLastError());
+    }
     return SC_OK;
   }
 
   // a block's source range, slot range and largest truncation
-  void block_range(int b, const std::vector<int32_t>& tau_row, int* s0, int* kbeg, int* kend,
-                   int* tmax) const {
+  BlockRef block_ref(int b, const int32_t* tau_row, int* tmax) const {
     const int64_t n = g->d.n;
-    *s0 = b * B;
-    const int s1 = static_cast<int>(std::min<int64_t>(n, static_cast<int64_t>(*s0) + B));
-    *kbeg = g->rowptr_h[*s0];
-    *kend = g->rowptr_h[s1];
-    int t = 0;
-    for (int x = *s0; x < s1; ++x) t = std::max(t, tau_row[x]);
-    *tmax = t;
+    BlockRef r;
+    r.s0 = b * B;
+    const int s1 = static_cast<int>(std::min<int64_t>(n, static_cast<int64_t>(r.s0) + B));
+    r.kbeg = g->rowptr_h[r.s0];
+    r.kend = g->rowptr_h[s1];
+    if (tmax) {
+      int t = 0;
+      for (int x = r.s0; x < s1; ++x) t = std::max(t, tau_row[x]);
+      *tmax = t;
+    }
+    return r;
   }
 };
 

@@ -43,26 +43,40 @@ struct ColStats {
   double maxN, minN;     // max / min over N(s_c)
 };
 
-// Per-edge accumulation job of one source block: slots [kbeg, kend) of the
-// block starting at s0 gain the step-ell term (gacc == nullptr: no job).  With
-// rdiag set instead, the job records p_ell(s,s) and p_ell(j,s) of every slot
-// into rdiag / roff (T[slots][L0 + 1], the learned closure's recordings).
+// The source blocks of one launch.  Block i covers sources s0 .. s0 + B - 1 (CSR
+// slots [kbeg, kend)) and keeps its state at buf * ystride of the Y arrays.
+constexpr int kMaxGroup = 32;
+struct BlockRef {
+  int32_t s0 = 0, kbeg = 0, kend = 0, buf = 0;
+};
+struct BlockList {
+  int32_t nb = 0;
+  BlockRef b[kMaxGroup];
+};
+
+// Per-edge accumulation job of a group: the slots of every listed block gain the
+// step-ell term.  With rdiag set instead, the job records p_ell(s,s) and p_ell(j,s)
+// of every slot into rdiag / roff (T[slots][L0 + 1], the learned closure's
+// recordings).
 struct AccJob {
-  int kbeg = 0, kend = 0, s0 = 0, ell = 0;
+  BlockList list;                // nb == 0: no job
+  int32_t wg0[kMaxGroup] = {};   // prefix of workgroup counts (filled at launch)
+  int32_t ell = 0;
   const int32_t* tau = nullptr;
   double* gacc = nullptr;
   void* rdiag = nullptr;
   void* roff = nullptr;
 };
-inline bool acc_job_set(const AccJob& a) { return (a.gacc || a.rdiag) && a.kend > a.kbeg; }
 
-// Neighbour-bit update of the two-hop masks: set the bits of block s_set in
-// buffer buf, clear those of block s_clear in buffer 1 - buf (s_* < 0: none).
+// Neighbour-bit update of the two-hop masks: set the bits of the blocks of `set` in
+// mask set buf, clear those of `clear` in set 1 - buf.  A set holds `slots` blocks'
+// arrays, block i of a group at position i.
 struct MaskJob {
-  int s_set = -1, s_clear = -1, B = 0, buf = 0;
-  int64_t mwords = 0, awords = 0;
-  unsigned long long* mask = nullptr;
-  unsigned* anymask = nullptr;
+  BlockList set, clear;
+  int32_t buf = 0;
+  int64_t slots = 0, awords = 0;
+  unsigned long long* mask = nullptr;   // [2][slots][n]
+  unsigned* anymask = nullptr;          // [2][slots][awords]
 };
 
 struct DeviceGraph {
@@ -77,10 +91,18 @@ struct DeviceGraph {
   int32_t* half_slot = nullptr;  // [2m] half id -> slot
   float* inv_deg_f = nullptr;    // [n]
   double* inv_deg_d = nullptr;   // [n]
-  Task* tasks = nullptr;         // [ntasks] wave tasks: rows with <= kChunk slots
+  Task* tasks = nullptr;         // [ntasks] wave tasks (B < 64): rows with <= kChunk slots
   int32_t ntasks = 0;
-  Task* ptasks = nullptr;        // [nptasks] wave tasks for B = 64: runs of consecutive light
-  int32_t nptasks = 0;           //   rows with <= 64 slots in total (part = row count)
+  // sliced lists for B = 64 (built with the first such run): the light rows sorted by
+  // degree (descending) in groups of 8; group g's ids in chunks of 8 slots, chunk q at
+  // slice_nb[grp[g].x + 64 q], row r's slot 8 q + k at 8 r + k of it, n where the row
+  // has ended; a group is as wide as its longest row, rounded up to 8 (grp[g].y)
+  int2* slice_grp = nullptr;     // [nslice_grp]
+  int32_t nslice_grp = 0;
+  int32_t* slice_row = nullptr;  // [8 * nslice_grp] rows (n: none)
+  int32_t* slice_nb = nullptr;
+  float* slice_inv_f = nullptr;  // [8 * nslice_grp] 1/degree
+  double* slice_inv_d = nullptr;
   Task* wg_tasks = nullptr;      // [nwg] workgroup tasks: heavy rows, giant-row chunks
   int32_t nwg = 0;
   HeavyRow* giant = nullptr;     // [ngiant] rows cut into chunks
@@ -163,102 +185,86 @@ hipError_t launch_tau(const DeviceGraph& g, int L, double eps_tau, double lam, i
                       int32_t* tau_slot, int32_t* tau_row, hipStream_t st,
                       unsigned long long* capped = nullptr);
 
-// Mark block s_set's neighbour bits in mask buffer `buf` and clear block
-// s_clear's bits (s_clear < 0: none) in the other buffer.  mask: 2 x n words,
-// anymask: 2 x ceil(n/32) words.
-hipError_t launch_mask_update(const DeviceGraph& g, int s_set, int s_clear, int B, int buf,
-                              unsigned long long* mask, unsigned* anymask, hipStream_t st);
+// Mask update in a launch of its own.
+hipError_t launch_mask_update(const DeviceGraph& g, int B, const MaskJob& mj, hipStream_t st);
 
-// Y2 = P P Y0 for the indicator block via the neighbour masks.  With B = 64
-// and nz, nz[x] = (row x of Y2 has a nonzero) for rows of at most kChunk
-// neighbours (heavier rows are left as they are, 1).
-template <typename T>
-hipError_t launch_twohop(const DeviceGraph& g, int B, const unsigned long long* mask,
-                         const unsigned* anymask, T* Y, T* partials, uint8_t* nz, hipStream_t st);
+// Fills DeviceGraph::slice_nb from the CSR (the other slice arrays are set).
+hipError_t launch_fill_slices(const DeviceGraph& g, hipStream_t st);
 
-// The two launches of launch_propagate, separately: the row gathers (giant
-// rows leave chunk sums in partials) and the giant-row fix-up.  With B = 64
-// and nz, neighbours u with nz[u] == 0 are not gathered (their rows of Yp are
-// exact zeros, so every sum is unchanged).  Non-null ev_start / ev_stop take
-// the start and end times of the row-gather kernel itself.
-// mj (may be null): a mask update carried by extra workgroups of the same launch.
+// One step of a group of blocks: Yn = P Yp, or with mask the two-hop state
+// Yn = P P Y0 of the indicators from the neighbour masks.  acc accumulates the
+// states held in Yp and mj updates masks, carried as extra workgroups when B = 64.
 template <typename T>
-hipError_t launch_propagate_rows(const DeviceGraph& g, int B, const T* Yp, T* Yn, T* partials,
-                                 const AccJob& acc, hipStream_t st, const uint8_t* nz = nullptr,
-                                 hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
-                                 const MaskJob* mj = nullptr);
-MaskJob mask_job(const DeviceGraph& g, int s_set, int s_clear, int B, int buf,
-                 unsigned long long* mask, unsigned* anymask);
-template <typename T>
-hipError_t launch_fixup(const DeviceGraph& g, int B, const T* partials, T* Y, hipStream_t st);
-
-// Yn = P Yp (dense block gather); `acc` (may be empty) accumulates the step in Yp.
-template <typename T>
-hipError_t launch_propagate(const DeviceGraph& g, int B, const T* Yp, T* Yn, T* partials,
-                            const AccJob& acc, hipStream_t st);
-
-// gacc[k] += (Y[s][c] - Y[j][c]) / d_s for the job's slots with l <= tau_k.
-template <typename T>
-hipError_t launch_accumulate(const DeviceGraph& g, int B, const T* Y, const AccJob& acc,
-                             hipStream_t st);
-
-// Last pass of a block's flattened walks: gacc[k] += (slot k's chunk sums in
-// chunk order) / n_r.  It may ride on a later launch of the same stream that
-// comes before the next block's walks (which reuse chunk_off, part and ctl).
-struct FinishJob {
-  int kbeg = 0, kend = 0;
-  const int64_t* nr = nullptr;
-  const int64_t* chunk_off = nullptr;
-  const int64_t* ctl = nullptr;
-  const double* part = nullptr;
-  double* gacc = nullptr;   // null: no job
+struct StepJob {
+  BlockList blocks;
+  const T* Yp = nullptr;         // [buf][n * B], ystride elements apart
+  T* Yn = nullptr;
+  int64_t ystride = 0;
+  T* partials = nullptr;         // [buf][nparts * B]
+  // B = 64: the two-hop step writes nz[buf][slice][x] = (the 128-byte slice of row x
+  // has a nonzero; always 1 for heavy rows); with skip, rows flagged 0 are exact
+  // zeros in Yp and are not gathered
+  uint8_t* nz = nullptr;
+  bool skip = false;
+  const unsigned long long* mask = nullptr;   // two-hop: [i][n]
+  const unsigned* anymask = nullptr;          // [i][ceil(n/32)]
+  AccJob acc;
+  MaskJob mj;
+  hipEvent_t ev_start = nullptr, ev_stop = nullptr;   // the row kernel's own start and end
 };
-
-// Algorithm 3 summary per column of the block (top-gamma, rho bound, extremes).
-// scratch: kColScratchBytes of device memory.
-constexpr int kColParts = 2048;  // row chunks of the coalesced first pass (multiple of 4 * 64/B)
-constexpr size_t kColScratchBytes =
-    static_cast<size_t>(kColParts) * 64 *
-        (kMaxGamma * (sizeof(double) + sizeof(int)) + 2 * sizeof(double) + sizeof(int)) +
-    64 * (sizeof(int) + sizeof(double));
-// acc / fin (optional): an accumulation step and a previous block's walk
-// finish carried by the first launch as extra workgroups.
 template <typename T>
-hipError_t launch_colstats(const DeviceGraph& g, int s0, int B, int gamma, const T* Y,
-                           ColStats* cs, void* scratch, hipStream_t st,
-                           const AccJob* acc = nullptr, const FinishJob* fin = nullptr);
+hipError_t launch_step(const DeviceGraph& g, int B, const StepJob<T>& job, hipStream_t st);
+
+// The accumulation in a launch of its own.
+template <typename T>
+hipError_t launch_accumulate(const DeviceGraph& g, int B, const AccJob& acc, const T* Y,
+                             int64_t ystride, hipStream_t st);
+
+// Work buffers of the tails of a group, one set per block of the list.
+struct TailScratch {
+  ColStats* cs = nullptr;         // [blocks][64]
+  char* col = nullptr;            // [blocks] col_bytes each
+  size_t col_bytes = 0;
+  int nparts = 0;                 // row chunks of the candidate summary
+  int64_t* chunk_off = nullptr;   // [slots + blocks of the graph]; a block's at kbeg + s0 / B
+  double* part = nullptr;         // [blocks][capacity] chunk sums
+  int64_t capacity = 0;
+  int64_t* ctl = nullptr;         // [blocks][2]
+};
+// Row chunks of the candidate summary of an n-node graph (a power of two; at most
+// kColParts) and the bytes of its scratch per block.
+constexpr int kColParts = 2048;
+int col_parts(int64_t n);
+size_t col_scratch_bytes(int nparts);
+
+// The tail kernels take every block of the list in one launch; block i's state is at
+// Y + buf * ystride.
+// Algorithm 3 summary per column (top-gamma, rho bound, extremes); acc (optional): the
+// accumulation of those states, carried by the first launch.
+template <typename T>
+hipError_t launch_colstats(const DeviceGraph& g, const BlockList& blocks, int B, int gamma,
+                           const T* Y, int64_t ystride, const TailScratch& ts, hipStream_t st,
+                           const AccJob* acc = nullptr);
 
 // n_r per slot (Eq. 13 with chi of Eq. 17 / Eq. 15); 0 where tau_k <= tilde.
 template <typename T>
-hipError_t launch_walk_counts(const DeviceGraph& g, int kbeg, int kend, int s0, int B, int tilde,
-                              int gamma,
-                              double coef, int64_t nr_cap, const T* Y, const ColStats* cs,
-                              const int32_t* tau_slot, int64_t* nr_slot, hipStream_t st);
+hipError_t launch_walk_counts(const DeviceGraph& g, const BlockList& blocks, int B, int tilde,
+                              int gamma, double coef, int64_t nr_cap, const T* Y, int64_t ystride,
+                              const TailScratch& ts, const int32_t* tau_slot, int64_t* nr_slot,
+                              hipStream_t st);
 
-// work[0] += walk pairs, work[1] += single-walk steps over slots [kbeg, kend)
-hipError_t launch_work_totals(int kbeg, int kend, int tilde, const int32_t* tau_slot,
-                              const int64_t* nr_slot, unsigned long long* work, hipStream_t st);
+// work[stride * i] += walk pairs, work[stride * i + 1] += single-walk steps of block i
+hipError_t launch_work_totals(const BlockList& blocks, int tilde, const int32_t* tau_slot,
+                              const int64_t* nr_slot, unsigned long long* work, int stride,
+                              hipStream_t st);
 
-// Scratch of the flattened walks (required by launch_walks).
-struct WalkScratch {
-  int64_t* chunk_off = nullptr;   // [slots of a block + 1]
-  double* part = nullptr;         // [capacity] chunk sums
-  int64_t capacity = 0;
-  int64_t* ctl = nullptr;         // [2]
-};
-
-
-// Walk tail: gacc[k] += mean_r X_r (Eq. 11) for the block's slots (ws must hold
-// the chunk buffers; blocks whose chunks do not fit walk one slot per wave).
-// With defer, the last pass is not launched but returned in *defer (gacc null
-// when there is none); the caller runs it with launch_walk_finish or carries
-// it on launch_colstats.
+// Walk tail: gacc[k] += mean_r X_r (Eq. 11) for the blocks' slots (a block whose
+// chunk sums do not fit ts.capacity walks one slot per wave).
 template <typename T>
-hipError_t launch_walks(const DeviceGraph& g, int kbeg, int kend, int s0, int B, int tilde,
-                        uint64_t seed, const T* Y, const int32_t* tau_slot,
-                        const int64_t* nr_slot, double* gacc, const WalkScratch& ws,
-                        hipStream_t st, FinishJob* defer = nullptr);
-hipError_t launch_walk_finish(const FinishJob& job, hipStream_t st);
+hipError_t launch_walks(const DeviceGraph& g, const BlockList& blocks, int B, int tilde,
+                        uint64_t seed, const T* Y, int64_t ystride, const int32_t* tau_slot,
+                        const int64_t* nr_slot, double* gacc, const TailScratch& ts,
+                        hipStream_t st);
 // the nodes of walk pair r of half-edge (i, j) over len steps: nodes[0, len)
 // from i, nodes[len, 2 len) from j (device memory)
 hipError_t launch_walk_trace(const DeviceGraph& g, int i, int j, uint32_t r, int len,
@@ -365,14 +371,11 @@ constexpr int kRecSteps = 8;   // L0
 
 template <typename T>
 hipError_t launch_record_init(const DeviceGraph& g, T* rdiag, T* roff, hipStream_t st);
-template <typename T>
-hipError_t launch_record(const DeviceGraph& g, int kbeg, int kend, int s0, int B, int ell,
-                         const T* Y, T* rdiag, T* roff, hipStream_t st);
-// Recordings of steps ell - 1 and ell of a block from the state at ell - 1
+// Recordings of steps ell - 1 and ell of the blocks from their states at ell - 1
 // (no dense step for ell); 3 <= ell <= kRecSteps.
 template <typename T>
-hipError_t launch_record_last(const DeviceGraph& g, int kbeg, int kend, int s0, int B, int ell,
-                              const T* Y, T* rdiag, T* roff, hipStream_t st);
+hipError_t launch_record_last(const DeviceGraph& g, const BlockList& blocks, int B, int ell,
+                              const T* Y, int64_t ystride, T* rdiag, T* roff, hipStream_t st);
 template <typename T>
 hipError_t launch_features(const DeviceGraph& g, const T* rdiag, const T* roff, double lam,
                            float* X, double* s0, double* uK, double* lo, double* hi,

@@ -369,25 +369,36 @@ int record_and_features(sc_graph* g, int B, hipStream_t st, double lam, float* X
   R.record_to = sc::kRecSteps;
   const int64_t n = g->d.n;
   const int nblocks = static_cast<int>((n + B - 1) / B);
-  std::vector<int32_t> dummy_tau(n, sc::kRecSteps);
-  for (int b = 0; b < nblocks; ++b) {
-    int s0b, kbeg, kend, tmax;
-    R.block_range(b, dummy_tau, &s0b, &kbeg, &kend, &tmax);
-    // the next block's neighbour masks ride on this block's first dense step
-    // steps 2 .. L0 - 1 (recordings ride on the next launch), then steps
-    // L0 - 1 and L0 recorded from the state at L0 - 1 (no full last step)
-    const int rc = R.traverse(s0b, kbeg, kend, sc::kRecSteps - 1, false, nullptr,
-                              b + 1 < nblocks ? s0b + B : -1);
+  auto group_at = [&](int b0) {
+    sc::BlockList bl;
+    for (int b = b0; b < std::min(nblocks, b0 + R.lay.group); ++b) {
+      bl.b[bl.nb] = R.block_ref(b, nullptr, nullptr);
+      bl.b[bl.nb].buf = bl.nb;
+      ++bl.nb;
+    }
+    return bl;
+  };
+  // steps 2 .. L0 - 1 (recordings ride on the next launch), then steps L0 - 1 and L0
+  // recorded from the states at L0 - 1 (no full last step); the next group's
+  // neighbour masks ride on this group's first dense step
+  int lend[sc::kMaxGroup];
+  std::fill(lend, lend + sc::kMaxGroup, sc::kRecSteps - 1);
+  g->mask_clean = false;
+  sc::BlockList cur = group_at(0);
+  for (int b = 0; b < nblocks; b += R.lay.group) {
+    const sc::BlockList next = group_at(b + R.lay.group);
+    const int rc = R.traverse(cur, lend, false, nullptr, &next);
     if (rc) return rc;
-    R.pending_acc = sc::AccJob{};
-    if (kend > kbeg)
-      HIP_TRY(sc::launch_record_last<T>(g->d, kbeg, kend, s0b, B, sc::kRecSteps, R.Yb(R.cur),
-                                        R.rdiag, R.roff, st));
+    R.pending = sc::AccJob{};
+    HIP_TRY(sc::launch_record_last<T>(g->d, cur, B, sc::kRecSteps, R.Y(R.par), R.lay.ystride,
+                                      R.rdiag, R.roff, st));
+    cur = next;
   }
   {
     const int rc = R.flush_masks();
     if (rc) return rc;
   }
+  g->mask_clean = true;
   R.rdiag = nullptr;
   R.roff = nullptr;
   HIP_TRY(sc::launch_features<T>(g->d, static_cast<const T*>(g->rdiag), static_cast<const T*>(g->roff),
@@ -399,7 +410,7 @@ template <typename T>
 int closure_features_t(sc_graph* g, hipStream_t st, float* X, double* s0, double* uK, double* lo,
                        double* hi) {
   const int B = 64;
-  int rc = sc::ensure_buffers(g, B, sizeof(T));
+  int rc = sc::ensure_buffers(g, B, sizeof(T), st);
   if (rc) return rc;
   rc = sc::ensure_closure_buffers(g, sizeof(T));
   if (rc) return rc;
@@ -422,7 +433,7 @@ int learned_t(sc_graph* g, double eps, const sc_options& o, double* out_user, sc
   if (!o.mlp) return fail(SC_EINVAL, "SC_LEARNED needs options.mlp");
   const sc_mlp* net = o.mlp;
   const bool dev_ptrs = (o.flags & SC_DEVICE_PTRS) != 0;
-  int rc = sc::ensure_buffers(g, B, sizeof(T));
+  int rc = sc::ensure_buffers(g, B, sizeof(T), st);
   if (rc) return rc;
   rc = sc::ensure_closure_buffers(g, sizeof(T));
   if (rc) return rc;
@@ -484,18 +495,35 @@ int learned_t(sc_graph* g, double eps, const sc_options& o, double* out_user, sc
   HIP_TRY(hipStreamSynchronize(st));
   int Lmax = sc::kRecSteps;
   if (cnt[0] > 0) {
+    // the flagged blocks again by TGT, group by group
+    sc::BlockList bl;
+    int lend[sc::kMaxGroup];
+    auto run = [&]() -> int {
+      int rc1 = R.traverse(bl, lend, true, g->gacc);
+      if (rc1 == SC_OK) rc1 = R.flush_acc();
+      bl = sc::BlockList{};
+      return rc1;
+    };
+    g->mask_clean = false;
     for (int b = 0; b < nblocks; ++b) {
       if (!flags[b]) continue;
-      int s0b, kbeg, kend, tmax;
-      R.block_range(b, tau_row, &s0b, &kbeg, &kend, &tmax);
+      int tmax;
+      sc::BlockRef r = R.block_ref(b, tau_row.data(), &tmax);
       Lmax = std::max(Lmax, tmax);
-      rc = R.traverse(s0b, kbeg, kend, tmax, true, g->gacc);
-      if (rc) return rc;
-      rc = R.flush_acc();
-      if (rc) return rc;
+      if (tmax < 2) continue;   // the accumulator holds the l = 0, 1 terms
+      r.buf = bl.nb;
+      lend[bl.nb] = tmax;
+      bl.b[bl.nb++] = r;
+      if (bl.nb == R.lay.group) {
+        rc = run();
+        if (rc) return rc;
+      }
     }
+    rc = run();
+    if (rc) return rc;
     rc = R.flush_masks();
     if (rc) return rc;
+    g->mask_clean = true;
     HIP_TRY(sc::launch_combine_masked(g->d, g->gacc, g->fb, out_dev, st));
   }
   HIP_TRY(hipEventRecord(t1, st));
