@@ -282,12 +282,12 @@ __device__ inline void accumulate_group(const AccJob& acc, const int32_t* __rest
 
 // Sum over the 64-slot pieces first, first + step, ... of [beg, end) of the
 // neighbour rows of Yp (column c); lanes c, c+B, ... share a column and are
-// combined at the end.  kSkip (B = 64): rows whose flags in nz (nslices arrays of
-// n bytes) are all zero are exact zeros in Yp and are not gathered.
+// combined at the end.  kSkip (B = 64): rows whose flags in nz (one array of nzs
+// bytes per slice) are all zero are exact zeros in Yp and are not gathered.
 template <typename T, int B, bool kSkip = false>
 __device__ inline T gather_pieces(const RowArgs<T>& a, const T* __restrict__ Yp, int beg, int end,
                                   int first, int step, int lane, int c, int gq,
-                                  const uint8_t* nz = nullptr, int n = 0) {
+                                  const uint8_t* nz = nullptr, int64_t nzs = 0) {
   constexpr int G = 64 / B;
   constexpr int kBatch = sizeof(T) == 4 ? 32 : 16;   // gathers in flight per lane
   constexpr int kSlices = static_cast<int>(sizeof(T)) / 2;   // of 128 bytes per 64-column row
@@ -302,7 +302,7 @@ __device__ inline T gather_pieces(const RowArgs<T>& a, const T* __restrict__ Yp,
       unsigned any = 0;
       if (lane < cnt) {
 #pragma unroll
-        for (int q = 0; q < kSlices; ++q) any |= nz[static_cast<size_t>(q) * n + myu];
+        for (int q = 0; q < kSlices; ++q) any |= nz[q * nzs + myu];
       }
       unsigned long long rem = __ballot(any != 0);
       while (rem) {
@@ -409,29 +409,39 @@ __device__ inline void wg_finish(const RowArgs<T>& a, const Task& tk, T sum, int
 // columns: one cache line), and a slice's light rows are one XCD's work: workgroup
 // w runs on XCD w mod 8 and takes slice w mod 8 (+ 8, 16, ...) of the launch, so
 // each XCD's 4 MB L2 holds one slice of one block at a time instead of parts of
-// whole rows of the same block in all eight.  BA, n = 34,401, 12 edges per node
-// (a slice is 4.4 MB): 25 -> 9 us per step and block; n = 100,000 (12.8 MB): 63 ->
-// 45 us, where the bound stays the rate of rows fetched past L2.
+// whole rows of the same block in all eight.
 //
 // Light rows are read through the sliced lists of DeviceGraph (rows sorted by
 // degree in groups of 8): a wave takes a group, 8 lanes x 16 bytes per row, so one
 // load instruction fetches the neighbours of 8 rows; the ids of 8 rows x 8 slots
-// are one coalesced load, spread within each row's lanes by ds_swizzle.  Padding
-// (id n) and, in kSkip, rows the two-hop step flagged zero issue no load.
+// are one coalesced load, spread within each row's lanes by ds_swizzle.  Padding is
+// id n, whose offset lies past the buffer descriptor's end: such loads return zero
+// and move nothing, without a branch (a vector instruction takes four cycles here,
+// so at 20 slots per row the addressing and the additions cost about as much as the
+// gathers).  Sums are in slot order.
+//
+// The two-hop step and the step after it test one bit per neighbour (is it joined
+// to a source of the block; is its slice of the two-hop state nonzero) in a bitmap
+// in LDS, filled once per workgroup, so these two launch as many workgroups as are
+// resident and stride over the groups.  From memory such a test fetches a line per
+// neighbour, as much as gathering the row.
 //
 // A launch covers every block of a group (up to kMaxGroup): the launch and drain of
 // a step and its longest row's chain of dependent loads are paid once per group.
-enum StepMode { kFull, kSkip, kTwoHop };
+// kTwoHopBig: the two-hop step of graphs whose bitmap is too large for LDS.
+enum StepMode { kFull, kSkip, kTwoHop, kTwoHopBig };
+constexpr bool is_twohop(int mode) { return mode == kTwoHop || mode == kTwoHopBig; }
 
 template <typename T>
 struct StepArgs {
   int n;
   int nslices;                 // slices of the launch: blocks.nb * slices per block
-  int slice_wgs;               // workgroups per slice
+  int slice_wgs;               // workgroups per slice in the whole rounds of 8 slices
+  int rem_wgs;                 // workgroups per slice of the remaining nslices mod 8
   int heavy_wgs;               // workgroups of the heavy tasks (multiple of 8, before the slices)
   int light_wgs;               // workgroups of the slices
   int acc_wgs;                 // workgroups of the accumulation, then the mask update
-  const int2* grp;             // [ngrp] (first id word, padded width)
+  const int2* grp;             // [ngrp] (first chunk, padded width)
   int ngrp;
   const int32_t* grow;         // [ngrp * 8] rows (n: none)
   const T* ginv;               // [ngrp * 8] 1/degree
@@ -439,7 +449,8 @@ struct StepArgs {
   const T* Yp;                 // state at l - 1 / at l, block buf at buf * ystride
   T* Yn;
   int64_t ystride;
-  uint8_t* nz;                 // [buf][slice][n]: row flags of the two-hop state
+  uint8_t* nz;                 // [buf][slice][nzs]: row flags of the two-hop state
+  int64_t nzs;
   const unsigned long long* mask;   // [i][n], i = position of the block in the group
   const unsigned* anymask;
   int64_t awords;
@@ -476,131 +487,199 @@ template <typename T>
 struct alignas(16) Vec16 {
   T v[16 / sizeof(T)];
 };
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
-// Loads of one chunk: the rows of ids (8 per row group lane set) in flight at once.
-template <typename T, int k>
-__device__ inline void load_step(const char* Yp, int ids, int n, uint32_t coff, Vec16<T>& out) {
-  constexpr uint32_t kRow = 64 * sizeof(T);
-  const int u = row_lane<k>(ids);
-  if (u < n) {
-    out = *reinterpret_cast<const Vec16<T>*>(Yp + (static_cast<size_t>(static_cast<uint32_t>(u)) * kRow + coff));
-  } else {
+// The block state rows are gathered from.  kWide: states of 4 GiB or more, which a
+// buffer descriptor's 32-bit offsets do not reach.
+template <typename T, bool kWide>
+struct RowSource {
+  static constexpr int kShift = sizeof(T) == 4 ? 8 : 9;   // log2 of the bytes of a row
+  const char* base;
+  __amdgpu_buffer_rsrc_t rsrc;
+  int n;
+  uint32_t coff;   // the lane's byte offset inside a row
+  __device__ RowSource(const T* Y, int n_, uint32_t coff_) : n(n_), coff(coff_) {
+    base = reinterpret_cast<const char*>(Y);
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0,
+                                             static_cast<uint32_t>(n_) << kShift, 0x00020000);
+  }
+  // 16 bytes of row u, zeros for u == n
+  __device__ Vec16<T> load(int u) const {
+    if constexpr (kWide) {
+      if (u < n)
+        return *reinterpret_cast<const Vec16<T>*>(base + ((static_cast<size_t>(u) << kShift) + coff));
+      Vec16<T> z;
 #pragma unroll
-    for (int e = 0; e < static_cast<int>(16 / sizeof(T)); ++e) out.v[e] = T(0);
+      for (int e = 0; e < static_cast<int>(16 / sizeof(T)); ++e) z.v[e] = T(0);
+      return z;
+    } else {
+      const u32x4_t w = __builtin_amdgcn_raw_buffer_load_b128(
+          rsrc, (static_cast<uint32_t>(u) << kShift) + coff, 0, 0);
+      return __builtin_bit_cast(Vec16<T>, w);
+    }
+  }
+};
+
+// Steps [0, K) of a chunk: the loads in flight together, then added in slot order.
+template <typename T, int K, typename Src>
+__device__ inline void load_chunk(const Src& src, int ids, Vec16<T>* v) {
+  v[0] = src.load(row_lane<0>(ids));
+  v[1] = src.load(row_lane<1>(ids));
+  v[2] = src.load(row_lane<2>(ids));
+  v[3] = src.load(row_lane<3>(ids));
+  if constexpr (K == 8) {
+    v[4] = src.load(row_lane<4>(ids));
+    v[5] = src.load(row_lane<5>(ids));
+    v[6] = src.load(row_lane<6>(ids));
+    v[7] = src.load(row_lane<7>(ids));
   }
 }
 
-template <typename T>
-__device__ inline void load_chunk(const char* Yp, int ids, int n, uint32_t coff, Vec16<T> (&v)[8]) {
-  load_step<T, 0>(Yp, ids, n, coff, v[0]);
-  load_step<T, 1>(Yp, ids, n, coff, v[1]);
-  load_step<T, 2>(Yp, ids, n, coff, v[2]);
-  load_step<T, 3>(Yp, ids, n, coff, v[3]);
-  load_step<T, 4>(Yp, ids, n, coff, v[4]);
-  load_step<T, 5>(Yp, ids, n, coff, v[5]);
-  load_step<T, 6>(Yp, ids, n, coff, v[6]);
-  load_step<T, 7>(Yp, ids, n, coff, v[7]);
-}
-
-template <typename T>
-__device__ inline void add_chunk(const Vec16<T> (&v)[8], T (&acc)[16 / sizeof(T)]) {
+template <typename T, int K>
+__device__ inline void add_chunk(const Vec16<T>* v, T (&acc)[16 / sizeof(T)]) {
 #pragma unroll
-  for (int k = 0; k < 8; ++k)
+  for (int k = 0; k < K; ++k)
 #pragma unroll
     for (int e = 0; e < static_cast<int>(16 / sizeof(T)); ++e) acc[e] += v[k].v[e];
 }
 
-// two-hop: neighbour u adds 1/d_u to the columns whose source it is joined to
+// two-hop: neighbour u adds 1/d_u to the columns whose source it is joined to; hits:
+// the lanes whose neighbour has any such column
 template <typename T, int k>
-__device__ inline void twohop_step(unsigned m, T w, int c, T (&acc)[16 / sizeof(T)]) {
+__device__ inline void twohop_step(unsigned long long hits, unsigned m, T w, int c,
+                                   T (&acc)[16 / sizeof(T)]) {
   constexpr int V = 16 / sizeof(T);
+  if ((hits & (0x0101010101010101ull << k)) == 0ull) return;   // wave-uniform
   const unsigned mk = static_cast<unsigned>(row_lane<k>(static_cast<int>(m))) >> (c * V);
   const T wk = row_lane_f<k>(w);
 #pragma unroll
   for (int e = 0; e < V; ++e) acc[e] += ((mk >> e) & 1u) ? wk : T(0);
 }
 
-template <typename T, int MODE>
-__device__ inline void light_rows(const StepArgs<T>& a, int sl, int wg, int lane, int wave) {
+// The light rows of slice sl: groups wg * 4 + wave, + 4 wgs, ...
+template <typename T, int MODE, bool kWide>
+__device__ inline void light_rows(const StepArgs<T>& a, int sl, int wg, int wgs, int lane, int wave,
+                                  unsigned* s_bits) {
   constexpr int V = 16 / sizeof(T);        // columns per lane
   constexpr int C = 8 * V;                 // columns per slice
   constexpr int kSlices = 64 / C;          // slices per block
-  const int gi = wg * kWavesPerBlock + wave;
-  if (gi >= a.ngrp) return;
   const int i = sl / kSlices, h = sl % kSlices;
   const int buf = a.blocks.b[i].buf;
   const int n = a.n;
-  const int2 g = a.grp[gi];
-  const int r = lane >> 3, c = lane & 7;
-  const int row = a.grow[gi * 8 + r];
-  const T iv = a.ginv[gi * 8 + r];
-  const int32_t* __restrict__ p = a.gnb + g.x + lane;
-  const int nch = g.y >> 3;
-  T acc[V];
-#pragma unroll
-  for (int e = 0; e < V; ++e) acc[e] = T(0);
-  const uint32_t coff = static_cast<uint32_t>(h * 128 + c * 16);
+  const int words = (n + 31) / 32;
+  const unsigned* __restrict__ am =
+      is_twohop(MODE) ? a.anymask + static_cast<size_t>(i) * a.awords : nullptr;
   if constexpr (MODE == kTwoHop) {
-    const unsigned long long* __restrict__ mask = a.mask + static_cast<size_t>(i) * n;
-    const unsigned* __restrict__ am = a.anymask + static_cast<size_t>(i) * a.awords;
-    for (int ch = 0; ch < nch; ++ch) {
-      const int u = p[ch * 64];
-      // the small bitmap filters out the neighbours no column marks
-      const bool hit = u < n && ((am[u >> 5] >> (u & 31)) & 1u);
-      unsigned m = 0;
-      if (hit) m = static_cast<unsigned>(mask[u] >> (h * C)) & (C == 32 ? 0xFFFFFFFFu : ((1u << (C & 31)) - 1u));
-      if (__ballot(m != 0) == 0ull) continue;
-      const T w = m ? a.inv[u] : T(0);
-      twohop_step<T, 0>(m, w, c, acc);
-      twohop_step<T, 1>(m, w, c, acc);
-      twohop_step<T, 2>(m, w, c, acc);
-      twohop_step<T, 3>(m, w, c, acc);
-      twohop_step<T, 4>(m, w, c, acc);
-      twohop_step<T, 5>(m, w, c, acc);
-      twohop_step<T, 6>(m, w, c, acc);
-      twohop_step<T, 7>(m, w, c, acc);
+    for (int q = threadIdx.x; q < words; q += kThreads) s_bits[q] = am[q];
+    __syncthreads();
+  } else if constexpr (MODE == kSkip) {
+    // 32 byte flags (0 or 1) to one word; the flag array is padded to 64 bytes
+    const uint4* __restrict__ nz = reinterpret_cast<const uint4*>(
+        a.nz + (static_cast<size_t>(buf) * kSlices + h) * a.nzs);
+    for (int q = threadIdx.x; q < words; q += kThreads) {
+      const uint4 x = nz[2 * q], y = nz[2 * q + 1];
+      auto four = [](unsigned w) { return (w * 0x10204080u) >> 28; };
+      s_bits[q] = four(x.x) | four(x.y) << 4 | four(x.z) << 8 | four(x.w) << 12 |
+                  four(y.x) << 16 | four(y.y) << 20 | four(y.z) << 24 | four(y.w) << 28;
     }
-  } else {
-    const char* Yp = reinterpret_cast<const char*>(a.Yp + buf * a.ystride);
-    const uint8_t* __restrict__ nz =
-        MODE == kSkip ? a.nz + (static_cast<size_t>(buf) * kSlices + h) * n : nullptr;
-    // two chunks (16 slots of each row) in flight; sums in slot order
-    int ch = 0;
-    for (; ch + 1 < nch; ch += 2) {
-      int i0 = p[ch * 64], i1 = p[ch * 64 + 64];
-      if (MODE == kSkip) {
-        if (i0 < n && !nz[i0]) i0 = n;
-        if (i1 < n && !nz[i1]) i1 = n;
+    __syncthreads();
+  }
+  const int r = lane >> 3, c = lane & 7;
+  const uint32_t coff = static_cast<uint32_t>(h * 128 + c * 16);
+  [[maybe_unused]] const RowSource<T, kWide> src(a.Yp + buf * a.ystride, n, coff);
+  for (int gi = wg * kWavesPerBlock + wave; gi < a.ngrp; gi += wgs * kWavesPerBlock) {
+    const int2 g = a.grp[gi];
+    const int row = a.grow[gi * 8 + r];
+    const T iv = a.ginv[gi * 8 + r];
+    const int32_t* __restrict__ p = a.gnb + static_cast<int64_t>(g.x) * 64 + lane;
+    T acc[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) acc[e] = T(0);
+    if constexpr (is_twohop(MODE)) {
+      const unsigned long long* __restrict__ mask = a.mask + static_cast<size_t>(i) * n;
+      const int nch = (g.y + 7) >> 3;
+      int next = p[0];
+      for (int ch = 0; ch < nch; ++ch) {
+        const int u = next;
+        if (ch + 1 < nch) next = p[ch * 64 + 64];
+        const bool hit =
+            u < n && (((MODE == kTwoHop ? s_bits[u >> 5] : am[u >> 5]) >> (u & 31)) & 1u);
+        if (__ballot(hit) == 0ull) continue;
+        unsigned m = 0;
+        T w = T(0);
+        if (hit) {
+          m = static_cast<unsigned>(mask[u] >> (h * C)) &
+              (C == 32 ? 0xFFFFFFFFu : ((1u << (C & 31)) - 1u));
+          w = a.inv[u];
+        }
+        const unsigned long long hits = __ballot(m != 0);
+        twohop_step<T, 0>(hits, m, w, c, acc);
+        twohop_step<T, 1>(hits, m, w, c, acc);
+        twohop_step<T, 2>(hits, m, w, c, acc);
+        twohop_step<T, 3>(hits, m, w, c, acc);
+        twohop_step<T, 4>(hits, m, w, c, acc);
+        twohop_step<T, 5>(hits, m, w, c, acc);
+        twohop_step<T, 6>(hits, m, w, c, acc);
+        twohop_step<T, 7>(hits, m, w, c, acc);
       }
-      Vec16<T> v0[8], v1[8];
-      load_chunk<T>(Yp, i0, n, coff, v0);
-      load_chunk<T>(Yp, i1, n, coff, v1);
-      add_chunk<T>(v0, acc);
-      add_chunk<T>(v1, acc);
+    } else {
+      auto live = [&](int u) {   // a zero row reads as padding
+        if constexpr (MODE == kSkip)
+          return u < n && ((s_bits[u >> 5] >> (u & 31)) & 1u) ? u : n;
+        else
+          return u;
+      };
+      // two chunks (16 slots of each row) in flight
+      const int nf = g.y >> 3;
+      const bool half = (g.y & 4) != 0;
+      int q = 0;
+      for (; q + 1 < nf; q += 2) {
+        const int i0 = live(p[q * 64]), i1 = live(p[q * 64 + 64]);
+        Vec16<T> v0[8], v1[8];
+        load_chunk<T, 8>(src, i0, v0);
+        load_chunk<T, 8>(src, i1, v1);
+        add_chunk<T, 8>(v0, acc);
+        add_chunk<T, 8>(v1, acc);
+      }
+      if (q < nf && half) {
+        const int i0 = live(p[q * 64]), i1 = live(p[q * 64 + 64]);
+        Vec16<T> v0[8], v1[4];
+        load_chunk<T, 8>(src, i0, v0);
+        load_chunk<T, 4>(src, i1, v1);
+        add_chunk<T, 8>(v0, acc);
+        add_chunk<T, 4>(v1, acc);
+      } else if (q < nf) {
+        Vec16<T> v0[8];
+        load_chunk<T, 8>(src, live(p[q * 64]), v0);
+        add_chunk<T, 8>(v0, acc);
+      } else if (half) {
+        Vec16<T> v0[4];
+        load_chunk<T, 4>(src, live(p[q * 64]), v0);
+        add_chunk<T, 4>(v0, acc);
+      }
     }
-    if (ch < nch) {
-      int i0 = p[ch * 64];
-      if (MODE == kSkip && i0 < n && !nz[i0]) i0 = n;
-      Vec16<T> v0[8];
-      load_chunk<T>(Yp, i0, n, coff, v0);
-      add_chunk<T>(v0, acc);
+    if (is_twohop(MODE)) {
+      bool any = false;
+#pragma unroll
+      for (int e = 0; e < V; ++e) any |= acc[e] != T(0);
+      const unsigned long long b = __ballot(any);
+      if (c == 0 && row < n)
+        a.nz[(static_cast<size_t>(buf) * kSlices + h) * a.nzs + row] =
+            (b >> (8 * r)) & 0xFFull ? 1 : 0;
+    }
+    if (row < n) {
+      Vec16<T> o;
+#pragma unroll
+      for (int e = 0; e < V; ++e) o.v[e] = acc[e] * iv;
+      char* Yn = reinterpret_cast<char*>(a.Yn + buf * a.ystride);
+      *reinterpret_cast<Vec16<T>*>(Yn + (static_cast<size_t>(row) * (64 * sizeof(T)) + coff)) = o;
     }
   }
-  if (MODE == kTwoHop) {
-    bool any = false;
-#pragma unroll
-    for (int e = 0; e < V; ++e) any |= acc[e] != T(0);
-    const unsigned long long b = __ballot(any);
-    if (c == 0 && row < n)
-      a.nz[(static_cast<size_t>(buf) * kSlices + h) * n + row] = (b >> (8 * r)) & 0xFFull ? 1 : 0;
-  }
-  if (row < n) {
-    Vec16<T> o;
-#pragma unroll
-    for (int e = 0; e < V; ++e) o.v[e] = acc[e] * iv;
-    char* Yn = reinterpret_cast<char*>(a.Yn + buf * a.ystride);
-    *reinterpret_cast<Vec16<T>*>(Yn + (static_cast<size_t>(row) * (64 * sizeof(T)) + coff)) = o;
-  }
+}
+
+// XCDs per slice when rem (1..7) slices share the eight
+__host__ __device__ inline int rem_xcds(int rem) {
+  return rem > 4 ? 1 : rem > 2 ? 2 : rem > 1 ? 4 : 8;
 }
 
 // Heavy task of one block: the four waves take interleaved 64-slot pieces, lane =
@@ -610,26 +689,26 @@ __device__ inline void heavy_rows(const StepArgs<T>& a, int i, int t, int lane, 
   constexpr int kSlices = static_cast<int>(sizeof(T)) / 2;
   const int buf = a.blocks.b[i].buf;
   const Task tk = a.row.wg_tasks[t];
-  uint8_t* nz = a.nz + static_cast<size_t>(buf) * kSlices * a.n;
+  uint8_t* nz = a.nz + static_cast<size_t>(buf) * kSlices * a.nzs;
   RowArgs<T> ra = a.row;
   ra.partials += static_cast<size_t>(buf) * a.part_rows * 64;
   T sum;
-  if constexpr (MODE == kTwoHop) {
+  if constexpr (is_twohop(MODE)) {
     sum = twohop_pieces<T, 64>(ra, a.mask + static_cast<size_t>(i) * a.n,
                                a.anymask + static_cast<size_t>(i) * a.awords, tk.beg, tk.end, wave,
                                kWavesPerBlock, lane, lane, 0);
     if (static_cast<int>(threadIdx.x) < kSlices)   // heavy rows count as nonzero
-      nz[static_cast<size_t>(threadIdx.x) * a.n + tk.row] = 1;
+      nz[static_cast<size_t>(threadIdx.x) * a.nzs + tk.row] = 1;
   } else {
     sum = gather_pieces<T, 64, MODE == kSkip>(ra, a.Yp + buf * a.ystride, tk.beg, tk.end, wave,
-                                              kWavesPerBlock, lane, lane, 0, nz, a.n);
+                                              kWavesPerBlock, lane, lane, 0, nz, a.nzs);
   }
   wg_finish<T, 64>(ra, tk, sum, wave, lane, a.Yn + buf * a.ystride);
 }
 
-template <typename T, int MODE>
+template <typename T, int MODE, bool kWide>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_step(StepArgs<T> a) {
-  constexpr int kSlices = static_cast<int>(sizeof(T)) / 2;
+  extern __shared__ unsigned s_bits[];   // one bit per node (kSkip, kTwoHop)
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   int w = static_cast<int>(blockIdx.x);
@@ -652,17 +731,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   if (w < a.light_wgs) {
     const int x = w & 7, j = w >> 3;
     const int rounds = a.nslices >> 3, rem = a.nslices & 7;
-    int sl, wg;
+    int sl, wg, wgs;
     if (j < rounds * a.slice_wgs) {
       sl = x + 8 * (j / a.slice_wgs);
       wg = j % a.slice_wgs;
+      wgs = a.slice_wgs;
     } else {   // the last rem < 8 slices, each on 8, 4, 2 or 1 XCDs
-      const int k = rem > 4 ? 1 : rem > 2 ? 2 : rem > 1 ? 4 : 8;
+      const int k = rem_xcds(rem);
       if (x / k >= rem) return;
       sl = 8 * rounds + x / k;
       wg = (j - rounds * a.slice_wgs) * k + x % k;
+      wgs = a.rem_wgs;
+      if (wg >= wgs) return;
     }
-    light_rows<T, MODE>(a, sl, wg, lane, wave);
+    light_rows<T, MODE, kWide>(a, sl, wg, wgs, lane, wave, s_bits);
     return;
   }
   w -= a.light_wgs;
@@ -672,7 +754,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   }
   mask_update_wave((w - a.acc_wgs) * kWavesPerBlock + wave, lane, a.n, 64, a.mj, a.rowptr,
                    a.row.col);
-  (void)kSlices;
 }
 
 // ------------------------------------------------------------------ one step of a block, B < 64
@@ -762,9 +843,9 @@ __global__ __launch_bounds__(256) void k_fill_slices(int n, int ngrp, const int2
   const int row = grow[gi * 8 + (lane >> 3)];
   const int beg = row < n ? rowptr[row] : 0;
   const int end = row < n ? rowptr[row + 1] : 0;
-  for (int q = 0; q < (g.y >> 3); ++q) {
+  for (int q = 0; 8 * q < g.y; ++q) {
     const int k = beg + 8 * q + (lane & 7);
-    gnb[g.x + q * 64 + lane] = k < end ? col[k] : n;
+    gnb[(static_cast<int64_t>(g.x) + q) * 64 + lane] = k < end ? col[k] : n;
   }
 }
 
@@ -977,11 +1058,24 @@ hipError_t launch_step(const DeviceGraph& g, int B, const StepJob<T>& job, hipSt
   StepArgs<T> a;
   a.n = g.n;
   a.nslices = nb * static_cast<int>(sizeof(T) / 2);
-  a.slice_wgs = static_cast<int>(grid_for(g.nslice_grp, kWavesPerBlock));
-  a.heavy_wgs = (nb * g.nwg + 7) / 8 * 8;
+  const int groups_wgs = static_cast<int>(grid_for(g.nslice_grp, kWavesPerBlock));
   const int rem = a.nslices & 7;
-  const int k = rem > 4 ? 1 : rem > 2 ? 2 : rem > 1 ? 4 : 8;
-  a.light_wgs = 8 * (a.nslices >> 3) * a.slice_wgs + (rem ? 8 * ((a.slice_wgs + k - 1) / k) : 0);
+  const int k = rem ? rem_xcds(rem) : 1;
+  size_t lds = 0;
+  a.slice_wgs = a.rem_wgs = groups_wgs;
+  const bool skip = job.skip && step_can_skip(g.n);
+  const bool big = twohop && !step_can_skip(g.n);
+  if ((twohop && !big) || skip) {
+    // the bitmap's workgroups: as many as are resident on the slice's XCDs (32 CUs
+    // each, 160 KB of LDS, and 8 or 5 workgroups by registers)
+    lds = static_cast<size_t>(awords) * 4;
+    const int per_cu = static_cast<int>(
+        std::max<size_t>(1, std::min<size_t>(twohop ? 8 : 5, (size_t(160) << 10) / (lds + 2048))));
+    a.slice_wgs = std::min(groups_wgs, 32 * per_cu);
+    a.rem_wgs = std::min(groups_wgs, 32 * per_cu * k);
+  }
+  a.heavy_wgs = (nb * g.nwg + 7) / 8 * 8;
+  a.light_wgs = 8 * (a.nslices >> 3) * a.slice_wgs + (rem ? 8 * ((a.rem_wgs + k - 1) / k) : 0);
   a.grp = g.slice_grp;
   a.ngrp = g.nslice_grp;
   a.grow = g.slice_row;
@@ -991,6 +1085,7 @@ hipError_t launch_step(const DeviceGraph& g, int B, const StepJob<T>& job, hipSt
   a.Yn = job.Yn;
   a.ystride = job.ystride;
   a.nz = job.nz;
+  a.nzs = flag_stride(g.n);
   a.mask = job.mask;
   a.anymask = job.anymask;
   a.awords = awords;
@@ -1009,12 +1104,18 @@ hipError_t launch_step(const DeviceGraph& g, int B, const StepJob<T>& job, hipSt
   const int64_t grid = static_cast<int64_t>(a.heavy_wgs) + a.light_wgs + a.acc_wgs + mask_wgs;
   if (grid <= 0 || grid > INT_MAX) return hipErrorInvalidValue;
   const dim3 gd(static_cast<unsigned>(grid)), bd(kThreads);
-  if (twohop)
-    k_step<T, kTwoHop><<<gd, bd, 0, st>>>(a);
-  else if (job.skip)
-    k_step<T, kSkip><<<gd, bd, 0, st>>>(a);
-  else
-    hipExtLaunchKernelGGL((k_step<T, kFull>), gd, bd, 0, st, job.ev_start, job.ev_stop, 0, a);
+  const bool wide = static_cast<uint64_t>(g.n) * 64 * sizeof(T) > 0xFFFFFC00ull;
+  if (big) {
+    k_step<T, kTwoHopBig, false><<<gd, bd, 0, st>>>(a);
+  } else if (twohop) {
+    k_step<T, kTwoHop, false><<<gd, bd, lds, st>>>(a);
+  } else if (skip) {
+    k_step<T, kSkip, false><<<gd, bd, lds, st>>>(a);
+  } else if (!wide) {
+    hipExtLaunchKernelGGL((k_step<T, kFull, false>), gd, bd, 0, st, job.ev_start, job.ev_stop, 0, a);
+  } else {
+    hipExtLaunchKernelGGL((k_step<T, kFull, true>), gd, bd, 0, st, job.ev_start, job.ev_stop, 0, a);
+  }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_fixup<T>(g, B, job.blocks, job.partials, job.Yn, job.ystride, st);

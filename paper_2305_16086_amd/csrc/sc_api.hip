@@ -1091,11 +1091,9 @@ int build_slice_lists(sc_graph* g, hipStream_t st) {
     grp.resize(ngrp);
     int64_t off = 0;
     for (int32_t k = 0; k < ngrp; ++k) {
-      const int32_t width = (g->deg_h[rows[8 * k]] + 7) / 8 * 8;
-      grp[k] = make_int2(static_cast<int>(off), width);
-      off += 8 * static_cast<int64_t>(width);
-      if (off > std::numeric_limits<int32_t>::max() - 64)
-        return fail(SC_EINVAL, "graph too large for the block path's neighbour lists");
+      const int32_t width = (g->deg_h[rows[8 * k]] + 3) / 4 * 4;
+      grp[k] = make_int2(static_cast<int>(off), width);   // below 2^31 / 8 + n / 8 chunks
+      off += (width + 7) / 8;
     }
     std::vector<float> invf(rows.size(), 0.0f);
     std::vector<double> invd(rows.size(), 0.0);
@@ -1117,7 +1115,7 @@ int build_slice_lists(sc_graph* g, hipStream_t st) {
     if (e == hipSuccess) e = up(&d.slice_inv_f, invf);
     if (e == hipSuccess) e = up(&d.slice_inv_d, invd);
     int32_t* nb = nullptr;
-    if (e == hipSuccess) e = dev_alloc(&nb, static_cast<size_t>(off));
+    if (e == hipSuccess) e = dev_alloc(&nb, 64 * static_cast<size_t>(off));
     if (e == hipSuccess) {
       d.slice_nb = nb;
       e = launch_fill_slices(d, st);
@@ -1152,7 +1150,7 @@ int ensure_buffers(sc_graph* g, int B, size_t tsize, hipStream_t st) {
   if (B == 64) {
     const int rc = build_slice_lists(g, st);
     if (rc) return rc;
-    const size_t nzb = static_cast<size_t>(lay.bufs()) * (tsize / 2) * n;
+    const size_t nzb = static_cast<size_t>(lay.bufs()) * (tsize / 2) * flag_stride(n);
     HIP_TRY(grow_zeroed(&g->nz, &g->nz_bytes, nzb, st));
   }
   const size_t pb = static_cast<size_t>(lay.bufs()) * std::max(g->d.nparts, 1) * B * tsize;

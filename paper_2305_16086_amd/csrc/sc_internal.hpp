@@ -95,8 +95,8 @@ struct DeviceGraph {
   int32_t ntasks = 0;
   // sliced lists for B = 64 (built with the first such run): the light rows sorted by
   // degree (descending) in groups of 8; group g's ids in chunks of 8 slots, chunk q at
-  // slice_nb[grp[g].x + 64 q], row r's slot 8 q + k at 8 r + k of it, n where the row
-  // has ended; a group is as wide as its longest row, rounded up to 8 (grp[g].y)
+  // slice_nb[64 (grp[g].x + q)], row r's slot 8 q + k at 8 r + k of it, n where the row
+  // has ended; a group is as wide as its longest row, rounded up to 4 (grp[g].y)
   int2* slice_grp = nullptr;     // [nslice_grp]
   int32_t nslice_grp = 0;
   int32_t* slice_row = nullptr;  // [8 * nslice_grp] rows (n: none)
@@ -191,6 +191,12 @@ hipError_t launch_mask_update(const DeviceGraph& g, int B, const MaskJob& mj, hi
 // Fills DeviceGraph::slice_nb from the CSR (the other slice arrays are set).
 hipError_t launch_fill_slices(const DeviceGraph& g, hipStream_t st);
 
+// Bytes between the row-flag arrays of StepJob::nz, and whether the step after the
+// two-hop step can skip zero rows (their bitmap has to leave five workgroups per CU
+// their LDS).
+inline int64_t flag_stride(int64_t n) { return (n + 63) / 64 * 64; }
+inline bool step_can_skip(int64_t n) { return n <= 240000; }
+
 // One step of a group of blocks: Yn = P Yp, or with mask the two-hop state
 // Yn = P P Y0 of the indicators from the neighbour masks.  acc accumulates the
 // states held in Yp and mj updates masks, carried as extra workgroups when B = 64.
@@ -202,8 +208,8 @@ struct StepJob {
   int64_t ystride = 0;
   T* partials = nullptr;         // [buf][nparts * B]
   // B = 64: the two-hop step writes nz[buf][slice][x] = (the 128-byte slice of row x
-  // has a nonzero; always 1 for heavy rows); with skip, rows flagged 0 are exact
-  // zeros in Yp and are not gathered
+  // has a nonzero; always 1 for heavy rows), flag_stride(n) bytes per slice; with skip,
+  // rows flagged 0 are exact zeros in Yp and are not gathered (where step_can_skip)
   uint8_t* nz = nullptr;
   bool skip = false;
   const unsigned long long* mask = nullptr;   // two-hop: [i][n]

@@ -25,6 +25,8 @@ DEGREES = (8, 9, 16, 17, 64, 65, 255, 256, 257)
 
 @pytest.fixture(scope="module")
 def sc():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
     from paper_2305_16086_amd import sc as scmod
     return scmod
 
