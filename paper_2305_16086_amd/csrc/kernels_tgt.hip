@@ -405,11 +405,9 @@ __device__ inline void wg_finish(const RowArgs<T>& a, const Task& tk, T sum, int
 }
 
 // ------------------------------------------------------------------ one step of a group, B = 64
-// A block's state is cut into slices of 128 bytes per row (32 FP32 or 16 FP64
-// columns: one cache line), and a slice's light rows are one XCD's work: workgroup
-// w runs on XCD w mod 8 and takes slice w mod 8 (+ 8, 16, ...) of the launch, so
-// each XCD's 4 MB L2 holds one slice of one block at a time instead of parts of
-// whole rows of the same block in all eight.
+// The light rows of a slice (SliceGrid) are one XCD's work, so each XCD's L2 holds one
+// slice of one block at a time instead of parts of whole rows of the same block in all
+// eight.
 //
 // Light rows are read through the sliced lists of DeviceGraph (rows sorted by
 // degree in groups of 8): a wave takes a group, 8 lanes x 16 bytes per row, so one
@@ -435,9 +433,7 @@ constexpr bool is_twohop(int mode) { return mode == kTwoHop || mode == kTwoHopBi
 template <typename T>
 struct StepArgs {
   int n;
-  int nslices;                 // slices of the launch: blocks.nb * slices per block
-  int slice_wgs;               // workgroups per slice in the whole rounds of 8 slices
-  int rem_wgs;                 // workgroups per slice of the remaining nslices mod 8
+  SliceGrid slices;            // light rows of the blocks' slices
   int heavy_wgs;               // workgroups of the heavy tasks (multiple of 8, before the slices)
   int light_wgs;               // workgroups of the slices
   int acc_wgs;                 // workgroups of the accumulation, then the mask update
@@ -677,11 +673,6 @@ __device__ inline void light_rows(const StepArgs<T>& a, int sl, int wg, int wgs,
   }
 }
 
-// XCDs per slice when rem (1..7) slices share the eight
-__host__ __device__ inline int rem_xcds(int rem) {
-  return rem > 4 ? 1 : rem > 2 ? 2 : rem > 1 ? 4 : 8;
-}
-
 // Heavy task of one block: the four waves take interleaved 64-slot pieces, lane =
 // column.
 template <typename T, int MODE>
@@ -729,21 +720,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   }
   w -= a.heavy_wgs;
   if (w < a.light_wgs) {
-    const int x = w & 7, j = w >> 3;
-    const int rounds = a.nslices >> 3, rem = a.nslices & 7;
     int sl, wg, wgs;
-    if (j < rounds * a.slice_wgs) {
-      sl = x + 8 * (j / a.slice_wgs);
-      wg = j % a.slice_wgs;
-      wgs = a.slice_wgs;
-    } else {   // the last rem < 8 slices, each on 8, 4, 2 or 1 XCDs
-      const int k = rem_xcds(rem);
-      if (x / k >= rem) return;
-      sl = 8 * rounds + x / k;
-      wg = (j - rounds * a.slice_wgs) * k + x % k;
-      wgs = a.rem_wgs;
-      if (wg >= wgs) return;
-    }
+    if (!a.slices.decode(w, &sl, &wg, &wgs)) return;
     light_rows<T, MODE, kWide>(a, sl, wg, wgs, lane, wave, s_bits);
     return;
   }
@@ -1057,12 +1035,10 @@ hipError_t launch_step(const DeviceGraph& g, int B, const StepJob<T>& job, hipSt
   }
   StepArgs<T> a;
   a.n = g.n;
-  a.nslices = nb * static_cast<int>(sizeof(T) / 2);
   const int groups_wgs = static_cast<int>(grid_for(g.nslice_grp, kWavesPerBlock));
-  const int rem = a.nslices & 7;
-  const int k = rem ? rem_xcds(rem) : 1;
+  a.slices.nslices = nb * static_cast<int>(sizeof(T) / 2);
+  a.slices.slice_wgs = a.slices.rem_wgs = groups_wgs;
   size_t lds = 0;
-  a.slice_wgs = a.rem_wgs = groups_wgs;
   const bool skip = job.skip && step_can_skip(g.n);
   const bool big = twohop && !step_can_skip(g.n);
   if ((twohop && !big) || skip) {
@@ -1071,11 +1047,12 @@ hipError_t launch_step(const DeviceGraph& g, int B, const StepJob<T>& job, hipSt
     lds = static_cast<size_t>(awords) * 4;
     const int per_cu = static_cast<int>(
         std::max<size_t>(1, std::min<size_t>(twohop ? 8 : 5, (size_t(160) << 10) / (lds + 2048))));
-    a.slice_wgs = std::min(groups_wgs, 32 * per_cu);
-    a.rem_wgs = std::min(groups_wgs, 32 * per_cu * k);
+    const int rem = a.slices.nslices & 7;
+    a.slices.slice_wgs = std::min(groups_wgs, 32 * per_cu);
+    a.slices.rem_wgs = std::min(groups_wgs, 32 * per_cu * SliceGrid::rem_xcds(rem));
   }
   a.heavy_wgs = (nb * g.nwg + 7) / 8 * 8;
-  a.light_wgs = 8 * (a.nslices >> 3) * a.slice_wgs + (rem ? 8 * ((a.rem_wgs + k - 1) / k) : 0);
+  a.light_wgs = a.slices.size();
   a.grp = g.slice_grp;
   a.ngrp = g.nslice_grp;
   a.grow = g.slice_row;

@@ -128,7 +128,7 @@ void sc_graph::release() {
   dev_free(tail.part);
   dev_free(tail.ctl);
   tail = sc::TailScratch{};
-  tail_blocks = tail_walk_blocks = 0;
+  tail_blocks = 0;
   dev_free(work);
   dev_free(plan_work);
   dev_free(nz);
@@ -1050,11 +1050,8 @@ PipeLayout pipe_layout(const sc_graph* g, int B, size_t tsize) {
   const int64_t unit = std::max<int64_t>(1, 16 / static_cast<int64_t>(tsize));
   if (group > unit && group < nblocks) group = group / unit * unit;
   l.group = static_cast<int>(group);
-  const size_t tail = col_scratch_bytes(col_parts(n)) +
-                      8 * static_cast<size_t>(std::min<int64_t>(int64_t(1) << 22,
-                                                                4 * g->d.nslots + 65536));
-  l.tail_group = static_cast<int>(
-      std::min<int64_t>(group, std::max<int64_t>(1, static_cast<int64_t>(kTailBytes / tail))));
+  l.tail_group = static_cast<int>(std::min<int64_t>(
+      group, std::max<int64_t>(1, static_cast<int64_t>(kTailBytes / col_scratch_bytes(col_parts(n))))));
   return l;
 }
 
@@ -1205,11 +1202,12 @@ int ensure_tail(sc_graph* g, int blocks, bool walks) {
   if (!t.ctl) {
     t.nparts = col_parts(n);
     t.col_bytes = col_scratch_bytes(t.nparts);
-    // flattened walks: a block whose chunks do not fit walks one slot per wave
+    // flattened walks: the chunk sums of a launch (a block whose sums do not fit
+    // walks one slot per wave)
     t.capacity = std::min<int64_t>(int64_t(1) << 22, 4 * S + 65536);
     if (const char* cap = std::getenv("SC_WALK_CHUNK_CAPACITY"))   // smaller buffer (tests)
       t.capacity = std::max<int64_t>(1, std::min<int64_t>(t.capacity, std::atoll(cap)));
-    HIP_TRY(dev_alloc(&t.ctl, 2 * static_cast<size_t>(kMaxGroup)));
+    HIP_TRY(dev_alloc(&t.ctl, static_cast<size_t>(kMaxGroup)));
   }
   if (!t.cs) HIP_TRY(dev_alloc(&t.cs, static_cast<size_t>(kMaxGroup) * 64));
   if (static_cast<size_t>(blocks) > g->tail_blocks) {
@@ -1220,12 +1218,7 @@ int ensure_tail(sc_graph* g, int blocks, bool walks) {
   }
   if (walks) {
     if (!t.chunk_off) HIP_TRY(dev_alloc(&t.chunk_off, S + n / 16 + 2));
-    if (static_cast<size_t>(blocks) > g->tail_walk_blocks) {
-      dev_free(t.part);
-      g->tail_walk_blocks = 0;
-      HIP_TRY(dev_alloc(&t.part, static_cast<size_t>(t.capacity) * blocks));
-      g->tail_walk_blocks = blocks;
-    }
+    if (!t.part) HIP_TRY(dev_alloc(&t.part, static_cast<size_t>(t.capacity)));
   }
   return SC_OK;
 }

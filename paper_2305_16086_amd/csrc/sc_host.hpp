@@ -45,16 +45,16 @@ void dev_free(P*& p) {
 
 // Source blocks run in groups of up to kMaxGroup, one launch per step and group (see
 // k_step).  TGT+ overlaps the tails of a group with the traversal of the next on a
-// second stream, the groups alternating between kPipeSets sets of states.  A group is
-// as large as keeps its states (two per block) within kGroupBytes, which leaves them
-// in the 256 MB last-level cache together with what the tails read; but at least 4
-// blocks (8 slices of FP32 states: one per XCD) where the states of all sets fit
-// kPipeBudgetBytes.
+// second stream, the groups alternating between kPipeSets sets of states.  A group
+// takes states (two per block) of up to kGroupBytes, but at least kMinGroup blocks where
+// the states of all sets fit kPipeBudgetBytes (BA, TGT+, ms per call with 2, 4, 8, 16
+// blocks: n = 100,000 210, 200, 190, 187; TGT n = 34,401 45.2, 36.8, 34.5, 34.6 and 36.7
+// with 32; G(n, m) n = 10,000 with 4, 8, 16, 32: 3.37, 2.89, 2.69, 2.62).
 constexpr int kPipeSets = 2;
-constexpr int kMinGroup = 4;
+constexpr int kMinGroup = 8;
 constexpr size_t kGroupBytes = size_t(160) << 20;
 constexpr size_t kPipeBudgetBytes = size_t(2) << 30;
-constexpr size_t kTailBytes = size_t(256) << 20;   // candidate-summary and walk scratch
+constexpr size_t kTailBytes = size_t(256) << 20;   // candidate-summary scratch
 
 // Blocks per group and the layout of the state arrays for block width B.
 struct PipeLayout {
@@ -131,7 +131,6 @@ struct sc_graph {
   unsigned long long* plan_work = nullptr;   // [4][2 x 64] walk totals per candidate switch step
   sc::TailScratch tail;                      // candidate summaries and flattened walks
   size_t tail_blocks = 0;                    // blocks the tail buffers hold
-  size_t tail_walk_blocks = 0;
   // cached switch-step plan (the cost model depends only on these inputs)
   struct PlanKey {
     double eps;

@@ -43,6 +43,42 @@ struct ColStats {
   double maxN, minN;     // max / min over N(s_c)
 };
 
+// A block's state is cut into slices of one 128-byte line per row (32 FP32 or 16 FP64
+// columns).  Work that reads one slice is laid out so that workgroup w, which runs on
+// XCD w mod 8, takes slice w mod 8 (+ 8, 16, ...) of the launch: an XCD's 4 MB L2 then
+// holds lines of one slice at a time.  Each slice has slice_wgs workgroups in the
+// whole rounds of 8 slices; the remaining 1..7 slices have rem_wgs each, on 8, 4, 2 or
+// 1 XCDs.
+struct SliceGrid {
+  int nslices = 0, slice_wgs = 0, rem_wgs = 0;
+  // XCDs per slice when rem (1..7) slices share the eight
+  __host__ __device__ static int rem_xcds(int rem) {
+    return rem > 4 ? 1 : rem > 2 ? 2 : rem > 1 ? 4 : 8;
+  }
+  __host__ __device__ int size() const {
+    const int rem = nslices & 7;
+    const int k = rem ? rem_xcds(rem) : 1;
+    return 8 * (nslices >> 3) * slice_wgs + (rem ? 8 * ((rem_wgs + k - 1) / k) : 0);
+  }
+  // slice, workgroup of the slice and workgroups of the slice of workgroup w; false: none
+  __device__ bool decode(int w, int* sl, int* wg, int* wgs) const {
+    const int x = w & 7, j = w >> 3;
+    const int rounds = nslices >> 3, rem = nslices & 7;
+    if (j < rounds * slice_wgs) {
+      *sl = x + 8 * (j / slice_wgs);
+      *wg = j % slice_wgs;
+      *wgs = slice_wgs;
+      return true;
+    }
+    const int k = rem_xcds(rem);
+    if (x / k >= rem) return false;
+    *sl = 8 * rounds + x / k;
+    *wg = (j - rounds * slice_wgs) * k + x % k;
+    *wgs = rem_wgs;
+    return *wg < rem_wgs;
+  }
+};
+
 // The source blocks of one launch.  Block i covers sources s0 .. s0 + B - 1 (CSR
 // slots [kbeg, kend)) and keeps its state at buf * ystride of the Y arrays.
 constexpr int kMaxGroup = 32;
@@ -233,9 +269,9 @@ struct TailScratch {
   size_t col_bytes = 0;
   int nparts = 0;                 // row chunks of the candidate summary
   int64_t* chunk_off = nullptr;   // [slots + blocks of the graph]; a block's at kbeg + s0 / B
-  double* part = nullptr;         // [blocks][capacity] chunk sums
+  double* part = nullptr;         // [capacity] chunk sums, shared by the blocks of a launch
   int64_t capacity = 0;
-  int64_t* ctl = nullptr;         // [blocks][2]
+  int64_t* ctl = nullptr;         // [blocks] chunks
 };
 // Row chunks of the candidate summary of an n-node graph (a power of two; at most
 // kColParts) and the bytes of its scratch per block.
@@ -265,7 +301,8 @@ hipError_t launch_work_totals(const BlockList& blocks, int tilde, const int32_t*
                               hipStream_t st);
 
 // Walk tail: gacc[k] += mean_r X_r (Eq. 11) for the blocks' slots (a block whose
-// chunk sums do not fit ts.capacity walks one slot per wave).
+// chunk sums end beyond ts.capacity, those of the blocks before it counted, walks one
+// slot per wave).
 template <typename T>
 hipError_t launch_walks(const DeviceGraph& g, const BlockList& blocks, int B, int tilde,
                         uint64_t seed, const T* Y, int64_t ystride, const int32_t* tau_slot,
