@@ -845,51 +845,6 @@ __global__ void k_trace(int64_t m, const int32_t* __restrict__ half_slot,
   if (nr_out) nr_out[h] = nr_slot ? nr_slot[k] : 0;
 }
 
-// ------------------------------------------------------------------ Lanczos helpers
-__global__ __launch_bounds__(kThreads) void k_nmat_spmv(int n, const int32_t* __restrict__ rowptr,
-                                                        const int32_t* __restrict__ col,
-                                                        const double* __restrict__ sid,
-                                                        const double* __restrict__ x,
-                                                        double* __restrict__ y) {
-  const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-  if (r >= n) return;
-  double acc = 0.0;
-  for (int k = rowptr[r] + lane; k < rowptr[r + 1]; k += 64) {
-    const int u = col[k];
-    acc += sid[u] * x[u];
-  }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if (lane == 0) y[r] = sid[r] * acc;
-}
-
-__global__ __launch_bounds__(256) void k_multi_dot(const double* __restrict__ V, int64_t ld,
-                                                   const double* __restrict__ w, int64_t n,
-                                                   double* __restrict__ out) {
-  __shared__ double red[256];
-  const int j = blockIdx.x;
-  const double* vj = V + static_cast<size_t>(j) * ld;
-  double acc = 0.0;
-  for (int64_t x = threadIdx.x; x < n; x += 256) acc += vj[x] * w[x];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = 128; s >= 1; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[j] = red[0];
-}
-
-__global__ void k_multi_axpy(const double* __restrict__ V, int ncols, int64_t ld,
-                             const double* __restrict__ h, double* __restrict__ w, int64_t n) {
-  const int64_t x = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (x >= n) return;
-  double acc = 0.0;
-  for (int j = 0; j < ncols; ++j) acc += V[static_cast<size_t>(j) * ld + x] * h[j];
-  w[x] -= acc;
-}
-
 }  // namespace
 
 // ====================================================================== wrappers
@@ -1120,26 +1075,6 @@ hipError_t launch_trace(const DeviceGraph& g, const int32_t* tau_slot, const int
   if (!tau_out && !nr_out) return hipSuccess;
   k_trace<<<grid_for(2 * g.m, 256), 256, 0, st>>>(g.m, g.half_slot, tau_slot, nr_slot, tau_out,
                                                    nr_out);
-  return hipGetLastError();
-}
-
-hipError_t launch_nmat_spmv(const DeviceGraph& g, const double* sid, const double* x, double* y,
-                            hipStream_t st) {
-  k_nmat_spmv<<<grid_for(g.n, kWavesPerBlock), kThreads, 0, st>>>(g.n, g.rowptr, g.col, sid, x, y);
-  return hipGetLastError();
-}
-
-hipError_t launch_multi_dot(const double* V, int ncols, int64_t ld, const double* w, int64_t n,
-                            double* out, hipStream_t st) {
-  if (ncols <= 0) return hipSuccess;
-  k_multi_dot<<<ncols, 256, 0, st>>>(V, ld, w, n, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_multi_axpy(const double* V, int ncols, int64_t ld, const double* h, double* w,
-                             int64_t n, hipStream_t st) {
-  if (ncols <= 0) return hipSuccess;
-  k_multi_axpy<<<grid_for(n, 256), 256, 0, st>>>(V, ncols, ld, h, w, n);
   return hipGetLastError();
 }
 

@@ -494,70 +494,153 @@ extern "C" void sc_free_graph(sc_graph* g) {
 
 namespace {
 
-__global__ void k_scale_into(const double* __restrict__ w, double s, double* __restrict__ dst,
-                             int64_t n) {
-  const int64_t x = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (x < n) dst[x] = w[x] * s;
-}
+// Device side of one or two Lanczos runs (kernels_lanczos.hip), driven in windows of
+// steps: advance() enqueues a window and the copy of alpha and beta behind it, take()
+// makes the oldest window's values readable.  With two windows under way the host
+// evaluates one while the device works on the next.
+struct LanczosDriver {
+  sc::LanczosArgs a;
+  std::vector<double*> owned;
+  double* host = nullptr;          // pinned [2 windows][alpha, beta][runs][kcols]
+  hipEvent_t ev[2] = {};
+  hipStream_t st = nullptr;
+  int kmax = 0;
+  int enqueued = 0;                // steps enqueued
+  int upto[2] = {};                // last step of the window in copy q
+  int issued = 0, taken = 0;       // windows (issued - taken <= 2)
 
-// Lanczos start for N = D^-1/2 A D^-1/2: column 0 of V holds the top
-// eigenvector sqrt(d / 2m) (eigenvalue 1, deflated by the re-orthogonalisation),
-// column 1 a fixed pseudo-random unit vector orthogonal to it; sid = 1/sqrt(d).
-hipError_t lanczos_start(const sc::DeviceGraph& dg, const int32_t* deg_host, double* V, int64_t ld,
-                         double* sid, hipStream_t st, uint64_t seed = 0) {
-  const int64_t n = dg.n;
-  std::vector<double> hv(n), sidh(n);
-  const double two_m = static_cast<double>(dg.nslots);
-  for (int64_t x = 0; x < n; ++x) {
-    hv[x] = std::sqrt(deg_host[x] / two_m);
-    sidh[x] = 1.0 / std::sqrt(static_cast<double>(deg_host[x]));
+  ~LanczosDriver() {
+    for (double* p : owned) (void)sc::tracked_free(p);
+    if (host) (void)hipHostFree(host);
+    for (auto& e : ev)
+      if (e) (void)hipEventDestroy(e);
   }
-  std::vector<double> v0(n);
-  uint64_t z = 0x9E3779B97F4A7C15ull * (2 * seed + 1);
-  double dot = 0.0;
-  for (int64_t x = 0; x < n; ++x) {
-    z += 0x9E3779B97F4A7C15ull;
-    uint64_t r = z;
-    r = (r ^ (r >> 30)) * 0xBF58476D1CE4E5B9ull;
-    r = (r ^ (r >> 27)) * 0x94D049BB133111EBull;
-    r ^= r >> 31;
-    v0[x] = (static_cast<double>(r >> 11) * (1.0 / 9007199254740992.0)) * 2.0 - 1.0;
-    dot += v0[x] * hv[x];
+
+  hipError_t alloc(double** p, size_t count) {
+    const hipError_t e = dev_alloc(p, count);
+    if (e == hipSuccess) owned.push_back(*p);
+    return e;
   }
-  double nrm = 0.0;
-  for (int64_t x = 0; x < n; ++x) {
-    v0[x] -= dot * hv[x];
-    nrm += v0[x] * v0[x];
+
+  // Column 0 of the basis: the top eigenvector sqrt(d / 2m) (eigenvalue 1, deflated by
+  // the re-orthogonalisation); w[0]: a fixed pseudo-random unit vector orthogonal to
+  // it, run r from seed r.
+  hipError_t start(const sc::DeviceGraph& dg, const int32_t* deg_host, int runs, int kmax_,
+                   hipStream_t st_) {
+    st = st_;
+    kmax = kmax_;
+    const int64_t n = dg.n;
+    a.n = n;
+    a.runs = runs;
+    a.rows = sc::lanczos_rows(n);
+    a.chunks = static_cast<int>((n + a.rows - 1) / a.rows);
+    a.kcols = kmax + 2;
+    a.rowptr = dg.rowptr;
+    a.col = dg.col;
+    a.vstride = static_cast<int64_t>(a.kcols) * n;
+    double *sid = nullptr, *small = nullptr;
+    const size_t parts = static_cast<size_t>(runs) * a.chunks * a.kcols;
+    hipError_t e = alloc(&a.V, static_cast<size_t>(runs) * a.vstride);
+    if (e == hipSuccess) e = alloc(&a.w[0], static_cast<size_t>(runs) * n);
+    if (e == hipSuccess) e = alloc(&a.w[1], static_cast<size_t>(runs) * n);
+    if (e == hipSuccess) e = alloc(&sid, n);
+    if (e == hipSuccess) e = alloc(&a.part[0], parts);
+    if (e == hipSuccess) e = alloc(&a.part[1], parts);
+    if (e == hipSuccess) e = alloc(&small, static_cast<size_t>(runs) * (a.chunks + 2 * a.kcols));
+    if (e == hipSuccess)
+      e = hipHostMalloc(reinterpret_cast<void**>(&host),
+                        2 * static_cast<size_t>(runs) * 2 * a.kcols * sizeof(double));
+    for (auto& x : ev)
+      if (e == hipSuccess) e = hipEventCreateWithFlags(&x, hipEventDisableTiming);
+    if (e != hipSuccess) return e;
+    a.sid = sid;
+    a.alpha = small;
+    a.beta = small + static_cast<size_t>(runs) * a.kcols;
+    a.norm = a.beta + static_cast<size_t>(runs) * a.kcols;
+    std::vector<double> hv(n), sidh(n), v0(n);
+    const double two_m = static_cast<double>(dg.nslots);
+    for (int64_t x = 0; x < n; ++x) {
+      hv[x] = std::sqrt(deg_host[x] / two_m);
+      sidh[x] = 1.0 / std::sqrt(static_cast<double>(deg_host[x]));
+    }
+    e = hipMemcpyAsync(sid, sidh.data(), n * sizeof(double), hipMemcpyHostToDevice, st);
+    for (int r = 0; r < runs && e == hipSuccess; ++r) {
+      uint64_t z = 0x9E3779B97F4A7C15ull * (2 * static_cast<uint64_t>(r) + 1);
+      double dot = 0.0;
+      for (int64_t x = 0; x < n; ++x) {
+        z += 0x9E3779B97F4A7C15ull;
+        uint64_t q = z;
+        q = (q ^ (q >> 30)) * 0xBF58476D1CE4E5B9ull;
+        q = (q ^ (q >> 27)) * 0x94D049BB133111EBull;
+        q ^= q >> 31;
+        v0[x] = (static_cast<double>(q >> 11) * (1.0 / 9007199254740992.0)) * 2.0 - 1.0;
+        dot += v0[x] * hv[x];
+      }
+      double nrm = 0.0;
+      for (int64_t x = 0; x < n; ++x) {
+        v0[x] -= dot * hv[x];
+        nrm += v0[x] * v0[x];
+      }
+      nrm = std::sqrt(nrm);
+      for (int64_t x = 0; x < n; ++x) v0[x] /= nrm;
+      e = hipMemcpyAsync(a.V + r * a.vstride, hv.data(), n * sizeof(double), hipMemcpyHostToDevice, st);
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(a.w[0] + r * n, v0.data(), n * sizeof(double), hipMemcpyHostToDevice, st);
+      if (e == hipSuccess) e = hipStreamSynchronize(st);   // v0 is drawn again
+    }
+    return e;
   }
-  nrm = std::sqrt(nrm);
-  for (int64_t x = 0; x < n; ++x) v0[x] /= nrm;
-  hipError_t e = hipMemcpy(V, hv.data(), n * sizeof(double), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(V + ld, v0.data(), n * sizeof(double), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(sid, sidh.data(), n * sizeof(double), hipMemcpyHostToDevice);
-  (void)st;
-  return e;
-}
+
+  // enqueues a window of up to `steps` steps
+  hipError_t advance(int steps) {
+    const int last = std::min(enqueued + steps, kmax);
+    hipError_t e = hipSuccess;
+    for (int j = enqueued + 1; j <= last && e == hipSuccess; ++j) e = sc::launch_lanczos_step(a, j, st);
+    enqueued = last;
+    if (e == hipSuccess) e = sc::launch_lanczos_beta(a, last, st);
+    const size_t words = static_cast<size_t>(a.runs) * 2 * a.kcols;
+    const int q = issued & 1;
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(host + q * words, a.alpha, words * sizeof(double), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipEventRecord(ev[q], st);
+    upto[q] = last;
+    ++issued;
+    return e;
+  }
+
+  // waits for the oldest window; its values are in copy *q up to step *last
+  hipError_t take(int* q, int* last) {
+    *q = taken & 1;
+    *last = upto[*q];
+    ++taken;
+    return hipEventSynchronize(ev[*q]);
+  }
+  double alpha(int q, int run, int j) const {
+    return host[(static_cast<size_t>(q) * 2 * a.runs + run) * a.kcols + j];
+  }
+  double beta(int q, int run, int j) const {
+    return host[(static_cast<size_t>(q) * 2 * a.runs + a.runs + run) * a.kcols + j];
+  }
+  // first step in (from, to] with beta below 1e-12 (the Krylov space is exhausted; what
+  // follows it is not used), else 0
+  int exhausted(int q, int run, int from, int to) const {
+    for (int j = from + 1; j <= to; ++j)
+      if (!(beta(q, run, j) >= 1e-12)) return j;
+    return 0;
+  }
+};
 
 // Eigenvalues of the symmetric tridiagonal matrix (diagonal d[0..k), off-diagonal
 // e[0..k-1)) by implicit QL iterations with Wilkinson-type shifts (Wilkinson and
 // Reinsch; Golub and Van Loan, implicit symmetric tridiagonal QR).  d receives
-// the eigenvalues (unordered).  zt (k x k), if given, receives the eigenvectors
-// as rows (zt[c * k + i] = component i of the vector of d[c]); zlast, if given,
-// their last components only.
+// the eigenvalues (unordered) and zlast the last components of their vectors.
 // Returns false if an eigenvalue needs more than 60 iterations.
-bool tridiag_eigen(std::vector<double>& d, std::vector<double> e, std::vector<double>* zt,
-                   std::vector<double>* zlast) {
+bool tridiag_eigen(std::vector<double>& d, std::vector<double> e, std::vector<double>& zlast) {
   const int k = static_cast<int>(d.size());
   e.resize(k, 0.0);
   e[k - 1] = 0.0;
-  if (zt) {
-    zt->assign(static_cast<size_t>(k) * k, 0.0);
-    for (int i = 0; i < k; ++i) (*zt)[static_cast<size_t>(i) * k + i] = 1.0;
-  }
-  if (zlast) {
-    zlast->assign(k, 0.0);
-    (*zlast)[k - 1] = 1.0;
-  }
+  zlast.assign(k, 0.0);
+  zlast[k - 1] = 1.0;
   const double ulp = std::numeric_limits<double>::epsilon();
   for (int l = 0; l < k; ++l) {
     for (int iter = 0;; ++iter) {
@@ -568,14 +651,14 @@ bool tridiag_eigen(std::vector<double>& d, std::vector<double> e, std::vector<do
       if (iter == 60) return false;
       // shift from the leading 2 x 2 block, then chase the bulge from m up to l
       double g = (d[l + 1] - d[l]) / (2.0 * e[l]);
-      double r = std::hypot(g, 1.0);
+      double r = std::sqrt(g * g + 1.0);
       g = d[m] - d[l] + e[l] / (g + std::copysign(r, g));
       double sn = 1.0, cs = 1.0, p = 0.0;
       bool split = false;
       for (int i = m - 1; i >= l; --i) {
         const double f = sn * e[i];
         const double b = cs * e[i];
-        r = std::hypot(f, g);
+        r = std::sqrt(f * f + g * g);   // entries of N are at most 1: no overflow
         e[i + 1] = r;
         if (r == 0.0) {   // the matrix splits: deflate and restart from l
           d[i + 1] -= p;
@@ -590,20 +673,9 @@ bool tridiag_eigen(std::vector<double>& d, std::vector<double> e, std::vector<do
         p = sn * r;
         d[i + 1] = g + p;
         g = cs * r - b;
-        if (zt) {   // rotate vectors i and i + 1 (two contiguous rows)
-          double* ri = zt->data() + static_cast<size_t>(i) * k;
-          double* rj = ri + k;
-          for (int q = 0; q < k; ++q) {
-            const double t = rj[q];
-            rj[q] = sn * ri[q] + cs * t;
-            ri[q] = cs * ri[q] - sn * t;
-          }
-        }
-        if (zlast) {
-          const double t = (*zlast)[i + 1];
-          (*zlast)[i + 1] = sn * (*zlast)[i] + cs * t;
-          (*zlast)[i] = cs * (*zlast)[i] - sn * t;
-        }
+        const double t = zlast[i + 1];
+        zlast[i + 1] = sn * zlast[i] + cs * t;
+        zlast[i] = cs * zlast[i] - sn * t;
       }
       if (split) continue;
       d[l] -= p;
@@ -614,6 +686,88 @@ bool tridiag_eigen(std::vector<double>& d, std::vector<double> e, std::vector<do
   return true;
 }
 
+// Eigenvectors of the same matrix for the count eigenvalues lam (any order) by inverse
+// iteration (Golub and Van Loan, section 8.2.2; the tridiagonal systems by Gaussian
+// elimination with partial pivoting), each orthogonalised against the vectors already
+// found whose eigenvalues lie within 1e-3: row c of z (count x k) is the vector of
+// lam[c].  O(k) per vector, where accumulating the QL rotations costs O(k^2).
+void tridiag_vectors(const std::vector<double>& d, const std::vector<double>& e,
+                     const double* lam, int count, std::vector<double>& z) {
+  const int k = static_cast<int>(d.size());
+  z.assign(static_cast<size_t>(count) * k, 0.0);
+  const double tiny = std::numeric_limits<double>::epsilon();
+  std::vector<double> u0(k), u1(k), u2(k), l(k), x(k);
+  std::vector<char> swapped(k);
+  uint64_t seed = 0x9E3779B97F4A7C15ull;
+  for (int c = 0; c < count; ++c) {
+    double* v = z.data() + static_cast<size_t>(c) * k;
+    // P (T - lam I) = L U, U with two superdiagonals
+    double a0 = d[0] - lam[c], a1 = k > 1 ? e[0] : 0.0, a2 = 0.0;
+    for (int i = 0; i + 1 < k; ++i) {
+      const double b0 = e[i], b1 = d[i + 1] - lam[c], b2 = i + 2 < k ? e[i + 1] : 0.0;
+      if (std::fabs(b0) > std::fabs(a0)) {
+        swapped[i] = 1;
+        l[i] = a0 / b0;
+        u0[i] = b0;
+        u1[i] = b1;
+        u2[i] = b2;
+        a0 = a1 - l[i] * b1;
+        a1 = a2 - l[i] * b2;
+      } else {
+        swapped[i] = 0;
+        if (a0 == 0.0) a0 = tiny;
+        l[i] = b0 / a0;
+        u0[i] = a0;
+        u1[i] = a1;
+        u2[i] = a2;
+        a0 = b1 - l[i] * a1;
+        a1 = b2 - l[i] * a2;
+      }
+      a2 = 0.0;
+    }
+    u0[k - 1] = std::fabs(a0) < tiny ? tiny : a0;
+    for (int i = 0; i < k; ++i) {
+      seed = seed * 6364136223846793005ull + 1442695040888963407ull;
+      x[i] = static_cast<double>(seed >> 11) * (1.0 / 9007199254740992.0) - 0.5;
+    }
+    for (int it = 0; it < 4; ++it) {
+      if (it > 0)   // the start vector stands for L applied to a random one
+        for (int i = 0; i + 1 < k; ++i) {
+          if (swapped[i]) std::swap(x[i], x[i + 1]);
+          x[i + 1] -= l[i] * x[i];
+        }
+      for (int i = k - 1; i >= 0; --i) {
+        double s = x[i];
+        if (i + 1 < k) s -= u1[i] * x[i + 1];
+        if (i + 2 < k) s -= u2[i] * x[i + 2];
+        x[i] = s / u0[i];
+      }
+      auto normalise = [&]() {
+        double m = 0.0, s = 0.0;
+        for (double t : x) m = std::max(m, std::fabs(t));
+        for (double& t : x) {
+          t /= m;
+          s += t * t;
+        }
+        s = 1.0 / std::sqrt(s);
+        for (double& t : x) t *= s;
+      };
+      normalise();
+      bool close = false;
+      for (int q = 0; q < c; ++q) {
+        if (std::fabs(lam[q] - lam[c]) > 1e-3) continue;
+        close = true;
+        const double* w = z.data() + static_cast<size_t>(q) * k;
+        double dot = 0.0;
+        for (int i = 0; i < k; ++i) dot += w[i] * x[i];
+        for (int i = 0; i < k; ++i) x[i] -= dot * w[i];
+      }
+      if (close) normalise();
+    }
+    std::copy(x.begin(), x.end(), v);
+  }
+}
+
 // extreme Ritz estimate: max over the two ends of |theta| + residual, where the
 // residual of a Ritz pair is |beta_last * (last component of its vector)|
 // (eigenvalues and last components by implicit QL, O(k^2) per check)
@@ -621,7 +775,7 @@ double ritz_bound(const std::vector<double>& alpha, const std::vector<double>& b
                   double beta_last, double* worst_res) {
   std::vector<double> d(alpha.begin(), alpha.begin() + k), zl;
   std::vector<double> e(beta.begin(), beta.begin() + std::min<size_t>(beta.size(), k));
-  if (!tridiag_eigen(d, e, nullptr, &zl)) {
+  if (!tridiag_eigen(d, e, zl)) {
     *worst_res = 1.0;   // no answer: report as unconverged
     return 1.0;
   }
@@ -639,87 +793,53 @@ double ritz_bound(const std::vector<double>& alpha, const std::vector<double>& b
 }  // namespace
 
 int sc::compute_lambda_star(sc_graph* g, hipStream_t st, double* out) {
-  // two Lanczos runs from independent start vectors; the larger estimate is kept
-  // (a start vector nearly orthogonal to the extreme eigenvector would make one
+  // two Lanczos runs from independent start vectors, side by side; the larger estimate
+  // is kept (a start vector nearly orthogonal to the extreme eigenvector would make one
   // run under-estimate), converged only if both runs passed the residual test
-  double a = 0.0, b = 0.0;
-  int ca = 0, cb = 0;
-  int rc = lanczos_lambda_star(g->d, g->deg_h.data(), st, &a, &ca, 0);
-  if (rc != SC_OK) return rc;
-  rc = lanczos_lambda_star(g->d, g->deg_h.data(), st, &b, &cb, 1);
-  if (rc != SC_OK) return rc;
-  *out = std::max(a, b);
-  g->lambda_converged = (ca && cb) ? 1 : 0;
-  return SC_OK;
-}
-
-int sc::lanczos_lambda_star(const DeviceGraph& dg, const int32_t* deg_host, hipStream_t st,
-                            double* out, int* converged, uint64_t seed) {
-  using namespace sc;
-  const int64_t n = dg.n;
-  // up to 600 steps, the basis held to 4 GiB
+  const int64_t n = g->d.n;
+  // up to 600 steps, a run's basis held to 4 GiB
   const int64_t kcap = std::max<int64_t>(40, (int64_t(1) << 29) / std::max<int64_t>(n, 1) - 2);
   const int kmax = static_cast<int>(std::min<int64_t>({n - 1, 600, kcap}));
-  if (converged) *converged = 0;
-  const int64_t ld = n;
-  double *V = nullptr, *w = nullptr, *h = nullptr, *sid = nullptr;
-  auto cleanup = [&]() {
-    dev_free(V);
-    dev_free(w);
-    dev_free(h);
-    dev_free(sid);
-  };
-  const ScopeExit<decltype(cleanup)> guard{cleanup};   // also on early error returns
-  hipError_t e = dev_alloc(&V, static_cast<size_t>(kmax + 2) * ld);
-  if (e == hipSuccess) e = dev_alloc(&w, n);
-  if (e == hipSuccess) e = dev_alloc(&h, kmax + 2);
-  if (e == hipSuccess) e = dev_alloc(&sid, n);
-  if (e != hipSuccess) {
-    cleanup();
-    return fail(e == hipErrorOutOfMemory ? SC_ENOMEM : SC_EHIP, "lanczos allocation failed");
-  }
-  HIP_TRY(lanczos_start(dg, deg_host, V, ld, sid, st, seed));
-
-  std::vector<double> alpha, beta, hh(kmax + 2);
-  double result = -1.0;
-  const unsigned grid = static_cast<unsigned>((n + 255) / 256);
-  for (int j = 1; j <= kmax; ++j) {
-    const double* vj = V + static_cast<size_t>(j) * ld;
-    HIP_TRY(sc::launch_nmat_spmv(dg, sid, vj, w, st));
-    double a_j = 0.0;
-    for (int pass = 0; pass < 2; ++pass) {   // full re-orthogonalisation, twice
-      HIP_TRY(sc::launch_multi_dot(V, j + 1, ld, w, n, h, st));
-      HIP_TRY(hipMemcpyAsync(hh.data(), h, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
-      HIP_TRY(hipStreamSynchronize(st));
-      a_j += hh[j];
-      HIP_TRY(sc::launch_multi_axpy(V, j + 1, ld, h, w, n, st));
-    }
-    HIP_TRY(sc::launch_multi_dot(w, 1, ld, w, n, h, st));
-    HIP_TRY(hipMemcpyAsync(hh.data(), h, sizeof(double), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    const double b_j = std::sqrt(std::max(hh[0], 0.0));
-    alpha.push_back(a_j);
-    const bool exhausted = b_j < 1e-12 || j == kmax;
-    if ((j % 20 == 0) || exhausted) {
+  constexpr int kRuns = 2, kWindow = 20;
+  LanczosDriver lz;
+  const hipError_t e0 = lz.start(g->d, g->deg_h.data(), kRuns, kmax, st);
+  if (e0 != hipSuccess)
+    return fail(e0 == hipErrorOutOfMemory ? SC_ENOMEM : SC_EHIP, "lanczos allocation failed");
+  double result[kRuns] = {-1.0, -1.0};
+  bool done[kRuns] = {}, converged[kRuns] = {};
+  std::vector<double> al, be;
+  HIP_TRY(lz.advance(kWindow));
+  for (int checked = 0; checked < kmax && !(done[0] && done[1]);) {
+    if (lz.enqueued < kmax) HIP_TRY(lz.advance(kWindow));   // beside the evaluation
+    int q = 0, upto = 0;
+    HIP_TRY(lz.take(&q, &upto));
+    for (int r = 0; r < kRuns; ++r) {
+      if (done[r]) continue;
+      const int ex = lz.exhausted(q, r, checked, upto);
+      const int j = ex ? ex : upto;
+      const double b_j = lz.beta(q, r, j);
+      const bool last = ex || j == kmax;
+      al.resize(j);
+      be.resize(j - 1);
+      for (int i = 1; i <= j; ++i) al[i - 1] = lz.alpha(q, r, i);
+      for (int i = 1; i < j; ++i) be[i - 1] = lz.beta(q, r, i);
       double res = 0.0;
-      const double bound = ritz_bound(alpha, beta, j, exhausted ? 0.0 : b_j, &res);
-      result = bound;
-      if (b_j < 1e-12 || res < 1e-9) {   // Krylov space exhausted, or both ends converged
-        if (converged) *converged = 1;
-        break;
+      result[r] = ritz_bound(al, be, j, last ? 0.0 : b_j, &res);
+      if (ex || res < 1e-9) {   // Krylov space exhausted, or both ends converged
+        converged[r] = true;
+        done[r] = true;
       }
-      if (exhausted) break;
+      if (last) done[r] = true;
     }
-    beta.push_back(b_j);
-    k_scale_into<<<grid, 256, 0, st>>>(w, 1.0 / b_j, V + static_cast<size_t>(j + 1) * ld, n);
-    HIP_TRY(hipGetLastError());
+    checked = upto;
   }
   HIP_TRY(hipStreamSynchronize(st));
-  cleanup();
-  if (!(result > 0.0) || !(result < 1.0))
-    return fail(SC_EINVAL, "lambda* estimate outside (0, 1): " + std::to_string(result) +
-                               " (graph bipartite or too small?)");
-  *out = result;
+  for (double r : result)
+    if (!(r > 0.0) || !(r < 1.0))
+      return fail(SC_EINVAL, "lambda* estimate outside (0, 1): " + std::to_string(r) +
+                                 " (graph bipartite or too small?)");
+  *out = std::max(result[0], result[1]);
+  g->lambda_converged = (converged[0] && converged[1]) ? 1 : 0;
   return SC_OK;
 }
 
@@ -744,28 +864,14 @@ int sc::lanczos_spectrum(sc_graph* g, int omega, int max_iter, double tol, hipSt
                          int* kept, double* worst) {
   const sc::DeviceGraph& dg = g->d;
   const int64_t n = dg.n;
-  const int64_t ld = n;
   // the basis is held whole: at most ~16 GiB of it
   const int64_t cap = std::max<int64_t>(omega + 8, (int64_t(16) << 30) / (8 * n) - 2);
   const int kmax = static_cast<int>(std::min<int64_t>({n - 1, static_cast<int64_t>(max_iter), cap}));
-  double *V = nullptr, *w = nullptr, *h = nullptr, *sid = nullptr, *Yd = nullptr;
-  auto cleanup = [&]() {
-    dev_free(V);
-    dev_free(w);
-    dev_free(h);
-    dev_free(sid);
-    dev_free(Yd);
-  };
-  const ScopeExit<decltype(cleanup)> guard{cleanup};   // also on early error returns
-  hipError_t e = dev_alloc(&V, static_cast<size_t>(kmax + 2) * ld);
-  if (e == hipSuccess) e = dev_alloc(&w, n);
-  if (e == hipSuccess) e = dev_alloc(&h, kmax + 2);
-  if (e == hipSuccess) e = dev_alloc(&sid, n);
-  if (e == hipSuccess) e = lanczos_start(dg, g->deg_h.data(), V, ld, sid, st);
-  if (e != hipSuccess) {
-    cleanup();
+  constexpr int kWindow = 25;
+  LanczosDriver lz;
+  hipError_t e = lz.start(dg, g->deg_h.data(), 1, kmax, st);
+  if (e != hipSuccess)
     return fail(e == hipErrorOutOfMemory ? SC_ENOMEM : SC_EHIP, "spectrum: allocation failed");
-  }
   const int want = omega - 1;
   // Ritz pairs ordered by |theta| descending (ties: theta descending)
   auto order_of = [](const std::vector<double>& th) {
@@ -777,81 +883,72 @@ int sc::lanczos_spectrum(sc_graph* g, int omega, int max_iter, double tol, hipSt
     });
     return idx;
   };
-  std::vector<double> alpha, beta, hh(kmax + 2);
-  const unsigned grid = static_cast<unsigned>((n + 255) / 256);
+  std::vector<double> alpha, beta, th, zl;
   int steps = 0;
   double b_last = 0.0;
-  for (int j = 1; j <= kmax; ++j) {
-    const double* vj = V + static_cast<size_t>(j) * ld;
-    HIP_TRY(sc::launch_nmat_spmv(dg, sid, vj, w, st));
-    double a_j = 0.0;
-    for (int pass = 0; pass < 2; ++pass) {
-      HIP_TRY(sc::launch_multi_dot(V, j + 1, ld, w, n, h, st));
-      HIP_TRY(hipMemcpyAsync(hh.data(), h, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
-      HIP_TRY(hipStreamSynchronize(st));
-      a_j += hh[j];
-      HIP_TRY(sc::launch_multi_axpy(V, j + 1, ld, h, w, n, st));
-    }
-    HIP_TRY(sc::launch_multi_dot(w, 1, ld, w, n, h, st));
-    HIP_TRY(hipMemcpyAsync(hh.data(), h, sizeof(double), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    const double b_j = std::sqrt(std::max(hh[0], 0.0));
-    alpha.push_back(a_j);
-    steps = j;
-    b_last = b_j;
-    const bool exhausted = b_j < 1e-12 || j == kmax;
-    if (exhausted) break;
-    if (j % 25 == 0 && j >= want) {
-      std::vector<double> th = alpha, zl;
-      if (!tridiag_eigen(th, beta, nullptr, &zl)) break;
+  HIP_TRY(lz.advance(kWindow));
+  for (int checked = 0;;) {
+    if (lz.enqueued < kmax) HIP_TRY(lz.advance(kWindow));   // beside the evaluation
+    int q = 0, upto = 0;
+    HIP_TRY(lz.take(&q, &upto));
+    const int ex = lz.exhausted(q, 0, checked, upto);
+    steps = ex ? ex : upto;
+    b_last = lz.beta(q, 0, steps);
+    if (!(b_last >= 0.0)) b_last = 0.0;
+    alpha.resize(steps);
+    beta.resize(steps - 1);
+    for (int i = 1; i <= steps; ++i) alpha[i - 1] = lz.alpha(q, 0, i);
+    for (int i = 1; i < steps; ++i) beta[i - 1] = lz.beta(q, 0, i);
+    checked = upto;
+    if (ex || steps == kmax) break;
+    if (steps >= want) {
+      th = alpha;
+      if (!tridiag_eigen(th, beta, zl)) break;
       const std::vector<int> idx = order_of(th);
       bool done = true;
-      for (int c = 0; c < want && done; ++c) done = std::fabs(b_j * zl[idx[c]]) <= tol;
+      for (int c = 0; c < want && done; ++c) done = std::fabs(b_last * zl[idx[c]]) <= tol;
       if (done) break;
     }
-    beta.push_back(b_j);
-    k_scale_into<<<grid, 256, 0, st>>>(w, 1.0 / b_j, V + static_cast<size_t>(j + 1) * ld, n);
-    HIP_TRY(hipGetLastError());
   }
-  // Ritz pairs of the final tridiagonal matrix
-  std::vector<double> th = alpha, Z;
-  beta.resize(steps - 1);
-  if (!tridiag_eigen(th, beta, &Z, nullptr)) {
-    cleanup();
+  // Ritz pairs of the final tridiagonal matrix: all eigenvalues, the vectors of those kept
+  th = alpha;
+  if (!tridiag_eigen(th, beta, zl))
     return fail(SC_EINVAL, "spectrum: tridiagonal eigenvalues did not converge");
-  }
   const std::vector<int> idx = order_of(th);
   const bool exact = b_last < 1e-12;   // invariant subspace: the Ritz pairs are eigenpairs
   int p = 0;
   double wres = 0.0;
   while (p < want && p < steps) {
-    const double r = exact ? 0.0 : std::fabs(b_last * Z[static_cast<size_t>(idx[p]) * steps + steps - 1]);
+    const double r = exact ? 0.0 : std::fabs(b_last * zl[idx[p]]);
     if (r > tol) break;
     wres = std::max(wres, r);
     ++p;
   }
-  if (p == 0) {
-    cleanup();
+  if (p == 0)
     return fail(SC_EINVAL, "spectrum: no Ritz pair reached the tolerance (raise max_iter)");
-  }
   const int om = p + 1;
   const int p32 = (p + kRitzCols - 1) / kRitzCols * kRitzCols;
-  std::vector<double> Y(static_cast<size_t>(steps) * p32, 0.0);
-  for (int i = 0; i < steps; ++i)
-    for (int c = 0; c < p; ++c) Y[static_cast<size_t>(i) * p32 + c] = Z[static_cast<size_t>(idx[c]) * steps + i];
   std::vector<double> lam(om);
   lam[0] = 1.0;
   for (int c = 0; c < p; ++c) lam[1 + c] = th[idx[c]];
+  std::vector<double> Z;
+  tridiag_vectors(alpha, beta, lam.data() + 1, p, Z);
+  std::vector<double> Y(static_cast<size_t>(steps) * p32, 0.0);
+  for (int i = 0; i < steps; ++i)
+    for (int c = 0; c < p; ++c) Y[static_cast<size_t>(i) * p32 + c] = Z[static_cast<size_t>(c) * steps + i];
+  double* Yd = nullptr;
   double* lam_d = nullptr;
   double* phi_d = nullptr;
   e = dev_alloc(&Yd, Y.size());
   if (e == hipSuccess) e = dev_alloc(&lam_d, om);
   if (e == hipSuccess) e = dev_alloc(&phi_d, static_cast<size_t>(n) * om);
-  if (e == hipSuccess) e = hipMemcpy(Yd, Y.data(), Y.size() * sizeof(double), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(lam_d, lam.data(), om * sizeof(double), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = sc::launch_ritz(n, ld, V, steps, Yd, p32, p, om, phi_d, st);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(Yd, Y.data(), Y.size() * sizeof(double), hipMemcpyHostToDevice, st);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(lam_d, lam.data(), om * sizeof(double), hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) e = sc::launch_ritz(n, n, lz.a.V, steps, Yd, p32, p, om, phi_d, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
-  cleanup();
+  dev_free(Yd);
   if (e != hipSuccess) {
     dev_free(lam_d);
     dev_free(phi_d);

@@ -214,15 +214,11 @@ int build_host_csr(int64_t n, int64_t m, const int64_t* u, const int64_t* v, uns
 int upload_csr(const HostCSR& h, DeviceGraph& d);
 // New handle owning an upload of h (h.rowptr and h.deg are moved into it).
 int graph_from_csr(HostCSR& h, sc_graph** out);
-// One Lanczos run from start vector number `seed`; *converged = 1 when the
-// extreme Ritz pairs passed the residual test (or the Krylov space closed).
 // TGT+ with the frontier-sparse traversal and the per-source switch step of
 // Eq. 14 (SC_PER_SOURCE).
 int run_per_source(sc_graph* g, double eps, int L, const sc_options& o, double* out,
                    sc_stats* st);
 
-int lanczos_lambda_star(const DeviceGraph& d, const int32_t* deg_host, hipStream_t st, double* out,
-                        int* converged = nullptr, uint64_t seed = 0);
 // Lanczos for the omega eigenpairs of largest |lambda| (stores the converged prefix in g)
 int lanczos_spectrum(sc_graph* g, int omega, int max_iter, double tol, hipStream_t st, int* kept,
                      double* worst);

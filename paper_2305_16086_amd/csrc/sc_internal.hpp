@@ -451,13 +451,30 @@ hipError_t launch_closure_apply(const DeviceGraph& g, const float* zpred, const 
 hipError_t launch_combine_masked(const DeviceGraph& g, const double* gacc,
                                  const unsigned char* fb, double* out, hipStream_t st);
 
-// --------------------------------------------------------------- Lanczos helpers
-hipError_t launch_nmat_spmv(const DeviceGraph& g, const double* sid, const double* x,
-                            double* y, hipStream_t st);
-hipError_t launch_multi_dot(const double* V, int ncols, int64_t ld, const double* w,
-                            int64_t n, double* out, hipStream_t st);
-hipError_t launch_multi_axpy(const double* V, int ncols, int64_t ld, const double* h,
-                             double* w, int64_t n, hipStream_t st);
+// --------------------------------------------------------------- Lanczos
+constexpr int kLanczosMaxRows = 2048;   // rows of a chunk
+constexpr int kLanczosCols = 1024;      // basis columns of an update segment
+// Buffers of `runs` Lanczos runs on an n-node graph cut into chunks of `rows` rows.
+// Column 0 of a run's basis is the deflated top eigenvector; w[0] holds the unit start
+// vector before step 1.  Step j writes column j, alpha[j] and beta[j - 1].
+struct LanczosArgs {
+  int64_t n = 0;
+  int runs = 1, rows = 0, chunks = 0, kcols = 0;   // kcols: basis columns allocated
+  const int32_t* rowptr = nullptr;
+  const int32_t* col = nullptr;
+  const double* sid = nullptr;      // [n] 1/sqrt(degree)
+  double* V = nullptr;              // [runs] vstride = kcols * n, column major
+  int64_t vstride = 0;
+  double* w[2] = {nullptr, nullptr};      // [runs][n]
+  double* part[2] = {nullptr, nullptr};   // [runs][chunks][kcols]
+  double* norm = nullptr;           // [runs][chunks]
+  double* alpha = nullptr;          // [runs][kcols]
+  double* beta = nullptr;           // [runs][kcols]
+};
+int lanczos_rows(int64_t n);
+hipError_t launch_lanczos_step(const LanczosArgs& a, int j, hipStream_t st);
+// beta[j] after step j when no further step follows
+hipError_t launch_lanczos_beta(const LanczosArgs& a, int j, hipStream_t st);
 
 // Persistent batch kernel for items of block width B: workgroups of nt
 // threads (256, 512, 1024) take items from *ticket (zero before the launch)
