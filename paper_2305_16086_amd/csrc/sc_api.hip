@@ -768,6 +768,41 @@ void tridiag_vectors(const std::vector<double>& d, const std::vector<double>& e,
   }
 }
 
+// Number of eigenvalues below x (Sturm sequence); e2: squared off-diagonal.
+int sturm_count(const std::vector<double>& d, const std::vector<double>& e2, double x) {
+  int cnt = 0;
+  double q = 1.0;
+  for (size_t i = 0; i < d.size(); ++i) {
+    q = d[i] - x - (i > 0 ? e2[i - 1] / q : 0.0);
+    if (q == 0.0) q = 1e-300;
+    cnt += q < 0.0;
+  }
+  return cnt;
+}
+
+// Residual estimate |beta_last z_last| of the Ritz pair at the boundary of `passes`: the
+// smallest t in [lo, hi] for which passes(t) holds, by bisection to 1e-13, times sign.
+// O(k) per probe: a check far from convergence costs no QL sweep over all eigenvalues.
+template <typename F>
+double boundary_residual(const std::vector<double>& d, const std::vector<double>& e, double beta_last,
+                         double lo, double hi, double sign, F passes, double* theta = nullptr) {
+  while (hi - lo > 1e-13) {
+    const double mid = 0.5 * (lo + hi);
+    (passes(mid) ? hi : lo) = mid;
+  }
+  std::vector<double> z;
+  const double t = sign * 0.5 * (lo + hi);
+  if (theta) *theta = t;
+  tridiag_vectors(d, e, &t, 1, z);
+  return std::fabs(beta_last * z.back());
+}
+
+std::vector<double> squares(const std::vector<double>& e) {
+  std::vector<double> s(e);
+  for (double& x : s) x *= x;
+  return s;
+}
+
 // extreme Ritz estimate: max over the two ends of |theta| + residual, where the
 // residual of a Ritz pair is |beta_last * (last component of its vector)|
 // (eigenvalues and last components by implicit QL, O(k^2) per check)
@@ -824,6 +859,16 @@ int sc::compute_lambda_star(sc_graph* g, hipStream_t st, double* out) {
       for (int i = 1; i <= j; ++i) al[i - 1] = lz.alpha(q, r, i);
       for (int i = 1; i < j; ++i) be[i - 1] = lz.beta(q, r, i);
       double res = 0.0;
+      if (!last) {   // an end still far from converged ends the check here
+        const int k = j;
+        const std::vector<double> e2 = squares(be);
+        res = boundary_residual(al, be, b_j, -1.1, 1.1, 1.0,
+                                [&](double t) { return sturm_count(al, e2, t) == k; });
+        if (res > 1e-7) continue;
+        res = boundary_residual(al, be, b_j, -1.1, 1.1, 1.0,
+                                [&](double t) { return sturm_count(al, e2, t) > 0; });
+        if (res > 1e-7) continue;
+      }
       result[r] = ritz_bound(al, be, j, last ? 0.0 : b_j, &res);
       if (ex || res < 1e-9) {   // Krylov space exhausted, or both ends converged
         converged[r] = true;
@@ -902,6 +947,20 @@ int sc::lanczos_spectrum(sc_graph* g, int omega, int max_iter, double tol, hipSt
     checked = upto;
     if (ex || steps == kmax) break;
     if (steps >= want) {
+      // the pair of want-th largest |theta| first: the largest t with fewer than `want`
+      // eigenvalues of magnitude above it
+      const std::vector<double> e2 = squares(beta);
+      auto above = [&](double t) {
+        return steps - sturm_count(alpha, e2, t) + sturm_count(alpha, e2, -t);
+      };
+      double at = 0.0;
+      const double rp = boundary_residual(alpha, beta, b_last, 0.0, 1.1, 1.0,
+                                          [&](double t) { return above(t) < want; }, &at);
+      const double rn = boundary_residual(alpha, beta, b_last, at, at, -1.0,
+                                          [](double) { return true; });
+      // the pair's sign is not known: the nearer eigenvalue answers with its own residual,
+      // the other end's start vector converges to some other pair
+      if (std::min(rp, rn) > 100.0 * tol) continue;
       th = alpha;
       if (!tridiag_eigen(th, beta, zl)) break;
       const std::vector<int> idx = order_of(th);
