@@ -4,8 +4,8 @@
 // All floating-point reductions use fixed orders; the walk randomness is a
 // pure function of (seed, i, j, r, side, step) so results do not depend on
 // the thread schedule.
-#include "philox.hpp"
 #include "sc_internal.hpp"
+#include "walk.hpp"
 #include "accumulate.hpp"
 
 #include <algorithm>
@@ -647,9 +647,7 @@ __global__ __launch_bounds__(256) void k_work_totals(BlockList blocks, int tilde
 // lane + 64, ...; gacc[k] += their mean (Eq. 11).
 template <typename T, int B>
 __device__ inline void slot_walks(int k, int lane, int s0, int tilde, unsigned k0, unsigned k1,
-                                  const int32_t* __restrict__ rowptr,
-                                  const int32_t* __restrict__ col,
-                                  const int32_t* __restrict__ slot_row,
+                                  const WalkGraph<int32_t>& wg, const int32_t* __restrict__ slot_row,
                                   const double* __restrict__ inv_deg, const T* __restrict__ Y,
                                   const int32_t* __restrict__ tau,
                                   const long long* __restrict__ nr, double* __restrict__ gacc) {
@@ -657,30 +655,13 @@ __device__ inline void slot_walks(int k, int lane, int s0, int tilde, unsigned k
   if (n_r <= 0) return;
   const int len = tau[k] - tilde;
   const int s = slot_row[k];
-  const int c = s - s0;
-  const int j = col[k];
+  const T* __restrict__ Yc = Y + (s - s0);
   double acc = 0.0;
   for (long long r = lane; r < n_r; r += 64) {
-    // the two walks of the pair advance in lockstep so their loads overlap
-    int pos0 = s, pos1 = j;
-    double sum0 = 0.0, sum1 = 0.0;
-    for (int t4 = 0; t4 < len; t4 += 4) {   // four steps per Philox draw
-      const uint32_t hi = static_cast<uint32_t>(t4 >> 2);
-      const U32x4 w0 = philox4x32_10(static_cast<uint32_t>(s), static_cast<uint32_t>(j),
-                                     static_cast<uint32_t>(r), hi, k0, k1);
-      const U32x4 w1 = philox4x32_10(static_cast<uint32_t>(s), static_cast<uint32_t>(j),
-                                     static_cast<uint32_t>(r), (1u << 31) | hi, k0, k1);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (t4 + u >= len) break;
-        const int b0 = rowptr[pos0], e0 = rowptr[pos0 + 1];
-        const int b1 = rowptr[pos1], e1 = rowptr[pos1 + 1];
-        pos0 = col[b0 + static_cast<int>(pick_neighbour(w0.w[u], static_cast<uint32_t>(e0 - b0)))];
-        pos1 = col[b1 + static_cast<int>(pick_neighbour(w1.w[u], static_cast<uint32_t>(e1 - b1)))];
-        sum0 += static_cast<double>(Y[static_cast<size_t>(pos0) * B + c]);
-        sum1 += static_cast<double>(Y[static_cast<size_t>(pos1) * B + c]);
-      }
-    }
+    double sum0, sum1;
+    walk_pair(wg, s, k, r, len, k0, k1,
+              [&](int y) { return static_cast<double>(Yc[static_cast<size_t>(y) * B]); }, &sum0,
+              &sum1);
     acc += (sum0 - sum1) * inv_deg[s];   // X of Eq. 11
   }
   acc = wave_sum(acc);
@@ -761,8 +742,7 @@ __global__ __launch_bounds__(kScanThreads) void k_walk_scan(BlockList blocks,
 template <typename T, int B>
 __global__ __launch_bounds__(kThreads) void k_walks_flat(
     SliceGrid sg, BlockList blocks, int n, int tilde, unsigned k0, unsigned k1,
-    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
-    const int32_t* __restrict__ slot_row, const double* __restrict__ inv_deg,
+    WalkGraph<int32_t> g, const int32_t* __restrict__ slot_row, const double* __restrict__ inv_deg,
     const T* __restrict__ Yg, int64_t ystride, const int32_t* __restrict__ tau,
     const long long* __restrict__ nr, const long long* __restrict__ chunk_off_g,
     const long long* __restrict__ ctl, double* __restrict__ part_g, long long capacity,
@@ -778,7 +758,7 @@ __global__ __launch_bounds__(kThreads) void k_walks_flat(
   const T* __restrict__ Y = Yg + br.buf * ystride;
   const int c_first = s0 + (sl % (B / C)) * C;
   if (c_first >= n) return;
-  const int ks = rowptr[c_first], ke = rowptr[min(n, c_first + C)];   // the slice's slots
+  const int ks = g.rowptr[c_first], ke = g.rowptr[min(n, c_first + C)];   // the slice's slots
   const long long* __restrict__ chunk_off = chunk_off_g + kbeg + s0 / B;
   const long long base = part_base(ctl, bi);
   double* __restrict__ part = part_g + base;
@@ -788,8 +768,8 @@ __global__ __launch_bounds__(kThreads) void k_walks_flat(
   if (base + ctl[bi] > capacity) {
     // the chunks do not fit the partial-sum buffer: one wave per slot instead
     for (long long k = ks + w; k < ke; k += nwaves)
-      slot_walks<T, B>(static_cast<int>(k), lane, s0, tilde, k0, k1, rowptr, col, slot_row,
-                       inv_deg, Y, tau, nr, gacc);
+      slot_walks<T, B>(static_cast<int>(k), lane, s0, tilde, k0, k1, g, slot_row, inv_deg, Y, tau,
+                       nr, gacc);
     return;
   }
   const long long first = chunk_off[ks - kbeg], last = chunk_off[ke - kbeg];
@@ -819,30 +799,11 @@ __global__ __launch_bounds__(kThreads) void k_walks_flat(
     if (r < n_r) {
       const int len = tau[k] - tilde;
       const int s = slot_row[k];
-      const int cc = s - s0;
-      const int j = col[k];
-      int pos0 = s, pos1 = j;
-      double sum0 = 0.0, sum1 = 0.0;
-      // four steps per Philox draw, the word of each step a compile-time index
-      // (a run-time index would put the draw in scratch memory)
-      for (int t4 = 0; t4 < len; t4 += 4) {
-        const uint32_t h = static_cast<uint32_t>(t4 >> 2);
-        const U32x4 w0 = philox4x32_10(static_cast<uint32_t>(s), static_cast<uint32_t>(j),
-                                       static_cast<uint32_t>(r), h, k0, k1);
-        const U32x4 w1 = philox4x32_10(static_cast<uint32_t>(s), static_cast<uint32_t>(j),
-                                       static_cast<uint32_t>(r), (1u << 31) | h, k0, k1);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if (t4 + u >= len) break;
-          // the two walks of the pair advance in lockstep so their loads overlap
-          const int b0 = rowptr[pos0], e0 = rowptr[pos0 + 1];
-          const int b1 = rowptr[pos1], e1 = rowptr[pos1 + 1];
-          pos0 = col[b0 + static_cast<int>(pick_neighbour(w0.w[u], static_cast<uint32_t>(e0 - b0)))];
-          pos1 = col[b1 + static_cast<int>(pick_neighbour(w1.w[u], static_cast<uint32_t>(e1 - b1)))];
-          sum0 += static_cast<double>(Y[static_cast<size_t>(pos0) * B + cc]);
-          sum1 += static_cast<double>(Y[static_cast<size_t>(pos1) * B + cc]);
-        }
-      }
+      const T* __restrict__ Yc = Y + (s - s0);
+      double sum0, sum1;
+      walk_pair(g, s, k, r, len, k0, k1,
+                [&](int y) { return static_cast<double>(Yc[static_cast<size_t>(y) * B]); }, &sum0,
+                &sum1);
       x = (sum0 - sum1) * inv_deg[s];   // X of Eq. 11
     }
     x = wave_sum(x);
@@ -997,9 +958,10 @@ hipError_t launch_walks(const DeviceGraph& g, const BlockList& blocks, int B, in
   if (e != hipSuccess) return e;
   // kWalkBlocks resident workgroups on the chip, an eighth of them per slice
   const SliceGrid sg = tail_grid(blocks, B, sizeof(T), kWalkBlocks / 8, false);
+  const WalkGraph<int32_t> wg{g.rowptr, g.col};
   SC_DISPATCH_B(B, (k_walks_flat<T, kB><<<sg.size(), kThreads, 0, st>>>(
-                        sg, blocks, g.n, tilde, k0, k1, g.rowptr, g.col, g.slot_row, g.inv_deg_d,
-                        Y, ystride, tau_slot, nr, off, ctl, ts.part, ts.capacity, gacc)));
+                        sg, blocks, g.n, tilde, k0, k1, wg, g.slot_row, g.inv_deg_d, Y, ystride,
+                        tau_slot, nr, off, ctl, ts.part, ts.capacity, gacc)));
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   SC_DISPATCH_B(B, (k_walk_finish<kB><<<dim3(grid_for(slots, 256), nb), 256, 0, st>>>(

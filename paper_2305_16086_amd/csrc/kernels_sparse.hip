@@ -19,8 +19,8 @@
 // first l where the frontier volume exceeds the walk work becomes tilde_tau_i.
 // The walks of a wave of sources then run flat over the whole GPU (chunks of
 // 64 walk pairs, fixed-order sums), reading q from the sources' slots.
-#include "philox.hpp"
 #include "sc_internal.hpp"
+#include "walk.hpp"
 
 #include <cfloat>
 #include <climits>
@@ -29,45 +29,23 @@ namespace sc {
 
 namespace {
 
-constexpr int kT = kSrcThreads;           // threads of the per-source workgroup
-constexpr int kTW = kT / 64;              // its waves
 constexpr double kInvUnit = 1.0 / 9223372036854775808.0;   // 2^-63
-constexpr int kWalkGrid = 2048;
-constexpr int kLongRow = 2048;   // N(j) longer than this is scanned by the whole workgroup
-constexpr int kLongList = 256;
+constexpr int kWalkGrid = 2048;   // a multiple of 8
+constexpr int kUnit = 128;        // chunks a workgroup of k_src_walks_lds takes at a time
+constexpr int kUnitThreads = 1024, kUnitGrid = 256;
+constexpr int kLdsNodes = 13600;  // 12 bytes of LDS each
+constexpr int kLdsMinChunks = 32;
+constexpr int kShortRow = 128;    // N(j) up to this is scanned by 16 lanes, up to kLongRow by a
+constexpr int kLongRow = 2048;    // wave, and a longer one by the whole workgroup
+constexpr int kHubEdges = 1024;   // a longer list is pushed by the whole workgroup
+constexpr int kLongList = 1024;
+constexpr int kCandList = 64;     // rho candidates whose pairs are looked up one by one
 
-__device__ inline int block_scan_excl(int v, int* s_w, int* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int x = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
-  if (lane == 63) s_w[wave] = x;
-  __syncthreads();
-  int pre = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < kTW; ++w) {
-    pre += w < wave ? s_w[w] : 0;
-    tot += s_w[w];
-  }
-  __syncthreads();
-  *total = tot;
-  return pre + x - v;
-}
-
-template <typename V, typename Op>
-__device__ inline V block_reduce(V v, V* s, Op op) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = op(v, __shfl_xor(v, off, 64));
-  if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
-  __syncthreads();
-  V r = s[0];
-#pragma unroll
-  for (int w = 1; w < kTW; ++w) r = op(r, s[w]);
-  __syncthreads();
-  return r;
+// Lanes of one wave share LDS without a barrier: their LDS operations are in
+// order, the fence keeps the compiler from moving them.
+__device__ inline void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 struct MaxU64 {
@@ -83,43 +61,115 @@ struct AddD {
   __device__ double operator()(double a, double b) const { return a + b; }
 };
 
-// Visit every (entry, neighbour) pair of the entries [0, cnt) of a node list
-// that pass `keep`, edge-parallel over the workgroup: each pass loads 256
-// entries, scans their degrees and spreads the neighbour slots over the
-// threads (a hub's list is shared by all of them).  act(entry, value, y).
-template <typename Keep, typename Act>
-__device__ inline void for_each_edge(const int32_t* __restrict__ list, int cnt,
-                                     const int32_t* __restrict__ rowptr,
-                                     const int32_t* __restrict__ col, Keep keep, Act act,
-                                     int* s_off, int* s_beg, uint64_t* s_val, int* s_w) {
-  for (int base = 0; base < cnt; base += kT) {
-    const int e = base + static_cast<int>(threadIdx.x);
+template <typename V, typename Op>
+__device__ inline V wave_reduce(V v, Op op) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v = op(v, __shfl_xor(v, off, 64));
+  return v;
+}
+
+template <int kT, typename V, typename Op>
+__device__ inline V block_reduce(V v, V* s, Op op) {
+  v = wave_reduce(v, op);
+  if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
+  __syncthreads();
+  V r = s[0];
+#pragma unroll
+  for (int w = 1; w < kT / 64; ++w) r = op(r, s[w]);
+  __syncthreads();
+  return r;
+}
+
+constexpr int kEdgeIlp = 4;   // neighbour slots of one lane in flight
+
+// Visit every (value, neighbour) pair of the entries [0, cnt) of a node list that
+// pass `keep`.  Each wave takes 64 entries at a time, scans their degrees and
+// spreads the neighbour slots over its lanes without a workgroup barrier; an
+// entry with more than kHubEdges neighbours is left to the whole workgroup.
+// act(value[], y[], live[]) gets kEdgeIlp pairs of the lane at once, so that
+// their memory operations are in flight together.  Called by the whole
+// workgroup; barriers inside.
+template <int kT, typename Keep, typename Act>
+__device__ inline void visit_edges(const int32_t* __restrict__ list, int cnt,
+                                   const int32_t* __restrict__ rowptr,
+                                   const int32_t* __restrict__ col, Keep keep, Act act, int* s_off,
+                                   int* s_beg, uint64_t* s_val, int* s_long, int* s_nlong) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (tid == 0) *s_nlong = 0;
+  __syncthreads();
+  int* so = s_off + wave * 64;
+  int* sb = s_beg + wave * 64;
+  uint64_t* sv = s_val + wave * 64;
+  for (int base = wave * 64; base < cnt; base += kT) {
+    const int e = base + lane;
     int du = 0, beg = 0;
     uint64_t val = 0;
     if (e < cnt) {
       const int u = list[e];
-      if (keep(e, u, &val)) {
+      if (keep(u, &val)) {
         beg = rowptr[u];
         du = rowptr[u + 1] - beg;
+        if (du > kHubEdges) {
+          const int slot = atomicAdd(s_nlong, 1);
+          if (slot < kLongList) {
+            s_long[slot] = u;
+            du = 0;
+          }
+        }
       }
     }
-    int total = 0;
-    const int off = block_scan_excl(du, s_w, &total);
-    s_off[threadIdx.x] = off;
-    s_beg[threadIdx.x] = beg;
-    s_val[threadIdx.x] = val;
-    __syncthreads();
-    for (int x = threadIdx.x; x < total; x += kT) {
-      int lo = 0, hi = kT - 1;   // last t with s_off[t] <= x (entries without edges share offsets)
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (s_off[mid] <= x) lo = mid;
-        else hi = mid - 1;
-      }
-      act(lo, s_val[lo], col[s_beg[lo] + (x - s_off[lo])]);
+    int x = du;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int y = __shfl_up(x, off, 64);
+      if (lane >= off) x += y;
     }
-    __syncthreads();
+    const int total = __shfl(x, 63, 64);
+    so[lane] = x - du;
+    sb[lane] = beg - (x - du);
+    sv[lane] = val;
+    wave_fence();
+    for (int x0 = lane; x0 < total; x0 += 64 * kEdgeIlp) {
+      uint64_t v[kEdgeIlp];
+      int y[kEdgeIlp];
+      bool live[kEdgeIlp];
+#pragma unroll
+      for (int q = 0; q < kEdgeIlp; ++q) {
+        const int xx = x0 + 64 * q;
+        live[q] = xx < total;
+        int lo = 0;   // last entry with so[] <= xx (entries without slots share offsets)
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1)
+          if (so[lo + s] <= xx) lo += s;
+        v[q] = sv[lo];
+        y[q] = live[q] ? col[sb[lo] + xx] : 0;
+      }
+      act(v, y, live);
+    }
+    wave_fence();
   }
+  __syncthreads();
+  const int nlong = min(*s_nlong, kLongList);
+  for (int t = 0; t < nlong; ++t) {
+    const int u = s_long[t];
+    const int b = rowptr[u], total = rowptr[u + 1] - b;
+    uint64_t val = 0;
+    keep(u, &val);
+    for (int x0 = tid; x0 < total; x0 += kT * kEdgeIlp) {
+      uint64_t v[kEdgeIlp];
+      int y[kEdgeIlp];
+      bool live[kEdgeIlp];
+#pragma unroll
+      for (int q = 0; q < kEdgeIlp; ++q) {
+        const int xx = x0 + kT * q;
+        live[q] = xx < total;
+        v[q] = val;
+        y[q] = live[q] ? col[b + xx] : 0;
+      }
+      act(v, y, live);
+    }
+  }
+  __syncthreads();
 }
 
 // x in the sorted neighbour list col[b, e)
@@ -134,35 +184,28 @@ __device__ inline bool adjacent(const int32_t* __restrict__ col, int b, int e, i
   return false;
 }
 
-__device__ inline double wave_max_d(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-  return v;
-}
-__device__ inline double wave_min_d(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmin(v, __shfl_xor(v, off, 64));
-  return v;
-}
-__device__ inline double wave_sum_d(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
+// One source per workgroup of kT threads.  A step is a chain of dependent
+// accesses (list, degree, neighbour, column word) with a barrier between its
+// phases, so it is bound by how many of them one workgroup has in flight: the
+// waves spread edges by themselves with four slots per lane, the Eq. 13 scans
+// give 16 lanes to a short list, and the selection of the gamma-th largest entry
+// ranks the last 64 keys in one wave.
+template <int kT>
 __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
+  constexpr int kTW = kT / 64;
   __shared__ int s_off[kT], s_beg[kT];
   __shared__ uint64_t s_val[kT];
-  __shared__ int s_w[kTW];
-  __shared__ uint64_t s_r64[kTW];
+  __shared__ uint64_t s_r64[5][kTW];
   __shared__ double s_rd[kTW];
   __shared__ unsigned s_hist[256];
-  __shared__ unsigned long long s_bmin[256], s_bmax[256];
   __shared__ int s_cnt;
-  __shared__ int s_long[kLongList];   // halves whose N(j) the whole workgroup scans
+  __shared__ int s_long[kLongList];   // list positions or halves left to more lanes
   __shared__ int s_nlong;
-  __shared__ uint64_t s_sel[3];   // prefix, threshold, done flag
-  __shared__ int s_rank;
+  __shared__ uint64_t s_key[64];   // the last keys of the selection
+  __shared__ int s_cand[kCandList];
+  __shared__ int s_ncand;
+  __shared__ uint64_t s_prefix;   // digits chosen so far; the threshold at the end
+  __shared__ int s_rank, s_left;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -197,34 +240,25 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
   int32_t* Sc = a.S + static_cast<size_t>(2 * w) * n;
   int32_t* Sn = Sc + n;
   int parity = 0;
+  // r_0 = e_i, and what the loop below keeps of the support at each l: its
+  // volume (Eq. 14 left side), extremes over it and over N(i)
+  const uint64_t q0 = ((1ull << 63) + static_cast<uint64_t>(di) / 2) / static_cast<uint64_t>(di);
   if (tid == 0) {
-    const uint64_t one = 1ull << 63;
-    Qc[i] = (one + static_cast<uint64_t>(di) / 2) / static_cast<uint64_t>(di);   // r_0 = e_i
+    Qc[i] = q0;
     Sc[0] = i;
   }
   int cnt = 1;
   int ell = 0;
   uint64_t pushed = 0;
+  uint64_t vol = static_cast<uint64_t>(di), qmx = q0, qmn = q0, qmx_i = 0, qmn_i = 0;
   __syncthreads();
 
   for (;;) {
-    // ---- (1) the support: volume (Eq. 14 left side), extremes, select keys
-    uint64_t vol = 0, qmx = 0, qmn = ~0ull;
-    for (int e = tid; e < cnt; e += kT) {
-      const int y = Sc[e];
-      const uint64_t v = Qc[y];
-      vol += static_cast<uint64_t>(a.rowptr[y + 1] - a.rowptr[y]);
-      qmx = v > qmx ? v : qmx;
-      qmn = v < qmn ? v : qmn;
-      Qn[e] = v;   // keys of the radix select (Qn is all zero here)
-    }
-    vol = block_reduce(vol, s_r64, AddU64{});
-    qmx = block_reduce(qmx, s_r64, MaxU64{});
-    qmn = block_reduce(qmn, s_r64, MinU64{});
     const double maxV = static_cast<double>(qmx);
     const double minV = cnt == n ? static_cast<double>(qmn) : 0.0;   // zeros outside S
+    bool keyed = false;   // Qn holds the selection's keys
 
-    // ---- (2)-(5) walk counts at this l (skipped where no half needs walks)
+    // ---- (1)-(4) walk counts at this l (skipped where no half needs walks)
     // a forced switch step (tests, and a fixed tilde_tau option) skips Eq. 14 and
     // evaluates the walk counts only where it stops.  Eq. 14 itself is not
     // evaluated at l = 0: its left side is then d_i while each of the d_i halves
@@ -234,92 +268,154 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
     const bool need = ell < taup && (forced ? ell == stop_forced : ell > 0);
     double rhs = 0.0;
     double rhoQ = 0.0;
-    double maxNi = 0.0, minNi = 0.0;
+    const double maxNi = static_cast<double>(qmx_i), minNi = static_cast<double>(qmn_i);
     if (need) {
-      // (2) threshold T = the gamma-th largest q (Algorithm 3 line 2); 0 when the
-      // support has fewer than gamma nodes (the candidate list then holds zeros)
+      // (1) threshold T = the gamma-th largest q (Algorithm 3 line 2); 0 when the
+      // support has fewer than gamma nodes (the candidate list then holds zeros).
+      // Digits of up to 8 bits from the highest set one down: a histogram of the
+      // keys that share the digits chosen so far, until at most 64 keys are left,
+      // which one wave ranks against each other.
       uint64_t T = 0;
       if (a.gamma > 0 && cnt < a.gamma && cnt == n) T = qmn;   // every node is a candidate
       if (a.gamma > 0 && cnt >= a.gamma) {
-        const int top = 63 - __clzll(static_cast<long long>(qmx | 1ull));
-        int shift = (top / 8) * 8;
-        uint64_t prefix = 0, pmask = shift + 8 >= 64 ? 0ull : ~((1ull << (shift + 8)) - 1);
+        int pos = 64 - __clzll(static_cast<long long>(qmx | 1ull));   // bits below pos undecided
+        uint64_t prefix = 0;
         if (tid == 0) {
           s_rank = a.gamma;
-          s_sel[2] = 0;
+          s_left = cnt;
         }
         __syncthreads();
-        for (; shift >= 0; shift -= 8) {
-          for (int d = tid; d < 256; d += kT) {
-            s_hist[d] = 0;
-            s_bmin[d] = ~0ull;
-            s_bmax[d] = 0;
+        int left = cnt;
+        while (left > 64 && pos > 0) {
+          const int width = pos < 8 ? pos : 8;
+          const int shift = pos - width;
+          for (int d = tid; d < 256; d += kT) s_hist[d] = 0;
+          __syncthreads();
+          if (!keyed) {
+            for (int e = tid; e < cnt; e += kT) {
+              const uint64_t v = Qc[Sc[e]];
+              Qn[e] = v;   // Qn is all zero here
+              atomicAdd(&s_hist[v >> shift], 1u);   // no digit is chosen yet
+            }
+            keyed = true;
+          } else {
+            for (int e = tid; e < cnt; e += kT) {
+              const uint64_t v = Qn[e];
+              if ((v >> pos) == (prefix >> pos))
+                atomicAdd(&s_hist[(v >> shift) & ((1u << width) - 1u)], 1u);
+            }
           }
+          __syncthreads();
+          if (wave == 0) {   // lane's buckets 255 - 4 lane .. 252 - 4 lane, from the top
+            unsigned c[4], sum = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              c[q] = s_hist[255 - 4 * lane - q];
+              sum += c[q];
+            }
+            unsigned x = sum;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+              const unsigned y = __shfl_up(x, off, 64);
+              if (lane >= off) x += y;
+            }
+            const unsigned k = static_cast<unsigned>(s_rank);
+            unsigned above = x - sum;
+            if (above < k && k <= x) {   // one lane
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                if (above < k && k <= above + c[q]) {
+                  s_prefix = prefix | (static_cast<uint64_t>(255 - 4 * lane - q) << shift);
+                  s_rank = static_cast<int>(k - above);
+                  s_left = static_cast<int>(c[q]);
+                }
+                above += c[q];
+              }
+            }
+          }
+          __syncthreads();
+          prefix = s_prefix;
+          left = s_left;
+          pos = shift;
+        }
+        if (pos == 0) {
+          T = prefix;   // every bit is decided
+        } else {
+          if (tid == 0) s_ncand = 0;
           __syncthreads();
           for (int e = tid; e < cnt; e += kT) {
-            const uint64_t v = Qn[e];
-            if ((v & pmask) == prefix) {
-              const int d = static_cast<int>((v >> shift) & 255u);
-              atomicAdd(&s_hist[d], 1u);
-              atomicMin(&s_bmin[d], static_cast<unsigned long long>(v));
-              atomicMax(&s_bmax[d], static_cast<unsigned long long>(v));
-            }
+            const uint64_t v = keyed ? Qn[e] : Qc[Sc[e]];
+            if (pos == 64 || (v >> pos) == (prefix >> pos)) s_key[atomicAdd(&s_ncand, 1)] = v;
           }
           __syncthreads();
-          if (tid == 0) {
-            int k = s_rank, d = 255;
-            for (; d > 0; --d) {
-              if (static_cast<int>(s_hist[d]) >= k) break;
-              k -= static_cast<int>(s_hist[d]);
+          if (wave == 0) {
+            const uint64_t v = lane < left ? s_key[lane] : 0;
+            int gt = 0, eq = 0;
+            for (int q = 0; q < left; ++q) {
+              const uint64_t x = s_key[q];
+              gt += x > v ? 1 : 0;
+              eq += x == v ? 1 : 0;
             }
-            s_rank = k;
-            s_sel[0] = prefix | (static_cast<uint64_t>(d) << shift);
-            if (s_bmin[d] == s_bmax[d]) {   // one value left in the bucket
-              s_sel[1] = s_bmin[d];
-              s_sel[2] = 1;
-            }
+            if (lane < left && gt < s_rank && s_rank <= gt + eq) s_prefix = v;   // equal values
           }
           __syncthreads();
-          prefix = s_sel[0];
-          pmask |= 255ull << shift;
-          if (s_sel[2]) break;
-          __syncthreads();
+          T = s_prefix;
         }
-        T = s_sel[2] ? s_sel[1] : prefix;
-        __syncthreads();
       }
-      // (3) rho-hat (Eq. 16 bound, Algorithm 3 lines 3-5, safe reading): the best
-      // candidate-pair edge against q[c_1] + q[c_gamma]
+      // (2) rho-hat (Eq. 16 bound, Algorithm 3 lines 3-5, safe reading): the best
+      // candidate-pair edge against q[c_1] + q[c_gamma].  Few candidates (ties may
+      // add more): every pair of them is looked up in the shorter of its two sorted
+      // lists; else every edge of a candidate is visited.
       if (a.gamma > 0) {
         const uint64_t thr = T > 0 ? T : 1;
         unsigned long long best = 0;
-        for_each_edge(
-            Sc, cnt, a.rowptr, a.col,
-            [&](int, int u, uint64_t* val) {
-              *val = Qc[u];
-              return *val >= thr;
-            },
-            [&](int, uint64_t qc, int y) {
-              const uint64_t qy = Qc[y];
-              if (qy >= thr) {
-                const unsigned long long s = qc + qy;
-                best = s > best ? s : best;
-              }
-            },
-            s_off, s_beg, s_val, s_w);
-        best = block_reduce(static_cast<uint64_t>(best), s_r64, MaxU64{});
+        if (tid == 0) s_ncand = 0;
+        __syncthreads();
+        for (int e = tid; e < cnt; e += kT) {
+          const int y = Sc[e];
+          const uint64_t v = keyed ? Qn[e] : Qc[y];
+          if (v >= thr) {
+            const int slot = atomicAdd(&s_ncand, 1);
+            if (slot < kCandList) s_cand[slot] = y;
+          }
+        }
+        __syncthreads();
+        const int nc = s_ncand;
+        if (nc <= kCandList) {
+          for (int pq = tid; pq < nc * nc; pq += kT) {
+            const int p = pq / nc, q = pq % nc;
+            if (p >= q) continue;
+            int c1 = s_cand[p], c2 = s_cand[q];
+            int b1 = a.rowptr[c1], e1 = a.rowptr[c1 + 1];
+            const int b2 = a.rowptr[c2], e2 = a.rowptr[c2 + 1];
+            const unsigned long long s = Qc[c1] + Qc[c2];
+            if (e2 - b2 < e1 - b1) {
+              b1 = b2;
+              e1 = e2;
+              c2 = c1;
+            }
+            if (s > best && adjacent(a.col, b1, e1, c2)) best = s;
+          }
+        } else {
+          visit_edges<kT>(
+              Sc, cnt, a.rowptr, a.col,
+              [&](int u, uint64_t* val) {
+                *val = Qc[u];
+                return *val >= thr;
+              },
+              [&](const uint64_t(&v)[kEdgeIlp], const int(&y)[kEdgeIlp], const bool(&live)[kEdgeIlp]) {
+#pragma unroll
+                for (int q = 0; q < kEdgeIlp; ++q) {
+                  const uint64_t qy = live[q] ? Qc[y[q]] : 0;
+                  if (qy >= thr) best = v[q] + qy > best ? v[q] + qy : best;
+                }
+              },
+              s_off, s_beg, s_val, s_long, &s_nlong);
+        }
+        best = block_reduce<kT>(static_cast<uint64_t>(best), s_r64[0], MaxU64{});
         rhoQ = fmax(static_cast<double>(best), maxV + static_cast<double>(T));
       }
-      // (4) extremes over N(i)
-      double mx = -DBL_MAX, mn = DBL_MAX;
-      for (int k = rb + tid; k < re; k += kT) {
-        const double v = static_cast<double>(Qc[a.col[k]]);
-        mx = fmax(mx, v);
-        mn = fmin(mn, v);
-      }
-      maxNi = block_reduce(mx, s_rd, [](double x, double y) { return fmax(x, y); });
-      minNi = block_reduce(mn, s_rd, [](double x, double y) { return fmin(x, y); });
-      // (5) per half (i, j): extremes over N(j), chi (Eq. 17 / Eq. 15), n_r (Eq. 13)
+      // (3) per half (i, j): extremes over N(j), chi (Eq. 17 / Eq. 15), n_r (Eq. 13)
       double part = 0.0;
       auto count_walks = [&](int k, int len, double jmx, double jmn) {
         double chiQ;
@@ -340,93 +436,125 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
         a.nr_slot[k] = nr;
         part += a.rule == 0 ? static_cast<double>(nr) : 2.0 * len * static_cast<double>(nr);
       };
+      // a short support against a long N(j): visit the support and test adjacency
+      // to j instead
+      auto by_support = [&](int dj) { return static_cast<int64_t>(cnt) * 16 < dj; };
+      // extremes over N(j) seen by lane `ln` of `st` lanes, and the support nodes
+      // found in it (by_support only); q is zero off the support
+      auto scan_row = [&](int jb, int je, int j, int ln, int st, uint64_t* mx, uint64_t* mn,
+                          int* hits) {
+        *mx = 0;
+        *mn = ~0ull;
+        *hits = 0;
+        if (by_support(je - jb)) {
+          for (int e = ln; e < cnt; e += st) {
+            const int y = Sc[e];
+            const int yb = a.rowptr[y], ye = a.rowptr[y + 1];
+            const bool in_j = ye - yb < je - jb ? adjacent(a.col, yb, ye, j)
+                                                : adjacent(a.col, jb, je, y);
+            if (in_j) {
+              const uint64_t v = Qc[y];
+              *mx = v > *mx ? v : *mx;
+              *mn = v < *mn ? v : *mn;
+              ++*hits;
+            }
+          }
+          return;
+        }
+        for (int q = jb + ln; q < je; q += st * kEdgeIlp) {
+          int y[kEdgeIlp];
+          uint64_t v[kEdgeIlp];
+#pragma unroll
+          for (int x = 0; x < kEdgeIlp; ++x) y[x] = a.col[min(q + x * st, je - 1)];   // repeats the last
+#pragma unroll
+          for (int x = 0; x < kEdgeIlp; ++x) v[x] = Qc[y[x]];
+#pragma unroll
+          for (int x = 0; x < kEdgeIlp; ++x) {
+            *mx = v[x] > *mx ? v[x] : *mx;
+            *mn = v[x] < *mn ? v[x] : *mn;
+          }
+        }
+      };
+      auto row_min = [&](uint64_t mn, int hits, int dj) {
+        // by support: the minimum is 0 unless the support fills N(j)
+        return by_support(dj) && hits < dj ? 0.0 : static_cast<double>(mn);
+      };
       if (tid == 0) s_nlong = 0;
       __syncthreads();
-      for (int k = rb + wave; k < re; k += kTW) {
+      const int sub = tid & 15;
+      for (int k = rb + tid / 16; k < re; k += kT / 16) {
+        // 16 lanes per half; longer lists go to the list below while it has room
         const int len = a.tau_slot[k] - ell;
         if (len <= 0) {
-          if (lane == 0) a.nr_slot[k] = 0;
-          continue;
-        }
-        if (a.gamma > 0) {
+          if (sub == 0) a.nr_slot[k] = 0;
+        } else if (a.gamma <= 0) {
+          if (sub == 0) count_walks(k, len, 0.0, 0.0);
+        } else {
           const int j = a.col[k];
           const int jb = a.rowptr[j], je = a.rowptr[j + 1];
-          double jmx, jmn;
-          if (je - jb > kLongRow && static_cast<int64_t>(cnt) * 16 >= je - jb) {
-            // a hub's list: left to the whole workgroup below (or scanned here
-            // when the list of such halves is full)
-            int slot = -1;
-            if (lane == 0) slot = atomicAdd(&s_nlong, 1);
-            slot = __shfl(slot, 0, 64);
-            if (slot < kLongList) {
-              if (lane == 0) s_long[slot] = k;
-              continue;
-            }
+          bool later = false;
+          if (je - jb > kShortRow) {
+            int slot = 0;
+            if (sub == 0) slot = atomicAdd(&s_nlong, 1);
+            slot = __shfl(slot, lane & 48, 64);
+            later = slot < kLongList;
+            if (later && sub == 0) s_long[slot] = k;
           }
-          if (static_cast<int64_t>(cnt) * 16 < je - jb) {
-            // a short support against a long N(j) (a hub): visit the support and
-            // test adjacency to j instead; q is zero off the support, so the
-            // extremes over N(j) are those of the support nodes in N(j), with
-            // the minimum 0 unless they fill N(j)
-            double mx = 0.0, mn = DBL_MAX;
-            int hits = 0;
-            for (int e = lane; e < cnt; e += 64) {
-              const int y = Sc[e];
-              const int yb = a.rowptr[y], ye = a.rowptr[y + 1];
-              const bool in_j = ye - yb < je - jb ? adjacent(a.col, yb, ye, j)
-                                                  : adjacent(a.col, jb, je, y);
-              if (in_j) {
-                const double v = static_cast<double>(Qc[y]);
-                mx = fmax(mx, v);
-                mn = fmin(mn, v);
-                ++hits;
-              }
-            }
-            jmx = wave_max_d(mx);
-            mn = wave_min_d(mn);
+          if (!later) {
+            uint64_t mx, mn;
+            int hits;
+            scan_row(jb, je, j, sub, 16, &mx, &mn, &hits);
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) hits += __shfl_xor(hits, off, 64);
-            jmn = hits < je - jb ? 0.0 : mn;
-          } else {
-            double mx = -DBL_MAX, mn = DBL_MAX;
-            for (int q = jb + lane; q < je; q += 64) {
-              const double v = static_cast<double>(Qc[a.col[q]]);
-              mx = fmax(mx, v);
-              mn = fmin(mn, v);
+            for (int off = 8; off >= 1; off >>= 1) {
+              mx = MaxU64{}(mx, __shfl_xor(mx, off, 64));
+              mn = MinU64{}(mn, __shfl_xor(mn, off, 64));
+              hits += __shfl_xor(hits, off, 64);
             }
-            jmx = wave_max_d(mx);
-            jmn = wave_min_d(mn);
+            if (sub == 0) count_walks(k, len, static_cast<double>(mx), row_min(mn, hits, je - jb));
           }
-          if (lane == 0) count_walks(k, len, jmx, jmn);
-        } else if (lane == 0) {
-          count_walks(k, len, 0.0, 0.0);
         }
       }
       __syncthreads();
       const int nlong = s_nlong < kLongList ? s_nlong : kLongList;
+      for (int t = wave; t < nlong; t += kTW) {   // a wave per list
+        const int k = s_long[t];
+        const int j = a.col[k];
+        const int jb = a.rowptr[j], je = a.rowptr[j + 1];
+        if (je - jb > kLongRow && !by_support(je - jb)) continue;
+        uint64_t mx, mn;
+        int hits;
+        scan_row(jb, je, j, lane, 64, &mx, &mn, &hits);
+        mx = wave_reduce(mx, MaxU64{});
+        mn = wave_reduce(mn, MinU64{});
+        hits = wave_reduce(hits, [](int x, int y) { return x + y; });
+        if (lane == 0)
+          count_walks(k, a.tau_slot[k] - ell, static_cast<double>(mx), row_min(mn, hits, je - jb));
+      }
       for (int t = 0; t < nlong; ++t) {   // hubs' lists, all threads at once
         const int k = s_long[t];
         const int j = a.col[k];
-        double mx = -DBL_MAX, mn = DBL_MAX;
-        for (int q = a.rowptr[j] + tid; q < a.rowptr[j + 1]; q += kT) {
-          const double v = static_cast<double>(Qc[a.col[q]]);
-          mx = fmax(mx, v);
-          mn = fmin(mn, v);
-        }
-        mx = block_reduce(mx, s_rd, [](double x, double y) { return fmax(x, y); });
-        mn = block_reduce(mn, s_rd, [](double x, double y) { return fmin(x, y); });
-        if (tid == 0) count_walks(k, a.tau_slot[k] - ell, mx, mn);
+        const int jb = a.rowptr[j], je = a.rowptr[j + 1];
+        if (je - jb <= kLongRow || by_support(je - jb)) continue;
+        uint64_t mx, mn;
+        int hits;
+        scan_row(jb, je, j, tid, kT, &mx, &mn, &hits);
+        mx = block_reduce<kT>(mx, s_r64[0], MaxU64{});
+        mn = block_reduce<kT>(mn, s_r64[1], MinU64{});
+        if (tid == 0)
+          count_walks(k, a.tau_slot[k] - ell, static_cast<double>(mx), static_cast<double>(mn));
       }
-      rhs = block_reduce(part, s_rd, AddD{});
+      rhs = block_reduce<kT>(part, s_rd, AddD{});
     }
-    // ---- (6) Eq. 14: switch when the next push costs more than the walks
+    // ---- (4) Eq. 14: switch when the next push costs more than the walks
     const bool done = forced ? ell >= stop_forced
                              : (ell >= taup || (need && static_cast<double>(vol) > rhs));
     if (done) {
       // clear the select keys, record the outcome
-      for (int e = tid; e < cnt; e += kT) Qn[e] = 0;
+      if (keyed)
+        for (int e = tid; e < cnt; e += kT) Qn[e] = 0;
       unsigned long long wk = 0, ws = 0;
       const int64_t pbase = (a.hoff ? a.hoff[li] : static_cast<int64_t>(rb)) - a.pos_base;
+      __syncthreads();   // walk counts written by other threads of the workgroup
       for (int k = rb + tid; k < re; k += kT) {
         const int len = a.tau_slot[k] - ell;
         const long long nr = len > 0 ? a.nr_slot[k] : 0;
@@ -438,8 +566,8 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
         wk += static_cast<unsigned long long>(nr);
         ws += static_cast<unsigned long long>(nr) * 2ull * static_cast<unsigned long long>(len > 0 ? len : 0);
       }
-      wk = block_reduce(static_cast<uint64_t>(wk), s_r64, AddU64{});
-      ws = block_reduce(static_cast<uint64_t>(ws), s_r64, AddU64{});
+      wk = block_reduce<kT>(static_cast<uint64_t>(wk), s_r64[0], AddU64{});
+      ws = block_reduce<kT>(static_cast<uint64_t>(ws), s_r64[1], AddU64{});
       if (tid == 0) {
         a.tilde_row[i] = ell;
         a.slot_ctl[2 * w] = cnt;
@@ -453,37 +581,81 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
       return;
     }
 
-    // ---- (7) push l -> l + 1: r_{l+1}[y] = sum over u in N(y) of Q_l[u]
-    for (int e = tid; e < cnt; e += kT) Qn[e] = 0;   // the select keys
+    // ---- (5) push l -> l + 1: r_{l+1}[y] = sum over u in N(y) of Q_l[u]
+    if (keyed)
+      for (int e = tid; e < cnt; e += kT) Qn[e] = 0;
     if (tid == 0) s_cnt = 0;
     __syncthreads();
-    for_each_edge(
+    visit_edges<kT>(
         Sc, cnt, a.rowptr, a.col,
-        [&](int, int u, uint64_t* val) {
+        [&](int u, uint64_t* val) {
           *val = Qc[u];
           return *val != 0;
         },
-        [&](int, uint64_t qv, int y) {
-          const unsigned long long old = atomicAdd(reinterpret_cast<unsigned long long*>(&Qn[y]),
-                                                   static_cast<unsigned long long>(qv));
-          if (old == 0) Sn[atomicAdd(&s_cnt, 1)] = y;
+        [&](const uint64_t(&v)[kEdgeIlp], const int(&y)[kEdgeIlp], const bool(&live)[kEdgeIlp]) {
+          unsigned long long old[kEdgeIlp];
+#pragma unroll
+          for (int q = 0; q < kEdgeIlp; ++q) {
+            old[q] = 1;
+            if (live[q])
+              old[q] = atomicAdd(reinterpret_cast<unsigned long long*>(&Qn[y[q]]),
+                                 static_cast<unsigned long long>(v[q]));
+          }
+#pragma unroll
+          for (int q = 0; q < kEdgeIlp; ++q)
+            if (old[q] == 0) Sn[atomicAdd(&s_cnt, 1)] = y[q];
         },
-        s_off, s_beg, s_val, s_w);
+        s_off, s_beg, s_val, s_long, &s_nlong);
     pushed += vol;
     const int cntn = s_cnt;
-    // ---- (8) Q_{l+1}[y] = r_{l+1}[y] / d_y (rounded to nearest); (9) clear Q_l
+    // ---- (6) Q_{l+1}[y] = r_{l+1}[y] / d_y (rounded to nearest), the support's
+    // volume and extremes; (7) clear Q_l
+    uint64_t r_vol = 0, r_mx = 0, r_mn = ~0ull;
     for (int e = tid; e < cntn; e += kT) {
       const int y = Sn[e];
       const uint64_t d = static_cast<uint64_t>(a.rowptr[y + 1] - a.rowptr[y]);
-      Qn[y] = (Qn[y] + d / 2) / d;
+      const uint64_t v = (Qn[y] + d / 2) / d;
+      Qn[y] = v;
+      r_vol += d;
+      r_mx = v > r_mx ? v : r_mx;
+      r_mn = v < r_mn ? v : r_mn;
     }
     for (int e = tid; e < cnt; e += kT) Qc[Sc[e]] = 0;
     __syncthreads();
-    // ---- (10) step l + 1 of Eq. 9: g(i, j) += (p(i,i) - p(j,i)) / d_i = (Q[i] - Q[j]) 2^-63
+    // ---- (8) step l + 1 of Eq. 9: g(i, j) += (p(i,i) - p(j,i)) / d_i = (Q[i] - Q[j]) 2^-63,
+    // and the extremes over N(i)
     const double qi = static_cast<double>(Qn[i]);
-    for (int k = rb + tid; k < re; k += kT)
+    uint64_t r_imx = 0, r_imn = ~0ull;
+    for (int k = rb + tid; k < re; k += kT) {
+      const uint64_t v = Qn[a.col[k]];
+      r_imx = v > r_imx ? v : r_imx;
+      r_imn = v < r_imn ? v : r_imn;
       if (ell + 1 <= a.tau_slot[k])
-        a.gacc[k] += (qi - static_cast<double>(Qn[a.col[k]])) * kInvUnit;
+        a.gacc[k] += (qi - static_cast<double>(v)) * kInvUnit;
+    }
+    r_vol = wave_reduce(r_vol, AddU64{});
+    r_mx = wave_reduce(r_mx, MaxU64{});
+    r_mn = wave_reduce(r_mn, MinU64{});
+    r_imx = wave_reduce(r_imx, MaxU64{});
+    r_imn = wave_reduce(r_imn, MinU64{});
+    if (lane == 0) {
+      s_r64[0][wave] = r_vol;
+      s_r64[1][wave] = r_mx;
+      s_r64[2][wave] = r_mn;
+      s_r64[3][wave] = r_imx;
+      s_r64[4][wave] = r_imn;
+    }
+    __syncthreads();
+    vol = 0;
+    qmx = qmx_i = 0;
+    qmn = qmn_i = ~0ull;
+    for (int x = 0; x < kTW; ++x) {
+      vol += s_r64[0][x];
+      qmx = MaxU64{}(qmx, s_r64[1][x]);
+      qmn = MinU64{}(qmn, s_r64[2][x]);
+      qmx_i = MaxU64{}(qmx_i, s_r64[3][x]);
+      qmn_i = MinU64{}(qmn_i, s_r64[4][x]);
+    }
     __syncthreads();
     uint64_t* tq = Qc;
     Qc = Qn;
@@ -499,16 +671,17 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
 
 // ---------------------------------------------------------------- walks of a wave
 // chunk_off[p] = exclusive prefix of ceil(nr_pos[p] / 64); ctl = {chunks, fits}
-__global__ __launch_bounds__(256) void k_src_scan(int64_t P, const int64_t* __restrict__ nr_pos,
-                                                  int64_t* __restrict__ chunk_off, int64_t capacity,
-                                                  int64_t* __restrict__ ctl) {
-  __shared__ int64_t s_w[4];
-  __shared__ int64_t s_carry;
+// One workgroup:
+// 1024 threads of eight positions take a wave of a small graph in one or two rounds
+// (n = 3,000, k = 5: 11.6 us a wave with 256).
+__global__ __launch_bounds__(1024) void k_src_scan(int64_t P, const int64_t* __restrict__ nr_pos,
+                                                   int64_t* __restrict__ chunk_off,
+                                                   int64_t capacity, int64_t* __restrict__ ctl) {
+  constexpr int kPer = 8, kScan = 1024;
+  __shared__ int64_t s_w[kScan / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  constexpr int kPer = 8;
-  if (tid == 0) s_carry = 0;
-  __syncthreads();
-  for (int64_t base = 0; base < P; base += 256 * kPer) {
+  int64_t carry = 0;
+  for (int64_t base = 0; base < P; base += kScan * kPer) {
     int64_t v[kPer];
     int64_t ts = 0;
 #pragma unroll
@@ -526,58 +699,55 @@ __global__ __launch_bounds__(256) void k_src_scan(int64_t P, const int64_t* __re
     }
     if (lane == 63) s_w[wave] = x;
     __syncthreads();
-    int64_t pre = 0;
-    for (int q = 0; q < wave; ++q) pre += s_w[q];
-    int64_t run = s_carry + pre + x - ts;
+    int64_t pre = 0, all = 0;
+#pragma unroll
+    for (int q = 0; q < kScan / 64; ++q) {
+      pre += q < wave ? s_w[q] : 0;
+      all += s_w[q];
+    }
+    int64_t run = carry + pre + x - ts;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
       const int64_t p = base + tid * kPer + q;
       if (p < P) chunk_off[p] = run;
       run += v[q];
     }
-    __syncthreads();
-    if (tid == 255) s_carry = run;
+    carry += all;
     __syncthreads();
   }
   if (tid == 0) {
-    chunk_off[P] = s_carry;
-    ctl[0] = s_carry;
-    ctl[1] = s_carry <= capacity ? 1 : 0;
+    chunk_off[P] = carry;
+    ctl[0] = carry;
+    ctl[1] = carry <= capacity ? 1 : 0;
+    ctl[2] = 0;   // units drawn by k_src_walks_lds
   }
 }
 
-// One walk pair of half-edge (i, j): the sums of Q over W_i and W_j (Eq. 11
-// numerator in units of 2^-63 / d_i), Philox counters as the other walk kernels.
-__device__ inline double walk_pair(int i, int j, long long r, int len, unsigned k0, unsigned k1,
-                                   const int32_t* __restrict__ rowptr,
-                                   const int32_t* __restrict__ col,
-                                   const uint64_t* __restrict__ Qs) {
-  int p0 = i, p1 = j;
-  double s0 = 0.0, s1 = 0.0;
-  for (int t4 = 0; t4 < len; t4 += 4) {
-    const uint32_t h = static_cast<uint32_t>(t4 >> 2);
-    const U32x4 w0 = philox4x32_10(static_cast<uint32_t>(i), static_cast<uint32_t>(j),
-                                   static_cast<uint32_t>(r), h, k0, k1);
-    const U32x4 w1 = philox4x32_10(static_cast<uint32_t>(i), static_cast<uint32_t>(j),
-                                   static_cast<uint32_t>(r), (1u << 31) | h, k0, k1);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (t4 + u >= len) break;
-      const int b0 = rowptr[p0], e0 = rowptr[p0 + 1];
-      const int b1 = rowptr[p1], e1 = rowptr[p1 + 1];
-      p0 = col[b0 + static_cast<int>(pick_neighbour(w0.w[u], static_cast<uint32_t>(e0 - b0)))];
-      p1 = col[b1 + static_cast<int>(pick_neighbour(w1.w[u], static_cast<uint32_t>(e1 - b1)))];
-      s0 += static_cast<double>(Qs[p0]);
-      s1 += static_cast<double>(Qs[p1]);
-    }
+// Largest p in [lo, hi) with off[p] <= c (off is not decreasing and off[lo] <= c):
+// 64 probes a round, so two to four rounds of one load each.
+template <typename V>
+__device__ inline long long find_position(const V* __restrict__ off, long long lo, long long hi,
+                                          long long c, int lane) {
+  while (hi - lo > 1) {
+    const long long step = (hi - lo + 63) / 64;
+    const long long q = lo + lane * step;
+    const uint64_t below = __ballot(q < hi && off[q] <= c);
+    lo += (63 - __clzll(static_cast<long long>(below))) * step;
+    hi = min(hi, lo + step);
   }
-  return (s0 - s1) * kInvUnit;   // X of Eq. 11
+  return lo;
 }
 
-__global__ __launch_bounds__(256) void k_src_walks(SrcWalkArgs a) {
+// Chunks are taken in turn by all waves of the grid, those of one XCD together, so that
+// at any time its L2 holds the columns of the one or two sources it walks on.
+template <typename Id>
+__global__ __launch_bounds__(256) void k_src_walks(SrcWalkArgs a, const Id* __restrict__ ids) {
+  const WalkGraph<Id> g{a.rowptr, ids};
   const int lane = threadIdx.x & 63;
   const long long nwaves = static_cast<long long>(gridDim.x) * 4;
-  const long long wv = static_cast<long long>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  // workgroup w runs on XCD w % 8: the waves of one XCD are numbered one after another
+  const long long wv = static_cast<long long>((blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8) * 4 +
+                       (threadIdx.x >> 6);
   const size_t n = static_cast<size_t>(a.n);
   auto slot_q = [&](int w) {
     return a.Q + (2 * static_cast<size_t>(w) + static_cast<size_t>(a.slot_ctl[2 * w + 1])) * n;
@@ -588,13 +758,17 @@ __global__ __launch_bounds__(256) void k_src_walks(SrcWalkArgs a) {
       const long long nr = a.nr_pos[p];
       if (nr <= 0) continue;
       const int k = a.pos_slot[p];
-      const int i = a.slot_row[k], j = a.col[k];
+      const int i = a.slot_row[k];
       const int len = a.tau_slot[k] - a.tilde_row[i];
       const uint64_t* Qs = slot_q(a.pos_w[p]);
       double acc = 0.0;
-      for (long long r = lane; r < nr; r += 64)
-        acc += walk_pair(i, j, r, len, a.k0, a.k1, a.rowptr, a.col, Qs);
-      acc = wave_sum_d(acc);
+      for (long long r = lane; r < nr; r += 64) {
+        double s0, s1;
+        walk_pair(g, i, k, r, len, a.k0, a.k1,
+                  [&](int y) { return static_cast<double>(Qs[y]); }, &s0, &s1);
+        acc += (s0 - s1) * kInvUnit;   // X of Eq. 11
+      }
+      acc = wave_reduce(acc, AddD{});
       if (lane == 0) a.gacc[k] += acc / static_cast<double>(nr);
     }
     return;
@@ -602,34 +776,108 @@ __global__ __launch_bounds__(256) void k_src_walks(SrcWalkArgs a) {
   // chunks [cb, ce): a batch given by the host, or all of them
   const long long cb = a.cend < 0 ? 0 : a.cbeg;
   const long long ce = a.cend < 0 ? a.ctl[0] : a.cend;
-  const long long per = (ce - cb + nwaves - 1) / nwaves;
-  const long long c0 = cb + wv * per;
-  const long long c1 = min(ce, c0 + per);
-  if (c0 >= c1) return;
-  long long lo = 0, hi = a.P;   // chunk_off[lo] <= c0 < chunk_off[hi]
-  while (hi - lo > 1) {
-    const long long mid = (lo + hi) >> 1;
-    if (a.chunk_off[mid] <= c0) lo = mid;
-    else hi = mid;
-  }
-  long long p = lo;
-  long long next = a.chunk_off[p + 1];
-  for (long long c = c0; c < c1; ++c) {
-    while (c >= next) {
-      ++p;
-      next = a.chunk_off[p + 1];
-    }
+  long long p = 0;
+  for (long long c = cb + wv; c < ce; c += nwaves) {
+    if (c >= a.chunk_off[p + 1]) p = find_position(a.chunk_off, p, a.P, c, lane);
     const int k = a.pos_slot[p];
     const long long nr = a.nr_pos[p];
     const long long r = (c - a.chunk_off[p]) * 64 + lane;
     double x = 0.0;
     if (r < nr) {
-      const int i = a.slot_row[k], j = a.col[k];
+      const int i = a.slot_row[k];
       const int len = a.tau_slot[k] - a.tilde_row[i];
-      x = walk_pair(i, j, r, len, a.k0, a.k1, a.rowptr, a.col, slot_q(a.pos_w[p]));
+      const uint64_t* Qs = slot_q(a.pos_w[p]);
+      double s0, s1;
+      walk_pair(g, i, k, r, len, a.k0, a.k1,
+                [&](int y) { return static_cast<double>(Qs[y]); }, &s0, &s1);
+      x = (s0 - s1) * kInvUnit;   // X of Eq. 11
     }
-    x = wave_sum_d(x);
+    x = wave_reduce(x, AddD{});
     if (lane == 0) a.part[c - cb] = x;
+  }
+}
+
+// The same for a wave whose sources have many chunks each.  A CU's vector memory path
+// takes about half a line per clock of such gathers, whatever cache they hit (R-MAT
+// scale 15, 7.7 G steps: three gathers a step 78 ms, with the row bounds in LDS 57 ms), so
+// a workgroup takes the whole CU and keeps the row bounds and the column of the nodes
+// below `kc` in LDS: all of a small graph, the hubs where ids go by degree or age
+// (31 ms, the time of one gather a step; 118 ms with a contiguous run of chunks per wave).
+// Workgroups draw units of kUnit chunks and change the column where the source changes.
+template <typename Id>
+struct PrefixGraph {
+  WalkGraph<Id> g;
+  const Id* __restrict__ col;
+  const int32_t* s_row;
+  int kc;
+
+  __device__ int step(int node, uint32_t word) const {
+    int b, e;
+    if (node < kc) {
+      b = s_row[node];
+      e = s_row[node + 1];
+    } else {
+      b = g.rowptr[node];
+      e = g.rowptr[node + 1];
+    }
+    return static_cast<int>(
+        col[b + static_cast<int>(pick_neighbour(word, static_cast<uint32_t>(e - b)))]);
+  }
+};
+
+template <typename Id>
+__global__ __launch_bounds__(kUnitThreads) void k_src_walks_lds(SrcWalkArgs a,
+                                                                const Id* __restrict__ ids, int kc) {
+  extern __shared__ uint64_t s_mem[];   // [kc] column, then [kc + 1] row bounds
+  __shared__ long long s_unit;
+  uint64_t* s_q = s_mem;
+  int32_t* s_row = reinterpret_cast<int32_t*>(s_mem + kc);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int x = tid; x <= kc; x += kUnitThreads) s_row[x] = a.rowptr[x];
+  const PrefixGraph<Id> g{{a.rowptr, ids}, ids, s_row, kc};
+  const size_t n = static_cast<size_t>(a.n);
+  int cur = -1;
+  for (;;) {
+    __syncthreads();
+    if (tid == 0)
+      s_unit = static_cast<long long>(
+          atomicAdd(reinterpret_cast<unsigned long long*>(a.ctl + 2), 1ull));
+    __syncthreads();
+    long long c = a.cbeg + s_unit * kUnit;
+    const long long end = min(static_cast<long long>(a.cend), c + kUnit);
+    if (c >= end) return;
+    while (c < end) {
+      const long long p0 = find_position(a.chunk_off, 0, a.P, c, lane);
+      const int w = a.pos_w[p0];   // the source's positions follow one another
+      const long long pe = find_position(a.pos_w, p0, a.P, w, lane) + 1;
+      const long long stop = min(end, static_cast<long long>(a.chunk_off[pe]));
+      const uint64_t* Qs =
+          a.Q + (2 * static_cast<size_t>(w) + static_cast<size_t>(a.slot_ctl[2 * w + 1])) * n;
+      if (w != cur) {
+        __syncthreads();
+        for (int x = tid; x < kc; x += kUnitThreads) s_q[x] = Qs[x];
+        __syncthreads();
+        cur = w;
+      }
+      long long p = p0;
+      for (long long x = c + wave; x < stop; x += kUnitThreads / 64) {
+        if (x >= a.chunk_off[p + 1]) p = find_position(a.chunk_off, p, pe, x, lane);
+        const int k = a.pos_slot[p];
+        const long long r = (x - a.chunk_off[p]) * 64 + lane;
+        double v = 0.0;
+        if (r < a.nr_pos[p]) {
+          const int i = a.slot_row[k];
+          const int len = a.tau_slot[k] - a.tilde_row[i];
+          double s0, s1;
+          walk_pair(g, i, k, r, len, a.k0, a.k1,
+                    [&](int y) { return static_cast<double>(y < kc ? s_q[y] : Qs[y]); }, &s0, &s1);
+          v = (s0 - s1) * kInvUnit;   // X of Eq. 11
+        }
+        v = wave_reduce(v, AddD{});
+        if (lane == 0) a.part[x - a.cbeg] = v;
+      }
+      c = stop;
+    }
   }
 }
 
@@ -643,28 +891,35 @@ __device__ inline bool finish_range(const SrcWalkArgs& a, long long p, long long
   return *lo < *hi;
 }
 
-// gacc[k] += (chunk sums of half p in chunk order) / n_r, one thread per half
-// with at most finish_seg chunks in the batch
+// gacc[k] += (chunk sums of half p in chunk order) / n_r, one thread per half with
+// at most finish_seg chunks in the batch.  The halves with more are then taken one
+// by one by the whole workgroup, each thread summing one fixed segment of
+// ceil(chunks / 256) in order, then the 256 segment sums in order (the order depends
+// only on the chunk count).
 __global__ __launch_bounds__(256) void k_src_finish(SrcWalkArgs a) {
-  const long long p = static_cast<long long>(blockIdx.x) * 256 + threadIdx.x;
-  if (p >= a.P || (a.cend < 0 && a.ctl[1] == 0)) return;
-  long long cb, lo, hi;
-  if (!finish_range(a, p, &cb, &lo, &hi) || hi - lo > a.finish_seg) return;
-  double s = 0.0;
-  for (long long c = lo; c < hi; ++c) s += a.part[c - cb];
-  a.gacc[a.pos_slot[p]] += s / static_cast<double>(a.nr_pos[p]);
-}
-
-// The same for the halves with more chunks: a workgroup per half, each thread
-// summing one fixed segment of ceil(chunks / 256) in order, then the 256
-// segment sums in order (the order depends only on the chunk count)
-__global__ __launch_bounds__(256) void k_src_finish_long(SrcWalkArgs a) {
   __shared__ double s_seg[256];
+  __shared__ int s_long[256];
+  __shared__ int s_nlong;
   if (a.cend < 0 && a.ctl[1] == 0) return;
   const int tid = threadIdx.x;
-  for (long long p = blockIdx.x; p < a.P; p += gridDim.x) {
-    long long cb, lo, hi;
-    if (!finish_range(a, p, &cb, &lo, &hi) || hi - lo <= a.finish_seg) continue;
+  if (tid == 0) s_nlong = 0;
+  if (tid == 0 && blockIdx.x == 0) a.ctl[2] = 0;   // for the next batch
+  __syncthreads();
+  const long long base = static_cast<long long>(blockIdx.x) * 256;
+  long long cb, lo, hi;
+  if (base + tid < a.P && finish_range(a, base + tid, &cb, &lo, &hi)) {
+    if (hi - lo > a.finish_seg) {
+      s_long[atomicAdd(&s_nlong, 1)] = tid;
+    } else {
+      double s = 0.0;
+      for (long long c = lo; c < hi; ++c) s += a.part[c - cb];
+      a.gacc[a.pos_slot[base + tid]] += s / static_cast<double>(a.nr_pos[base + tid]);
+    }
+  }
+  __syncthreads();
+  for (int x = 0; x < s_nlong; ++x) {
+    const long long p = base + s_long[x];
+    finish_range(a, p, &cb, &lo, &hi);
     const long long seg = (hi - lo + 255) / 256;
     const long long c0 = lo + tid * seg;
     const long long c1 = min(hi, c0 + seg);
@@ -706,6 +961,25 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t* __restrict__ p, int6
   for (int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; k < count;
        k += static_cast<int64_t>(gridDim.x) * 256)
     p[k] = value;
+}
+
+__global__ __launch_bounds__(256) void k_src_init(unsigned long long* __restrict__ totals,
+                                                  int ntotals, int64_t* __restrict__ nr_slot,
+                                                  int64_t slots, int32_t* __restrict__ slot_ctl,
+                                                  int64_t nctl, int32_t* __restrict__ tilde_row,
+                                                  int64_t n) {
+  const int64_t k0 = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  const int64_t st = static_cast<int64_t>(gridDim.x) * 256;
+  for (int64_t k = k0; k < slots; k += st) nr_slot[k] = 0;
+  for (int64_t k = k0; k < nctl; k += st) slot_ctl[k] = 0;
+  for (int64_t k = k0; k < n; k += st) tilde_row[k] = -1;
+  if (k0 < ntotals) totals[k0] = k0 == 3 || k0 == 6 ? ~0ull : 0ull;
+}
+
+__global__ __launch_bounds__(256) void k_narrow(const int32_t* __restrict__ src,
+                                                uint16_t* __restrict__ dst, int64_t count) {
+  const int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (k < count) dst[k] = static_cast<uint16_t>(src[k]);
 }
 
 // smallest and largest row truncation (tau_row) into mm[0] / mm[1]
@@ -766,6 +1040,21 @@ hipError_t launch_fill_u32(uint32_t* p, int64_t count, uint32_t value, hipStream
   return hipGetLastError();
 }
 
+hipError_t launch_src_init(unsigned long long* totals, int ntotals, int64_t* nr_slot, int64_t slots,
+                           int32_t* slot_ctl, int64_t nctl, int32_t* tilde_row, int64_t n,
+                           hipStream_t st) {
+  if (ntotals > 256) return hipErrorInvalidValue;
+  k_src_init<<<fill_grid(std::max(slots, nctl)), 256, 0, st>>>(totals, ntotals, nr_slot, slots,
+                                                               slot_ctl, nctl, tilde_row, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_narrow(const int32_t* src, uint16_t* dst, int64_t count, hipStream_t st) {
+  if (count <= 0) return hipSuccess;
+  k_narrow<<<static_cast<unsigned>((count + 255) / 256), 256, 0, st>>>(src, dst, count);
+  return hipGetLastError();
+}
+
 hipError_t launch_nbr_volume(const DeviceGraph& g, int64_t* vol, hipStream_t st) {
   k_nbr_volume<<<static_cast<unsigned>((g.n + 3) / 4), 256, 0, st>>>(g.n, g.rowptr, g.col, vol);
   return hipGetLastError();
@@ -778,25 +1067,33 @@ hipError_t launch_tau_range(int n, const int32_t* tau_row, unsigned long long* m
 
 hipError_t launch_src_head(const SrcArgs& a, int grid, hipStream_t st) {
   if (grid <= 0) return hipSuccess;
-  k_src_head<<<grid, kT, 0, st>>>(a);
+  // A source's time is that of one workgroup's chain of phases, so it gets as many
+  // threads as leave every source of the launch a place on the chip at once.
+  if (grid <= 512) k_src_head<1024><<<grid, 1024, 0, st>>>(a);
+  else if (grid <= 1024) k_src_head<512><<<grid, 512, 0, st>>>(a);
+  else k_src_head<256><<<grid, 256, 0, st>>>(a);
   return hipGetLastError();
 }
 
 hipError_t launch_src_scan(const SrcWalkArgs& a, hipStream_t st) {
   if (a.P <= 0) return hipSuccess;
-  k_src_scan<<<1, 256, 0, st>>>(a.P, a.nr_pos, a.chunk_off, a.capacity, a.ctl);
+  k_src_scan<<<1, 1024, 0, st>>>(a.P, a.nr_pos, a.chunk_off, a.capacity, a.ctl);
   return hipGetLastError();
 }
 
 hipError_t launch_src_walk_batch(const SrcWalkArgs& a, hipStream_t st) {
   if (a.P <= 0) return hipSuccess;
-  k_src_walks<<<kWalkGrid, 256, 0, st>>>(a);
+  // (kLdsMinChunks a source: a change of source costs a workgroup some 10 us)
+  const int kc = std::min(a.n, kLdsNodes);
+  const size_t lds = static_cast<size_t>(kc) * 12 + 4;
+  if (a.cend >= 0 && a.cend - a.cbeg >= kLdsMinChunks * static_cast<int64_t>(a.nsources)) {
+    if (a.col16) k_src_walks_lds<<<kUnitGrid, kUnitThreads, lds, st>>>(a, a.col16, kc);
+    else k_src_walks_lds<<<kUnitGrid, kUnitThreads, lds, st>>>(a, a.col, kc);
+  } else if (a.col16) k_src_walks<<<kWalkGrid, 256, 0, st>>>(a, a.col16);
+  else k_src_walks<<<kWalkGrid, 256, 0, st>>>(a, a.col);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   k_src_finish<<<static_cast<unsigned>((a.P + 255) / 256), 256, 0, st>>>(a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  k_src_finish_long<<<static_cast<unsigned>(std::min<int64_t>(a.P, 1024)), 256, 0, st>>>(a);
   return hipGetLastError();
 }
 

@@ -132,6 +132,7 @@ void sc_graph::release() {
   dev_free(work);
   dev_free(plan_work);
   dev_free(nz);
+  dev_free(d.col16);
   dev_free(out_dev);
   dev_free(tau_out_dev);
   dev_free(nr_out_dev);
@@ -1286,6 +1287,25 @@ int build_slice_lists(sc_graph* g, hipStream_t st) {
 }
 
 }  // namespace
+
+int ensure_narrow_ids(sc_graph* g, hipStream_t st) {
+  sc::DeviceGraph& d = g->d;
+  if (d.col16 || d.n > 65536) return SC_OK;
+  uint16_t* c = nullptr;
+  hipError_t e = sc::dev_alloc(&c, static_cast<size_t>(d.nslots));
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    return SC_OK;
+  }
+  if (e == hipSuccess) e = sc::launch_narrow(d.col, c, d.nslots, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);   // once: later calls may use other streams
+  if (e != hipSuccess) {
+    sc::dev_free(c);
+    return sc::fail(SC_EHIP, std::string("narrow ids: ") + hipGetErrorString(e));
+  }
+  d.col16 = c;
+  return SC_OK;
+}
 
 int ensure_buffers(sc_graph* g, int B, size_t tsize, hipStream_t st) {
   using namespace sc;

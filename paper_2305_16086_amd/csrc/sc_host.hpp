@@ -226,6 +226,8 @@ int lanczos_spectrum(sc_graph* g, int omega, int max_iter, double tol, hipStream
 PipeLayout pipe_layout(const sc_graph* g, int B, size_t tsize);
 // work buffers of the traversal (and the sliced lists for B = 64)
 int ensure_buffers(sc_graph* g, int B, size_t tsize, hipStream_t st);
+// DeviceGraph::col16, where the ids fit and the memory is there
+int ensure_narrow_ids(sc_graph* g, hipStream_t st);
 // buffers of `blocks` tails; walks: also the chunk sums
 int ensure_tail(sc_graph* g, int blocks, bool walks);
 int ensure_pipeline(sc_graph* g);

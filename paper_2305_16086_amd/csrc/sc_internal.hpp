@@ -144,6 +144,8 @@ struct DeviceGraph {
   HeavyRow* giant = nullptr;     // [ngiant] rows cut into chunks
   int32_t ngiant = 0;
   int32_t nparts = 0;            // total partial rows
+  // col in 16 bits for the walks (built with the first per-source run where n <= 65,536)
+  uint16_t* col16 = nullptr;     // [2m]
 };
 
 // One graph of a batch as the persistent kernel sees it (device pointers).
@@ -326,7 +328,6 @@ hipError_t launch_trace(const DeviceGraph& g, const int32_t* tau_slot, const int
 // workgroup per source (kernels_sparse.hip).  Columns are 64-bit fixed point
 // Q[y] = p_l(i, y) / d_y in units of 2^-63, one pair of n-word columns and one
 // pair of n-entry support lists per workgroup slot.
-constexpr int kSrcThreads = 256;
 
 struct SrcArgs {
   int32_t n = 0;
@@ -361,6 +362,7 @@ struct SrcWalkArgs {
   int64_t P = 0;                   // positions of this wave
   const int32_t* rowptr = nullptr;
   const int32_t* col = nullptr;
+  const uint16_t* col16 = nullptr;   // as DeviceGraph's
   const int32_t* slot_row = nullptr;
   const int32_t* tau_slot = nullptr;
   const int32_t* tilde_row = nullptr;
@@ -372,7 +374,8 @@ struct SrcWalkArgs {
   const int32_t* pos_w = nullptr;
   const int64_t* nr_pos = nullptr;
   int64_t* chunk_off = nullptr;    // [P + 1]
-  int64_t* ctl = nullptr;          // [2]
+  int64_t* ctl = nullptr;          // [3] chunks, whether they fit, units drawn
+  int32_t nsources = 0;            // sources of this wave
   double* part = nullptr;          // [capacity]
   int64_t capacity = 0;
   double* gacc = nullptr;
@@ -386,6 +389,13 @@ struct SrcWalkArgs {
   int64_t finish_seg = 4096;
 };
 
+// dst[k] = src[k] (n <= 65,536)
+hipError_t launch_narrow(const int32_t* src, uint16_t* dst, int64_t count, hipStream_t st);
+// what a call starts from: totals (entries 3 and 6 are minima), no walks, no slot
+// holding a column to clear yet (the heads clear their slot's last one), no tilde
+hipError_t launch_src_init(unsigned long long* totals, int ntotals, int64_t* nr_slot, int64_t slots,
+                           int32_t* slot_ctl, int64_t nctl, int32_t* tilde_row, int64_t n,
+                           hipStream_t st);
 hipError_t launch_src_head(const SrcArgs& a, int grid, hipStream_t st);
 // plain fills (kernels, so that a captured sequence holds no memset nodes)
 hipError_t launch_fill_u64(uint64_t* p, int64_t count, uint64_t value, hipStream_t st);

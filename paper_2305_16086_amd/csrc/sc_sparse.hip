@@ -116,8 +116,8 @@ int enqueue_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
   const bool spectral = L == 0 && (o.flags & SC_TAU_SPECTRAL) != 0;
   const double eps_tau = eps / 2.0;   // Algorithm 4 line 2
   auto* tot = B.totals;
-  const unsigned long long init[kTotals] = {0, 0, 0, ~0ull, 0, 0, ~0ull, 0};
-  for (int k = 0; k < kTotals; ++k) HIP_TRY(sc::launch_fill_u64(reinterpret_cast<uint64_t*>(tot + k), 1, init[k], st));
+  HIP_TRY(sc::launch_src_init(tot, kTotals, B.nr_slot, S2, B.slot_ctl, 2 * static_cast<int64_t>(B.W),
+                              B.tilde_row, n, st));
   if (spectral)
     HIP_TRY(sc::launch_caltau(g->d, g->spec_lam, g->spec_phi, g->spec_omega, eps_tau, max_L,
                               B.tau_slot, B.tau_row, st, tot + 5));
@@ -126,11 +126,6 @@ int enqueue_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
   HIP_TRY(sc::launch_tau_range(static_cast<int>(n), B.tau_row, tot + 6, st));
   if (!B.Q_clean)
     HIP_TRY(sc::launch_fill_u64(B.Q, static_cast<int64_t>(2) * B.W * n, 0, st));
-  HIP_TRY(sc::launch_fill_u64(reinterpret_cast<uint64_t*>(B.nr_slot), S2, 0, st));
-  // no slot holds a column to clear yet (the heads clear their slot's last one)
-  HIP_TRY(sc::launch_fill_u32(reinterpret_cast<uint32_t*>(B.slot_ctl), 2 * static_cast<int64_t>(B.W),
-                              0, st));
-  HIP_TRY(sc::launch_fill_u32(reinterpret_cast<uint32_t*>(B.tilde_row), n, 0xFFFFFFFFu, st));
   HIP_TRY(sc::launch_gacc_init(g->d, B.tau_slot, 0, B.gacc, st));
 
   const double delta = o.delta > 0.0 ? o.delta : 1.0 / static_cast<double>(n);
@@ -163,6 +158,7 @@ int enqueue_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
   wa.n = static_cast<int32_t>(n);
   wa.rowptr = g->d.rowptr;
   wa.col = g->d.col;
+  wa.col16 = g->d.col16;
   wa.slot_row = g->d.slot_row;
   wa.tau_slot = B.tau_slot;
   wa.tilde_row = B.tilde_row;
@@ -191,6 +187,7 @@ int enqueue_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
     a.pos_base = at(b);
     HIP_TRY(sc::launch_src_head(a, cnt, st));
     wa.P = at(b + cnt) - at(b);
+    wa.nsources = cnt;
     if (walk_ev) HIP_TRY(hipEventRecord((*walk_ev)[2 * wave], st));
     if (batch_walks && wa.P > 0) {
       // the host reads the wave's chunk count and walks them in batches of the
@@ -303,6 +300,10 @@ int sc::run_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
   const int64_t Pmax = wave_positions(nsrc, B.W, hp, g->rowptr_h);
 
   // ---- buffers owned by the handle
+  {
+    const int rr = ensure_narrow_ids(g, st);
+    if (rr) return rr;
+  }
   auto& sb = g->src;
   if (!g->gacc) HIP_TRY(dev_alloc(&g->gacc, S2));
   if (!g->tau_slot) HIP_TRY(dev_alloc(&g->tau_slot, S2));
@@ -326,7 +327,7 @@ int sc::run_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
   HIP_TRY(grow(&sb.nr_pos, &sb.nrp_cap, static_cast<size_t>(Pmax)));
   HIP_TRY(grow(&sb.chunk_off, &sb.co_cap, static_cast<size_t>(Pmax) + 1));
   HIP_TRY(grow(&sb.part, &sb.part_cap, static_cast<size_t>(kPartCapacity)));
-  HIP_TRY(grow(&sb.ctl, &sb.ctl2_cap, size_t(2)));
+  HIP_TRY(grow(&sb.ctl, &sb.ctl2_cap, size_t(3)));
   HIP_TRY(grow(&sb.totals, &sb.tot_cap, size_t(kTotals)));
   HIP_TRY(grow(&sb.list, &sb.list_cap, static_cast<size_t>(nsrc)));
   HIP_TRY(grow(&sb.hoff, &sb.hoff_cap, static_cast<size_t>(nsrc) + 1));
@@ -498,7 +499,7 @@ size_t carve(unsigned char* base, int64_t n, int64_t S2, int W, int64_t P, SrcBu
   take(&b.tau_row, sizeof(int32_t) * n);
   take(&b.tilde_row, sizeof(int32_t) * n);
   take(&b.totals, sizeof(unsigned long long) * kTotals);
-  take(&b.ctl, sizeof(int64_t) * 2);
+  take(&b.ctl, sizeof(int64_t) * 3);
   take(&b.slot_ctl, sizeof(int32_t) * 2 * W);
   take(&b.Q, sizeof(uint64_t) * 2 * static_cast<size_t>(W) * n);
   take(&b.S, sizeof(int32_t) * 2 * static_cast<size_t>(W) * n);
@@ -539,14 +540,14 @@ extern "C" int sc_all_edges_static(sc_graph* g, double eps, int L, const sc_opti
   } restore{g->device, cur};
   hipStream_t stream = static_cast<hipStream_t>(o->stream);
 
-  // the largest slot count whose buffers fit the array
-  int W = static_cast<int>(std::min<int64_t>(kMaxSlots, n));
+  // the fewest waves whose buffers fit the array, all of about the same size (halving
+  // the slots until they fit took three waves of 1,024 where two of 1,500 fit)
+  int W = 1;
   size_t need = 0;
-  for (;;) {
-    const int64_t P = wave_positions(n, W, nullptr, g->rowptr_h);
-    need = carve(nullptr, n, S2, W, P, nullptr);
+  for (int64_t waves = (n + kMaxSlots - 1) / kMaxSlots;; waves += std::max<int64_t>(1, waves / 16)) {
+    W = static_cast<int>(std::max<int64_t>(1, (n + waves - 1) / waves));
+    need = carve(nullptr, n, S2, W, wave_positions(n, W, nullptr, g->rowptr_h), nullptr);
     if (need <= kStaticScratchBytes || W == 1) break;
-    W = std::max(1, W / 2);
   }
   if (need > kStaticScratchBytes)
     return fail(SC_EINVAL, "graph too large for sc_all_edges_static: it needs " +

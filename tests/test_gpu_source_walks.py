@@ -1,0 +1,51 @@
+"""Per-source TGT+: the variants of its kernels agree.
+
+* walks with the column in LDS (waves with many chunks per source) against the
+  general walk kernel, for a graph that fits the LDS, one with a prefix of its
+  nodes there, and one whose ids need 32 bits: the same walk counts, and sums
+  that differ by the rounding of their grouping only (1e-12);
+* the head's workgroup sizes (chosen by the number of sources): the same switch
+  steps and walk counts per source;
+* selections with ties and long candidate lists against the oracle.
+"""
+import numpy as np
+import pytest
+
+import graphgen as gg
+from test_gpu_per_source import TOL, check_against_oracle, run_ps, sc  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [300, 13600, 13601, 70000])
+def test_walks_with_column_in_lds(sc, n, monkeypatch):  # noqa: F811
+    graph = gg.tree_plus_gnp(n, 8.0, 11)
+    src = np.arange(0, n, n // 8, dtype=np.int32)[:8]
+    kw = dict(sources=src, tilde_tau=1, L=9)
+    out, _, _, _, nr = run_ps(sc, graph, 0.02, **kw)
+    assert np.ceil(nr[nr > 0] / 64).sum() >= 32 * len(src)   # enough chunks a source
+    monkeypatch.setenv("SC_SOURCE_PART_CAPACITY", "200")     # batches below that
+    ref, _, _, _, nr2 = run_ps(sc, graph, 0.02, **kw)
+    np.testing.assert_array_equal(nr, nr2)
+    np.testing.assert_allclose(out, ref, atol=TOL, rtol=0)
+
+
+def test_head_workgroup_sizes(sc):  # noqa: F811
+    graph = gg.barabasi_albert(1200, 6, 4)
+    n, u, v = graph
+    _, _, _, tt, nr = run_ps(sc, graph, 0.02)                # 1,200 sources: 256 threads
+    for count in (512, 513, 1024):                           # 1,024, 512 and 512 threads
+        src = np.random.default_rng(count).permutation(n)[:count].astype(np.int32)
+        _, _, _, tt2, nr2 = run_ps(sc, graph, 0.02, sources=src)
+        np.testing.assert_array_equal(tt2[src], tt[src])
+        listed = np.zeros(n, bool)
+        listed[src] = True
+        hl = np.concatenate([listed[u], listed[v]])
+        np.testing.assert_array_equal(nr2[hl], nr[hl])
+
+
+@pytest.mark.parametrize("gamma", [64, 65, 100, 200])
+def test_selection_with_ties(sc, gamma):  # noqa: F811
+    graph = gg.king_grid(200)
+    out, _, tau, tt, nr = run_ps(sc, graph, 0.05, gamma=gamma, max_L=31)
+    check_against_oracle(graph, 0.05, out, None, tau, tt, nr, gamma=gamma)
