@@ -1647,6 +1647,7 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
   struct Group {
     sc::BlockList all, trav, tail;   // tail: blocks with edges beyond the switch step
     int lend[sc::kMaxGroup];         // last traversal step per block of trav
+    uint32_t keep = 0;               // blocks of trav whose last state a tail reads
   };
   std::vector<Group> groups;
   bool any_tail = false;
@@ -1663,6 +1664,7 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
     gr.all.b[gr.all.nb++] = r;
     if (lend >= 2) {
       gr.lend[gr.trav.nb] = lend;
+      if (tail) gr.keep |= 1u << gr.trav.nb;
       gr.trav.b[gr.trav.nb++] = r;
     }
     if (tail) {
@@ -1696,7 +1698,8 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
     if (tail_recorded[qset])
       HIP_TRY(hipStreamWaitEvent(st, g->pipe_ev[1 + sc::kPipeSets + qset], 0));
     R.st = st;
-    rc = R.traverse(gr.trav, gr.lend, true, g->gacc, q + 1 < groups.size() ? &groups[q + 1].trav : nullptr);
+    rc = R.traverse(gr.trav, gr.lend, true, g->gacc,
+                    q + 1 < groups.size() ? &groups[q + 1].trav : nullptr, gr.keep);
     if (rc) return rc;
     if (gr.tail.nb == 0) {
       rc = R.flush_acc();

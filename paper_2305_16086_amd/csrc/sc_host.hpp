@@ -344,8 +344,10 @@ struct Runner {
   // launches it).  The first dense step also sets the masks of the blocks of
   // `next` (may be null) and clears these blocks' (the two-hop step, the only
   // reader, is done by then).
+  // Bit i of `keep`: the state block i ends with is read by the caller; else only its
+  // accumulation is (B = 64).
   int traverse(const BlockList& blocks, const int* lend, bool acc, double* gacc,
-               const BlockList* next = nullptr) {
+               const BlockList* next = nullptr, uint32_t keep = ~0u) {
     pending = AccJob{};
     if (blocks.nb == 0) return SC_OK;
     int L = 2;
@@ -405,11 +407,21 @@ struct Runner {
     pending = job(2);
     for (int ell = 3; ell <= L; ++ell) {
       // the first dense step skips the rows the two-hop step left at zero (B = 64);
-      // the later ones gather every neighbour row and are the launches the stats
-      // count.  Every kTimeEvery-th of those is timed by events that take the row
+      // the later ones gather every neighbour row and, where no block is at a last
+      // step of which few rows are read, are the launches the stats count.  Every kTimeEvery-th of those is timed by events that take the row
       // kernel's own start and end; the others run without events.
       s.skip = ell == 3 && B == 64;
-      const bool timed = timing && !s.skip && stats.prop_launches % kTimeEvery == 0;
+      s.last = 0;
+      if (acc && B == 64) {
+        int at = 0;
+        for (int i = 0; i < blocks.nb; ++i) {
+          if (lend[i] < ell) continue;
+          if (lend[i] == ell && !((keep >> i) & 1u)) s.last |= 1u << at;
+          ++at;
+        }
+      }
+      const bool dense = !s.skip && s.last == 0;   // every row of every block
+      const bool timed = timing && dense && stats.prop_launches % kTimeEvery == 0;
       s.ev_start = s.ev_stop = nullptr;
       if (timed) {
         const int rc = event_pair(&s.ev_start, &s.ev_stop);
@@ -421,7 +433,7 @@ struct Runner {
       s.acc = pending;
       s.mj = ell == 3 ? next_masks() : MaskJob{};
       HIP_TRY(launch_step<T>(g->d, B, s, st));
-      if (!s.skip) {
+      if (dense) {
         ++stats.prop_launches;
         stats.prop_bytes += step_bytes() * s.blocks.nb;
       }

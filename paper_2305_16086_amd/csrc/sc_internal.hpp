@@ -250,6 +250,10 @@ struct StepJob {
   // rows flagged 0 are exact zeros in Yp and are not gathered (where step_can_skip)
   uint8_t* nz = nullptr;
   bool skip = false;
+  // B = 64: bit i: of block i's new state only the rows of its sources and their
+  // neighbours are read (its last step with nothing but the accumulation to follow);
+  // the light ones among the other rows are not written
+  uint32_t last = 0;
   const unsigned long long* mask = nullptr;   // two-hop: [i][n]
   const unsigned* anymask = nullptr;          // [i][ceil(n/32)]
   AccJob acc;

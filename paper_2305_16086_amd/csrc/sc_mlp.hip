@@ -499,7 +499,7 @@ int learned_t(sc_graph* g, double eps, const sc_options& o, double* out_user, sc
     sc::BlockList bl;
     int lend[sc::kMaxGroup];
     auto run = [&]() -> int {
-      int rc1 = R.traverse(bl, lend, true, g->gacc);
+      int rc1 = R.traverse(bl, lend, true, g->gacc, nullptr, 0);
       if (rc1 == SC_OK) rc1 = R.flush_acc();
       bl = sc::BlockList{};
       return rc1;
