@@ -39,6 +39,9 @@ constexpr int kShortRow = 128;    // N(j) up to this is scanned by 16 lanes, up 
 constexpr int kLongRow = 2048;    // wave, and a longer one by the whole workgroup
 constexpr int kHubEdges = 1024;   // a longer list is pushed by the whole workgroup
 constexpr int kLongList = 1024;
+// Graphs of up to this many nodes keep both columns in LDS (64 KB, two workgroups a CU):
+// the pushes are LDS atomics then (3,000 nodes, 3,000 sources in two launches: 589 -> 425 us).
+constexpr int kLdsColumns = 4096;
 constexpr int kCandList = 64;     // rho candidates whose pairs are looked up one by one
 
 // Lanes of one wave share LDS without a barrier: their LDS operations are in
@@ -80,7 +83,26 @@ __device__ inline V block_reduce(V v, V* s, Op op) {
   return r;
 }
 
-constexpr int kEdgeIlp = 4;   // neighbour slots of one lane in flight
+constexpr int kEdgeIlp = 4;   // neighbour slots (or entries) of one lane in flight
+
+// (x + d / 2) / d, exactly, for 0 < d < 2^31: the quotient by a double reciprocal (off by
+// up to 2^12), once more for the remainder, and a last step either way.  The compiler's
+// division of 64-bit words takes several times as long.
+__device__ inline uint64_t div_round(uint64_t x, uint32_t d) {
+  x += d / 2;
+  const double inv = 1.0 / static_cast<double>(d);
+  uint64_t q = static_cast<uint64_t>(static_cast<double>(x) * inv);
+  int64_t r = static_cast<int64_t>(x - q * d);
+  const int64_t c = static_cast<int64_t>(static_cast<double>(r) * inv);
+  q += static_cast<uint64_t>(c);
+  r -= c * static_cast<int64_t>(d);
+  if (r < 0) {
+    --q;
+    r += d;
+  }
+  if (r >= static_cast<int64_t>(d)) ++q;
+  return q;
+}
 
 // Visit every (value, neighbour) pair of the entries [0, cnt) of a node list that
 // pass `keep`.  Each wave takes 64 entries at a time, scans their degrees and
@@ -190,8 +212,9 @@ __device__ inline bool adjacent(const int32_t* __restrict__ col, int b, int e, i
 // waves spread edges by themselves with four slots per lane, the Eq. 13 scans
 // give 16 lanes to a short list, and the selection of the gamma-th largest entry
 // ranks the last 64 keys in one wave.
-template <int kT>
+template <int kT, bool kLds>
 __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
+  extern __shared__ uint64_t s_col[];   // kLds: [2 n], both columns
   constexpr int kTW = kT / 64;
   __shared__ int s_off[kT], s_beg[kT];
   __shared__ uint64_t s_val[kT];
@@ -235,8 +258,13 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
   const int rb = a.rowptr[i], re = a.rowptr[i + 1];
   const int di = re - rb;
   const int taup = a.tau_row[i];
-  uint64_t* Qc = a.Q + static_cast<size_t>(2 * w) * n;
-  uint64_t* Qn = Qc + n;
+  // the columns at l and l + 1: Q[oc + y], Q[on + y]
+  uint64_t* const Q = kLds ? s_col : a.Q + static_cast<size_t>(2 * w) * n;
+  int oc = 0, on = n;
+  if constexpr (kLds) {
+    for (int x = tid; x < 2 * n; x += kT) s_col[x] = 0;
+    __syncthreads();
+  }
   int32_t* Sc = a.S + static_cast<size_t>(2 * w) * n;
   int32_t* Sn = Sc + n;
   int parity = 0;
@@ -244,7 +272,7 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
   // volume (Eq. 14 left side), extremes over it and over N(i)
   const uint64_t q0 = ((1ull << 63) + static_cast<uint64_t>(di) / 2) / static_cast<uint64_t>(di);
   if (tid == 0) {
-    Qc[i] = q0;
+    Q[oc + i] = q0;
     Sc[0] = i;
   }
   int cnt = 1;
@@ -292,15 +320,24 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
           for (int d = tid; d < 256; d += kT) s_hist[d] = 0;
           __syncthreads();
           if (!keyed) {
-            for (int e = tid; e < cnt; e += kT) {
-              const uint64_t v = Qc[Sc[e]];
-              Qn[e] = v;   // Qn is all zero here
-              atomicAdd(&s_hist[v >> shift], 1u);   // no digit is chosen yet
+            for (int e0 = tid; e0 < cnt; e0 += kT * kEdgeIlp) {
+              uint64_t v[kEdgeIlp];
+              int y[kEdgeIlp];
+#pragma unroll
+              for (int q = 0; q < kEdgeIlp; ++q) y[q] = Sc[min(e0 + q * kT, cnt - 1)];
+#pragma unroll
+              for (int q = 0; q < kEdgeIlp; ++q) v[q] = Q[oc + y[q]];
+#pragma unroll
+              for (int q = 0; q < kEdgeIlp; ++q)
+                if (e0 + q * kT < cnt) {
+                  Q[on + e0 + q * kT] = v[q];   // Qn is all zero here
+                  atomicAdd(&s_hist[v[q] >> shift], 1u);   // no digit is chosen yet
+                }
             }
             keyed = true;
           } else {
             for (int e = tid; e < cnt; e += kT) {
-              const uint64_t v = Qn[e];
+              const uint64_t v = Q[on + e];
               if ((v >> pos) == (prefix >> pos))
                 atomicAdd(&s_hist[(v >> shift) & ((1u << width) - 1u)], 1u);
             }
@@ -344,7 +381,7 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
           if (tid == 0) s_ncand = 0;
           __syncthreads();
           for (int e = tid; e < cnt; e += kT) {
-            const uint64_t v = keyed ? Qn[e] : Qc[Sc[e]];
+            const uint64_t v = keyed ? Q[on + e] : Q[oc + Sc[e]];
             if (pos == 64 || (v >> pos) == (prefix >> pos)) s_key[atomicAdd(&s_ncand, 1)] = v;
           }
           __syncthreads();
@@ -373,7 +410,7 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
         __syncthreads();
         for (int e = tid; e < cnt; e += kT) {
           const int y = Sc[e];
-          const uint64_t v = keyed ? Qn[e] : Qc[y];
+          const uint64_t v = keyed ? Q[on + e] : Q[oc + y];
           if (v >= thr) {
             const int slot = atomicAdd(&s_ncand, 1);
             if (slot < kCandList) s_cand[slot] = y;
@@ -388,7 +425,7 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
             int c1 = s_cand[p], c2 = s_cand[q];
             int b1 = a.rowptr[c1], e1 = a.rowptr[c1 + 1];
             const int b2 = a.rowptr[c2], e2 = a.rowptr[c2 + 1];
-            const unsigned long long s = Qc[c1] + Qc[c2];
+            const unsigned long long s = Q[oc + c1] + Q[oc + c2];
             if (e2 - b2 < e1 - b1) {
               b1 = b2;
               e1 = e2;
@@ -400,13 +437,13 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
           visit_edges<kT>(
               Sc, cnt, a.rowptr, a.col,
               [&](int u, uint64_t* val) {
-                *val = Qc[u];
+                *val = Q[oc + u];
                 return *val >= thr;
               },
               [&](const uint64_t(&v)[kEdgeIlp], const int(&y)[kEdgeIlp], const bool(&live)[kEdgeIlp]) {
 #pragma unroll
                 for (int q = 0; q < kEdgeIlp; ++q) {
-                  const uint64_t qy = live[q] ? Qc[y[q]] : 0;
+                  const uint64_t qy = live[q] ? Q[oc + y[q]] : 0;
                   if (qy >= thr) best = v[q] + qy > best ? v[q] + qy : best;
                 }
               },
@@ -453,7 +490,7 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
             const bool in_j = ye - yb < je - jb ? adjacent(a.col, yb, ye, j)
                                                 : adjacent(a.col, jb, je, y);
             if (in_j) {
-              const uint64_t v = Qc[y];
+              const uint64_t v = Q[oc + y];
               *mx = v > *mx ? v : *mx;
               *mn = v < *mn ? v : *mn;
               ++*hits;
@@ -467,7 +504,7 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
 #pragma unroll
           for (int x = 0; x < kEdgeIlp; ++x) y[x] = a.col[min(q + x * st, je - 1)];   // repeats the last
 #pragma unroll
-          for (int x = 0; x < kEdgeIlp; ++x) v[x] = Qc[y[x]];
+          for (int x = 0; x < kEdgeIlp; ++x) v[x] = Q[oc + y[x]];
 #pragma unroll
           for (int x = 0; x < kEdgeIlp; ++x) {
             *mx = v[x] > *mx ? v[x] : *mx;
@@ -549,9 +586,13 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
     const bool done = forced ? ell >= stop_forced
                              : (ell >= taup || (need && static_cast<double>(vol) > rhs));
     if (done) {
-      // clear the select keys, record the outcome
-      if (keyed)
-        for (int e = tid; e < cnt; e += kT) Qn[e] = 0;
+      // clear the select keys (or hand the column to the walks), record the outcome
+      if constexpr (kLds) {
+        uint64_t* Qg = a.Q + (2 * static_cast<size_t>(w) + static_cast<size_t>(parity)) * n;
+        for (int e = tid; e < cnt; e += kT) Qg[Sc[e]] = Q[oc + Sc[e]];
+      } else if (keyed) {
+        for (int e = tid; e < cnt; e += kT) Q[on + e] = 0;
+      }
       unsigned long long wk = 0, ws = 0;
       const int64_t pbase = (a.hoff ? a.hoff[li] : static_cast<int64_t>(rb)) - a.pos_base;
       __syncthreads();   // walk counts written by other threads of the workgroup
@@ -583,13 +624,13 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
 
     // ---- (5) push l -> l + 1: r_{l+1}[y] = sum over u in N(y) of Q_l[u]
     if (keyed)
-      for (int e = tid; e < cnt; e += kT) Qn[e] = 0;
+      for (int e = tid; e < cnt; e += kT) Q[on + e] = 0;
     if (tid == 0) s_cnt = 0;
     __syncthreads();
     visit_edges<kT>(
         Sc, cnt, a.rowptr, a.col,
         [&](int u, uint64_t* val) {
-          *val = Qc[u];
+          *val = Q[oc + u];
           return *val != 0;
         },
         [&](const uint64_t(&v)[kEdgeIlp], const int(&y)[kEdgeIlp], const bool(&live)[kEdgeIlp]) {
@@ -598,7 +639,7 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
           for (int q = 0; q < kEdgeIlp; ++q) {
             old[q] = 1;
             if (live[q])
-              old[q] = atomicAdd(reinterpret_cast<unsigned long long*>(&Qn[y[q]]),
+              old[q] = atomicAdd(reinterpret_cast<unsigned long long*>(&Q[on + y[q]]),
                                  static_cast<unsigned long long>(v[q]));
           }
 #pragma unroll
@@ -611,23 +652,40 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
     // ---- (6) Q_{l+1}[y] = r_{l+1}[y] / d_y (rounded to nearest), the support's
     // volume and extremes; (7) clear Q_l
     uint64_t r_vol = 0, r_mx = 0, r_mn = ~0ull;
-    for (int e = tid; e < cntn; e += kT) {
-      const int y = Sn[e];
-      const uint64_t d = static_cast<uint64_t>(a.rowptr[y + 1] - a.rowptr[y]);
-      const uint64_t v = (Qn[y] + d / 2) / d;
-      Qn[y] = v;
-      r_vol += d;
-      r_mx = v > r_mx ? v : r_mx;
-      r_mn = v < r_mn ? v : r_mn;
+    for (int e0 = tid; e0 < cntn; e0 += kT * kEdgeIlp) {
+      int y[kEdgeIlp], d[kEdgeIlp];
+      uint64_t v[kEdgeIlp];
+#pragma unroll
+      for (int q = 0; q < kEdgeIlp; ++q) y[q] = Sn[min(e0 + q * kT, cntn - 1)];
+#pragma unroll
+      for (int q = 0; q < kEdgeIlp; ++q) {
+        d[q] = a.rowptr[y[q] + 1] - a.rowptr[y[q]];
+        v[q] = Q[on + y[q]];
+      }
+#pragma unroll
+      for (int q = 0; q < kEdgeIlp; ++q)
+        if (e0 + q * kT < cntn) {
+          v[q] = div_round(v[q], static_cast<uint32_t>(d[q]));
+          Q[on + y[q]] = v[q];
+          r_vol += static_cast<uint64_t>(d[q]);
+          r_mx = v[q] > r_mx ? v[q] : r_mx;
+          r_mn = v[q] < r_mn ? v[q] : r_mn;
+        }
     }
-    for (int e = tid; e < cnt; e += kT) Qc[Sc[e]] = 0;
+    for (int e0 = tid; e0 < cnt; e0 += kT * kEdgeIlp) {
+      int y[kEdgeIlp];
+#pragma unroll
+      for (int q = 0; q < kEdgeIlp; ++q) y[q] = Sc[min(e0 + q * kT, cnt - 1)];
+#pragma unroll
+      for (int q = 0; q < kEdgeIlp; ++q) Q[oc + y[q]] = 0;
+    }
     __syncthreads();
     // ---- (8) step l + 1 of Eq. 9: g(i, j) += (p(i,i) - p(j,i)) / d_i = (Q[i] - Q[j]) 2^-63,
     // and the extremes over N(i)
-    const double qi = static_cast<double>(Qn[i]);
+    const double qi = static_cast<double>(Q[on + i]);
     uint64_t r_imx = 0, r_imn = ~0ull;
     for (int k = rb + tid; k < re; k += kT) {
-      const uint64_t v = Qn[a.col[k]];
+      const uint64_t v = Q[on + a.col[k]];
       r_imx = v > r_imx ? v : r_imx;
       r_imn = v < r_imn ? v : r_imn;
       if (ell + 1 <= a.tau_slot[k])
@@ -657,9 +715,9 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
       qmn_i = MinU64{}(qmn_i, s_r64[4][x]);
     }
     __syncthreads();
-    uint64_t* tq = Qc;
-    Qc = Qn;
-    Qn = tq;
+    const int to = oc;
+    oc = on;
+    on = to;
     int32_t* ts = Sc;
     Sc = Sn;
     Sn = ts;
@@ -1068,10 +1126,17 @@ hipError_t launch_tau_range(int n, const int32_t* tau_row, unsigned long long* m
 hipError_t launch_src_head(const SrcArgs& a, int grid, hipStream_t st) {
   if (grid <= 0) return hipSuccess;
   // A source's time is that of one workgroup's chain of phases, so it gets as many
-  // threads as leave every source of the launch a place on the chip at once.
-  if (grid <= 512) k_src_head<1024><<<grid, 1024, 0, st>>>(a);
-  else if (grid <= 1024) k_src_head<512><<<grid, 512, 0, st>>>(a);
-  else k_src_head<256><<<grid, 256, 0, st>>>(a);
+  // threads as leave every source of the launch a place on the chip at once.  Up to
+  // kLdsColumns nodes, both columns are kept in LDS.
+  if (a.n <= kLdsColumns) {
+    k_src_head<512, true><<<grid, 512, static_cast<size_t>(a.n) * 16, st>>>(a);
+  } else if (grid <= 512) {
+    k_src_head<1024, false><<<grid, 1024, 0, st>>>(a);
+  } else if (grid <= 1024) {
+    k_src_head<512, false><<<grid, 512, 0, st>>>(a);
+  } else {
+    k_src_head<256, false><<<grid, 256, 0, st>>>(a);
+  }
   return hipGetLastError();
 }
 

@@ -4,8 +4,8 @@
   general walk kernel, for a graph that fits the LDS, one with a prefix of its
   nodes there, and one whose ids need 32 bits: the same walk counts, and sums
   that differ by the rounding of their grouping only (1e-12);
-* the head's workgroup sizes (chosen by the number of sources): the same switch
-  steps and walk counts per source;
+* the head's workgroup sizes (chosen by the number of sources) and places of the
+  columns (by the number of nodes): the same switch steps and walk counts per source;
 * selections with ties and long candidate lists against the oracle.
 """
 import numpy as np
@@ -30,10 +30,11 @@ def test_walks_with_column_in_lds(sc, n, monkeypatch):  # noqa: F811
     np.testing.assert_allclose(out, ref, atol=TOL, rtol=0)
 
 
-def test_head_workgroup_sizes(sc):  # noqa: F811
-    graph = gg.barabasi_albert(1200, 6, 4)
+@pytest.mark.parametrize("n", [1200, 4096, 4097])            # both columns in LDS up to 4,096 nodes
+def test_head_workgroup_sizes(sc, n):  # noqa: F811
+    graph = gg.barabasi_albert(n, 6, 4)
     n, u, v = graph
-    _, _, _, tt, nr = run_ps(sc, graph, 0.02)                # 1,200 sources: 256 threads
+    _, _, _, tt, nr = run_ps(sc, graph, 0.02)                # more than 1,024: 256 threads
     for count in (512, 513, 1024):                           # 1,024, 512 and 512 threads
         src = np.random.default_rng(count).permutation(n)[:count].astype(np.int32)
         _, _, _, tt2, nr2 = run_ps(sc, graph, 0.02, sources=src)
@@ -42,6 +43,14 @@ def test_head_workgroup_sizes(sc):  # noqa: F811
         listed[src] = True
         hl = np.concatenate([listed[u], listed[v]])
         np.testing.assert_array_equal(nr2[hl], nr[hl])
+
+
+@pytest.mark.parametrize("n", [4096, 4097])
+def test_columns_against_oracle(sc, n):  # noqa: F811
+    graph = gg.barabasi_albert(n, 5, 8)
+    src = np.array([0, 1, 17, n // 2, n - 1], np.int32)
+    out, st, tau, tt, nr = run_ps(sc, graph, 0.03, sources=src)
+    check_against_oracle(graph, 0.03, out, st, tau, tt, nr, sources=src)
 
 
 @pytest.mark.parametrize("gamma", [64, 65, 100, 200])
