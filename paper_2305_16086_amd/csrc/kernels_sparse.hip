@@ -104,25 +104,43 @@ __device__ inline uint64_t div_round(uint64_t x, uint32_t d) {
   return q;
 }
 
+// What the phases of a source's workgroup share.
+template <int kT>
+struct SrcLds {
+  int off[kT], beg[kT];
+  uint64_t val[kT];
+  uint64_t r64[5][kT / 64];
+  double rd[kT / 64];
+  unsigned hist[256];
+  int cnt;               // entries of the next support
+  int lng[kLongList];    // list entries or halves left to more lanes
+  int nlong;
+  uint64_t key[64];      // the last keys of the selection
+  int cand[kCandList];
+  int ncand;
+  uint64_t prefix;       // digits chosen so far; the threshold at the end
+  int rank, left;
+};
+
 // Visit every (value, neighbour) pair of the entries [0, cnt) of a node list that
-// pass `keep`.  Each wave takes 64 entries at a time, scans their degrees and
-// spreads the neighbour slots over its lanes without a workgroup barrier; an
-// entry with more than kHubEdges neighbours is left to the whole workgroup.
+// pass `keep` (of `parts` workgroups, workgroup `part` takes its tiles).  Each wave
+// takes 64 entries at a time, scans their degrees and spreads the neighbour slots over
+// its lanes without a workgroup barrier; an entry with more than kHubEdges neighbours
+// is left to the whole workgroup.
 // act(value[], y[], live[]) gets kEdgeIlp pairs of the lane at once, so that
 // their memory operations are in flight together.  Called by the whole
 // workgroup; barriers inside.
 template <int kT, typename Keep, typename Act>
-__device__ inline void visit_edges(const int32_t* __restrict__ list, int cnt,
-                                   const int32_t* __restrict__ rowptr,
-                                   const int32_t* __restrict__ col, Keep keep, Act act, int* s_off,
-                                   int* s_beg, uint64_t* s_val, int* s_long, int* s_nlong) {
+__device__ inline void visit_edges(SrcLds<kT>& s, const int32_t* __restrict__ list, int cnt,
+                                   int part, int parts, const int32_t* __restrict__ rowptr,
+                                   const int32_t* __restrict__ col, Keep keep, Act act) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) *s_nlong = 0;
+  if (tid == 0) s.nlong = 0;
   __syncthreads();
-  int* so = s_off + wave * 64;
-  int* sb = s_beg + wave * 64;
-  uint64_t* sv = s_val + wave * 64;
-  for (int base = wave * 64; base < cnt; base += kT) {
+  int* so = s.off + wave * 64;
+  int* sb = s.beg + wave * 64;
+  uint64_t* sv = s.val + wave * 64;
+  for (int base = part * kT + wave * 64; base < cnt; base += parts * kT) {
     const int e = base + lane;
     int du = 0, beg = 0;
     uint64_t val = 0;
@@ -132,9 +150,9 @@ __device__ inline void visit_edges(const int32_t* __restrict__ list, int cnt,
         beg = rowptr[u];
         du = rowptr[u + 1] - beg;
         if (du > kHubEdges) {
-          const int slot = atomicAdd(s_nlong, 1);
+          const int slot = atomicAdd(&s.nlong, 1);
           if (slot < kLongList) {
-            s_long[slot] = u;
+            s.lng[slot] = u;
             du = 0;
           }
         }
@@ -161,8 +179,8 @@ __device__ inline void visit_edges(const int32_t* __restrict__ list, int cnt,
         live[q] = xx < total;
         int lo = 0;   // last entry with so[] <= xx (entries without slots share offsets)
 #pragma unroll
-        for (int s = 32; s >= 1; s >>= 1)
-          if (so[lo + s] <= xx) lo += s;
+        for (int h = 32; h >= 1; h >>= 1)
+          if (so[lo + h] <= xx) lo += h;
         v[q] = sv[lo];
         y[q] = live[q] ? col[sb[lo] + xx] : 0;
       }
@@ -171,9 +189,9 @@ __device__ inline void visit_edges(const int32_t* __restrict__ list, int cnt,
     wave_fence();
   }
   __syncthreads();
-  const int nlong = min(*s_nlong, kLongList);
+  const int nlong = min(s.nlong, kLongList);
   for (int t = 0; t < nlong; ++t) {
-    const int u = s_long[t];
+    const int u = s.lng[t];
     const int b = rowptr[u], total = rowptr[u + 1] - b;
     uint64_t val = 0;
     keep(u, &val);
@@ -206,6 +224,351 @@ __device__ inline bool adjacent(const int32_t* __restrict__ col, int b, int e, i
   return false;
 }
 
+// Threshold T = the gamma-th largest q (Algorithm 3 line 2); 0 when the
+// support has fewer than gamma nodes (the candidate list then holds zeros).
+// Digits of up to 8 bits from the highest set one down: a histogram of the
+// keys that share the digits chosen so far, until at most 64 keys are left,
+// which one wave ranks against each other.
+// kKeys: the keys are kept in the column at l + 1 (all zero before), *keyed tells so.
+template <int kT, bool kKeys>
+__device__ inline uint64_t threshold(SrcLds<kT>& s, const SrcArgs& a, uint64_t* Q, int oc, int on,
+                                     const int32_t* Sc, int cnt, uint64_t qmx, uint64_t qmn,
+                                     bool* keyed_out) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = a.n;
+  bool keyed = false;
+  uint64_t T = 0;
+  if (a.gamma > 0 && cnt < a.gamma && cnt == n) T = qmn;   // every node is a candidate
+  if (a.gamma > 0 && cnt >= a.gamma) {
+    int pos = 64 - __clzll(static_cast<long long>(qmx | 1ull));   // bits below pos undecided
+    uint64_t prefix = 0;
+    if (tid == 0) {
+      s.rank = a.gamma;
+      s.left = cnt;
+    }
+    __syncthreads();
+    int left = cnt;
+    while (left > 64 && pos > 0) {
+      const int width = pos < 8 ? pos : 8;
+      const int shift = pos - width;
+      for (int d = tid; d < 256; d += kT) s.hist[d] = 0;
+      __syncthreads();
+      if (!keyed) {
+        for (int e0 = tid; e0 < cnt; e0 += kT * kEdgeIlp) {
+          uint64_t v[kEdgeIlp];
+          int y[kEdgeIlp];
+#pragma unroll
+          for (int q = 0; q < kEdgeIlp; ++q) y[q] = Sc[min(e0 + q * kT, cnt - 1)];
+#pragma unroll
+          for (int q = 0; q < kEdgeIlp; ++q) v[q] = Q[oc + y[q]];
+#pragma unroll
+          for (int q = 0; q < kEdgeIlp; ++q)
+            if (e0 + q * kT < cnt) {
+              if (kKeys) Q[on + e0 + q * kT] = v[q];   // the column at l + 1 is all zero here
+              if (pos == 64 || (v[q] >> pos) == (prefix >> pos))
+                atomicAdd(&s.hist[(v[q] >> shift) & ((1u << width) - 1u)], 1u);
+            }
+        }
+        keyed = kKeys;
+      } else {
+        for (int e = tid; e < cnt; e += kT) {
+          const uint64_t v = Q[on + e];
+          if ((v >> pos) == (prefix >> pos))
+            atomicAdd(&s.hist[(v >> shift) & ((1u << width) - 1u)], 1u);
+        }
+      }
+      __syncthreads();
+      if (wave == 0) {   // lane's buckets 255 - 4 lane .. 252 - 4 lane, from the top
+        unsigned c[4], sum = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          c[q] = s.hist[255 - 4 * lane - q];
+          sum += c[q];
+        }
+        unsigned x = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          const unsigned y = __shfl_up(x, off, 64);
+          if (lane >= off) x += y;
+        }
+        const unsigned k = static_cast<unsigned>(s.rank);
+        unsigned above = x - sum;
+        if (above < k && k <= x) {   // one lane
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if (above < k && k <= above + c[q]) {
+              s.prefix = prefix | (static_cast<uint64_t>(255 - 4 * lane - q) << shift);
+              s.rank = static_cast<int>(k - above);
+              s.left = static_cast<int>(c[q]);
+            }
+            above += c[q];
+          }
+        }
+      }
+      __syncthreads();
+      prefix = s.prefix;
+      left = s.left;
+      pos = shift;
+    }
+    if (pos == 0) {
+      T = prefix;   // every bit is decided
+    } else {
+      if (tid == 0) s.ncand = 0;
+      __syncthreads();
+      for (int e = tid; e < cnt; e += kT) {
+        const uint64_t v = keyed ? Q[on + e] : Q[oc + Sc[e]];
+        if (pos == 64 || (v >> pos) == (prefix >> pos)) s.key[atomicAdd(&s.ncand, 1)] = v;
+      }
+      __syncthreads();
+      if (wave == 0) {
+        const uint64_t v = lane < left ? s.key[lane] : 0;
+        int gt = 0, eq = 0;
+        for (int q = 0; q < left; ++q) {
+          const uint64_t x = s.key[q];
+          gt += x > v ? 1 : 0;
+          eq += x == v ? 1 : 0;
+        }
+        if (lane < left && gt < s.rank && s.rank <= gt + eq) s.prefix = v;   // equal values
+      }
+      __syncthreads();
+      T = s.prefix;
+    }
+  }
+  *keyed_out = keyed;
+  return T;
+}
+
+// rho-hat (Eq. 16 bound, Algorithm 3 lines 3-5, safe reading): the best
+// candidate-pair edge against q[c_1] + q[c_gamma].  Few candidates (ties may
+// add more): every pair of them is looked up in the shorter of its two sorted
+// lists; else every edge of a candidate is visited.
+template <int kT>
+__device__ inline double rho_hat(SrcLds<kT>& s, const SrcArgs& a, const uint64_t* Q, int oc, int on,
+                                 const int32_t* Sc, int cnt, uint64_t T, double maxV, bool keyed) {
+  const int tid = threadIdx.x;
+  const uint64_t thr = T > 0 ? T : 1;
+  unsigned long long best = 0;
+  if (tid == 0) s.ncand = 0;
+  __syncthreads();
+  for (int e = tid; e < cnt; e += kT) {
+    const int y = Sc[e];
+    const uint64_t v = keyed ? Q[on + e] : Q[oc + y];
+    if (v >= thr) {
+      const int slot = atomicAdd(&s.ncand, 1);
+      if (slot < kCandList) s.cand[slot] = y;
+    }
+  }
+  __syncthreads();
+  const int nc = s.ncand;
+  if (nc <= kCandList) {
+    for (int pq = tid; pq < nc * nc; pq += kT) {
+      const int p = pq / nc, q = pq % nc;
+      if (p >= q) continue;
+      int c1 = s.cand[p], c2 = s.cand[q];
+      int b1 = a.rowptr[c1], e1 = a.rowptr[c1 + 1];
+      const int b2 = a.rowptr[c2], e2 = a.rowptr[c2 + 1];
+      const unsigned long long pair = Q[oc + c1] + Q[oc + c2];
+      if (e2 - b2 < e1 - b1) {
+        b1 = b2;
+        e1 = e2;
+        c2 = c1;
+      }
+      if (pair > best && adjacent(a.col, b1, e1, c2)) best = pair;
+    }
+  } else {
+    visit_edges<kT>(
+        s, Sc, cnt, 0, 1, a.rowptr, a.col,
+        [&](int u, uint64_t* val) {
+          *val = Q[oc + u];
+          return *val >= thr;
+        },
+        [&](const uint64_t(&v)[kEdgeIlp], const int(&y)[kEdgeIlp], const bool(&live)[kEdgeIlp]) {
+#pragma unroll
+          for (int q = 0; q < kEdgeIlp; ++q) {
+            const uint64_t qy = live[q] ? Q[oc + y[q]] : 0;
+            if (qy >= thr) best = v[q] + qy > best ? v[q] + qy : best;
+          }
+        });
+  }
+  best = block_reduce<kT>(static_cast<uint64_t>(best), s.r64[0], MaxU64{});
+  return fmax(static_cast<double>(best), maxV + static_cast<double>(T));
+}
+
+// Per half (i, j) of row [rb, re): extremes over N(j), chi (Eq. 17 / Eq. 15), n_r (Eq.
+// 13).  Returns the thread's share of Eq. 14's right side; of `parts` workgroups, this
+// one takes the halves of part_wg.
+template <int kT>
+__device__ inline double scan_halves(SrcLds<kT>& s, const SrcArgs& a, const uint64_t* Q, int oc,
+                                     const int32_t* Sc, int cnt, int rb, int re, int ell,
+                                     int part_wg, int parts, double maxV, double minV, double maxNi,
+                                     double minNi, double rhoQ) {
+  constexpr int kTW = kT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double part = 0.0;
+  auto count_walks = [&](int k, int len, double jmx, double jmn) {
+    double chiQ;
+    if (a.gamma > 0) {
+      const double lb_i = minNi + (len - 1) * minV;
+      const double ub_i = maxNi * 0.5 + maxV * 0.5 + (len - 1) * rhoQ * 0.5;
+      const double lb_j = jmn + (len - 1) * minV;
+      const double ub_j = jmx * 0.5 + maxV * 0.5 + (len - 1) * rhoQ * 0.5;
+      chiQ = ub_i + ub_j - lb_i - lb_j;
+    } else {
+      chiQ = 2.0 * len * (maxV - minV);
+    }
+    // q = d_i Q 2^-63 and Eq. 13 divides chi^2 by d_i^2: d_i cancels
+    const double chi = chiQ * kInvUnit;
+    double r = ceil(a.coef * chi * chi);
+    if (!(r >= 1.0)) r = 1.0;
+    const long long nr = r > static_cast<double>(a.nr_cap) ? a.nr_cap : static_cast<long long>(r);
+    a.nr_slot[k] = nr;
+    part += a.rule == 0 ? static_cast<double>(nr) : 2.0 * len * static_cast<double>(nr);
+  };
+  // a short support against a long N(j): visit the support and test adjacency
+  // to j instead
+  auto by_support = [&](int dj) { return static_cast<int64_t>(cnt) * 16 < dj; };
+  // extremes over N(j) seen by lane `ln` of `st` lanes, and the support nodes
+  // found in it (by_support only); q is zero off the support
+  auto scan_row = [&](int jb, int je, int j, int ln, int st, uint64_t* mx, uint64_t* mn,
+                      int* hits) {
+    *mx = 0;
+    *mn = ~0ull;
+    *hits = 0;
+    if (by_support(je - jb)) {
+      for (int e = ln; e < cnt; e += st) {
+        const int y = Sc[e];
+        const int yb = a.rowptr[y], ye = a.rowptr[y + 1];
+        const bool in_j = ye - yb < je - jb ? adjacent(a.col, yb, ye, j)
+                                            : adjacent(a.col, jb, je, y);
+        if (in_j) {
+          const uint64_t v = Q[oc + y];
+          *mx = v > *mx ? v : *mx;
+          *mn = v < *mn ? v : *mn;
+          ++*hits;
+        }
+      }
+      return;
+    }
+    for (int q = jb + ln; q < je; q += st * kEdgeIlp) {
+      int y[kEdgeIlp];
+      uint64_t v[kEdgeIlp];
+#pragma unroll
+      for (int x = 0; x < kEdgeIlp; ++x) y[x] = a.col[min(q + x * st, je - 1)];   // repeats the last
+#pragma unroll
+      for (int x = 0; x < kEdgeIlp; ++x) v[x] = Q[oc + y[x]];
+#pragma unroll
+      for (int x = 0; x < kEdgeIlp; ++x) {
+        *mx = v[x] > *mx ? v[x] : *mx;
+        *mn = v[x] < *mn ? v[x] : *mn;
+      }
+    }
+  };
+  auto row_min = [&](uint64_t mn, int hits, int dj) {
+    // by support: the minimum is 0 unless the support fills N(j)
+    return by_support(dj) && hits < dj ? 0.0 : static_cast<double>(mn);
+  };
+  if (tid == 0) s.nlong = 0;
+  __syncthreads();
+  const int sub = tid & 15;
+  for (int k = rb + (part_wg * kT + tid) / 16; k < re; k += parts * kT / 16) {
+    // 16 lanes per half; longer lists go to the list below while it has room
+    const int len = a.tau_slot[k] - ell;
+    if (len <= 0) {
+      if (sub == 0) a.nr_slot[k] = 0;
+    } else if (a.gamma <= 0) {
+      if (sub == 0) count_walks(k, len, 0.0, 0.0);
+    } else {
+      const int j = a.col[k];
+      const int jb = a.rowptr[j], je = a.rowptr[j + 1];
+      bool later = false;
+      if (je - jb > kShortRow) {
+        int slot = 0;
+        if (sub == 0) slot = atomicAdd(&s.nlong, 1);
+        slot = __shfl(slot, lane & 48, 64);
+        later = slot < kLongList;
+        if (later && sub == 0) s.lng[slot] = k;
+      }
+      if (!later) {
+        uint64_t mx, mn;
+        int hits;
+        scan_row(jb, je, j, sub, 16, &mx, &mn, &hits);
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) {
+          mx = MaxU64{}(mx, __shfl_xor(mx, off, 64));
+          mn = MinU64{}(mn, __shfl_xor(mn, off, 64));
+          hits += __shfl_xor(hits, off, 64);
+        }
+        if (sub == 0) count_walks(k, len, static_cast<double>(mx), row_min(mn, hits, je - jb));
+      }
+    }
+  }
+  __syncthreads();
+  const int nlong = s.nlong < kLongList ? s.nlong : kLongList;
+  for (int t = wave; t < nlong; t += kTW) {   // a wave per list
+    const int k = s.lng[t];
+    const int j = a.col[k];
+    const int jb = a.rowptr[j], je = a.rowptr[j + 1];
+    if (je - jb > kLongRow && !by_support(je - jb)) continue;
+    uint64_t mx, mn;
+    int hits;
+    scan_row(jb, je, j, lane, 64, &mx, &mn, &hits);
+    mx = wave_reduce(mx, MaxU64{});
+    mn = wave_reduce(mn, MinU64{});
+    hits = wave_reduce(hits, [](int x, int y) { return x + y; });
+    if (lane == 0)
+      count_walks(k, a.tau_slot[k] - ell, static_cast<double>(mx), row_min(mn, hits, je - jb));
+  }
+  for (int t = 0; t < nlong; ++t) {   // hubs' lists, all threads at once
+    const int k = s.lng[t];
+    const int j = a.col[k];
+    const int jb = a.rowptr[j], je = a.rowptr[j + 1];
+    if (je - jb <= kLongRow || by_support(je - jb)) continue;
+    uint64_t mx, mn;
+    int hits;
+    scan_row(jb, je, j, tid, kT, &mx, &mn, &hits);
+    mx = block_reduce<kT>(mx, s.r64[0], MaxU64{});
+    mn = block_reduce<kT>(mn, s.r64[1], MinU64{});
+    if (tid == 0)
+      count_walks(k, a.tau_slot[k] - ell, static_cast<double>(mx), static_cast<double>(mn));
+  }
+  return part;
+}
+
+// The outcome of the source in list entry li at its switch step: positions, walk counts
+// and totals for the walks.
+template <int kT>
+__device__ inline void finish_source(SrcLds<kT>& s, const SrcArgs& a, int64_t li, int i, int w, int ell,
+                                     int cnt, int parity, uint64_t pushed) {
+  const int tid = threadIdx.x;
+  const int rb = a.rowptr[i], re = a.rowptr[i + 1];
+  unsigned long long wk = 0, ws = 0;
+  const int64_t pbase = (a.hoff ? a.hoff[li] : static_cast<int64_t>(rb)) - a.pos_base;
+  __syncthreads();   // walk counts written by other threads of the workgroup
+  for (int k = rb + tid; k < re; k += kT) {
+    const int len = a.tau_slot[k] - ell;
+    const long long nr = len > 0 ? a.nr_slot[k] : 0;
+    if (len <= 0) a.nr_slot[k] = 0;
+    const int64_t p = pbase + (k - rb);
+    a.pos_slot[p] = k;
+    a.pos_w[p] = w;
+    a.nr_pos[p] = nr;
+    wk += static_cast<unsigned long long>(nr);
+    ws += static_cast<unsigned long long>(nr) * 2ull * static_cast<unsigned long long>(len > 0 ? len : 0);
+  }
+  wk = block_reduce<kT>(static_cast<uint64_t>(wk), s.r64[0], AddU64{});
+  ws = block_reduce<kT>(static_cast<uint64_t>(ws), s.r64[1], AddU64{});
+  if (tid == 0) {
+    a.tilde_row[i] = ell;
+    a.slot_ctl[2 * w] = cnt;
+    a.slot_ctl[2 * w + 1] = parity;
+    atomicAdd(&a.totals[0], wk);
+    atomicAdd(&a.totals[1], ws);
+    atomicAdd(&a.totals[2], static_cast<unsigned long long>(pushed));
+    atomicMin(&a.totals[3], static_cast<unsigned long long>(ell));
+    atomicMax(&a.totals[4], static_cast<unsigned long long>(ell));
+  }
+}
+
 // One source per workgroup of kT threads.  A step is a chain of dependent
 // accesses (list, degree, neighbour, column word) with a barrier between its
 // phases, so it is bound by how many of them one workgroup has in flight: the
@@ -215,21 +578,7 @@ __device__ inline bool adjacent(const int32_t* __restrict__ col, int b, int e, i
 template <int kT, bool kLds>
 __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
   extern __shared__ uint64_t s_col[];   // kLds: [2 n], both columns
-  constexpr int kTW = kT / 64;
-  __shared__ int s_off[kT], s_beg[kT];
-  __shared__ uint64_t s_val[kT];
-  __shared__ uint64_t s_r64[5][kTW];
-  __shared__ double s_rd[kTW];
-  __shared__ unsigned s_hist[256];
-  __shared__ int s_cnt;
-  __shared__ int s_long[kLongList];   // list positions or halves left to more lanes
-  __shared__ int s_nlong;
-  __shared__ uint64_t s_key[64];   // the last keys of the selection
-  __shared__ int s_cand[kCandList];
-  __shared__ int s_ncand;
-  __shared__ uint64_t s_prefix;   // digits chosen so far; the threshold at the end
-  __shared__ int s_rank, s_left;
-
+  __shared__ SrcLds<kT> s;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int w = blockIdx.x;
@@ -298,289 +647,11 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
     double rhoQ = 0.0;
     const double maxNi = static_cast<double>(qmx_i), minNi = static_cast<double>(qmn_i);
     if (need) {
-      // (1) threshold T = the gamma-th largest q (Algorithm 3 line 2); 0 when the
-      // support has fewer than gamma nodes (the candidate list then holds zeros).
-      // Digits of up to 8 bits from the highest set one down: a histogram of the
-      // keys that share the digits chosen so far, until at most 64 keys are left,
-      // which one wave ranks against each other.
-      uint64_t T = 0;
-      if (a.gamma > 0 && cnt < a.gamma && cnt == n) T = qmn;   // every node is a candidate
-      if (a.gamma > 0 && cnt >= a.gamma) {
-        int pos = 64 - __clzll(static_cast<long long>(qmx | 1ull));   // bits below pos undecided
-        uint64_t prefix = 0;
-        if (tid == 0) {
-          s_rank = a.gamma;
-          s_left = cnt;
-        }
-        __syncthreads();
-        int left = cnt;
-        while (left > 64 && pos > 0) {
-          const int width = pos < 8 ? pos : 8;
-          const int shift = pos - width;
-          for (int d = tid; d < 256; d += kT) s_hist[d] = 0;
-          __syncthreads();
-          if (!keyed) {
-            for (int e0 = tid; e0 < cnt; e0 += kT * kEdgeIlp) {
-              uint64_t v[kEdgeIlp];
-              int y[kEdgeIlp];
-#pragma unroll
-              for (int q = 0; q < kEdgeIlp; ++q) y[q] = Sc[min(e0 + q * kT, cnt - 1)];
-#pragma unroll
-              for (int q = 0; q < kEdgeIlp; ++q) v[q] = Q[oc + y[q]];
-#pragma unroll
-              for (int q = 0; q < kEdgeIlp; ++q)
-                if (e0 + q * kT < cnt) {
-                  Q[on + e0 + q * kT] = v[q];   // Qn is all zero here
-                  atomicAdd(&s_hist[v[q] >> shift], 1u);   // no digit is chosen yet
-                }
-            }
-            keyed = true;
-          } else {
-            for (int e = tid; e < cnt; e += kT) {
-              const uint64_t v = Q[on + e];
-              if ((v >> pos) == (prefix >> pos))
-                atomicAdd(&s_hist[(v >> shift) & ((1u << width) - 1u)], 1u);
-            }
-          }
-          __syncthreads();
-          if (wave == 0) {   // lane's buckets 255 - 4 lane .. 252 - 4 lane, from the top
-            unsigned c[4], sum = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              c[q] = s_hist[255 - 4 * lane - q];
-              sum += c[q];
-            }
-            unsigned x = sum;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-              const unsigned y = __shfl_up(x, off, 64);
-              if (lane >= off) x += y;
-            }
-            const unsigned k = static_cast<unsigned>(s_rank);
-            unsigned above = x - sum;
-            if (above < k && k <= x) {   // one lane
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                if (above < k && k <= above + c[q]) {
-                  s_prefix = prefix | (static_cast<uint64_t>(255 - 4 * lane - q) << shift);
-                  s_rank = static_cast<int>(k - above);
-                  s_left = static_cast<int>(c[q]);
-                }
-                above += c[q];
-              }
-            }
-          }
-          __syncthreads();
-          prefix = s_prefix;
-          left = s_left;
-          pos = shift;
-        }
-        if (pos == 0) {
-          T = prefix;   // every bit is decided
-        } else {
-          if (tid == 0) s_ncand = 0;
-          __syncthreads();
-          for (int e = tid; e < cnt; e += kT) {
-            const uint64_t v = keyed ? Q[on + e] : Q[oc + Sc[e]];
-            if (pos == 64 || (v >> pos) == (prefix >> pos)) s_key[atomicAdd(&s_ncand, 1)] = v;
-          }
-          __syncthreads();
-          if (wave == 0) {
-            const uint64_t v = lane < left ? s_key[lane] : 0;
-            int gt = 0, eq = 0;
-            for (int q = 0; q < left; ++q) {
-              const uint64_t x = s_key[q];
-              gt += x > v ? 1 : 0;
-              eq += x == v ? 1 : 0;
-            }
-            if (lane < left && gt < s_rank && s_rank <= gt + eq) s_prefix = v;   // equal values
-          }
-          __syncthreads();
-          T = s_prefix;
-        }
-      }
-      // (2) rho-hat (Eq. 16 bound, Algorithm 3 lines 3-5, safe reading): the best
-      // candidate-pair edge against q[c_1] + q[c_gamma].  Few candidates (ties may
-      // add more): every pair of them is looked up in the shorter of its two sorted
-      // lists; else every edge of a candidate is visited.
-      if (a.gamma > 0) {
-        const uint64_t thr = T > 0 ? T : 1;
-        unsigned long long best = 0;
-        if (tid == 0) s_ncand = 0;
-        __syncthreads();
-        for (int e = tid; e < cnt; e += kT) {
-          const int y = Sc[e];
-          const uint64_t v = keyed ? Q[on + e] : Q[oc + y];
-          if (v >= thr) {
-            const int slot = atomicAdd(&s_ncand, 1);
-            if (slot < kCandList) s_cand[slot] = y;
-          }
-        }
-        __syncthreads();
-        const int nc = s_ncand;
-        if (nc <= kCandList) {
-          for (int pq = tid; pq < nc * nc; pq += kT) {
-            const int p = pq / nc, q = pq % nc;
-            if (p >= q) continue;
-            int c1 = s_cand[p], c2 = s_cand[q];
-            int b1 = a.rowptr[c1], e1 = a.rowptr[c1 + 1];
-            const int b2 = a.rowptr[c2], e2 = a.rowptr[c2 + 1];
-            const unsigned long long s = Q[oc + c1] + Q[oc + c2];
-            if (e2 - b2 < e1 - b1) {
-              b1 = b2;
-              e1 = e2;
-              c2 = c1;
-            }
-            if (s > best && adjacent(a.col, b1, e1, c2)) best = s;
-          }
-        } else {
-          visit_edges<kT>(
-              Sc, cnt, a.rowptr, a.col,
-              [&](int u, uint64_t* val) {
-                *val = Q[oc + u];
-                return *val >= thr;
-              },
-              [&](const uint64_t(&v)[kEdgeIlp], const int(&y)[kEdgeIlp], const bool(&live)[kEdgeIlp]) {
-#pragma unroll
-                for (int q = 0; q < kEdgeIlp; ++q) {
-                  const uint64_t qy = live[q] ? Q[oc + y[q]] : 0;
-                  if (qy >= thr) best = v[q] + qy > best ? v[q] + qy : best;
-                }
-              },
-              s_off, s_beg, s_val, s_long, &s_nlong);
-        }
-        best = block_reduce<kT>(static_cast<uint64_t>(best), s_r64[0], MaxU64{});
-        rhoQ = fmax(static_cast<double>(best), maxV + static_cast<double>(T));
-      }
-      // (3) per half (i, j): extremes over N(j), chi (Eq. 17 / Eq. 15), n_r (Eq. 13)
-      double part = 0.0;
-      auto count_walks = [&](int k, int len, double jmx, double jmn) {
-        double chiQ;
-        if (a.gamma > 0) {
-          const double lb_i = minNi + (len - 1) * minV;
-          const double ub_i = maxNi * 0.5 + maxV * 0.5 + (len - 1) * rhoQ * 0.5;
-          const double lb_j = jmn + (len - 1) * minV;
-          const double ub_j = jmx * 0.5 + maxV * 0.5 + (len - 1) * rhoQ * 0.5;
-          chiQ = ub_i + ub_j - lb_i - lb_j;
-        } else {
-          chiQ = 2.0 * len * (maxV - minV);
-        }
-        // q = d_i Q 2^-63 and Eq. 13 divides chi^2 by d_i^2: d_i cancels
-        const double chi = chiQ * kInvUnit;
-        double r = ceil(a.coef * chi * chi);
-        if (!(r >= 1.0)) r = 1.0;
-        const long long nr = r > static_cast<double>(a.nr_cap) ? a.nr_cap : static_cast<long long>(r);
-        a.nr_slot[k] = nr;
-        part += a.rule == 0 ? static_cast<double>(nr) : 2.0 * len * static_cast<double>(nr);
-      };
-      // a short support against a long N(j): visit the support and test adjacency
-      // to j instead
-      auto by_support = [&](int dj) { return static_cast<int64_t>(cnt) * 16 < dj; };
-      // extremes over N(j) seen by lane `ln` of `st` lanes, and the support nodes
-      // found in it (by_support only); q is zero off the support
-      auto scan_row = [&](int jb, int je, int j, int ln, int st, uint64_t* mx, uint64_t* mn,
-                          int* hits) {
-        *mx = 0;
-        *mn = ~0ull;
-        *hits = 0;
-        if (by_support(je - jb)) {
-          for (int e = ln; e < cnt; e += st) {
-            const int y = Sc[e];
-            const int yb = a.rowptr[y], ye = a.rowptr[y + 1];
-            const bool in_j = ye - yb < je - jb ? adjacent(a.col, yb, ye, j)
-                                                : adjacent(a.col, jb, je, y);
-            if (in_j) {
-              const uint64_t v = Q[oc + y];
-              *mx = v > *mx ? v : *mx;
-              *mn = v < *mn ? v : *mn;
-              ++*hits;
-            }
-          }
-          return;
-        }
-        for (int q = jb + ln; q < je; q += st * kEdgeIlp) {
-          int y[kEdgeIlp];
-          uint64_t v[kEdgeIlp];
-#pragma unroll
-          for (int x = 0; x < kEdgeIlp; ++x) y[x] = a.col[min(q + x * st, je - 1)];   // repeats the last
-#pragma unroll
-          for (int x = 0; x < kEdgeIlp; ++x) v[x] = Q[oc + y[x]];
-#pragma unroll
-          for (int x = 0; x < kEdgeIlp; ++x) {
-            *mx = v[x] > *mx ? v[x] : *mx;
-            *mn = v[x] < *mn ? v[x] : *mn;
-          }
-        }
-      };
-      auto row_min = [&](uint64_t mn, int hits, int dj) {
-        // by support: the minimum is 0 unless the support fills N(j)
-        return by_support(dj) && hits < dj ? 0.0 : static_cast<double>(mn);
-      };
-      if (tid == 0) s_nlong = 0;
-      __syncthreads();
-      const int sub = tid & 15;
-      for (int k = rb + tid / 16; k < re; k += kT / 16) {
-        // 16 lanes per half; longer lists go to the list below while it has room
-        const int len = a.tau_slot[k] - ell;
-        if (len <= 0) {
-          if (sub == 0) a.nr_slot[k] = 0;
-        } else if (a.gamma <= 0) {
-          if (sub == 0) count_walks(k, len, 0.0, 0.0);
-        } else {
-          const int j = a.col[k];
-          const int jb = a.rowptr[j], je = a.rowptr[j + 1];
-          bool later = false;
-          if (je - jb > kShortRow) {
-            int slot = 0;
-            if (sub == 0) slot = atomicAdd(&s_nlong, 1);
-            slot = __shfl(slot, lane & 48, 64);
-            later = slot < kLongList;
-            if (later && sub == 0) s_long[slot] = k;
-          }
-          if (!later) {
-            uint64_t mx, mn;
-            int hits;
-            scan_row(jb, je, j, sub, 16, &mx, &mn, &hits);
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) {
-              mx = MaxU64{}(mx, __shfl_xor(mx, off, 64));
-              mn = MinU64{}(mn, __shfl_xor(mn, off, 64));
-              hits += __shfl_xor(hits, off, 64);
-            }
-            if (sub == 0) count_walks(k, len, static_cast<double>(mx), row_min(mn, hits, je - jb));
-          }
-        }
-      }
-      __syncthreads();
-      const int nlong = s_nlong < kLongList ? s_nlong : kLongList;
-      for (int t = wave; t < nlong; t += kTW) {   // a wave per list
-        const int k = s_long[t];
-        const int j = a.col[k];
-        const int jb = a.rowptr[j], je = a.rowptr[j + 1];
-        if (je - jb > kLongRow && !by_support(je - jb)) continue;
-        uint64_t mx, mn;
-        int hits;
-        scan_row(jb, je, j, lane, 64, &mx, &mn, &hits);
-        mx = wave_reduce(mx, MaxU64{});
-        mn = wave_reduce(mn, MinU64{});
-        hits = wave_reduce(hits, [](int x, int y) { return x + y; });
-        if (lane == 0)
-          count_walks(k, a.tau_slot[k] - ell, static_cast<double>(mx), row_min(mn, hits, je - jb));
-      }
-      for (int t = 0; t < nlong; ++t) {   // hubs' lists, all threads at once
-        const int k = s_long[t];
-        const int j = a.col[k];
-        const int jb = a.rowptr[j], je = a.rowptr[j + 1];
-        if (je - jb <= kLongRow || by_support(je - jb)) continue;
-        uint64_t mx, mn;
-        int hits;
-        scan_row(jb, je, j, tid, kT, &mx, &mn, &hits);
-        mx = block_reduce<kT>(mx, s_r64[0], MaxU64{});
-        mn = block_reduce<kT>(mn, s_r64[1], MinU64{});
-        if (tid == 0)
-          count_walks(k, a.tau_slot[k] - ell, static_cast<double>(mx), static_cast<double>(mn));
-      }
-      rhs = block_reduce<kT>(part, s_rd, AddD{});
+      const uint64_t T = threshold<kT, true>(s, a, Q, oc, on, Sc, cnt, qmx, qmn, &keyed);
+      if (a.gamma > 0) rhoQ = rho_hat<kT>(s, a, Q, oc, on, Sc, cnt, T, maxV, keyed);
+      const double part = scan_halves<kT>(s, a, Q, oc, Sc, cnt, rb, re, ell, 0, 1, maxV, minV, maxNi,
+                                          minNi, rhoQ);
+      rhs = block_reduce<kT>(part, s.rd, AddD{});
     }
     // ---- (4) Eq. 14: switch when the next push costs more than the walks
     const bool done = forced ? ell >= stop_forced
@@ -593,42 +664,37 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
       } else if (keyed) {
         for (int e = tid; e < cnt; e += kT) Q[on + e] = 0;
       }
-      unsigned long long wk = 0, ws = 0;
-      const int64_t pbase = (a.hoff ? a.hoff[li] : static_cast<int64_t>(rb)) - a.pos_base;
-      __syncthreads();   // walk counts written by other threads of the workgroup
-      for (int k = rb + tid; k < re; k += kT) {
-        const int len = a.tau_slot[k] - ell;
-        const long long nr = len > 0 ? a.nr_slot[k] : 0;
-        if (len <= 0) a.nr_slot[k] = 0;
-        const int64_t p = pbase + (k - rb);
-        a.pos_slot[p] = k;
-        a.pos_w[p] = w;
-        a.nr_pos[p] = nr;
-        wk += static_cast<unsigned long long>(nr);
-        ws += static_cast<unsigned long long>(nr) * 2ull * static_cast<unsigned long long>(len > 0 ? len : 0);
-      }
-      wk = block_reduce<kT>(static_cast<uint64_t>(wk), s_r64[0], AddU64{});
-      ws = block_reduce<kT>(static_cast<uint64_t>(ws), s_r64[1], AddU64{});
-      if (tid == 0) {
-        a.tilde_row[i] = ell;
-        a.slot_ctl[2 * w] = cnt;
-        a.slot_ctl[2 * w + 1] = parity;
-        atomicAdd(&a.totals[0], wk);
-        atomicAdd(&a.totals[1], ws);
-        atomicAdd(&a.totals[2], static_cast<unsigned long long>(pushed));
-        atomicMin(&a.totals[3], static_cast<unsigned long long>(ell));
-        atomicMax(&a.totals[4], static_cast<unsigned long long>(ell));
-      }
+      finish_source<kT>(s, a, li, i, w, ell, cnt, parity, pushed);
       return;
     }
 
     // ---- (5) push l -> l + 1: r_{l+1}[y] = sum over u in N(y) of Q_l[u]
     if (keyed)
       for (int e = tid; e < cnt; e += kT) Q[on + e] = 0;
-    if (tid == 0) s_cnt = 0;
+    if (!kLds && a.heavy && !forced && vol > a.heavy_vol) {
+      // left to the heavy kernels, which begin with this push
+      if (tid == 0) {
+        SrcHeavy h;
+        h.li = li;
+        h.row = i;
+        h.slot = w;
+        h.ell = ell;
+        h.cnt = cnt;
+        h.parity = parity;
+        h.pushed = pushed;
+        h.vol = vol;
+        h.qmx = qmx;
+        h.qmn = qmn;
+        h.rhs = DBL_MAX;
+        a.heavy[atomicAdd(&a.heavy_ctl[0], 1)] = h;
+        atomicAdd(&a.heavy_ctl[1], 1);
+      }
+      return;
+    }
+    if (tid == 0) s.cnt = 0;
     __syncthreads();
     visit_edges<kT>(
-        Sc, cnt, a.rowptr, a.col,
+        s, Sc, cnt, 0, 1, a.rowptr, a.col,
         [&](int u, uint64_t* val) {
           *val = Q[oc + u];
           return *val != 0;
@@ -638,17 +704,17 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
 #pragma unroll
           for (int q = 0; q < kEdgeIlp; ++q) {
             old[q] = 1;
-            if (live[q])
-              old[q] = atomicAdd(reinterpret_cast<unsigned long long*>(&Q[on + y[q]]),
-                                 static_cast<unsigned long long>(v[q]));
+            if (live[q])   // only this workgroup touches the slot
+              old[q] = __hip_atomic_fetch_add(reinterpret_cast<unsigned long long*>(&Q[on + y[q]]),
+                                              static_cast<unsigned long long>(v[q]),
+                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           }
 #pragma unroll
           for (int q = 0; q < kEdgeIlp; ++q)
-            if (old[q] == 0) Sn[atomicAdd(&s_cnt, 1)] = y[q];
-        },
-        s_off, s_beg, s_val, s_long, &s_nlong);
+            if (old[q] == 0) Sn[atomicAdd(&s.cnt, 1)] = y[q];
+        });
     pushed += vol;
-    const int cntn = s_cnt;
+    const int cntn = s.cnt;
     // ---- (6) Q_{l+1}[y] = r_{l+1}[y] / d_y (rounded to nearest), the support's
     // volume and extremes; (7) clear Q_l
     uint64_t r_vol = 0, r_mx = 0, r_mn = ~0ull;
@@ -697,22 +763,22 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
     r_imx = wave_reduce(r_imx, MaxU64{});
     r_imn = wave_reduce(r_imn, MinU64{});
     if (lane == 0) {
-      s_r64[0][wave] = r_vol;
-      s_r64[1][wave] = r_mx;
-      s_r64[2][wave] = r_mn;
-      s_r64[3][wave] = r_imx;
-      s_r64[4][wave] = r_imn;
+      s.r64[0][wave] = r_vol;
+      s.r64[1][wave] = r_mx;
+      s.r64[2][wave] = r_mn;
+      s.r64[3][wave] = r_imx;
+      s.r64[4][wave] = r_imn;
     }
     __syncthreads();
     vol = 0;
     qmx = qmx_i = 0;
     qmn = qmn_i = ~0ull;
-    for (int x = 0; x < kTW; ++x) {
-      vol += s_r64[0][x];
-      qmx = MaxU64{}(qmx, s_r64[1][x]);
-      qmn = MinU64{}(qmn, s_r64[2][x]);
-      qmx_i = MaxU64{}(qmx_i, s_r64[3][x]);
-      qmn_i = MinU64{}(qmn_i, s_r64[4][x]);
+    for (int x = 0; x < kT / 64; ++x) {
+      vol += s.r64[0][x];
+      qmx = MaxU64{}(qmx, s.r64[1][x]);
+      qmn = MinU64{}(qmn, s.r64[2][x]);
+      qmx_i = MaxU64{}(qmx_i, s.r64[3][x]);
+      qmn_i = MinU64{}(qmn_i, s.r64[4][x]);
     }
     __syncthreads();
     const int to = oc;
@@ -725,6 +791,281 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
     parity ^= 1;
     ++ell;
   }
+}
+
+// ---------------------------------------------------------------- heavy sources
+// Sources whose pushes outgrow one workgroup: where a launch has few sources, the slowest
+// would be alone on its CU (0.57 G pushed edges a second) while the others idle.
+// k_src_head leaves such a source in `heavy`, and the host runs rounds of four launches,
+// one step of all of them, each over `gridDim.x` workgroups per source (blockIdx.y):
+// k_heavy_push (Eq. 14's decision of the last round first; who is done is finished
+// there), k_heavy_divide, k_heavy_bound (one workgroup per source) and k_heavy_count.
+// All sums are of whole numbers, so the results are those of k_src_head (512 sources of
+// R-MAT scale 15, 268 of them heavy: 32 -> 8.7 ms).
+constexpr int kHeavyThreads = 512;
+
+struct HeavyView {
+  uint64_t* Q;   // [2 n]
+  int oc, on;
+  int32_t *Sc, *Sn;
+};
+__device__ inline HeavyView heavy_view(const SrcArgs& a, const SrcHeavy& h) {
+  const size_t base = static_cast<size_t>(2 * h.slot) * a.n;
+  const size_t at = static_cast<size_t>(h.parity) * a.n, next = static_cast<size_t>(1 - h.parity) * a.n;
+  return {a.Q + base, static_cast<int>(at), static_cast<int>(next), a.S + base + at, a.S + base + next};
+}
+
+// A workgroup's share of the next support's volume and extremes.
+template <int kT>
+__device__ inline void add_support(uint64_t* s0, uint64_t* s1, uint64_t* s2, SrcHeavy* hp, uint64_t vol,
+                                   uint64_t mx, uint64_t mn) {
+  vol = block_reduce<kT>(vol, s0, AddU64{});
+  mx = block_reduce<kT>(mx, s1, MaxU64{});
+  mn = block_reduce<kT>(mn, s2, MinU64{});
+  if (threadIdx.x == 0 && vol > 0) {
+    atomicAdd(&hp->vol_n, static_cast<unsigned long long>(vol));
+    atomicMax(&hp->mx_n, static_cast<unsigned long long>(mx));
+    atomicMin(&hp->mn_n, static_cast<unsigned long long>(mn));
+  }
+}
+
+// A push of a good part of all edges is made as a pull: the sum over each row's
+// neighbours needs no atomics, which the memory takes at 17 G/s against some 200 G
+// gathers.
+__device__ inline bool pulls(const SrcArgs& a, uint64_t vol) {
+  return vol * 8 > static_cast<uint64_t>(a.rowptr[a.n]);
+}
+
+// The rows of part blockIdx.x, in tiles of kPullTile: 16 lanes per row, longer ones by a
+// wave or the workgroup.  Rows reached are divided at once, and a tile's are appended
+// to the support together.
+constexpr int kPullTile = 1024;
+template <int kT>
+__device__ inline void pull_rows(SrcLds<kT>& s, const SrcArgs& a, SrcHeavy* hp, const HeavyView& v) {
+  __shared__ int s_new[kPullTile];
+  __shared__ int s_count, s_at;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sub = tid & 15;
+  const uint64_t* Qc = v.Q + v.oc;
+  uint64_t vol = 0, mx = 0, mn = ~0ull;
+  // the sum over col[b, e) seen by lane `ln` of `st`
+  auto row_sum = [&](int b, int e, int ln, int st) {
+    uint64_t r = 0;
+    for (int k = b + ln; k < e; k += st * kEdgeIlp) {
+      int y[kEdgeIlp];
+      uint64_t q[kEdgeIlp];
+#pragma unroll
+      for (int x = 0; x < kEdgeIlp; ++x) y[x] = a.col[min(k + x * st, e - 1)];
+#pragma unroll
+      for (int x = 0; x < kEdgeIlp; ++x) q[x] = Qc[y[x]];
+#pragma unroll
+      for (int x = 0; x < kEdgeIlp; ++x) r += k + x * st < e ? q[x] : 0;
+    }
+    return r;
+  };
+  auto reached = [&](int y, uint64_t r, int d) {
+    const uint64_t q = div_round(r, static_cast<uint32_t>(d));
+    v.Q[v.on + y] = q;
+    s_new[atomicAdd(&s_count, 1)] = y;
+    vol += static_cast<uint64_t>(d);
+    mx = MaxU64{}(mx, q);
+    mn = MinU64{}(mn, q);
+  };
+  // tile t has the rows t, t + tiles, ...: of similar total length also where ids go by
+  // degree
+  const int tiles = (a.n + kPullTile - 1) / kPullTile;
+  for (int t0 = static_cast<int>(blockIdx.x); t0 < tiles; t0 += static_cast<int>(gridDim.x)) {
+    if (tid == 0) {
+      s_count = 0;
+      s.nlong = 0;
+    }
+    __syncthreads();
+    for (int r0 = tid / 16; r0 < kPullTile; r0 += kT / 16) {
+      const int64_t y64 = t0 + static_cast<int64_t>(r0) * tiles;
+      if (y64 >= a.n) break;
+      const int y = static_cast<int>(y64);
+      const int b = a.rowptr[y], e = a.rowptr[y + 1];
+      if (e - b > kShortRow) {   // at most kPullTile = kLongList of them
+        if (sub == 0) s.lng[atomicAdd(&s.nlong, 1)] = y;
+        continue;
+      }
+      uint64_t r = row_sum(b, e, sub, 16);
+#pragma unroll
+      for (int off = 8; off >= 1; off >>= 1) r += __shfl_xor(r, off, 64);
+      if (sub == 0 && r != 0) reached(y, r, e - b);
+    }
+    __syncthreads();
+    const int nlong = s.nlong;
+    for (int t = wave; t < nlong; t += kT / 64) {
+      const int y = s.lng[t];
+      const int b = a.rowptr[y], e = a.rowptr[y + 1];
+      if (e - b > kLongRow) continue;
+      const uint64_t r = wave_reduce(row_sum(b, e, lane, 64), AddU64{});
+      if (lane == 0 && r != 0) reached(y, r, e - b);
+    }
+    for (int t = 0; t < nlong; ++t) {
+      const int y = s.lng[t];
+      const int b = a.rowptr[y], e = a.rowptr[y + 1];
+      if (e - b <= kLongRow) continue;
+      const uint64_t r = block_reduce<kT>(row_sum(b, e, tid, kT), s.r64[0], AddU64{});
+      if (tid == 0 && r != 0) reached(y, r, e - b);
+    }
+    __syncthreads();
+    const int count = s_count;
+    if (tid == 0) s_at = count > 0 ? atomicAdd(&hp->cntn, count) : 0;
+    __syncthreads();
+    for (int x = tid; x < count; x += kT) v.Sn[s_at + x] = s_new[x];
+    __syncthreads();
+  }
+  add_support<kT>(s.r64[0], s.r64[1], s.r64[2], hp, vol, mx, mn);
+}
+
+__global__ __launch_bounds__(kHeavyThreads) void k_heavy_push(SrcArgs a) {
+  constexpr int kT = kHeavyThreads;
+  __shared__ SrcLds<kT> s;
+  SrcHeavy* hp = a.heavy + blockIdx.y;
+  if (hp->done) return;
+  const SrcHeavy h = *hp;
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (h.ell >= a.tau_row[h.row] || static_cast<double>(h.vol) > h.rhs) {
+    if (blockIdx.x == 0) {   // the others see `done` or the same decision
+      finish_source<kT>(s, a, h.li, h.row, h.slot, h.ell, h.cnt, h.parity, h.pushed);
+      if (tid == 0) {
+        hp->done = 1;
+        atomicSub(&a.heavy_ctl[1], 1);
+      }
+    }
+    return;
+  }
+  const HeavyView v = heavy_view(a, h);
+  uint64_t* Q = v.Q;
+  if (pulls(a, h.vol)) {
+    pull_rows<kT>(s, a, hp, v);
+    return;
+  }
+  visit_edges<kT>(
+      s, v.Sc, h.cnt, static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x), a.rowptr, a.col,
+      [&](int u, uint64_t* val) {
+        *val = Q[v.oc + u];
+        return *val != 0;
+      },
+      [&](const uint64_t(&q)[kEdgeIlp], const int(&y)[kEdgeIlp], const bool(&live)[kEdgeIlp]) {
+        unsigned long long old[kEdgeIlp];
+#pragma unroll
+        for (int x = 0; x < kEdgeIlp; ++x) {
+          old[x] = 1;
+          if (live[x])
+            old[x] = atomicAdd(reinterpret_cast<unsigned long long*>(&Q[v.on + y[x]]),
+                               static_cast<unsigned long long>(q[x]));
+        }
+        // one addition to the support's length per wave
+        int mine = 0;
+#pragma unroll
+        for (int x = 0; x < kEdgeIlp; ++x) mine += old[x] == 0 ? 1 : 0;
+        int before = 0, total = 0;
+#pragma unroll
+        for (int bit = 0; bit < 3; ++bit) {   // mine <= 4
+          const uint64_t b = __ballot((mine >> bit) & 1);
+          before += __popcll(b & ((1ull << lane) - 1)) << bit;
+          total += __popcll(b) << bit;
+        }
+        if (total == 0) return;
+        int at = 0;
+        const uint64_t here = __ballot(1);
+        const int first = __ffsll(static_cast<unsigned long long>(here)) - 1;
+        if (lane == first) at = atomicAdd(&hp->cntn, total);
+        at = __shfl(at, first, 64) + before;
+#pragma unroll
+        for (int x = 0; x < kEdgeIlp; ++x)
+          if (old[x] == 0) v.Sn[at++] = y[x];
+      });
+}
+
+// Q_{l+1} = r_{l+1} / d_y, its volume and extremes; Q_l is cleared.
+__global__ __launch_bounds__(kHeavyThreads) void k_heavy_divide(SrcArgs a) {
+  constexpr int kT = kHeavyThreads;
+  __shared__ uint64_t s_r[3][kT / 64];
+  SrcHeavy* hp = a.heavy + blockIdx.y;
+  if (hp->done) return;
+  const HeavyView v = heavy_view(a, *hp);
+  const int cnt = hp->cnt, cntn = hp->cntn;
+  const int t0 = static_cast<int>(blockIdx.x) * kT + threadIdx.x;
+  const int stride = static_cast<int>(gridDim.x) * kT;
+  uint64_t vol = 0, mx = 0, mn = ~0ull;
+  if (pulls(a, hp->vol)) {   // divided already
+    for (int e = t0; e < cnt; e += stride) v.Q[v.oc + v.Sc[e]] = 0;
+    return;
+  }
+  for (int e = t0; e < cntn; e += stride) {
+    const int y = v.Sn[e];
+    const int d = a.rowptr[y + 1] - a.rowptr[y];
+    const uint64_t q = div_round(v.Q[v.on + y], static_cast<uint32_t>(d));
+    v.Q[v.on + y] = q;
+    vol += static_cast<uint64_t>(d);
+    mx = MaxU64{}(mx, q);
+    mn = MinU64{}(mn, q);
+  }
+  for (int e = t0; e < cnt; e += stride) v.Q[v.oc + v.Sc[e]] = 0;
+  add_support<kT>(s_r[0], s_r[1], s_r[2], hp, vol, mx, mn);
+}
+
+// Step l + 1 becomes the current one: its term of Eq. 9, the extremes over N(i) and,
+// unless the source ends here, rho-hat.
+__global__ __launch_bounds__(1024) void k_heavy_bound(SrcArgs a) {
+  constexpr int kT = 1024;
+  __shared__ SrcLds<kT> s;
+  SrcHeavy* hp = a.heavy + blockIdx.x;
+  if (hp->done) return;
+  SrcHeavy h = *hp;
+  const int tid = threadIdx.x;
+  __syncthreads();
+  h.pushed += h.vol;
+  h.cnt = h.cntn;
+  h.parity ^= 1;
+  ++h.ell;
+  h.vol = h.vol_n;
+  h.qmx = h.mx_n;
+  h.qmn = h.mn_n;
+  h.cntn = 0;
+  h.vol_n = h.mx_n = 0;
+  h.mn_n = ~0ull;
+  h.rhs = 0.0;
+  h.rho = 0.0;
+  const HeavyView v = heavy_view(a, h);
+  const double qi = static_cast<double>(v.Q[v.oc + h.row]);
+  uint64_t mx = 0, mn = ~0ull;
+  for (int k = a.rowptr[h.row] + tid; k < a.rowptr[h.row + 1]; k += kT) {
+    const uint64_t q = v.Q[v.oc + a.col[k]];
+    mx = MaxU64{}(mx, q);
+    mn = MinU64{}(mn, q);
+    if (h.ell <= a.tau_slot[k]) a.gacc[k] += (qi - static_cast<double>(q)) * kInvUnit;
+  }
+  h.qmx_i = block_reduce<kT>(mx, s.r64[0], MaxU64{});
+  h.qmn_i = block_reduce<kT>(mn, s.r64[1], MinU64{});
+  if (h.ell < a.tau_row[h.row] && a.gamma > 0) {
+    bool keyed;
+    const uint64_t T =
+        threshold<kT, false>(s, a, v.Q, v.oc, v.on, v.Sc, h.cnt, h.qmx, h.qmn, &keyed);
+    h.rho = rho_hat<kT>(s, a, v.Q, v.oc, v.on, v.Sc, h.cnt, T, static_cast<double>(h.qmx), false);
+  }
+  if (tid == 0) *hp = h;
+}
+
+// Walk counts at the new step and Eq. 14's right side.
+__global__ __launch_bounds__(kHeavyThreads) void k_heavy_count(SrcArgs a) {
+  constexpr int kT = kHeavyThreads;
+  __shared__ SrcLds<kT> s;
+  SrcHeavy* hp = a.heavy + blockIdx.y;
+  if (hp->done) return;
+  const SrcHeavy h = *hp;
+  if (h.ell >= a.tau_row[h.row]) return;
+  const HeavyView v = heavy_view(a, h);
+  const double part = block_reduce<kT>(
+      scan_halves<kT>(s, a, v.Q, v.oc, v.Sc, h.cnt, a.rowptr[h.row], a.rowptr[h.row + 1], h.ell,
+                      static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x),
+                      static_cast<double>(h.qmx), h.cnt == a.n ? static_cast<double>(h.qmn) : 0.0,
+                      static_cast<double>(h.qmx_i), static_cast<double>(h.qmn_i), h.rho),
+      s.rd, AddD{});
+  if (threadIdx.x == 0 && part != 0.0) atomicAdd(&hp->rhs, part);
 }
 
 // ---------------------------------------------------------------- walks of a wave
@@ -1136,6 +1477,20 @@ hipError_t launch_src_head(const SrcArgs& a, int grid, hipStream_t st) {
     k_src_head<512, false><<<grid, 512, 0, st>>>(a);
   } else {
     k_src_head<256, false><<<grid, 256, 0, st>>>(a);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_src_heavy(const SrcArgs& a, int count, int rounds, hipStream_t st) {
+  if (count <= 0) return hipSuccess;
+  // a workgroup of a source that is done, or beyond its work, ends at once
+  const dim3 grid(static_cast<unsigned>(std::max(4, std::min(64, 8192 / count))),
+                  static_cast<unsigned>(count));
+  for (int r = 0; r < rounds; ++r) {
+    k_heavy_push<<<grid, kHeavyThreads, 0, st>>>(a);
+    k_heavy_divide<<<grid, kHeavyThreads, 0, st>>>(a);
+    k_heavy_bound<<<count, 1024, 0, st>>>(a);
+    k_heavy_count<<<grid, kHeavyThreads, 0, st>>>(a);
   }
   return hipGetLastError();
 }

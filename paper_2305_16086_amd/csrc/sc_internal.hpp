@@ -333,6 +333,18 @@ hipError_t launch_trace(const DeviceGraph& g, const int32_t* tau_slot, const int
 // Q[y] = p_l(i, y) / d_y in units of 2^-63, one pair of n-word columns and one
 // pair of n-entry support lists per workgroup slot.
 
+// A source between two of its steps (see the heavy kernels): the state at l = ell, and
+// what the step being made collects.
+struct SrcHeavy {
+  int64_t li = 0;                 // list entry
+  int32_t row = 0, slot = 0;
+  int32_t ell = 0, cnt = 0, parity = 0, done = 0;
+  uint64_t pushed = 0, vol = 0, qmx = 0, qmn = 0, qmx_i = 0, qmn_i = 0;
+  double rho = 0.0, rhs = 0.0;    // rho-hat and Eq. 14's right side at ell
+  int32_t cntn = 0, pad_ = 0;
+  unsigned long long vol_n = 0, mx_n = 0, mn_n = ~0ull;
+};
+
 struct SrcArgs {
   int32_t n = 0;
   const int32_t* rowptr = nullptr;
@@ -359,6 +371,9 @@ struct SrcArgs {
   int gamma = 10;
   int rule = 0;                    // 0: Eq. 14 as printed (walk pairs), 1: walk steps
   int force_tilde = -1;            // >= 0: switch at min(force_tilde, tau_p) instead
+  SrcHeavy* heavy = nullptr;       // [sources of the launch] (null: every source ends here)
+  int32_t* heavy_ctl = nullptr;    // [2] sources in heavy, of those not done
+  uint64_t heavy_vol = 0;          // a push of more edges is left to the heavy kernels
 };
 
 struct SrcWalkArgs {
@@ -390,7 +405,7 @@ struct SrcWalkArgs {
   int64_t cbeg = 0, cend = -1;
   // a half with more chunks than this in the batch is summed by a whole
   // workgroup (fixed segments, then the segment sums in order)
-  int64_t finish_seg = 4096;
+  int64_t finish_seg = 256;
 };
 
 // dst[k] = src[k] (n <= 65,536)
@@ -401,6 +416,8 @@ hipError_t launch_src_init(unsigned long long* totals, int ntotals, int64_t* nr_
                            int32_t* slot_ctl, int64_t nctl, int32_t* tilde_row, int64_t n,
                            hipStream_t st);
 hipError_t launch_src_head(const SrcArgs& a, int grid, hipStream_t st);
+// `rounds` steps of the first `count` sources in heavy
+hipError_t launch_src_heavy(const SrcArgs& a, int count, int rounds, hipStream_t st);
 // plain fills (kernels, so that a captured sequence holds no memset nodes)
 hipError_t launch_fill_u64(uint64_t* p, int64_t count, uint64_t value, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, int64_t count, uint32_t value, hipStream_t st);

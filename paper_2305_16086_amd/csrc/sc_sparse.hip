@@ -23,6 +23,12 @@ using sc::fail;
 namespace {
 
 constexpr int kMaxSlots = 2048;
+// Of a launch of up to kHeavyMaxSources, a source whose next push has more than
+// kHeavyVolume edges (120 us on one CU) goes on in the heavy kernels, kHeavyRounds steps
+// between two looks of the host at what is left.
+constexpr int kHeavyMaxSources = 512;
+constexpr uint64_t kHeavyVolume = 65536;
+constexpr int kHeavyRounds = 4;
 constexpr int64_t kPartCapacity = int64_t(1) << 24;   // chunk sums of one wave (128 MiB)
 
 // totals: walk pairs, walk steps, pushed entries, min / max switch step,
@@ -47,6 +53,8 @@ struct SrcBufs {
   int64_t part_capacity = 0;
   int64_t* ctl = nullptr;
   unsigned long long* totals = nullptr;
+  sc::SrcHeavy* heavy = nullptr;   // [min(slots, kHeavyMaxSources)] (null: not split)
+  int32_t* heavy_ctl = nullptr;
   int32_t* list = nullptr;    // source list (null: all)
   int64_t* hoff = nullptr;
   bool Q_clean = false;       // Q is known to be all zero
@@ -153,6 +161,9 @@ int enqueue_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
   a.gamma = o.gamma < 0 ? 10 : o.gamma;
   a.rule = o.switch_rule;
   a.force_tilde = o.tilde_tau;
+  a.heavy_vol = kHeavyVolume;
+  if (const char* h = std::getenv("SC_SOURCE_HEAVY_VOLUME"))   // other limit (tests)
+    a.heavy_vol = static_cast<uint64_t>(std::max(1ll, std::atoll(h)));
 
   sc::SrcWalkArgs wa;
   wa.n = static_cast<int32_t>(n);
@@ -185,7 +196,21 @@ int enqueue_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
     const int cnt = static_cast<int>(std::min<int64_t>(B.W, nsrc - b));
     a.list_base = b;
     a.pos_base = at(b);
+    // few sources: those that outgrow a workgroup are left over and stepped together
+    const bool split = B.heavy && cnt <= kHeavyMaxSources;
+    a.heavy = split ? B.heavy : nullptr;
+    a.heavy_ctl = B.heavy_ctl;
+    if (split) HIP_TRY(sc::launch_fill_u32(reinterpret_cast<uint32_t*>(B.heavy_ctl), 2, 0, st));
     HIP_TRY(sc::launch_src_head(a, cnt, st));
+    if (split) {
+      int32_t left[2] = {0, 0};
+      for (;;) {
+        HIP_TRY(hipMemcpyAsync(left, B.heavy_ctl, sizeof(left), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        if (left[1] <= 0) break;
+        HIP_TRY(sc::launch_src_heavy(a, left[0], kHeavyRounds, st));
+      }
+    }
     wa.P = at(b + cnt) - at(b);
     wa.nsources = cnt;
     if (walk_ev) HIP_TRY(hipEventRecord((*walk_ev)[2 * wave], st));
@@ -329,6 +354,8 @@ int sc::run_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
   HIP_TRY(grow(&sb.part, &sb.part_cap, static_cast<size_t>(kPartCapacity)));
   HIP_TRY(grow(&sb.ctl, &sb.ctl2_cap, size_t(3)));
   HIP_TRY(grow(&sb.totals, &sb.tot_cap, size_t(kTotals)));
+  HIP_TRY(grow(&sb.heavy, &sb.heavy_cap, static_cast<size_t>(std::min(B.W, kHeavyMaxSources))));
+  HIP_TRY(grow(&sb.heavy_ctl, &sb.heavy_ctl_cap, size_t(2)));
   HIP_TRY(grow(&sb.list, &sb.list_cap, static_cast<size_t>(nsrc)));
   HIP_TRY(grow(&sb.hoff, &sb.hoff_cap, static_cast<size_t>(nsrc) + 1));
   int32_t* tau_o = nullptr;
@@ -359,6 +386,8 @@ int sc::run_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
     B.part_capacity = std::max<int64_t>(1, std::min<int64_t>(kPartCapacity, std::atoll(c)));
   B.ctl = sb.ctl;
   B.totals = sb.totals;
+  B.heavy = sb.heavy;
+  B.heavy_ctl = sb.heavy_ctl;
   B.list = sb.list;
   B.hoff = sb.hoff;
   B.Q_clean = sb.clean;

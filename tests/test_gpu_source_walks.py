@@ -58,3 +58,22 @@ def test_selection_with_ties(sc, gamma):  # noqa: F811
     graph = gg.king_grid(200)
     out, _, tau, tt, nr = run_ps(sc, graph, 0.05, gamma=gamma, max_L=31)
     check_against_oracle(graph, 0.05, out, None, tau, tt, nr, gamma=gamma)
+
+
+@pytest.mark.parametrize("gamma,rule", [(10, 0), (0, 0), (100, 1)])
+def test_heavy_sources_step_together(sc, gamma, rule, monkeypatch):  # noqa: F811
+    # every source left to the heavy kernels at its first push, and none
+    n, u, v = gg.barabasi_albert(6000, 5, 9)
+    hub = np.arange(1, 2501)                                  # node 0: a list of the whole workgroup
+    u, v = gg.canonical_edges(n, np.concatenate([u, np.zeros(len(hub), u.dtype)]),
+                              np.concatenate([v, hub]))
+    src = np.r_[0, 1, 2, np.random.default_rng(1).permutation(np.arange(3, n))[:60]].astype(np.int32)
+    kw = dict(sources=src, gamma=gamma, switch_rule=rule)
+    monkeypatch.setenv("SC_SOURCE_HEAVY_VOLUME", str(10 ** 12))
+    ref, st, _, tt, nr = run_ps(sc, (n, u, v), 0.02, **kw)
+    monkeypatch.setenv("SC_SOURCE_HEAVY_VOLUME", "1")
+    out, st2, _, tt2, nr2 = run_ps(sc, (n, u, v), 0.02, **kw)
+    np.testing.assert_array_equal(tt2, tt)
+    np.testing.assert_array_equal(nr2, nr)
+    np.testing.assert_array_equal(out, ref)
+    assert st2["push_edges"] == st["push_edges"] and st2["walk_steps"] == st["walk_steps"]
