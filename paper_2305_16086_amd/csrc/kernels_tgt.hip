@@ -34,9 +34,12 @@ inline unsigned grid_for(int64_t items, int per_block) {
 __global__ void k_gacc_init(int64_t nslots, const int32_t* __restrict__ slot_row,
                             const int32_t* __restrict__ col, const double* __restrict__ inv_deg,
                             const int32_t* __restrict__ tau, int include_l1,
-                            double* __restrict__ gacc) {
+                            double* __restrict__ gacc, int64_t* __restrict__ nr,
+                            unsigned long long* __restrict__ capped) {
   const int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (k == 0 && capped) *capped = 0ull;
   if (k >= nslots) return;
+  if (nr) nr[k] = 0;
   const int s = slot_row[k];
   const int j = col[k];
   double v = inv_deg[s];                          // l = 0: p_0(s,s)/d_s, p_0(j,s) = 0
@@ -924,10 +927,11 @@ __global__ void k_trace(int64_t m, const int32_t* __restrict__ half_slot,
 // ====================================================================== wrappers
 
 hipError_t launch_gacc_init(const DeviceGraph& g, const int32_t* tau_slot, int include_l1,
-                            double* gacc, hipStream_t st) {
+                            double* gacc, hipStream_t st, int64_t* nr,
+                            unsigned long long* capped) {
   const int64_t ns = g.nslots;
   k_gacc_init<<<grid_for(ns, 256), 256, 0, st>>>(ns, g.slot_row, g.col, g.inv_deg_d, tau_slot,
-                                                  include_l1, gacc);
+                                                  include_l1, gacc, nr, capped);
   return hipGetLastError();
 }
 

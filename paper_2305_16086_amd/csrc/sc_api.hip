@@ -1361,9 +1361,9 @@ int ensure_buffers(sc_graph* g, int B, size_t tsize, hipStream_t st) {
   }
   if (!g->gacc) HIP_TRY(dev_alloc(&g->gacc, S));
   if (!g->tau_slot) HIP_TRY(dev_alloc(&g->tau_slot, S));
-  if (!g->tau_row) HIP_TRY(dev_alloc(&g->tau_row, n));
+  if (!g->tau_row) HIP_TRY(dev_alloc(&g->tau_row, n + 4));
   if (!g->nr_slot) HIP_TRY(dev_alloc(&g->nr_slot, S));
-  if (!g->work) HIP_TRY(dev_alloc(&g->work, 4));   // [0..1] walk totals, [2] capped halves
+  if (!g->work) HIP_TRY(dev_alloc(&g->work, 4));   // [0..1] walk totals, [2] capped halves (learned)
   if (!g->plan_work) HIP_TRY(dev_alloc(&g->plan_work, 4 * 2 * 64));
   if (!g->out_dev) HIP_TRY(dev_alloc(&g->out_dev, g->d.m));
   if (!g->tau_host)
@@ -1582,7 +1582,12 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
   }
   R.stats.lambda_star = lam;
   const double eps_tau = plus ? eps / 2.0 : eps;
-  unsigned long long* capped = g->work + 2;
+  // the capped count follows the rows' truncations, so that one copy brings both; it is
+  // zeroed behind that copy for the next call
+  const int64_t n_even = (n + 1) / 2 * 2;
+  unsigned long long* capped = reinterpret_cast<unsigned long long*>(g->tau_row + n_even);
+  unsigned long long* reset = nullptr;
+  bool have_gacc = false;
   int32_t* const tau_row = g->tau_host;   // pinned: [n] row truncations, then the capped count
   if (L > 0) {
     // every edge has tau = Lodd: nothing to read back
@@ -1590,16 +1595,23 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
     std::fill(tau_row, tau_row + n, Lodd);
     R.stats.L_used = R.stats.L_min = Lodd;
   } else {
-    HIP_TRY(sc::launch_fill_u64(reinterpret_cast<uint64_t*>(capped), 1, 0, st));
+    if (!g->capped_clean)
+      HIP_TRY(sc::launch_fill_u64(reinterpret_cast<uint64_t*>(capped), 1, 0, st));
+    g->capped_clean = false;
+    reset = capped;
     if (spectral)
       HIP_TRY(sc::launch_caltau(g->d, g->spec_lam, g->spec_phi, g->spec_omega, eps_tau, max_L,
                                 g->tau_slot, g->tau_row, st, capped));
     else
       HIP_TRY(sc::launch_tau(g->d, Lodd, eps_tau, lam, max_L, g->tau_slot, g->tau_row, st, capped));
-    unsigned long long* capped_h =
-        reinterpret_cast<unsigned long long*>(tau_row + (n + 1) / 2 * 2);
-    HIP_TRY(hipMemcpyAsync(tau_row, g->tau_row, n * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(capped_h, capped, sizeof(*capped_h), hipMemcpyDeviceToHost, st));
+    const unsigned long long* capped_h =
+        reinterpret_cast<const unsigned long long*>(tau_row + n_even);
+    HIP_TRY(hipMemcpyAsync(tau_row, g->tau_row, (n_even + 2) * sizeof(int32_t),
+                           hipMemcpyDeviceToHost, st));
+    if (!plus) {   // what does not wait for the host goes ahead
+      HIP_TRY(sc::launch_gacc_init(g->d, g->tau_slot, 1, g->gacc, st, nullptr, reset));
+      have_gacc = true;
+    }
     HIP_TRY(hipStreamSynchronize(st));
     R.stats.L_capped = static_cast<int64_t>(*capped_h / 2);   // both halves of an edge share tau
     int Lmax = 0, Lmin = 1 << 30;
@@ -1633,12 +1645,14 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
       g->plan_tilde = tilde;
       g->plan_valid = true;
     }
-    HIP_TRY(sc::launch_fill_u64(reinterpret_cast<uint64_t*>(g->nr_slot), g->rowptr_h[n], 0, st));
     R.stats.tilde_tau = tilde;
     R.stats.tilde_min = tilde;
     R.stats.tilde_max = tilde;
   }
-  HIP_TRY(sc::launch_gacc_init(g->d, g->tau_slot, (plus && tilde < 1) ? 0 : 1, g->gacc, st));
+  if (!have_gacc)
+    HIP_TRY(sc::launch_gacc_init(g->d, g->tau_slot, (plus && tilde < 1) ? 0 : 1, g->gacc, st,
+                                 plus ? g->nr_slot : nullptr, reset));
+  if (reset) g->capped_clean = true;
   R.ev_used = 0;
   R.stats.prop_launches = 0;
   R.stats.prop_bytes = 0.0;

@@ -124,7 +124,8 @@ struct sc_graph {
   int mask_pending_B = 0;
   double* gacc = nullptr;
   int32_t* tau_slot = nullptr;
-  int32_t* tau_row = nullptr;
+  int32_t* tau_row = nullptr;           // [n], then (8-aligned) the capped count
+  bool capped_clean = false;            // which is zero between calls
   int64_t* nr_slot = nullptr;
   int32_t* tau_host = nullptr;          // pinned [n + 2]: tau_row, then the capped count
   unsigned long long* work = nullptr;

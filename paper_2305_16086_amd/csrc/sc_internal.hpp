@@ -201,8 +201,10 @@ struct BatchItem {
 // Eq. 9, whose probabilities are known in closed form (p_0 = e_s,
 // p_1(s,s) = 0, p_1(j,s) = 1/d_j).
 // include_l1 = 0 leaves the l = 1 term to the walk tail (TGT+ with tilde_tau = 0).
+// Also nr[k] = 0 and *capped = 0 (either may be null).
 hipError_t launch_gacc_init(const DeviceGraph& g, const int32_t* tau_slot, int include_l1,
-                            double* gacc, hipStream_t st);
+                            double* gacc, hipStream_t st, int64_t* nr = nullptr,
+                            unsigned long long* capped = nullptr);
 
 // tau per slot: uniform L (odd) when L > 0, else the lambda* bound of
 // Theorem 3.2 with Upsilon = Delta = 0.  Also the per-row maximum.

@@ -332,7 +332,7 @@ int sc::run_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
   auto& sb = g->src;
   if (!g->gacc) HIP_TRY(dev_alloc(&g->gacc, S2));
   if (!g->tau_slot) HIP_TRY(dev_alloc(&g->tau_slot, S2));
-  if (!g->tau_row) HIP_TRY(dev_alloc(&g->tau_row, n));
+  if (!g->tau_row) HIP_TRY(dev_alloc(&g->tau_row, n + 4));
   if (!g->nr_slot) HIP_TRY(dev_alloc(&g->nr_slot, S2));
   if (!g->out_dev) HIP_TRY(dev_alloc(&g->out_dev, m));
   const size_t qwords = static_cast<size_t>(2) * B.W * n;
