@@ -34,7 +34,6 @@ constexpr int kWalkGrid = 2048;   // a multiple of 8
 constexpr int kUnit = 128;        // chunks a workgroup of k_src_walks_lds takes at a time
 constexpr int kUnitThreads = 1024, kUnitGrid = 256;
 constexpr int kLdsNodes = 13600;  // 12 bytes of LDS each
-constexpr int kLdsMinChunks = 32;
 constexpr int kShortRow = 128;    // N(j) up to this is scanned by 16 lanes, up to kLongRow by a
 constexpr int kLongRow = 2048;    // wave, and a longer one by the whole workgroup
 constexpr int kHubEdges = 1024;   // a longer list is pushed by the whole workgroup
@@ -801,7 +800,7 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
 // k_heavy_push (Eq. 14's decision of the last round first; who is done is finished
 // there), k_heavy_divide, k_heavy_bound (one workgroup per source) and k_heavy_count.
 // All sums are of whole numbers, so the results are those of k_src_head (512 sources of
-// R-MAT scale 15, 268 of them heavy: 32 -> 8.7 ms).
+// R-MAT scale 15: 32 -> 7.7 ms).
 constexpr int kHeavyThreads = 512;
 
 struct HeavyView {
@@ -831,7 +830,8 @@ __device__ inline void add_support(uint64_t* s0, uint64_t* s1, uint64_t* s2, Src
 
 // A push of a good part of all edges is made as a pull: the sum over each row's
 // neighbours needs no atomics, which the memory takes at 17 G/s against some 200 G
-// gathers.
+// gathers (all heads of the sample above with an eighth of the edges 8.8 ms, a half 9.0,
+// a 32nd 8.8; with pushes alone 28).
 __device__ inline bool pulls(const SrcArgs& a, uint64_t vol) {
   return vol * 8 > static_cast<uint64_t>(a.rowptr[a.n]);
 }
@@ -1467,8 +1467,9 @@ hipError_t launch_tau_range(int n, const int32_t* tau_row, unsigned long long* m
 hipError_t launch_src_head(const SrcArgs& a, int grid, hipStream_t st) {
   if (grid <= 0) return hipSuccess;
   // A source's time is that of one workgroup's chain of phases, so it gets as many
-  // threads as leave every source of the launch a place on the chip at once.  Up to
-  // kLdsColumns nodes, both columns are kept in LDS.
+  // threads as leave every source of the launch a place on the chip at once (512 sources
+  // of R-MAT scale 15: 34.1 ms with 512 threads, 31.8 with 1,024; 1,500 of n = 3,000: 308
+  // us with 512, 289 with 256).  Up to kLdsColumns nodes, both columns are kept in LDS.
   if (a.n <= kLdsColumns) {
     k_src_head<512, true><<<grid, 512, static_cast<size_t>(a.n) * 16, st>>>(a);
   } else if (grid <= 512) {
@@ -1503,10 +1504,12 @@ hipError_t launch_src_scan(const SrcWalkArgs& a, hipStream_t st) {
 
 hipError_t launch_src_walk_batch(const SrcWalkArgs& a, hipStream_t st) {
   if (a.P <= 0) return hipSuccess;
-  // (kLdsMinChunks a source: a change of source costs a workgroup some 10 us)
   const int kc = std::min(a.n, kLdsNodes);
   const size_t lds = static_cast<size_t>(kc) * 12 + 4;
-  if (a.cend >= 0 && a.cend - a.cbeg >= kLdsMinChunks * static_cast<int64_t>(a.nsources)) {
+  // Two units per workgroup, and enough chunks a source to be worth its column (512
+  // sources of BA n = 20,000, us with k_src_walks / k_src_walks_lds: 45 k chunks 116 / 200,
+  // 52 k 191 / 144, 140 k 515 / 294; 64 sources: 16 k 62 / 75, 86 k 483 / 236)
+  if (a.cend >= 0 && a.cend - a.cbeg >= std::max<int64_t>(a.lds_chunks, a.lds_source * a.nsources)) {
     if (a.col16) k_src_walks_lds<<<kUnitGrid, kUnitThreads, lds, st>>>(a, a.col16, kc);
     else k_src_walks_lds<<<kUnitGrid, kUnitThreads, lds, st>>>(a, a.col, kc);
   } else if (a.col16) k_src_walks<<<kWalkGrid, 256, 0, st>>>(a, a.col16);

@@ -408,6 +408,8 @@ struct SrcWalkArgs {
   // a half with more chunks than this in the batch is summed by a whole
   // workgroup (fixed segments, then the segment sums in order)
   int64_t finish_seg = 256;
+  // chunks of a batch, and per source, from which k_src_walks_lds takes it
+  int64_t lds_chunks = 65536, lds_source = 96;
 };
 
 // dst[k] = src[k] (n <= 65,536)

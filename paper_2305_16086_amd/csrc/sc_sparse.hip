@@ -24,10 +24,11 @@ namespace {
 
 constexpr int kMaxSlots = 2048;
 // Of a launch of up to kHeavyMaxSources, a source whose next push has more than
-// kHeavyVolume edges (120 us on one CU) goes on in the heavy kernels, kHeavyRounds steps
-// between two looks of the host at what is left.
+// kHeavyVolume edges goes on in the heavy kernels, kHeavyRounds steps between two looks
+// of the host at what is left (heads of 512 sources of R-MAT scale 15, ms, with 16 k, 64 k,
+// 256 k, 512 k and 1 M edges: 9.2, 8.7, 7.7, 8.6 and 31.9).
 constexpr int kHeavyMaxSources = 512;
-constexpr uint64_t kHeavyVolume = 65536;
+constexpr uint64_t kHeavyVolume = 262144;
 constexpr int kHeavyRounds = 4;
 constexpr int64_t kPartCapacity = int64_t(1) << 24;   // chunk sums of one wave (128 MiB)
 
@@ -189,6 +190,10 @@ int enqueue_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
   wa.k1 = static_cast<unsigned>(o.seed >> 32);
   if (const char* f = std::getenv("SC_SOURCE_FINISH_SEG"))   // smaller segments (tests)
     wa.finish_seg = std::max<int64_t>(1, std::atoll(f));
+  if (const char* f = std::getenv("SC_SOURCE_LDS_CHUNKS")) {   // other limit (tests)
+    wa.lds_chunks = std::max<int64_t>(1, std::atoll(f));
+    wa.lds_source = 0;
+  }
 
   auto at = [&](int64_t k) -> int64_t { return hoff ? (*hoff)[k] : int64_t(g->rowptr_h[k]); };
   int64_t wave = 0;

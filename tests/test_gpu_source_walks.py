@@ -22,10 +22,14 @@ def test_walks_with_column_in_lds(sc, n, monkeypatch):  # noqa: F811
     graph = gg.tree_plus_gnp(n, 8.0, 11)
     src = np.arange(0, n, n // 8, dtype=np.int32)[:8]
     kw = dict(sources=src, tilde_tau=1, L=9)
-    out, _, _, _, nr = run_ps(sc, graph, 0.02, **kw)
-    assert np.ceil(nr[nr > 0] / 64).sum() >= 32 * len(src)   # enough chunks a source
-    monkeypatch.setenv("SC_SOURCE_PART_CAPACITY", "200")     # batches below that
+    monkeypatch.setenv("SC_SOURCE_LDS_CHUNKS", str(10 ** 12))
     ref, _, _, _, nr2 = run_ps(sc, graph, 0.02, **kw)
+    monkeypatch.setenv("SC_SOURCE_LDS_CHUNKS", "1")
+    out, _, _, _, nr = run_ps(sc, graph, 0.02, **kw)
+    assert np.ceil(nr[nr > 0] / 64).sum() > 128              # more than one unit
+    np.testing.assert_array_equal(out, ref)
+    monkeypatch.setenv("SC_SOURCE_PART_CAPACITY", "200")     # in batches
+    out, _, _, _, _ = run_ps(sc, graph, 0.02, **kw)
     np.testing.assert_array_equal(nr, nr2)
     np.testing.assert_allclose(out, ref, atol=TOL, rtol=0)
 
