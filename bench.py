@@ -29,21 +29,22 @@ SEED = 1
 BLOCK = 64
 HBM_PEAK_GBS = 8000.0
 GOLDEN = os.path.join(ROOT, "tests", "golden", "ba_100k_seed1_sampled_sc.npz")
-# HBM bytes per k_propagate launch on this workload (the generator's node order) from the
-# FETCH_SIZE / WRITE_SIZE counters, scaled by kernels of known traffic
-# (profiles/hbm_ba100k_k_propagate.md); valid only for the
+# HBM bytes per dense k_step launch (8 blocks) on this workload (the generator's node order)
+# from the FETCH_SIZE / WRITE_SIZE counters, scaled by kernels of known traffic
+# (profiles/hbm_ba100k_k_step.md); valid only for the
 # kernel sources they were taken on (first 16 hex digits of the SHA-256 of the files in order)
-PROP_TRAFFIC_BYTES = 419604636
+PROP_TRAFFIC_BYTES = 2733679290
 PROP_TRAFFIC_SOURCE = (("paper_2305_16086_amd/csrc/kernels_tgt.hip",
-                        "paper_2305_16086_amd/csrc/accumulate.hpp"), "a7a719226577e17d")
+                        "paper_2305_16086_amd/csrc/accumulate.hpp"), "7ea66baf6ffeeb73")
 
 
 # Fabric bytes per single-walk step of the per-source walk kernel on R-MAT scale 22 with the
 # nodes in degree order (the timed 4,096-source call), from the same counters and scale
 # factors (profiles/hbm_rmat22_k_src_walks.md); valid only for the sources they were taken on
-WALK_TRAFFIC_BYTES_PER_STEP = 252.0
+WALK_TRAFFIC_BYTES_PER_STEP = 198.0
 WALK_TRAFFIC_SOURCE = (("paper_2305_16086_amd/csrc/kernels_sparse.hip",
-                        "paper_2305_16086_amd/csrc/philox.hpp"), "250d6397ae5e35f7")
+                        "paper_2305_16086_amd/csrc/walk.hpp",
+                        "paper_2305_16086_amd/csrc/philox.hpp"), "37ce90cc64018fdf")
 
 
 def node_order_flag(sc, order):
@@ -1149,6 +1150,9 @@ def main():
     avg_launch_us = 1e3 * prop_ms / max(timed, 1)
     bytes_per_launch = prop_bytes / max(launches, 1)
     achieved = bytes_per_launch / (avg_launch_us * 1e-6) / 1e9 if launches else 0.0
+    # a launch covers a group of blocks; a block has dense steps 4 .. tilde_tau
+    blocks_per_launch = ((n + BLOCK - 1) // BLOCK * max(stats[-1]["tilde_tau"] - 3, 0) * a.steps
+                         / max(launches, 1))
 
     # accuracy on the sampled edges whose exact SC the oracle stored
     res = out.cpu().numpy()
@@ -1204,7 +1208,8 @@ def main():
         },
         "roofline": {
             "bound": "hbm",
-            "kernel": "k_propagate<float, 64, false> (dense block gather of every neighbour row, FP32, B=64)",
+            "kernel": "k_step<float, kFull, false> (dense step of a group of source blocks: gather of "
+                      "every neighbour row, FP32, B=64)",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
@@ -1215,7 +1220,9 @@ def main():
             "launches": launches,
             "timed_launches": timed,
             "alg_bytes_per_launch": bytes_per_launch,
-            "gathered_TBps": 2 * m * 64 * 4 / (avg_launch_us * 1e-6) / 1e12 if launches else None,
+            "blocks_per_launch": blocks_per_launch,
+            "gathered_TBps": (blocks_per_launch * 2 * m * 64 * 4 / (avg_launch_us * 1e-6) / 1e12
+                              if launches else None),
             "library_spmm": spmm_ref,
         },
         "cpu_baseline": cpu,

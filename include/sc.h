@@ -25,8 +25,8 @@
  *     flags, in which case they are device memory on the handle's device
  *     and results are stream-ordered on the options' stream;
  *   - with host outputs every call returns after the results are written;
- *   - sc_all_edges_ex runs the per-block tails (candidate summary, walk
- *     counts, walks, the last step's accumulation) on a second stream owned
+ *   - sc_all_edges_ex runs the tails of a group of blocks (candidate summary,
+ *     walk counts, walks, the last step's accumulation) on a second stream owned
  *     by the handle; it waits for the options' stream before its first
  *     launch and the options' stream waits for it before the combine, so
  *     the call stays ordered on the options' stream.
@@ -123,8 +123,9 @@ typedef struct sc_stats {
   int64_t walks;           /* walk pairs simulated                                    */
   int64_t walk_steps;      /* single-walk steps simulated                             */
   int64_t prop_launches;   /* dense propagation launches that gather every neighbour
-                              row (at block width 64 the first dense step after the
-                              two-hop step skips zero rows and is not counted)      */
+                              row, at block width 64 each of a group of blocks (there
+                              the first dense step after the two-hop step skips zero
+                              rows and a last step reads few rows: not counted)     */
   double prop_ms;          /* sum of the timed propagation launches (SC_TIME_KERNELS) */
   double prop_bytes;       /* algorithmic bytes of the counted propagation launches   */
   double total_ms;         /* wall time of the call on the stream                     */

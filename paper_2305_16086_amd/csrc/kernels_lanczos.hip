@@ -10,7 +10,9 @@
 // order, so nothing comes back to the host between steps (alpha and beta stay in device
 // arrays that the host reads every so many steps).  The basis V is column major and a
 // chunk's w stays in LDS within a launch.  Up to some 30,000 nodes a step is bound by
-// its launches' chains of dependent loads, beyond by the four reads of V.
+// its launches' chains of dependent loads, beyond by the four reads of V (n = 10,007, 260
+// steps of two runs: 42 us a step, of it 27 in k_lz_orth; 380 with a launch per vector
+// operation and a copy to the host for each dot product).
 #include "sc_internal.hpp"
 
 namespace sc {

@@ -748,7 +748,8 @@ __global__ __launch_bounds__(kThreads) void k_walks_flat(
     const long long* __restrict__ ctl, double* __restrict__ part_g, long long capacity,
     double* __restrict__ gacc) {
   // the walks of a slice's sources read one line per node of the state: they run on the
-  // slice's XCD (BA, n = 100,000: 27.5 -> 21 us per block)
+  // slice's XCD, beside the next group's steps (BA, n = 100,000: 228 us for 8 blocks; one
+  // block at a time with the chip to itself took 27.5)
   constexpr int C = B < 128 / static_cast<int>(sizeof(T)) ? B : 128 / static_cast<int>(sizeof(T));
   int sl, wg, wgs;
   if (!sg.decode(static_cast<int>(blockIdx.x), &sl, &wg, &wgs)) return;

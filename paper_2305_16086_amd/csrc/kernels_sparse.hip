@@ -17,8 +17,10 @@
 // threshold by radix select, rho-hat over the candidate edges, extremes over
 // N(i), N(j) and V), the walk counts of Eq. 13, and Eq. 14's two sides; the
 // first l where the frontier volume exceeds the walk work becomes tilde_tau_i.
-// The walks of a wave of sources then run flat over the whole GPU (chunks of
-// 64 walk pairs, fixed-order sums), reading q from the sources' slots.
+// Where a launch has few sources, those that outgrow a workgroup go on in kernels that
+// step them together (k_heavy_*).  The walks of a wave of sources then run flat over the
+// whole GPU (chunks of 64 walk pairs, fixed-order sums), reading q from the sources'
+// slots.
 #include "sc_internal.hpp"
 #include "walk.hpp"
 
