@@ -194,7 +194,9 @@ void sc_free_graph(sc_graph* g);
  * the truncation bound of Theorem 3.2 (Algorithm 1 line 1).  Computed once by
  * Lanczos on the GPU (deflated of the top eigenvector sqrt(d)/sqrt(2m)) and
  * cached in the handle.  The value returned is an upper estimate: the
- * extreme Ritz value plus its residual norm.
+ * extreme Ritz value plus its residual norm.  A run that reaches its step limit
+ * (600 steps, fewer where the basis would pass 4 GiB) adds the residual it has, or
+ * none where that would pass 1 (sc_stats.lambda_converged is then 0).
  */
 int sc_lambda_star(sc_graph* g, double* lam);
 

@@ -808,13 +808,15 @@ std::vector<double> squares(const std::vector<double>& e) {
 
 // extreme Ritz estimate: max over the two ends of |theta| + residual, where the
 // residual of a Ritz pair is |beta_last * (last component of its vector)|
-// (eigenvalues and last components by implicit QL, O(k^2) per check)
+// (eigenvalues and last components by implicit QL, O(k^2) per check); *plain is the
+// larger |theta| alone
 double ritz_bound(const std::vector<double>& alpha, const std::vector<double>& beta, int k,
-                  double beta_last, double* worst_res) {
+                  double beta_last, double* worst_res, double* plain) {
   std::vector<double> d(alpha.begin(), alpha.begin() + k), zl;
   std::vector<double> e(beta.begin(), beta.begin() + std::min<size_t>(beta.size(), k));
   if (!tridiag_eigen(d, e, zl)) {
     *worst_res = 1.0;   // no answer: report as unconverged
+    *plain = 1.0;
     return 1.0;
   }
   int imax = 0, imin = 0;
@@ -825,6 +827,7 @@ double ritz_bound(const std::vector<double>& alpha, const std::vector<double>& b
   const double rmax = std::fabs(beta_last * zl[imax]);
   const double rmin = std::fabs(beta_last * zl[imin]);
   *worst_res = std::max(rmax, rmin);
+  *plain = std::max(std::fabs(d[imax]), std::fabs(d[imin]));
   return std::max(std::fabs(d[imax]) + rmax, std::fabs(d[imin]) + rmin);
 }
 
@@ -856,7 +859,8 @@ int sc::compute_lambda_star(sc_graph* g, hipStream_t st, double* out) {
       const int ex = lz.exhausted(q, r, checked, upto);
       const int j = ex ? ex : upto;
       const double b_j = lz.beta(q, r, j);
-      const bool last = ex || j == kmax;
+      const bool closed = ex || j == n - 1;   // the Krylov space is all there is
+      const bool last = closed || j == kmax;
       al.resize(j);
       be.resize(j - 1);
       for (int i = 1; i <= j; ++i) al[i - 1] = lz.alpha(q, r, i);
@@ -872,12 +876,13 @@ int sc::compute_lambda_star(sc_graph* g, hipStream_t st, double* out) {
                                 [&](double t) { return sturm_count(al, e2, t) > 0; });
         if (res > 1e-7) continue;
       }
-      result[r] = ritz_bound(al, be, j, last ? 0.0 : b_j, &res);
-      if (ex || res < 1e-9) {   // Krylov space exhausted, or both ends converged
-        converged[r] = true;
-        done[r] = true;
-      }
-      if (last) done[r] = true;
+      double plain = 0.0;
+      result[r] = ritz_bound(al, be, j, closed ? 0.0 : b_j, &res, &plain);
+      converged[r] = closed || res < 1e-9;
+      done[r] = last || converged[r];
+      // at the step limit the residual can reach past 1, where it bounds nothing: the
+      // Ritz value alone then, reported as not converged
+      if (last && !converged[r] && result[r] >= 1.0) result[r] = plain;
     }
     checked = upto;
   }
