@@ -48,6 +48,7 @@ hipError_t tracked_malloc_bytes(void** p, size_t bytes) {
   }
   const hipError_t e = hipMalloc(p, bytes);
   if (e != hipSuccess) {
+    (void)hipGetLastError();   // a caller that goes on with less must not find it later
     *p = nullptr;
     return e;
   }
@@ -527,8 +528,8 @@ struct LanczosDriver {
 
   // Column 0 of the basis: the top eigenvector sqrt(d / 2m) (eigenvalue 1, deflated by
   // the re-orthogonalisation); w[0]: a fixed pseudo-random unit vector orthogonal to
-  // it, run r from seed r.
-  hipError_t start(const sc::DeviceGraph& dg, const int32_t* deg_host, int runs, int kmax_,
+  // it, run r from seed seed0 + r.
+  hipError_t start(const sc::DeviceGraph& dg, const int32_t* deg_host, int seed0, int runs, int kmax_,
                    hipStream_t st_) {
     st = st_;
     kmax = kmax_;
@@ -568,7 +569,7 @@ struct LanczosDriver {
     }
     e = hipMemcpyAsync(sid, sidh.data(), n * sizeof(double), hipMemcpyHostToDevice, st);
     for (int r = 0; r < runs && e == hipSuccess; ++r) {
-      uint64_t z = 0x9E3779B97F4A7C15ull * (2 * static_cast<uint64_t>(r) + 1);
+      uint64_t z = 0x9E3779B97F4A7C15ull * (2 * static_cast<uint64_t>(seed0 + r) + 1);
       double dot = 0.0;
       for (int64_t x = 0; x < n; ++x) {
         z += 0x9E3779B97F4A7C15ull;
@@ -831,30 +832,25 @@ double ritz_bound(const std::vector<double>& alpha, const std::vector<double>& b
   return std::max(std::fabs(d[imax]) + rmax, std::fabs(d[imin]) + rmin);
 }
 
-}  // namespace
-
-int sc::compute_lambda_star(sc_graph* g, hipStream_t st, double* out) {
-  // two Lanczos runs from independent start vectors, side by side; the larger estimate
-  // is kept (a start vector nearly orthogonal to the extreme eigenvector would make one
-  // run under-estimate), converged only if both runs passed the residual test
+// `runs` Lanczos runs side by side from seeds seed0, ...: lambda* estimate and whether
+// both ends passed the residual test, per run.
+int lambda_runs(sc_graph* g, hipStream_t st, int kmax, int seed0, int runs, double* result,
+                bool* converged) {
   const int64_t n = g->d.n;
-  // up to 600 steps, a run's basis held to 4 GiB
-  const int64_t kcap = std::max<int64_t>(40, (int64_t(1) << 29) / std::max<int64_t>(n, 1) - 2);
-  const int kmax = static_cast<int>(std::min<int64_t>({n - 1, 600, kcap}));
-  constexpr int kRuns = 2, kWindow = 20;
+  constexpr int kWindow = 20;
   LanczosDriver lz;
-  const hipError_t e0 = lz.start(g->d, g->deg_h.data(), kRuns, kmax, st);
+  const hipError_t e0 = lz.start(g->d, g->deg_h.data(), seed0, runs, kmax, st);
   if (e0 != hipSuccess)
     return fail(e0 == hipErrorOutOfMemory ? SC_ENOMEM : SC_EHIP, "lanczos allocation failed");
-  double result[kRuns] = {-1.0, -1.0};
-  bool done[kRuns] = {}, converged[kRuns] = {};
   std::vector<double> al, be;
+  std::vector<char> done(runs, 0);
+  int open = runs;   // runs not done
   HIP_TRY(lz.advance(kWindow));
-  for (int checked = 0; checked < kmax && !(done[0] && done[1]);) {
+  for (int checked = 0; checked < kmax && open > 0;) {
     if (lz.enqueued < kmax) HIP_TRY(lz.advance(kWindow));   // beside the evaluation
     int q = 0, upto = 0;
     HIP_TRY(lz.take(&q, &upto));
-    for (int r = 0; r < kRuns; ++r) {
+    for (int r = 0; r < runs; ++r) {
       if (done[r]) continue;
       const int ex = lz.exhausted(q, r, checked, upto);
       const int j = ex ? ex : upto;
@@ -879,14 +875,39 @@ int sc::compute_lambda_star(sc_graph* g, hipStream_t st, double* out) {
       double plain = 0.0;
       result[r] = ritz_bound(al, be, j, closed ? 0.0 : b_j, &res, &plain);
       converged[r] = closed || res < 1e-9;
-      done[r] = last || converged[r];
       // at the step limit the residual can reach past 1, where it bounds nothing: the
       // Ritz value alone then, reported as not converged
       if (last && !converged[r] && result[r] >= 1.0) result[r] = plain;
+      if (last || converged[r]) {
+        done[r] = 1;
+        --open;
+      }
     }
     checked = upto;
   }
   HIP_TRY(hipStreamSynchronize(st));
+  return SC_OK;
+}
+
+}  // namespace
+
+int sc::compute_lambda_star(sc_graph* g, hipStream_t st, double* out) {
+  // two Lanczos runs from independent start vectors; the larger estimate is kept (a
+  // start vector nearly orthogonal to the extreme eigenvector would make one run
+  // under-estimate), converged only if both runs passed the residual test.  Side by
+  // side, they share the launches; where there is no memory for both bases, one after
+  // the other with the same results (each basis up to 600 steps, held to 4 GiB)
+  const int64_t n = g->d.n;
+  const int64_t kcap = std::max<int64_t>(40, (int64_t(1) << 29) / std::max<int64_t>(n, 1) - 2);
+  const int kmax = static_cast<int>(std::min<int64_t>({n - 1, 600, kcap}));
+  double result[2] = {-1.0, -1.0};
+  bool converged[2] = {};
+  int rc = lambda_runs(g, st, kmax, 0, 2, result, converged);
+  if (rc == SC_ENOMEM) {
+    rc = lambda_runs(g, st, kmax, 0, 1, result, converged);
+    if (rc == SC_OK) rc = lambda_runs(g, st, kmax, 1, 1, result + 1, converged + 1);
+  }
+  if (rc) return rc;
   for (double r : result)
     if (!(r > 0.0) || !(r < 1.0))
       return fail(SC_EINVAL, "lambda* estimate outside (0, 1): " + std::to_string(r) +
@@ -922,7 +943,7 @@ int sc::lanczos_spectrum(sc_graph* g, int omega, int max_iter, double tol, hipSt
   const int kmax = static_cast<int>(std::min<int64_t>({n - 1, static_cast<int64_t>(max_iter), cap}));
   constexpr int kWindow = 25;
   LanczosDriver lz;
-  hipError_t e = lz.start(dg, g->deg_h.data(), 1, kmax, st);
+  hipError_t e = lz.start(dg, g->deg_h.data(), 0, 1, kmax, st);
   if (e != hipSuccess)
     return fail(e == hipErrorOutOfMemory ? SC_ENOMEM : SC_EHIP, "spectrum: allocation failed");
   const int want = omega - 1;
