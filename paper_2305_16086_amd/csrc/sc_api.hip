@@ -595,6 +595,18 @@ struct LanczosDriver {
     return e;
   }
 
+  // The first kProbes windows of kProbe steps are waited for one by one and only looked at
+  // for their end: where the Krylov space closes at once (complete graphs, hubs joined to
+  // everything) the steps of full windows would be for nothing (lambda* of the complete
+  // graph on 129 nodes 1.17 -> 0.25 ms, of 70 hubs joined to 6,000 nodes 2.9 -> 0.7).
+  static constexpr int kProbe = 2, kProbes = 2;
+  bool probing() const { return taken <= kProbes; }   // the window just taken was one
+  // enqueues what is to follow it, the last probe's window completing the first full one
+  hipError_t after_probe(int window) {
+    return enqueued >= kmax ? hipSuccess
+                            : advance(taken < kProbes ? kProbe : window - kProbes * kProbe);
+  }
+
   // enqueues a window of up to `steps` steps
   hipError_t advance(int steps) {
     const int last = std::min(enqueued + steps, kmax);
@@ -845,9 +857,10 @@ int lambda_runs(sc_graph* g, hipStream_t st, int kmax, int seed0, int runs, doub
   std::vector<double> al, be;
   std::vector<char> done(runs, 0);
   int open = runs;   // runs not done
-  HIP_TRY(lz.advance(kWindow));
+  HIP_TRY(lz.advance(lz.kProbe));
   for (int checked = 0; checked < kmax && open > 0;) {
-    if (lz.enqueued < kmax) HIP_TRY(lz.advance(kWindow));   // beside the evaluation
+    if (lz.taken >= lz.kProbes && lz.enqueued < kmax)
+      HIP_TRY(lz.advance(kWindow));   // beside the evaluation
     int q = 0, upto = 0;
     HIP_TRY(lz.take(&q, &upto));
     for (int r = 0; r < runs; ++r) {
@@ -857,6 +870,7 @@ int lambda_runs(sc_graph* g, hipStream_t st, int kmax, int seed0, int runs, doub
       const double b_j = lz.beta(q, r, j);
       const bool closed = ex || j == n - 1;   // the Krylov space is all there is
       const bool last = closed || j == kmax;
+      if (lz.probing() && !last) continue;   // checked every kWindow steps
       al.resize(j);
       be.resize(j - 1);
       for (int i = 1; i <= j; ++i) al[i - 1] = lz.alpha(q, r, i);
@@ -884,6 +898,7 @@ int lambda_runs(sc_graph* g, hipStream_t st, int kmax, int seed0, int runs, doub
       }
     }
     checked = upto;
+    if (lz.probing() && open > 0) HIP_TRY(lz.after_probe(kWindow));
   }
   HIP_TRY(hipStreamSynchronize(st));
   return SC_OK;
@@ -960,9 +975,10 @@ int sc::lanczos_spectrum(sc_graph* g, int omega, int max_iter, double tol, hipSt
   std::vector<double> alpha, beta, th, zl;
   int steps = 0;
   double b_last = 0.0;
-  HIP_TRY(lz.advance(kWindow));
+  HIP_TRY(lz.advance(lz.kProbe));
   for (int checked = 0;;) {
-    if (lz.enqueued < kmax) HIP_TRY(lz.advance(kWindow));   // beside the evaluation
+    if (lz.taken >= lz.kProbes && lz.enqueued < kmax)
+      HIP_TRY(lz.advance(kWindow));   // beside the evaluation
     int q = 0, upto = 0;
     HIP_TRY(lz.take(&q, &upto));
     const int ex = lz.exhausted(q, 0, checked, upto);
@@ -975,7 +991,9 @@ int sc::lanczos_spectrum(sc_graph* g, int omega, int max_iter, double tol, hipSt
     for (int i = 1; i < steps; ++i) beta[i - 1] = lz.beta(q, 0, i);
     checked = upto;
     if (ex || steps == kmax) break;
-    if (steps >= want) {
+    if (lz.probing()) {
+      HIP_TRY(lz.after_probe(kWindow));
+    } else if (steps >= want) {
       // the pair of want-th largest |theta| first: the largest t with fewer than `want`
       // eigenvalues of magnitude above it
       const std::vector<double> e2 = squares(beta);
