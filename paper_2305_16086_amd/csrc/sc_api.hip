@@ -1239,8 +1239,9 @@ extern "C" void sc_default_options(sc_options* o) {
 
 namespace sc {
 
-PipeLayout pipe_layout(const sc_graph* g, int B, size_t tsize) {
+PipeLayout pipe_layout(const sc_graph* g, int B, size_t tsize, int sets) {
   PipeLayout l;
+  l.sets = sets;
   const int64_t n = g->d.n;
   l.ystride = (n * B + 63) / 64 * 64;
   const size_t yb = static_cast<size_t>(l.ystride) * tsize;
@@ -1249,6 +1250,8 @@ PipeLayout pipe_layout(const sc_graph* g, int B, size_t tsize) {
   group = std::max<int64_t>(group, kMinGroup);
   while (group > 1 && 2 * kPipeSets * group * yb > kPipeBudgetBytes) --group;
   group = std::min<int64_t>({group, nblocks, kMaxGroup});
+  if (g->group_limit > 0)
+    group = std::min<int64_t>(group, std::max<int64_t>(1, g->group_limit / (2 * yb)));
   // whole rounds of the 8 XCDs (a block is tsize / 2 slices when B = 64)
   const int64_t unit = std::max<int64_t>(1, 16 / static_cast<int64_t>(tsize));
   if (group > unit && group < nblocks) group = group / unit * unit;
@@ -1353,11 +1356,37 @@ int ensure_narrow_ids(sc_graph* g, hipStream_t st) {
   return SC_OK;
 }
 
-int ensure_buffers(sc_graph* g, int B, size_t tsize, hipStream_t st) {
+bool shrink_groups(sc_graph* g, int B, size_t tsize, hipStream_t st) {
+  const PipeLayout l = pipe_layout(g, B, tsize, 1);
+  if (l.group <= 1) return false;
+  // what the failed call has enqueued still reads the buffers
+  if (hipStreamSynchronize(st) != hipSuccess) return false;
+  if (g->tail_stream && hipStreamSynchronize(g->tail_stream) != hipSuccess) return false;
+  g->group_limit = 2 * static_cast<size_t>(l.ystride) * tsize * (l.group / 2);
+  if (g->Y) (void)tracked_free(g->Y);
+  g->Y = nullptr;
+  g->ybytes = 0;
+  if (g->partials) (void)tracked_free(g->partials);
+  g->partials = nullptr;
+  g->pbytes = 0;
+  dev_free(g->nz);
+  g->nz_bytes = 0;
+  dev_free(g->mask);
+  g->mask_words = 0;
+  dev_free(g->anymask);
+  g->anymask_words = 0;
+  g->mask_clean = false;
+  g->mask_pending = BlockList{};
+  dev_free(g->tail.col);
+  g->tail_blocks = 0;
+  return true;
+}
+
+int ensure_buffers(sc_graph* g, int B, size_t tsize, int sets, hipStream_t st) {
   using namespace sc;
   const int64_t n = g->d.n;
   const int64_t S = static_cast<int64_t>(g->rowptr_h[n]);
-  const PipeLayout lay = pipe_layout(g, B, tsize);
+  const PipeLayout lay = pipe_layout(g, B, tsize, sets);
   const size_t yb = 2 * static_cast<size_t>(lay.bufs()) * lay.ystride * tsize;
   if (yb > g->ybytes) {
     if (g->Y) (void)sc::tracked_free(g->Y);
@@ -1589,12 +1618,14 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
   if (gamma > sc::kMaxGamma) return fail(SC_EINVAL, "gamma above 16 is not supported");
   int max_L = o.max_L > 0 ? o.max_L : 255;
   if (max_L % 2 == 0) --max_L;
-  int rc = sc::ensure_buffers(g, B, sizeof(T), st);
+  // TGT has no tails: its groups follow one another in one set of states
+  const int sets = plus ? sc::kPipeSets : 1;
+  int rc = sc::ensure_buffers(g, B, sizeof(T), sets, st);
   if (rc) return rc;
   const bool dev_ptrs = (o.flags & SC_DEVICE_PTRS) != 0;
 
   g->mask_clean = false;   // set again once the call's last clear is enqueued
-  Runner<T> R{g, B, st, (o.flags & SC_TIME_KERNELS) != 0};
+  Runner<T> R{g, B, sets, st, (o.flags & SC_TIME_KERNELS) != 0};
   const sc::PipeLayout& lay = R.lay;
   R.stats.block = B;
   R.stats.tilde_tau = -1;
@@ -1720,7 +1751,7 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
     if (lend < 2 && !tail) continue;
     if (groups.empty() || groups.back().all.nb == lay.group) groups.emplace_back();
     Group& gr = groups.back();
-    r.buf = static_cast<int>((groups.size() - 1) % sc::kPipeSets) * lay.group + gr.all.nb;
+    r.buf = static_cast<int>((groups.size() - 1) % lay.sets) * lay.group + gr.all.nb;
     gr.all.b[gr.all.nb++] = r;
     if (lend >= 2) {
       gr.lend[gr.trav.nb] = lend;
@@ -1754,7 +1785,7 @@ int run_method(sc_graph* g, double eps, int L, const sc_options& o, double* out_
   bool tail_recorded[sc::kPipeSets] = {};
   for (size_t q = 0; q < groups.size(); ++q) {
     const Group& gr = groups[q];
-    const int qset = static_cast<int>(q % sc::kPipeSets);
+    const int qset = static_cast<int>(q % lay.sets);
     if (tail_recorded[qset])
       HIP_TRY(hipStreamWaitEvent(st, g->pipe_ev[1 + sc::kPipeSets + qset], 0));
     R.st = st;
@@ -1901,8 +1932,12 @@ extern "C" int sc_all_edges_ex(sc_graph* g, double eps, int L, const sc_options*
   else if (opt.method == SC_LEARNED)
     rc = sc::run_learned(g, eps, opt, out, st);
   else
-    rc = opt.precision == 1 ? run_method<double>(g, eps, L, opt, out, st)
-                            : run_method<float>(g, eps, L, opt, out, st);
+    rc = sc::with_smaller_groups(
+        g, opt.block > 0 ? opt.block : 64, opt.precision == 1 ? sizeof(double) : sizeof(float),
+        static_cast<hipStream_t>(opt.stream), [&] {
+          return opt.precision == 1 ? run_method<double>(g, eps, L, opt, out, st)
+                                    : run_method<float>(g, eps, L, opt, out, st);
+        });
   if (cur != g->device) (void)hipSetDevice(cur);
   return rc;
 }

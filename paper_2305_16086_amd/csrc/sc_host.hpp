@@ -58,10 +58,11 @@ constexpr size_t kTailBytes = size_t(256) << 20;   // candidate-summary scratch
 
 // Blocks per group and the layout of the state arrays for block width B.
 struct PipeLayout {
+  int sets = kPipeSets;   // sets of states: one where no tails run beside the next group
   int group = 1;          // blocks per group
   int tail_group = 1;     // blocks per tail launch
   int64_t ystride = 0;    // elements per block state
-  int bufs() const { return kPipeSets * group; }
+  int bufs() const { return sets * group; }
 };
 
 // runs f when the scope ends (releases buffers on every return path)
@@ -105,6 +106,8 @@ struct sc_graph {
   // work buffers, grown on demand
   void* Y = nullptr;                    // [2 parities][bufs][ystride] block states
   size_t ybytes = 0;
+  size_t group_limit = 0;               // bytes of a group's states (0: kGroupBytes); less
+                                        // once a call has not found the memory for more
   hipStream_t tail_stream = nullptr;    // a group's tails overlap the next traversal
   // [0] stream joins, [1 + q] traversal of the group in set q done,
   // [1 + kPipeSets + q] its tails done
@@ -228,9 +231,20 @@ int run_per_source(sc_graph* g, double eps, int L, const sc_options& o, double* 
 int lanczos_spectrum(sc_graph* g, int omega, int max_iter, double tol, hipStream_t st, int* kept,
                      double* worst);
 
-PipeLayout pipe_layout(const sc_graph* g, int B, size_t tsize);
+PipeLayout pipe_layout(const sc_graph* g, int B, size_t tsize, int sets);
 // work buffers of the traversal (and the sliced lists for B = 64)
-int ensure_buffers(sc_graph* g, int B, size_t tsize, hipStream_t st);
+int ensure_buffers(sc_graph* g, int B, size_t tsize, int sets, hipStream_t st);
+// Gives back what is sized by the group and halves the groups to come; false when they
+// are single blocks already (or the device does not answer).
+bool shrink_groups(sc_graph* g, int B, size_t tsize, hipStream_t st);
+// f() until it does not run out of memory, each time with groups of half the size (f
+// starts over and writes no output before it has what it needs).
+template <typename F>
+int with_smaller_groups(sc_graph* g, int B, size_t tsize, hipStream_t st, F f) {
+  int rc = f();
+  while (rc == SC_ENOMEM && shrink_groups(g, B, tsize, st)) rc = f();
+  return rc;
+}
 // DeviceGraph::col16, where the ids fit and the memory is there
 int ensure_narrow_ids(sc_graph* g, hipStream_t st);
 // buffers of `blocks` tails; walks: also the chunk sums
@@ -279,8 +293,8 @@ struct Runner {
   T* roff = nullptr;
   int record_to = -1;     // record steps 2..record_to
 
-  Runner(sc_graph* g_, int B_, hipStream_t st_, bool timing_)
-      : g(g_), B(B_), st(st_), timing(timing_), lay(pipe_layout(g_, B_, sizeof(T))) {}
+  Runner(sc_graph* g_, int B_, int sets, hipStream_t st_, bool timing_)
+      : g(g_), B(B_), st(st_), timing(timing_), lay(pipe_layout(g_, B_, sizeof(T), sets)) {}
 
   T* Y(int parity) {
     return static_cast<T*>(g->Y) + static_cast<int64_t>(parity) * lay.bufs() * lay.ystride;

@@ -416,10 +416,9 @@ int record_and_features(sc_graph* g, int B, hipStream_t st, double lam, float* X
 }
 
 template <typename T>
-int closure_features_t(sc_graph* g, hipStream_t st, float* X, double* s0, double* uK, double* lo,
-                       double* hi) {
-  const int B = 64;
-  int rc = sc::ensure_buffers(g, B, sizeof(T), st);
+int closure_features_once(sc_graph* g, int B, hipStream_t st, float* X, double* s0, double* uK,
+                          double* lo, double* hi) {
+  int rc = sc::ensure_buffers(g, B, sizeof(T), 1, st);
   if (rc) return rc;
   rc = sc::ensure_closure_buffers(g, sizeof(T));
   if (rc) return rc;
@@ -428,9 +427,18 @@ int closure_features_t(sc_graph* g, hipStream_t st, float* X, double* s0, double
   if (rc) return rc;
   const int64_t m = g->d.m;
   double* base = g->cl_s0;
-  sc::Runner<T> R{g, B, st, false};
+  sc::Runner<T> R{g, B, 1, st, false};
   return record_and_features<T>(g, B, st, lam, X ? X : g->feat, s0 ? s0 : base,
                                 uK ? uK : base + m, lo ? lo : base + 2 * m, hi ? hi : base + 3 * m, R);
+}
+
+template <typename T>
+int closure_features_t(sc_graph* g, hipStream_t st, float* X, double* s0, double* uK, double* lo,
+                       double* hi) {
+  const int B = 64;
+  return sc::with_smaller_groups(g, B, sizeof(T), st, [&] {
+    return closure_features_once<T>(g, B, st, X, s0, uK, lo, hi);
+  });
 }
 
 template <typename T>
@@ -442,7 +450,7 @@ int learned_t(sc_graph* g, double eps, const sc_options& o, double* out_user, sc
   if (!o.mlp) return fail(SC_EINVAL, "SC_LEARNED needs options.mlp");
   const sc_mlp* net = o.mlp;
   const bool dev_ptrs = (o.flags & SC_DEVICE_PTRS) != 0;
-  int rc = sc::ensure_buffers(g, B, sizeof(T), st);
+  int rc = sc::ensure_buffers(g, B, sizeof(T), 1, st);
   if (rc) return rc;
   rc = sc::ensure_closure_buffers(g, sizeof(T));
   if (rc) return rc;
@@ -474,7 +482,7 @@ int learned_t(sc_graph* g, double eps, const sc_options& o, double* out_user, sc
   HIP_TRY(hipMemcpyAsync(&capped_h, capped, sizeof(capped_h), hipMemcpyDeviceToHost, st));
   HIP_TRY(sc::launch_gacc_init(g->d, g->tau_slot, 1, g->gacc, st));
 
-  sc::Runner<T> R{g, B, st, (o.flags & SC_TIME_KERNELS) != 0};
+  sc::Runner<T> R{g, B, 1, st, (o.flags & SC_TIME_KERNELS) != 0};
   R.stats.block = B;
   R.stats.tilde_tau = -1;
   R.stats.tilde_min = -1;
@@ -588,7 +596,12 @@ int dataset_t(sc_graph* g, int L_ref, hipStream_t st, float* X, float* z, float*
 }  // namespace
 
 int sc::run_learned(sc_graph* g, double eps, const sc_options& o, double* out, sc_stats* st) {
-  return o.precision == 1 ? learned_t<double>(g, eps, o, out, st) : learned_t<float>(g, eps, o, out, st);
+  return sc::with_smaller_groups(
+      g, o.block > 0 ? o.block : 64, o.precision == 1 ? sizeof(double) : sizeof(float),
+      static_cast<hipStream_t>(o.stream), [&] {
+        return o.precision == 1 ? learned_t<double>(g, eps, o, out, st)
+                                : learned_t<float>(g, eps, o, out, st);
+      });
 }
 
 extern "C" int sc_closure_features(sc_graph* g, int precision, float* X, double* s0, double* uK,
