@@ -1248,13 +1248,17 @@ PipeLayout pipe_layout(const sc_graph* g, int B, size_t tsize, int sets) {
   const int64_t nblocks = (n + B - 1) / B;
   int64_t group = static_cast<int64_t>(kGroupBytes / (2 * yb));
   group = std::max<int64_t>(group, kMinGroup);
-  while (group > 1 && 2 * kPipeSets * group * yb > kPipeBudgetBytes) --group;
+  while (group > 1 && 2 * sets * group * yb > kPipeBudgetBytes) --group;
   group = std::min<int64_t>({group, nblocks, kMaxGroup});
   if (g->group_limit > 0)
     group = std::min<int64_t>(group, std::max<int64_t>(1, g->group_limit / (2 * yb)));
-  // whole rounds of the 8 XCDs (a block is tsize / 2 slices when B = 64)
+  // whole rounds of the 8 XCDs (a block is tsize / 2 slices when B = 64), or a count of
+  // slices that divides them: 3 blocks of 2 slices would leave two XCDs idle (BA n =
+  // 600,000, k = 2: TGT L = 3 940 ms with 3 blocks, 774 with 4; TGT+ 2,792 with 3, 2,385
+  // with 2)
   const int64_t unit = std::max<int64_t>(1, 16 / static_cast<int64_t>(tsize));
   if (group > unit && group < nblocks) group = group / unit * unit;
+  while (group < unit && group < nblocks && unit % group) --group;
   l.group = static_cast<int>(group);
   l.tail_group = static_cast<int>(std::min<int64_t>(
       group, std::max<int64_t>(1, static_cast<int64_t>(kTailBytes / col_scratch_bytes(col_parts(n))))));
