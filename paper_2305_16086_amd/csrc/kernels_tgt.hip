@@ -429,14 +429,18 @@ __device__ inline void wg_finish(const RowArgs<T>& a, const Task& tk, T sum, int
 //
 // A launch covers every block of a group (up to kMaxGroup): the launch and drain of
 // a step and its longest row's chain of dependent loads are paid once per group.
-// kTwoHopBig: the two-hop step of graphs whose bitmap is too large for LDS.
-enum StepMode { kFull, kSkip, kTwoHop, kTwoHopBig };
+//
+// All this is for states of which an L2 holds a good part; larger graphs go by kTwoHopBig
+// and kSkipBig (whole_rows), and by kFull one slice after the other (kBitmapNodes).
+enum StepMode { kFull, kSkip, kTwoHop, kTwoHopBig, kSkipBig };
 constexpr bool is_twohop(int mode) { return mode == kTwoHop || mode == kTwoHopBig; }
+constexpr bool is_skip(int mode) { return mode == kSkip || mode == kSkipBig; }
 
 template <typename T>
 struct StepArgs {
   int n;
   SliceGrid slices;            // light rows of the blocks' slices
+  bool in_order;               // slice after slice over the whole chip instead
   int heavy_wgs;               // workgroups of the heavy tasks (multiple of 8, before the slices)
   int light_wgs;               // workgroups of the slices
   int acc_wgs;                 // workgroups of the accumulation, then the mask update
@@ -503,18 +507,18 @@ struct RowSource {
     rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0,
                                              static_cast<uint32_t>(n_) << kShift, 0x00020000);
   }
-  // 16 bytes of row u, zeros for u == n
-  __device__ Vec16<T> load(int u) const {
+  // 16 bytes of row u, `at` bytes after the lane's own, zeros for u == n
+  __device__ Vec16<T> load(int u, uint32_t at = 0) const {
     if constexpr (kWide) {
       if (u < n)
-        return *reinterpret_cast<const Vec16<T>*>(base + ((static_cast<size_t>(u) << kShift) + coff));
+        return *reinterpret_cast<const Vec16<T>*>(base + ((static_cast<size_t>(u) << kShift) + coff + at));
       Vec16<T> z;
 #pragma unroll
       for (int e = 0; e < static_cast<int>(16 / sizeof(T)); ++e) z.v[e] = T(0);
       return z;
     } else {
       const u32x4_t w = __builtin_amdgcn_raw_buffer_load_b128(
-          rsrc, (static_cast<uint32_t>(u) << kShift) + coff, 0, 0);
+          rsrc, (static_cast<uint32_t>(u) << kShift) + coff + at, 0, 0);
       return __builtin_bit_cast(Vec16<T>, w);
     }
   }
@@ -556,6 +560,86 @@ __device__ inline void twohop_step(unsigned long long hits, unsigned m, T w, int
   for (int e = 0; e < V; ++e) acc[e] += ((mk >> e) & 1u) ? wk : T(0);
 }
 
+// twohop_step for all slices of a row (m: the neighbour's whole mask)
+template <typename T, int k>
+__device__ inline void twohop_all(unsigned long long hits, unsigned long long m, T w, int c,
+                                  T (&acc)[sizeof(T) / 2][16 / sizeof(T)]) {
+  constexpr int V = 16 / sizeof(T), C = 8 * V, kSlices = 64 / C;
+  if ((hits & (0x0101010101010101ull << k)) == 0ull) return;   // wave-uniform
+  const unsigned lo = static_cast<unsigned>(row_lane<k>(static_cast<int>(m)));
+  const unsigned hi = static_cast<unsigned>(row_lane<k>(static_cast<int>(m >> 32)));
+  const T wk = row_lane_f<k>(w);
+#pragma unroll
+  for (int h = 0; h < kSlices; ++h) {
+    const unsigned mk = (h * C < 32 ? lo : hi) >> ((h * C & 31) + c * V);
+#pragma unroll
+    for (int e = 0; e < V; ++e) acc[h][e] += ((mk >> e) & 1u) ? wk : T(0);
+  }
+}
+
+// The next K of the slots of each row's chunk that `live` (bits of the row's 8 slots)
+// names, all slices of their rows: the loads in flight together, behind them what
+// `meanwhile` issues, then added in slot order.  Dead slots cost no load: a row has its
+// own k-th live slot in step k, zeros where it has none.
+template <typename T, int K, typename Src, typename F>
+__device__ inline void gather_live(const Src& src, int n, int ids, unsigned& live, int lane,
+                                   T (&acc)[sizeof(T) / 2][16 / sizeof(T)], F meanwhile) {
+  constexpr int V = 16 / sizeof(T), kSlices = static_cast<int>(sizeof(T)) / 2;
+  Vec16<T> v[K][kSlices];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int x = __shfl(ids, (lane & 56) + __builtin_ctz(live | 128u), 64);
+    const int u = live ? x : n;
+    live &= live - 1u;
+#pragma unroll
+    for (int h = 0; h < kSlices; ++h) v[k][h] = src.load(u, h * 128);
+  }
+  meanwhile();
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+#pragma unroll
+    for (int h = 0; h < kSlices; ++h)
+#pragma unroll
+      for (int e = 0; e < V; ++e) acc[h][e] += v[k][h].v[e];
+}
+
+// What a wave that strides over the groups of rows has fetched of those to come: the
+// list of the group after next; the list, rows, 1/degree and first ids of the next.
+template <typename T>
+struct GroupAhead {
+  int2 g0, g1;
+  int row, ids;
+  T iv;
+  __device__ int2 list(const StepArgs<T>& a, int x) const {
+    return x < a.ngrp ? a.grp[x] : make_int2(0, 0);
+  }
+  __device__ void rest(const StepArgs<T>& a, int x, int lane) {   // of group x, whose list is g0
+    row = a.n;
+    ids = a.n;
+    iv = T(0);
+    if (x < a.ngrp) {
+      row = a.grow[x * 8 + (lane >> 3)];
+      iv = a.ginv[x * 8 + (lane >> 3)];
+      if (g0.y > 0) ids = a.gnb[static_cast<int64_t>(g0.x) * 64 + lane];
+    }
+  }
+  __device__ void start(const StepArgs<T>& a, int x, int stride, int lane) {
+    g0 = list(a, x);
+    g1 = list(a, x + stride);
+    rest(a, x, lane);
+  }
+  __device__ void take(const StepArgs<T>& a, int x, int stride, int lane, int2* g, int* row_x,
+                       T* iv_x, int* ids_x) {
+    *g = g0;
+    *row_x = row;
+    *iv_x = iv;
+    *ids_x = ids;
+    g0 = g1;
+    g1 = list(a, x + 2 * stride);
+    rest(a, x + stride, lane);
+  }
+};
+
 // The light rows of slice sl: groups wg * 4 + wave, + 4 wgs, ...
 template <typename T, int MODE, bool kWide>
 __device__ inline void light_rows(const StepArgs<T>& a, int sl, int wg, int wgs, int lane, int wave,
@@ -567,9 +651,8 @@ __device__ inline void light_rows(const StepArgs<T>& a, int sl, int wg, int wgs,
   const int buf = a.blocks.b[i].buf;
   const int n = a.n;
   const int words = (n + 31) / 32;
-  const unsigned* __restrict__ am =
-      is_twohop(MODE) ? a.anymask + static_cast<size_t>(i) * a.awords : nullptr;
   if constexpr (MODE == kTwoHop) {
+    const unsigned* __restrict__ am = a.anymask + static_cast<size_t>(i) * a.awords;
     for (int q = threadIdx.x; q < words; q += kThreads) s_bits[q] = am[q];
     __syncthreads();
   } else if constexpr (MODE == kSkip) {
@@ -587,23 +670,38 @@ __device__ inline void light_rows(const StepArgs<T>& a, int sl, int wg, int wgs,
   const int r = lane >> 3, c = lane & 7;
   const uint32_t coff = static_cast<uint32_t>(h * 128 + c * 16);
   [[maybe_unused]] const RowSource<T, kWide> src(a.Yp + buf * a.ystride, n, coff);
-  for (int gi = wg * kWavesPerBlock + wave; gi < a.ngrp; gi += wgs * kWavesPerBlock) {
-    const int2 g = a.grp[gi];
-    const int row = a.grow[gi * 8 + r];
-    const T iv = a.ginv[gi * 8 + r];
+  // The two-hop step has little to do for a group of rows but wait for the chain of its
+  // list, rows and ids: the list is fetched two groups ahead, the rest one ahead (BA n =
+  // 100,000, k = 3, TGT L = 3: 16.2 -> 14.4 ms a call).
+  constexpr bool kAhead = MODE == kTwoHop;
+  const int stride = wgs * kWavesPerBlock;
+  int gi = wg * kWavesPerBlock + wave;
+  [[maybe_unused]] GroupAhead<T> ahead;
+  if constexpr (kAhead) ahead.start(a, gi, stride, lane);
+  for (; gi < a.ngrp; gi += stride) {
+    int2 g;
+    int row;
+    [[maybe_unused]] int first = 0;
+    T iv;
+    if constexpr (kAhead) {
+      ahead.take(a, gi, stride, lane, &g, &row, &iv, &first);
+    } else {
+      g = a.grp[gi];
+      row = a.grow[gi * 8 + r];
+      iv = a.ginv[gi * 8 + r];
+    }
     const int32_t* __restrict__ p = a.gnb + static_cast<int64_t>(g.x) * 64 + lane;
     T acc[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) acc[e] = T(0);
-    if constexpr (is_twohop(MODE)) {
+    if constexpr (MODE == kTwoHop) {
       const unsigned long long* __restrict__ mask = a.mask + static_cast<size_t>(i) * n;
       const int nch = (g.y + 7) >> 3;
-      int next = p[0];
+      int next = first;
       for (int ch = 0; ch < nch; ++ch) {
         const int u = next;
         if (ch + 1 < nch) next = p[ch * 64 + 64];
-        const bool hit =
-            u < n && (((MODE == kTwoHop ? s_bits[u >> 5] : am[u >> 5]) >> (u & 31)) & 1u);
+        const bool hit = u < n && ((s_bits[u >> 5] >> (u & 31)) & 1u);
         if (__ballot(hit) == 0ull) continue;
         unsigned m = 0;
         T w = T(0);
@@ -658,7 +756,7 @@ __device__ inline void light_rows(const StepArgs<T>& a, int sl, int wg, int wgs,
         add_chunk<T, 4>(v0, acc);
       }
     }
-    if (is_twohop(MODE)) {
+    if (MODE == kTwoHop) {
       bool any = false;
 #pragma unroll
       for (int e = 0; e < V; ++e) any |= acc[e] != T(0);
@@ -673,6 +771,93 @@ __device__ inline void light_rows(const StepArgs<T>& a, int sl, int wg, int wgs,
       for (int e = 0; e < V; ++e) o.v[e] = acc[e] * iv;
       char* Yn = reinterpret_cast<char*>(a.Yn + buf * a.ystride);
       *reinterpret_cast<Vec16<T>*>(Yn + (static_cast<size_t>(row) * (64 * sizeof(T)) + coff)) = o;
+    }
+  }
+}
+
+// The light rows of block i in the two steps that test neighbours, beyond kBitmapNodes:
+// all slices of a row at once, so that the tests, which come from memory there (the bitmap
+// of the sources' neighbours; the first slice's flags, written here for whole rows), are
+// made once per neighbour.  Per block of BA n = 400,000, k = 10: two-hop step 42 us, the
+// step after it 92 (95 and 258 by slices and without flags; 49 and 90 with a kernel that
+// takes a run of rows a wave, a lane per column).
+template <typename T, int MODE>
+__device__ inline void whole_rows(const StepArgs<T>& a, int i, int wg, int wgs, int lane, int wave) {
+  constexpr int V = 16 / sizeof(T);
+  constexpr int C = 8 * V;
+  constexpr int kSlices = 64 / C;
+  constexpr int kSlots = 16 / kSlices;     // slots of a row in flight (16 loads)
+  const int buf = a.blocks.b[i].buf;
+  const int n = a.n;
+  const int r = lane >> 3, c = lane & 7;
+  uint8_t* __restrict__ flags = a.nz + static_cast<size_t>(buf) * kSlices * a.nzs;
+  const RowSource<T, false> src(a.Yp + buf * a.ystride, n, static_cast<uint32_t>(c * 16));
+  char* __restrict__ Yn = reinterpret_cast<char*>(a.Yn + buf * a.ystride);
+  const int stride = wgs * kWavesPerBlock;
+  int gi = wg * kWavesPerBlock + wave;
+  GroupAhead<T> ahead;
+  ahead.start(a, gi, stride, lane);
+  // kSkipBig: the flags of a chunk are fetched behind the gathers of the one before
+  auto flag_of = [&](int u) { return MODE == kSkipBig ? flags[min(u, n - 1)] : 0; };
+  [[maybe_unused]] int live = flag_of(ahead.ids);
+  for (; gi < a.ngrp; gi += stride) {
+    int2 g;
+    int row, next;
+    T iv;
+    ahead.take(a, gi, stride, lane, &g, &row, &iv, &next);
+    const int32_t* __restrict__ p = a.gnb + static_cast<int64_t>(g.x) * 64 + lane;
+    T acc[kSlices][V];
+#pragma unroll
+    for (int h = 0; h < kSlices; ++h)
+#pragma unroll
+      for (int e = 0; e < V; ++e) acc[h][e] = T(0);
+    const int nch = (g.y + 7) >> 3;
+    for (int ch = 0; ch < nch; ++ch) {
+      const int u = next;
+      if (ch + 1 < nch) next = p[ch * 64 + 64];
+      if constexpr (MODE == kTwoHopBig) {
+        const unsigned* __restrict__ am = a.anymask + static_cast<size_t>(i) * a.awords;
+        const bool hit = u < n && ((am[u >> 5] >> (u & 31)) & 1u);
+        const unsigned long long hits = __ballot(hit);   // joined to a source of the block
+        if (hits == 0ull) continue;
+        unsigned long long m = 0;
+        T w = T(0);
+        if (hit) {
+          m = a.mask[static_cast<size_t>(i) * n + u];
+          w = a.inv[u];
+        }
+        twohop_all<T, 0>(hits, m, w, c, acc);
+        twohop_all<T, 1>(hits, m, w, c, acc);
+        twohop_all<T, 2>(hits, m, w, c, acc);
+        twohop_all<T, 3>(hits, m, w, c, acc);
+        twohop_all<T, 4>(hits, m, w, c, acc);
+        twohop_all<T, 5>(hits, m, w, c, acc);
+        twohop_all<T, 6>(hits, m, w, c, acc);
+        twohop_all<T, 7>(hits, m, w, c, acc);
+      } else {
+        // the rows' live slots, four at a time
+        unsigned bits = static_cast<unsigned>(__ballot(u < n && live != 0) >> (lane & 56)) & 0xFFu;
+        live = flag_of(ch + 1 < nch ? next : ahead.ids);
+        while (__ballot(bits != 0u) != 0ull) gather_live<T, 4>(src, n, u, bits, lane, acc, [] {});
+      }
+    }
+    if constexpr (MODE == kTwoHopBig) {
+      bool any = false;
+#pragma unroll
+      for (int h = 0; h < kSlices; ++h)
+#pragma unroll
+        for (int e = 0; e < V; ++e) any |= acc[h][e] != T(0);
+      const unsigned long long b = __ballot(any);
+      if (c == 0 && row < n) flags[row] = (b >> (8 * r)) & 0xFFull ? 1 : 0;
+    }
+    if (row < n) {
+#pragma unroll
+      for (int h = 0; h < kSlices; ++h) {
+        Vec16<T> o;
+#pragma unroll
+        for (int e = 0; e < V; ++e) o.v[e] = acc[h][e] * iv;
+        *reinterpret_cast<Vec16<T>*>(Yn + (static_cast<size_t>(row) * (64 * sizeof(T)) + h * 128 + c * 16)) = o;
+      }
     }
   }
 }
@@ -761,7 +946,7 @@ __device__ inline void heavy_rows(const StepArgs<T>& a, int i, int t, int lane, 
     if (static_cast<int>(threadIdx.x) < kSlices)   // heavy rows count as nonzero
       nz[static_cast<size_t>(threadIdx.x) * a.nzs + tk.row] = 1;
   } else {
-    sum = gather_pieces<T, 64, MODE == kSkip>(ra, a.Yp + buf * a.ystride, tk.beg, tk.end, wave,
+    sum = gather_pieces<T, 64, is_skip(MODE)>(ra, a.Yp + buf * a.ystride, tk.beg, tk.end, wave,
                                               kWavesPerBlock, lane, lane, 0, nz, a.nzs);
   }
   wg_finish<T, 64>(ra, tk, sum, wave, lane, a.Yn + buf * a.ystride);
@@ -790,16 +975,27 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
   }
   w -= a.heavy_wgs;
   if (w < a.light_wgs) {
-    int sl, wg, wgs;
-    if (!a.slices.decode(w, &sl, &wg, &wgs)) return;
-    if constexpr (!is_twohop(MODE)) {
-      constexpr int kSlices = static_cast<int>(sizeof(T)) / 2;
-      if ((a.last >> (sl / kSlices)) & 1u) {
-        last_rows<T, kWide>(a, sl, wg, wgs, lane, wave);
+    if constexpr (MODE == kTwoHopBig || MODE == kSkipBig) {   // block after block
+      const int wgs = a.slices.slice_wgs;
+      whole_rows<T, MODE>(a, w / wgs, w % wgs, wgs, lane, wave);
+    } else {
+      int sl, wg, wgs;
+      if (a.in_order) {
+        wgs = a.slices.slice_wgs;
+        sl = w / wgs;
+        wg = w % wgs;
+      } else if (!a.slices.decode(w, &sl, &wg, &wgs)) {
         return;
       }
+      constexpr int kSlices = static_cast<int>(sizeof(T)) / 2;
+      if constexpr (MODE != kTwoHop) {
+        if ((a.last >> (sl / kSlices)) & 1u) {
+          last_rows<T, kWide>(a, sl, wg, wgs, lane, wave);
+          return;
+        }
+      }
+      light_rows<T, MODE, kWide>(a, sl, wg, wgs, lane, wave, s_bits);
     }
-    light_rows<T, MODE, kWide>(a, sl, wg, wgs, lane, wave, s_bits);
     return;
   }
   w -= a.light_wgs;
@@ -1073,10 +1269,17 @@ hipError_t launch_step(const DeviceGraph& g, int B, const StepJob<T>& job, hipSt
   a.slices.slice_wgs = a.slices.rem_wgs = groups_wgs;
   size_t lds = 0;
   const bool all_last = job.last != 0 && job.last == static_cast<uint32_t>((1ull << nb) - 1);
-  const bool skip = job.skip && step_can_skip(g.n) && !all_last;
-  const bool big = twohop && !step_can_skip(g.n);
-  if ((twohop && !big) || skip) {
-    // the bitmap's workgroups: as many as are resident on the slice's XCDs (32 CUs
+  const bool wide = static_cast<uint64_t>(g.n) * 64 * sizeof(T) > job.buffer_bytes;
+  const bool big = g.n > job.bitmap_nodes;   // no bitmap in LDS
+  // (the registers of last_rows would halve the waves of kSkipBig: not with last blocks)
+  const bool skip = job.skip && !all_last && !(big && (wide || job.last));
+  a.in_order = big && !all_last;
+  if ((twohop || skip) && big) {
+    // workgroups that stride over a block's rows, as many as the chip holds
+    a.slices.nslices = nb;
+    a.slices.slice_wgs = std::min(groups_wgs, 256 * 8);
+  } else if (twohop || skip) {
+    // the same, with the bitmap: as many as are resident on the slice's XCDs (32 CUs
     // each, 160 KB of LDS, and 8 or 5 workgroups by registers)
     lds = static_cast<size_t>(awords) * 4;
     const int per_cu = static_cast<int>(
@@ -1093,7 +1296,7 @@ hipError_t launch_step(const DeviceGraph& g, int B, const StepJob<T>& job, hipSt
     a.slices.slice_wgs = a.slices.rem_wgs = wgs;
   }
   a.heavy_wgs = (nb * g.nwg + 7) / 8 * 8;
-  a.light_wgs = a.slices.size();
+  a.light_wgs = a.in_order ? a.slices.nslices * a.slices.slice_wgs : a.slices.size();
   a.grp = g.slice_grp;
   a.ngrp = g.nslice_grp;
   a.grow = g.slice_row;
@@ -1123,11 +1326,12 @@ hipError_t launch_step(const DeviceGraph& g, int B, const StepJob<T>& job, hipSt
   const int64_t grid = static_cast<int64_t>(a.heavy_wgs) + a.light_wgs + a.acc_wgs + mask_wgs;
   if (grid <= 0 || grid > INT_MAX) return hipErrorInvalidValue;
   const dim3 gd(static_cast<unsigned>(grid)), bd(kThreads);
-  const bool wide = static_cast<uint64_t>(g.n) * 64 * sizeof(T) > 0xFFFFFC00ull;
-  if (big) {
+  if (twohop && big) {
     k_step<T, kTwoHopBig, false><<<gd, bd, 0, st>>>(a);
   } else if (twohop) {
     k_step<T, kTwoHop, false><<<gd, bd, lds, st>>>(a);
+  } else if (skip && big) {
+    k_step<T, kSkipBig, false><<<gd, bd, 0, st>>>(a);
   } else if (skip) {
     k_step<T, kSkip, false><<<gd, bd, lds, st>>>(a);
   } else if (!wide) {

@@ -1242,6 +1242,10 @@ namespace sc {
 PipeLayout pipe_layout(const sc_graph* g, int B, size_t tsize, int sets) {
   PipeLayout l;
   l.sets = sets;
+  if (const char* b = std::getenv("SC_STEP_BITMAP_NODES"))   // other limits (tests)
+    l.bitmap_nodes = std::max(0ll, std::min(240000ll, std::atoll(b)));
+  if (const char* b = std::getenv("SC_STEP_BUFFER_BYTES"))
+    l.buffer_bytes = std::min<uint64_t>(kBufferBytes, std::max(0ll, std::atoll(b)));
   const int64_t n = g->d.n;
   l.ystride = (n * B + 63) / 64 * 64;
   const size_t yb = static_cast<size_t>(l.ystride) * tsize;

@@ -62,6 +62,8 @@ struct PipeLayout {
   int group = 1;          // blocks per group
   int tail_group = 1;     // blocks per tail launch
   int64_t ystride = 0;    // elements per block state
+  int64_t bitmap_nodes = kBitmapNodes;         // see StepJob
+  uint64_t buffer_bytes = kBufferBytes;
   int bufs() const { return sets * group; }
 };
 
@@ -408,6 +410,8 @@ struct Runner {
     s.ystride = lay.ystride;
     s.partials = parts();
     s.nz = g->nz;
+    s.bitmap_nodes = lay.bitmap_nodes;
+    s.buffer_bytes = lay.buffer_bytes;
     par = 0;
     s.blocks = blocks;
     s.Yp = Y(1);   // not read
@@ -472,6 +476,8 @@ struct Runner {
     s.ystride = lay.ystride;
     s.partials = parts();
     s.nz = g->nz;
+    s.bitmap_nodes = lay.bitmap_nodes;
+    s.buffer_bytes = lay.buffer_bytes;
     HIP_TRY(launch_step<T>(g->d, B, s, st));
     par = 1 - par;
     return SC_OK;

@@ -231,11 +231,20 @@ hipError_t launch_mask_update(const DeviceGraph& g, int B, const MaskJob& mj, hi
 // Fills DeviceGraph::slice_nb from the CSR (the other slice arrays are set).
 hipError_t launch_fill_slices(const DeviceGraph& g, hipStream_t st);
 
-// Bytes between the row-flag arrays of StepJob::nz, and whether the step after the
-// two-hop step can skip zero rows (their bitmap has to leave five workgroups per CU
-// their LDS).
+// Bytes between the row-flag arrays of StepJob::nz.
 inline int64_t flag_stride(int64_t n) { return (n + 63) / 64 * 64; }
-inline bool step_can_skip(int64_t n) { return n <= 240000; }
+// Nodes up to which a launch goes by slices, each on its own XCDs, and the two-hop step and
+// the step after it test a bitmap in LDS.  Beyond, an L2 holds little of a slice and the
+// memory-side cache not all the states of a group: the chip takes one slice (in those two
+// steps, one block's whole rows) after the other.  BA, ms per call by slices / in order, k
+// edges per node; FP32 TGT L = 5: n = 100,000 k = 3 69 / 69, k = 10 136 / 151; 130,000 117 /
+// 112, 237 / 252; 160,000 181 / 165, 376 / 388; 200,000 294 / 252, 612 / 617.  TGT+ (lambda* =
+// 0.7): 100,000 172 / 167, 85 / 88; 130,000 284 / 272, 139 / 138; 160,000 429 / 402, 211 / 201;
+// 200,000 694 / 615, 308 / 300.  FP64 TGT L = 5: 60,000 51 / 50, 89 / 102; 100,000 138 / 124, 273 /
+// 289; 160,000 361 / 298, 751 / 751.
+constexpr int64_t kBitmapNodes = 140000;
+// State bytes that a buffer descriptor's 32-bit offsets reach.
+constexpr uint64_t kBufferBytes = 0xFFFFFC00ull;
 
 // One step of a group of blocks: Yn = P Yp, or with mask the two-hop state
 // Yn = P P Y0 of the indicators from the neighbour masks.  acc accumulates the
@@ -249,9 +258,11 @@ struct StepJob {
   T* partials = nullptr;         // [buf][nparts * B]
   // B = 64: the two-hop step writes nz[buf][slice][x] = (the 128-byte slice of row x
   // has a nonzero; always 1 for heavy rows), flag_stride(n) bytes per slice; with skip,
-  // rows flagged 0 are exact zeros in Yp and are not gathered (where step_can_skip)
+  // rows flagged 0 are exact zeros in Yp and are not gathered
   uint8_t* nz = nullptr;
   bool skip = false;
+  int64_t bitmap_nodes = kBitmapNodes;
+  uint64_t buffer_bytes = kBufferBytes;
   // B = 64: bit i: of block i's new state only the rows of its sources and their
   // neighbours are read (its last step with nothing but the accumulation to follow);
   // the light ones among the other rows are not written
