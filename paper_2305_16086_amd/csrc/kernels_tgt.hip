@@ -1250,8 +1250,8 @@ hipError_t launch_step(const DeviceGraph& g, int B, const StepJob<T>& job, hipSt
                                     job.anymask + i * awords, job.Yn + off)));
       } else {
         SC_DISPATCH_B_NARROW(B, (hipExtLaunchKernelGGL(k_propagate<T, kB>, dim3(grid),
-                                                       dim3(kThreads), 0, st, job.ev_start,
-                                                       job.ev_stop, 0, a, job.Yp + off,
+                                                       dim3(kThreads), 0, st, job.ev[i].start,
+                                                       job.ev[i].stop, 0, a, job.Yp + off,
                                                        job.Yn + off)));
       }
       const hipError_t e = hipGetLastError();
@@ -1335,9 +1335,11 @@ hipError_t launch_step(const DeviceGraph& g, int B, const StepJob<T>& job, hipSt
   } else if (skip) {
     k_step<T, kSkip, false><<<gd, bd, lds, st>>>(a);
   } else if (!wide) {
-    hipExtLaunchKernelGGL((k_step<T, kFull, false>), gd, bd, 0, st, job.ev_start, job.ev_stop, 0, a);
+    hipExtLaunchKernelGGL((k_step<T, kFull, false>), gd, bd, 0, st, job.ev[0].start,
+                          job.ev[0].stop, 0, a);
   } else {
-    hipExtLaunchKernelGGL((k_step<T, kFull, true>), gd, bd, 0, st, job.ev_start, job.ev_stop, 0, a);
+    hipExtLaunchKernelGGL((k_step<T, kFull, true>), gd, bd, 0, st, job.ev[0].start,
+                          job.ev[0].stop, 0, a);
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -449,20 +449,22 @@ struct Runner {
         }
       }
       const bool dense = !s.skip && s.last == 0;   // every row of every block
-      const bool timed = timing && dense && stats.prop_launches % kTimeEvery == 0;
-      s.ev_start = s.ev_stop = nullptr;
-      if (timed) {
-        const int rc = event_pair(&s.ev_start, &s.ev_stop);
-        if (rc) return rc;
-      }
       s.blocks = having(ell);
+      const int launches = B == 64 ? 1 : s.blocks.nb;   // of one block each below 64
+      for (int i = 0; i < launches; ++i) {
+        s.ev[i] = {};
+        if (timing && dense && (stats.prop_launches + i) % kTimeEvery == 0) {
+          const int rc = event_pair(&s.ev[i].start, &s.ev[i].stop);
+          if (rc) return rc;
+        }
+      }
       s.Yp = Y(par);
       s.Yn = Y(1 - par);
       s.acc = pending;
       s.mj = ell == 3 ? next_masks() : MaskJob{};
       HIP_TRY(launch_step<T>(g->d, B, s, st));
       if (dense) {
-        ++stats.prop_launches;
+        stats.prop_launches += launches;
         stats.prop_bytes += step_bytes() * s.blocks.nb;
       }
       par = 1 - par;

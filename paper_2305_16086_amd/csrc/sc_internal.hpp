@@ -271,7 +271,11 @@ struct StepJob {
   const unsigned* anymask = nullptr;          // [i][ceil(n/32)]
   AccJob acc;
   MaskJob mj;
-  hipEvent_t ev_start = nullptr, ev_stop = nullptr;   // the row kernel's own start and end
+  // the row kernel's own start and end (B < 64: those of each block's kernel)
+  struct Events {
+    hipEvent_t start = nullptr, stop = nullptr;
+  };
+  Events ev[kMaxGroup];
 };
 template <typename T>
 hipError_t launch_step(const DeviceGraph& g, int B, const StepJob<T>& job, hipStream_t st);
