@@ -305,7 +305,7 @@ int sc_all_edges_ex(sc_graph* g, double eps, int L, const sc_options* o, double*
  * count of a half above which a workgroup sums its chunk sums (default 256),
  * SC_SOURCE_LDS_CHUNKS the chunk count of a batch from which its walks keep
  * the column in LDS, SC_SOURCE_HEAVY_VOLUME the edges of a push above which a
- * source of a small launch is stepped by many workgroups (default 262144).
+ * source is stepped by many workgroups (default 262144).
  */
 
 /*

@@ -17,10 +17,9 @@
 // threshold by radix select, rho-hat over the candidate edges, extremes over
 // N(i), N(j) and V), the walk counts of Eq. 13, and Eq. 14's two sides; the
 // first l where the frontier volume exceeds the walk work becomes tilde_tau_i.
-// Where a launch has few sources, those that outgrow a workgroup go on in kernels that
-// step them together (k_heavy_*).  The walks of a wave of sources then run flat over the
-// whole GPU (chunks of 64 walk pairs, fixed-order sums), reading q from the sources'
-// slots.
+// Sources that outgrow a workgroup go on in kernels that step them together (k_heavy_*).
+// The walks of a wave of sources then run flat over the whole GPU (chunks of 64 walk pairs,
+// fixed-order sums), reading q from the sources' slots.
 #include "sc_internal.hpp"
 #include "walk.hpp"
 
@@ -795,8 +794,8 @@ __global__ __launch_bounds__(kT) void k_src_head(SrcArgs a) {
 }
 
 // ---------------------------------------------------------------- heavy sources
-// Sources whose pushes outgrow one workgroup: where a launch has few sources, the slowest
-// would be alone on its CU (0.57 G pushed edges a second) while the others idle.
+// Sources whose pushes outgrow one workgroup: the slowest of a launch would be alone on its
+// CU (0.57 G pushed edges a second) while the others idle.
 // k_src_head leaves such a source in `heavy`, and the host runs rounds of four launches,
 // one step of all of them, each over `gridDim.x` workgroups per source (blockIdx.y):
 // k_heavy_push (Eq. 14's decision of the last round first; who is done is finished

@@ -388,7 +388,7 @@ struct SrcArgs {
   int gamma = 10;
   int rule = 0;                    // 0: Eq. 14 as printed (walk pairs), 1: walk steps
   int force_tilde = -1;            // >= 0: switch at min(force_tilde, tau_p) instead
-  SrcHeavy* heavy = nullptr;       // [sources of the launch] (null: every source ends here)
+  SrcHeavy* heavy = nullptr;       // [sources of the launch] (null: each ends in its head)
   int32_t* heavy_ctl = nullptr;    // [2] sources in heavy, of those not done
   uint64_t heavy_vol = 0;          // a push of more edges is left to the heavy kernels
 };

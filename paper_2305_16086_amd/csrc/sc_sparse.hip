@@ -23,11 +23,12 @@ using sc::fail;
 namespace {
 
 constexpr int kMaxSlots = 2048;
-// Of a launch of up to kHeavyMaxSources, a source whose next push has more than
-// kHeavyVolume edges goes on in the heavy kernels, kHeavyRounds steps between two looks
-// of the host at what is left (heads of 512 sources of R-MAT scale 15, ms, with 16 k, 64 k,
-// 256 k, 512 k and 1 M edges: 9.2, 8.7, 7.7, 8.6 and 31.9).
-constexpr int kHeavyMaxSources = 512;
+// A source whose next push has more than kHeavyVolume edges goes on in the heavy kernels,
+// kHeavyRounds steps between two looks of the host at what is left (heads of 512 sources of
+// R-MAT scale 15, ms, with 16 k, 64 k, 256 k, 512 k and 1 M edges: 9.2, 8.7, 7.7, 8.6 and
+// 31.9).  All of a launch may: calls on that graph with 513, 1,024, 2,048 and 8,192
+// sources took 71.6, 118, 223 and 823 ms with heads alone, 74 (700), 110, 216 and 802
+// with up to 256 sources left over and 39.7, 82, 159 and 602 with no limit.
 constexpr uint64_t kHeavyVolume = 262144;
 constexpr int kHeavyRounds = 4;
 constexpr int64_t kPartCapacity = int64_t(1) << 24;   // chunk sums of one wave (128 MiB)
@@ -54,7 +55,7 @@ struct SrcBufs {
   int64_t part_capacity = 0;
   int64_t* ctl = nullptr;
   unsigned long long* totals = nullptr;
-  sc::SrcHeavy* heavy = nullptr;   // [min(slots, kHeavyMaxSources)] (null: not split)
+  sc::SrcHeavy* heavy = nullptr;   // [W] (null: every source ends in its head)
   int32_t* heavy_ctl = nullptr;
   int32_t* list = nullptr;    // source list (null: all)
   int64_t* hoff = nullptr;
@@ -201,8 +202,8 @@ int enqueue_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
     const int cnt = static_cast<int>(std::min<int64_t>(B.W, nsrc - b));
     a.list_base = b;
     a.pos_base = at(b);
-    // few sources: those that outgrow a workgroup are left over and stepped together
-    const bool split = B.heavy && cnt <= kHeavyMaxSources;
+    // sources that outgrow a workgroup are left over and stepped together
+    const bool split = B.heavy != nullptr;
     a.heavy = split ? B.heavy : nullptr;
     a.heavy_ctl = B.heavy_ctl;
     if (split) HIP_TRY(sc::launch_fill_u32(reinterpret_cast<uint32_t*>(B.heavy_ctl), 2, 0, st));
@@ -359,7 +360,7 @@ int sc::run_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
   HIP_TRY(grow(&sb.part, &sb.part_cap, static_cast<size_t>(kPartCapacity)));
   HIP_TRY(grow(&sb.ctl, &sb.ctl2_cap, size_t(3)));
   HIP_TRY(grow(&sb.totals, &sb.tot_cap, size_t(kTotals)));
-  HIP_TRY(grow(&sb.heavy, &sb.heavy_cap, static_cast<size_t>(std::min(B.W, kHeavyMaxSources))));
+  HIP_TRY(grow(&sb.heavy, &sb.heavy_cap, static_cast<size_t>(B.W)));
   HIP_TRY(grow(&sb.heavy_ctl, &sb.heavy_ctl_cap, size_t(2)));
   HIP_TRY(grow(&sb.list, &sb.list_cap, static_cast<size_t>(nsrc)));
   HIP_TRY(grow(&sb.hoff, &sb.hoff_cap, static_cast<size_t>(nsrc) + 1));
