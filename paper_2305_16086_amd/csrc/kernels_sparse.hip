@@ -39,9 +39,6 @@ constexpr int kShortRow = 128;    // N(j) up to this is scanned by 16 lanes, up 
 constexpr int kLongRow = 2048;    // wave, and a longer one by the whole workgroup
 constexpr int kHubEdges = 1024;   // a longer list is pushed by the whole workgroup
 constexpr int kLongList = 1024;
-// Graphs of up to this many nodes keep both columns in LDS (64 KB, two workgroups a CU):
-// the pushes are LDS atomics then (3,000 nodes, 3,000 sources in two launches: 589 -> 425 us).
-constexpr int kLdsColumns = 4096;
 constexpr int kCandList = 64;     // rho candidates whose pairs are looked up one by one
 
 // Lanes of one wave share LDS without a barrier: their LDS operations are in
@@ -1470,8 +1467,8 @@ hipError_t launch_src_head(const SrcArgs& a, int grid, hipStream_t st) {
   // A source's time is that of one workgroup's chain of phases, so it gets as many
   // threads as leave every source of the launch a place on the chip at once (512 sources
   // of R-MAT scale 15: 34.1 ms with 512 threads, 31.8 with 1,024; 1,500 of n = 3,000: 308
-  // us with 512, 289 with 256).  Up to kLdsColumns nodes, both columns are kept in LDS.
-  if (a.n <= kLdsColumns) {
+  // us with 512, 289 with 256).  Up to kSrcLdsColumns nodes, both columns are kept in LDS.
+  if (a.n <= kSrcLdsColumns) {
     k_src_head<512, true><<<grid, 512, static_cast<size_t>(a.n) * 16, st>>>(a);
   } else if (grid <= 512) {
     k_src_head<1024, false><<<grid, 1024, 0, st>>>(a);

@@ -151,7 +151,6 @@ void sc_graph::release() {
   sc::dev_free(src.ctl);
   sc::dev_free(src.totals);
   sc::dev_free(src.heavy);
-  sc::dev_free(src.heavy_ctl);
   sc::dev_free(src.list);
   sc::dev_free(src.hoff);
   src = SourceBuffers{};

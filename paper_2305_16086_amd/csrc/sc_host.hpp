@@ -180,8 +180,6 @@ struct sc_graph {
     size_t tot_cap = 0;
     sc::SrcHeavy* heavy = nullptr;
     size_t heavy_cap = 0;
-    int32_t* heavy_ctl = nullptr;
-    size_t heavy_ctl_cap = 0;
     int32_t* list = nullptr;
     size_t list_cap = 0;
     int64_t* hoff = nullptr;

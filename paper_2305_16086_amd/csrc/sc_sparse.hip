@@ -53,10 +53,9 @@ struct SrcBufs {
   int64_t* chunk_off = nullptr;
   double* part = nullptr;
   int64_t part_capacity = 0;
-  int64_t* ctl = nullptr;
+  int64_t* ctl = nullptr;     // chunks, whether they fit, units drawn, heavy sources (2 x 32 bits)
   unsigned long long* totals = nullptr;
   sc::SrcHeavy* heavy = nullptr;   // [W] (null: every source ends in its head)
-  int32_t* heavy_ctl = nullptr;
   int32_t* list = nullptr;    // source list (null: all)
   int64_t* hoff = nullptr;
   bool Q_clean = false;       // Q is known to be all zero
@@ -202,32 +201,41 @@ int enqueue_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
     const int cnt = static_cast<int>(std::min<int64_t>(B.W, nsrc - b));
     a.list_base = b;
     a.pos_base = at(b);
-    // sources that outgrow a workgroup are left over and stepped together
-    const bool split = B.heavy != nullptr;
+    // sources that outgrow a workgroup are left over and stepped together (none can where
+    // the columns are in LDS, the switch step is given or the whole graph is too small)
+    const bool split = B.heavy && n > sc::kSrcLdsColumns && o.tilde_tau < 0 &&
+                       static_cast<uint64_t>(S2) > a.heavy_vol;
     a.heavy = split ? B.heavy : nullptr;
-    a.heavy_ctl = B.heavy_ctl;
-    if (split) HIP_TRY(sc::launch_fill_u32(reinterpret_cast<uint32_t*>(B.heavy_ctl), 2, 0, st));
+    a.heavy_ctl = reinterpret_cast<int32_t*>(B.ctl + 3);
+    if (split) HIP_TRY(sc::launch_fill_u32(reinterpret_cast<uint32_t*>(B.ctl + 3), 2, 0, st));
     HIP_TRY(sc::launch_src_head(a, cnt, st));
-    if (split) {
-      int32_t left[2] = {0, 0};
-      for (;;) {
-        HIP_TRY(hipMemcpyAsync(left, B.heavy_ctl, sizeof(left), hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        if (left[1] <= 0) break;
-        HIP_TRY(sc::launch_src_heavy(a, left[0], kHeavyRounds, st));
-      }
-    }
     wa.P = at(b + cnt) - at(b);
     wa.nsources = cnt;
     if (walk_ev) HIP_TRY(hipEventRecord((*walk_ev)[2 * wave], st));
     if (batch_walks && wa.P > 0) {
       // the host reads the wave's chunk count and walks them in batches of the
       // buffer's capacity, so no half is left to a single wave however many
-      // walks it has
+      // walks it has; the same copy brings the sources left over, whose rounds
+      // come before the count is made again
+      int64_t ctl[4] = {};
+      int32_t left[2] = {0, 0};
+      const size_t words = split ? 4 : 1;
       HIP_TRY(sc::launch_src_scan(wa, st));
-      int64_t total = 0;
-      HIP_TRY(hipMemcpyAsync(&total, B.ctl, sizeof(total), hipMemcpyDeviceToHost, st));
+      HIP_TRY(hipMemcpyAsync(ctl, B.ctl, words * sizeof(int64_t), hipMemcpyDeviceToHost, st));
       HIP_TRY(hipStreamSynchronize(st));
+      std::memcpy(left, ctl + 3, sizeof(left));
+      if (left[1] > 0) {
+        while (left[1] > 0) {
+          HIP_TRY(sc::launch_src_heavy(a, left[0], kHeavyRounds, st));
+          HIP_TRY(hipMemcpyAsync(left, B.ctl + 3, sizeof(left), hipMemcpyDeviceToHost, st));
+          HIP_TRY(hipStreamSynchronize(st));
+        }
+        if (walk_ev) HIP_TRY(hipEventRecord((*walk_ev)[2 * wave], st));
+        HIP_TRY(sc::launch_src_scan(wa, st));
+        HIP_TRY(hipMemcpyAsync(ctl, B.ctl, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+      }
+      const int64_t total = ctl[0];
       for (int64_t c = 0; c < total; c += wa.capacity) {
         sc::SrcWalkArgs wb = wa;
         wb.cbeg = c;
@@ -358,10 +366,9 @@ int sc::run_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
   HIP_TRY(grow(&sb.nr_pos, &sb.nrp_cap, static_cast<size_t>(Pmax)));
   HIP_TRY(grow(&sb.chunk_off, &sb.co_cap, static_cast<size_t>(Pmax) + 1));
   HIP_TRY(grow(&sb.part, &sb.part_cap, static_cast<size_t>(kPartCapacity)));
-  HIP_TRY(grow(&sb.ctl, &sb.ctl2_cap, size_t(3)));
+  HIP_TRY(grow(&sb.ctl, &sb.ctl2_cap, size_t(4)));
   HIP_TRY(grow(&sb.totals, &sb.tot_cap, size_t(kTotals)));
   HIP_TRY(grow(&sb.heavy, &sb.heavy_cap, static_cast<size_t>(B.W)));
-  HIP_TRY(grow(&sb.heavy_ctl, &sb.heavy_ctl_cap, size_t(2)));
   HIP_TRY(grow(&sb.list, &sb.list_cap, static_cast<size_t>(nsrc)));
   HIP_TRY(grow(&sb.hoff, &sb.hoff_cap, static_cast<size_t>(nsrc) + 1));
   int32_t* tau_o = nullptr;
@@ -393,7 +400,6 @@ int sc::run_per_source(sc_graph* g, double eps, int L, const sc_options& o, doub
   B.ctl = sb.ctl;
   B.totals = sb.totals;
   B.heavy = sb.heavy;
-  B.heavy_ctl = sb.heavy_ctl;
   B.list = sb.list;
   B.hoff = sb.hoff;
   B.Q_clean = sb.clean;
@@ -534,7 +540,7 @@ size_t carve(unsigned char* base, int64_t n, int64_t S2, int W, int64_t P, SrcBu
   take(&b.tau_row, sizeof(int32_t) * n);
   take(&b.tilde_row, sizeof(int32_t) * n);
   take(&b.totals, sizeof(unsigned long long) * kTotals);
-  take(&b.ctl, sizeof(int64_t) * 3);
+  take(&b.ctl, sizeof(int64_t) * 4);
   take(&b.slot_ctl, sizeof(int32_t) * 2 * W);
   take(&b.Q, sizeof(uint64_t) * 2 * static_cast<size_t>(W) * n);
   take(&b.S, sizeof(int32_t) * 2 * static_cast<size_t>(W) * n);
