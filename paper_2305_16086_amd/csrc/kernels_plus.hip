@@ -539,27 +539,20 @@ __device__ inline double wave_sum(double v) {
 // Three loads in flight per lane keep the kernel at 32 VGPRs, beside the dense step's
 // waves on the other stream.
 constexpr int kWcBatch = 3;
+// Workgroups of a slice: beyond that many, waves take its slots in turn (kTurns; a block of
+// hubs would launch as many for every slice of the group, past the limit of 2^32 threads
+// with 64 hubs joined to 40,000 nodes).  The loop costs eight registers, BA n = 100,000
+// 0.8% of a call.
+constexpr int kCountBlocks = 4096;
+
 template <typename T, int B>
-__global__ __launch_bounds__(kThreads) void k_walk_counts(
-    SliceGrid sg, BlockList blocks, int n, int tilde, int gamma, double coef, long long nr_cap,
-    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
-    const int32_t* __restrict__ slot_row, const int32_t* __restrict__ deg,
-    const T* __restrict__ Yg, int64_t ystride, const ColStats* __restrict__ csg,
-    const int32_t* __restrict__ tau, long long* __restrict__ nr) {
-  constexpr int C = B < 128 / static_cast<int>(sizeof(T)) ? B : 128 / static_cast<int>(sizeof(T));
-  int sl, wg, wgs;
-  if (!sg.decode(static_cast<int>(blockIdx.x), &sl, &wg, &wgs)) return;
-  const int bi = sl / (B / C);
-  const BlockRef br = blocks.b[bi];
-  const T* __restrict__ Y = Yg + br.buf * ystride;
-  const ColStats* __restrict__ cs = csg + bi * 64;
-  const int s0 = br.s0;
-  const int lane = threadIdx.x & 63;
-  // the slots of the slice's sources
-  const int c0 = s0 + (sl % (B / C)) * C;
-  if (c0 >= n) return;
-  const int k = rowptr[c0] + wg * kWavesPerBlock + (threadIdx.x >> 6);
-  if (k >= rowptr[min(n, c0 + C)]) return;
+__device__ inline void slot_walk_count(int k, int lane, int s0, int tilde, int gamma, double coef,
+                                       long long nr_cap, const int32_t* __restrict__ rowptr,
+                                       const int32_t* __restrict__ col,
+                                       const int32_t* __restrict__ slot_row,
+                                       const int32_t* __restrict__ deg, const T* __restrict__ Y,
+                                       const ColStats* __restrict__ cs,
+                                       const int32_t* __restrict__ tau, long long* __restrict__ nr) {
   const int len = tau[k] - tilde;
   if (len <= 0) {
     if (lane == 0) nr[k] = 0;
@@ -606,6 +599,36 @@ __global__ __launch_bounds__(kThreads) void k_walk_counts(
   if (!(r >= 1.0)) r = 1.0;
   long long w = r > static_cast<double>(nr_cap) ? nr_cap : static_cast<long long>(r);
   nr[k] = w;
+}
+
+template <typename T, int B, bool kTurns>
+__global__ __launch_bounds__(kThreads) void k_walk_counts(
+    SliceGrid sg, BlockList blocks, int n, int tilde, int gamma, double coef, long long nr_cap,
+    const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+    const int32_t* __restrict__ slot_row, const int32_t* __restrict__ deg,
+    const T* __restrict__ Yg, int64_t ystride, const ColStats* __restrict__ csg,
+    const int32_t* __restrict__ tau, long long* __restrict__ nr) {
+  constexpr int C = B < 128 / static_cast<int>(sizeof(T)) ? B : 128 / static_cast<int>(sizeof(T));
+  int sl, wg, wgs;
+  if (!sg.decode(static_cast<int>(blockIdx.x), &sl, &wg, &wgs)) return;
+  const int bi = sl / (B / C);
+  const BlockRef br = blocks.b[bi];
+  // the slots of the slice's sources
+  const int c0 = br.s0 + (sl % (B / C)) * C;
+  if (c0 >= n) return;
+  const int end = rowptr[min(n, c0 + C)];
+  const int first = wg * kWavesPerBlock + static_cast<int>(threadIdx.x >> 6);
+  auto count = [&](int k) {
+    slot_walk_count<T, B>(k, threadIdx.x & 63, br.s0, tilde, gamma, coef, nr_cap, rowptr, col,
+                          slot_row, deg, Yg + br.buf * ystride, csg + bi * 64, tau, nr);
+  };
+  if constexpr (kTurns) {
+    for (int64_t k = static_cast<int64_t>(rowptr[c0]) + first; k < end; k += wgs * kWavesPerBlock)
+      count(static_cast<int>(k));
+  } else {
+    const int k = rowptr[c0] + first;
+    if (k < end) count(k);
+  }
 }
 
 // walk pairs and single-walk steps of each block's slots into work[stride * block]:
@@ -921,11 +944,20 @@ hipError_t launch_walk_counts(const DeviceGraph& g, const BlockList& blocks, int
                               hipStream_t st) {
   const int slots = max_slots(blocks);
   if (slots == 0) return hipSuccess;
-  const SliceGrid sg = tail_grid(blocks, B, sizeof(T), static_cast<int>(grid_for(slots, kWavesPerBlock)), true);
-  SC_DISPATCH_B(B, (k_walk_counts<T, kB><<<sg.size(), kThreads, 0, st>>>(
-                        sg, blocks, g.n, tilde, gamma, coef, static_cast<long long>(nr_cap),
-                        g.rowptr, g.col, g.slot_row, g.deg, Y, ystride, ts.cs, tau_slot,
-                        reinterpret_cast<long long*>(nr_slot))));
+  const int64_t waves = grid_for(slots, kWavesPerBlock);
+  const SliceGrid sg = tail_grid(blocks, B, sizeof(T),
+                                 static_cast<int>(std::min<int64_t>(waves, kCountBlocks)), true);
+  auto launch = [&](auto kernel) {
+    kernel<<<sg.size(), kThreads, 0, st>>>(sg, blocks, g.n, tilde, gamma, coef,
+                                           static_cast<long long>(nr_cap), g.rowptr, g.col,
+                                           g.slot_row, g.deg, Y, ystride, ts.cs, tau_slot,
+                                           reinterpret_cast<long long*>(nr_slot));
+  };
+  if (waves > kCountBlocks) {
+    SC_DISPATCH_B(B, (launch(k_walk_counts<T, kB, true>)));
+  } else {
+    SC_DISPATCH_B(B, (launch(k_walk_counts<T, kB, false>)));
+  }
   return hipGetLastError();
 }
 
