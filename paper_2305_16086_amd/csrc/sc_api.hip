@@ -1314,7 +1314,6 @@ int build_slice_lists(sc_graph* g, hipStream_t st) {
       }
     d.nslice_grp = ngrp;
     auto up = [&](auto** dst, const auto& src) -> hipError_t {
-      if (*dst) return hipSuccess;
       hipError_t e = dev_alloc(dst, src.size());
       if (e == hipSuccess && !src.empty())
         e = hipMemcpyAsync(*dst, src.data(), src.size() * sizeof(src[0]), hipMemcpyHostToDevice, st);
@@ -1330,8 +1329,13 @@ int build_slice_lists(sc_graph* g, hipStream_t st) {
       d.slice_nb = nb;
       e = launch_fill_slices(d, st);
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(st);   // the host arrays end here
-    if (e != hipSuccess) {
+    const hipError_t done = hipStreamSynchronize(st);   // the host arrays end here
+    if (e == hipSuccess) e = done;
+    if (e != hipSuccess) {   // nothing is kept: a later call finds all of it or none
+      dev_free(d.slice_grp);
+      dev_free(d.slice_row);
+      dev_free(d.slice_inv_f);
+      dev_free(d.slice_inv_d);
       dev_free(d.slice_nb);
       return fail(e == hipErrorOutOfMemory ? SC_ENOMEM : SC_EHIP,
                   std::string("neighbour lists: ") + hipGetErrorString(e));

@@ -7,7 +7,7 @@ through the library's limits, and compared with the usual ones.  Every variant a
 neighbours in slot order, so sums, recordings and walk counts are equal.  Sizes: those
 of the group and slice bookkeeping, rows around the chunk, light and heavy lengths, a
 row cut into chunks (above 4,096 neighbours), hubs first (blocks with more half-edges
-than the graph has nodes), a complete graph.
+than the graph has nodes), complete graphs of light and of heavy rows only.
 """
 import os
 
@@ -37,6 +37,7 @@ GRAPHS = {
     "giant row": lambda: hub_graph(4700, 1, 4),
     "hubs first": lambda: hub_graph(700, 70, 5),
     "complete": lambda: gg.complete_graph(129),
+    "heavy rows only": lambda: gg.complete_graph(261),
 }
 
 
