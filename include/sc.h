@@ -327,7 +327,8 @@ int sc_all_edges_ex(sc_graph* g, double eps, int L, const sc_options* o, double*
  * Graphs whose buffers do not fit the array (about 20 bytes per half-edge plus
  * 24 bytes per node and workgroup slot) are refused with SC_EINVAL.  The array
  * is shared by every call on a GPU and keeps the last call's contents: calls
- * that overlap on one GPU race.  No memory is allocated; fills are kernels.
+ * that overlap on one GPU race.  No memory is allocated; fills are kernels.  A call
+ * may be recorded into a graph (st NULL) and replayed between other calls.
  */
 int sc_all_edges_static(sc_graph* g, double eps, int L, const sc_options* o, double* out,
                         sc_stats* st);

@@ -518,6 +518,9 @@ struct Layout {
   bool clean = false;
 };
 Layout g_scratch_last[kMaxDevices];
+// A call was recorded into a graph: its replays can leave anything in the array at any
+// time, so no later run on that device relies on it
+bool g_scratch_recorded[kMaxDevices];
 
 size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 
@@ -612,8 +615,13 @@ extern "C" int sc_all_edges_static(sc_graph* g, double eps, int L, const sc_opti
   SrcBufs B;
   carve(base, n, S2, W, wave_positions(n, W, nullptr, g->rowptr_h), &B);
   // the columns are cleared unless the last run on this GPU finished with the same layout
+  // (a recorded call clears them in every replay)
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
+  if (capture != hipStreamCaptureStatusNone) g_scratch_recorded[g->device] = true;
   Layout& last = g_scratch_last[g->device];
-  B.Q_clean = last.clean && last.n == n && last.slots == S2 && last.W == W;
+  B.Q_clean = !g_scratch_recorded[g->device] && last.clean && last.n == n && last.slots == S2 &&
+              last.W == W;
   last = Layout{n, S2, W, false};
   const auto host0 = std::chrono::steady_clock::now();
   rc = enqueue_per_source(g, eps, L, *o, lam, B, n, nullptr, out, o->tau_out, o->nr_out, stream);
