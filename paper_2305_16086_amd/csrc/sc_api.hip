@@ -1084,7 +1084,8 @@ extern "C" int sc_compute_spectrum(sc_graph* g, int omega, int max_iter, double 
   if (cur != g->device) (void)hipSetDevice(g->device);
   int kept = 0;
   double worst = 0.0;
-  const int rc = sc::lanczos_spectrum(g, omega, max_iter, tol, nullptr, &kept, &worst);
+  const int rc = sc::no_throw(
+      [&] { return sc::lanczos_spectrum(g, omega, max_iter, tol, nullptr, &kept, &worst); });
   if (cur != g->device) (void)hipSetDevice(cur);
   if (rc) return rc;
   if (omega_kept) *omega_kept = kept;
@@ -1177,7 +1178,7 @@ extern "C" int sc_get_spectrum(const sc_graph* g, int* omega, double* lambda, do
 
 extern "C" int sc_lambda_star(sc_graph* g, double* lam) {
   if (!g || !lam) return fail(SC_EINVAL, "NULL argument");
-  return sc::graph_lambda_star(g, nullptr, lam);
+  return sc::no_throw([&] { return sc::graph_lambda_star(g, nullptr, lam); });
 }
 
 extern "C" int sc_walk_trace(sc_graph* g, int32_t i, int32_t j, int64_t r, int32_t length,
@@ -1937,18 +1938,16 @@ extern "C" int sc_all_edges_ex(sc_graph* g, double eps, int L, const sc_options*
   if (per_source && opt.method != SC_TGT_PLUS)
     return fail(SC_ENOTIMPL, "SC_PER_SOURCE runs TGT+ (method 1) only");
   if (opt.sources && !per_source) return fail(SC_EINVAL, "a source list needs SC_PER_SOURCE");
-  int rc;
-  if (per_source)
-    rc = sc::run_per_source(g, eps, L, opt, out, st);
-  else if (opt.method == SC_LEARNED)
-    rc = sc::run_learned(g, eps, opt, out, st);
-  else
-    rc = sc::with_smaller_groups(
+  const int rc = sc::no_throw([&] {
+    if (per_source) return sc::run_per_source(g, eps, L, opt, out, st);
+    if (opt.method == SC_LEARNED) return sc::run_learned(g, eps, opt, out, st);
+    return sc::with_smaller_groups(
         g, opt.block > 0 ? opt.block : 64, opt.precision == 1 ? sizeof(double) : sizeof(float),
         static_cast<hipStream_t>(opt.stream), [&] {
           return opt.precision == 1 ? run_method<double>(g, eps, L, opt, out, st)
                                     : run_method<float>(g, eps, L, opt, out, st);
         });
+  });
   if (cur != g->device) (void)hipSetDevice(cur);
   return rc;
 }

@@ -5,6 +5,8 @@
 #include "sc_internal.hpp"
 
 #include <algorithm>
+#include <new>
+#include <stdexcept>
 #include <string>
 #include <vector>
 
@@ -66,6 +68,18 @@ struct PipeLayout {
   uint64_t buffer_bytes = kBufferBytes;
   int bufs() const { return sets * group; }
 };
+
+// f(), with host memory that runs out reported as SC_ENOMEM: no exception leaves an entry
+// point.  Device work enqueued before it uses buffers that the handle keeps.
+template <typename F>
+int no_throw(F f) {
+  try {
+    return f();
+  } catch (const std::bad_alloc&) {
+  } catch (const std::length_error&) {   // a vector beyond its own limit
+  }
+  return fail(SC_ENOMEM, "host allocation failed");
+}
 
 // runs f when the scope ends (releases buffers on every return path)
 template <typename F>

@@ -216,9 +216,16 @@ extern "C" int sc_mlp_train(sc_mlp* net, const float* X, const float* z, const f
   // The samples in the order of epoch ep.  Every order but the first is made while the
   // device trains on the one before (200,003 samples, two epochs: 2.8 -> 2.3 ms).
   std::vector<int64_t> order[2];
+  std::vector<float> losses;
+  const int64_t steps = (N + t.batch - 1) / t.batch;
+  rc = sc::no_throw([&] {   // all host memory before the device starts
+    for (int q = 0; q < std::min(t.epochs, 2); ++q) order[q].resize(N);
+    losses.resize(steps);
+    return SC_OK;
+  });
+  if (rc) return rc;
   auto shuffle = [&](int ep) {
     std::vector<int64_t>& perm = order[ep & 1];
-    perm.resize(N);
     for (int64_t i = 0; i < N; ++i) perm[i] = i;
     uint64_t s = t.seed + 0x1000193ull * static_cast<uint64_t>(ep + 1);
     for (int64_t i = N - 1; i > 0; --i) {
@@ -226,8 +233,6 @@ extern "C" int sc_mlp_train(sc_mlp* net, const float* X, const float* z, const f
       std::swap(perm[i], perm[j]);
     }
   };
-  const int64_t steps = (N + t.batch - 1) / t.batch;
-  std::vector<float> losses(steps);
   if (t.epochs > 0) shuffle(0);
   for (int ep = 0; ep < t.epochs; ++ep) {
     HIP_TRY(hipMemcpyAsync(net->idx, order[ep & 1].data(), N * sizeof(int64_t),
