@@ -1256,13 +1256,16 @@ PipeLayout pipe_layout(const sc_graph* g, int B, size_t tsize, int sets) {
   group = std::min<int64_t>({group, nblocks, kMaxGroup});
   if (g->group_limit > 0)
     group = std::min<int64_t>(group, std::max<int64_t>(1, g->group_limit / (2 * yb)));
-  // whole rounds of the 8 XCDs (a block is tsize / 2 slices when B = 64), or a count of
-  // slices that divides them: 3 blocks of 2 slices would leave two XCDs idle (BA n =
-  // 600,000, k = 2: TGT L = 3 940 ms with 3 blocks, 774 with 4; TGT+ 2,792 with 3, 2,385
-  // with 2)
-  const int64_t unit = std::max<int64_t>(1, 16 / static_cast<int64_t>(tsize));
-  if (group > unit && group < nblocks) group = group / unit * unit;
-  while (group < unit && group < nblocks && unit % group) --group;
+  // Where steps go by slices: whole rounds of the 8 XCDs (a block is tsize / 2 slices when
+  // B = 64), or a count of slices that divides them, since the 6 slices of 3 blocks would
+  // leave two XCDs idle (BA n = 600,000, k = 2, by slices: TGT L = 3 940 ms with 3 blocks,
+  // 774 with 4; TGT+ 2,792 with 3, 2,385 with 2).  Steps by whole rows take any count (TGT+
+  // 1,954 ms with 2 blocks, 1,828 with 3; n = 300,000, k = 3, L = 5: 580 with 4, 559 with 6).
+  if (n <= l.bitmap_nodes) {
+    const int64_t unit = std::max<int64_t>(1, 16 / static_cast<int64_t>(tsize));
+    if (group > unit && group < nblocks) group = group / unit * unit;
+    while (group < unit && group < nblocks && unit % group) --group;
+  }
   l.group = static_cast<int>(group);
   l.tail_group = static_cast<int>(std::min<int64_t>(
       group, std::max<int64_t>(1, static_cast<int64_t>(kTailBytes / col_scratch_bytes(col_parts(n))))));
