@@ -275,9 +275,15 @@ int sc_all_edges(sc_graph* g, double eps, int L, double* out);
  * SC_COST_TAIL_PER_NODE, SC_COST_WALK_STEP and SC_COST_OVERLAP override the
  * constants of the switch-step cost model (bytes/s, s, fraction of a dense
  * step, s, s per node, s per walk step, share);
- * SC_WALK_CHUNK_CAPACITY caps the
- * walk chunk-sum buffer when it is first allocated (blocks whose walks do not
- * fit then walk one slot per wave; used by the tests).
+ * SC_WALK_CHUNK_CAPACITY caps the walk chunk-sum buffer when it is first
+ * allocated (the blocks of a launch share it in order; one whose chunk sums would
+ * end beyond it walks one slot per wave; used by the tests), and
+ * SC_STEP_BITMAP_NODES and SC_STEP_BUFFER_BYTES lower the graph size and the state
+ * size from which a dense step takes its variants for large graphs (tests; the
+ * results are the same).
+ * Where device memory is short (or SC_DEVICE_BYTES_LIMIT, a budget in bytes for
+ * all the library holds, is) the call works with smaller groups of blocks, down
+ * to one, before it returns SC_ENOMEM; the results are the same.
  */
 int sc_all_edges_ex(sc_graph* g, double eps, int L, const sc_options* o, double* out,
                     sc_stats* st);

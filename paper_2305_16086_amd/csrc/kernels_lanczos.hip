@@ -12,7 +12,10 @@
 // chunk's w stays in LDS within a launch.  Up to some 30,000 nodes a step is bound by
 // its launches' chains of dependent loads, beyond by the four reads of V (n = 10,007, 260
 // steps of two runs: 42 us a step, of it 27 in k_lz_orth; 380 with a launch per vector
-// operation and a copy to the host for each dot product).
+// operation and a copy to the host for each dot product).  A chunk has at most 2,048
+// rows, so above 262,144 nodes their number grows, and with its square the reads of the
+// parts in k_lz_orth (from the L2s; a column's parts are 0.73 of its rows' bytes at 3 M
+// nodes, 2.4 times them at 10 M).  BA n = 1,000,000: 1.8 s in all, 5.2 before.
 #include "sc_internal.hpp"
 
 namespace sc {

@@ -1505,8 +1505,12 @@ using sc::Runner;
 // Switch-step cost model.  The traversal of a block runs on the critical
 // stream, its tail (candidate summary, walk counts, walks) on the tail stream,
 // so a block costs about max(traversal, tail) plus an interference share of
-// the shorter one.  Constants are whole-GPU rates measured on MI355X; the
-// environment can override them for tuning.
+// the shorter one.  Constants are whole-GPU rates measured on MI355X with one
+// block per launch; a block of a group takes less of each, in about the same
+// proportions, and the choice (which the results depend on) has stayed the best
+// one (BA n = 100,000, eps = 1e-3, ms with switch steps 3, 4, 5, 6: 439, 174, 223,
+// 294, 4 chosen; G(n, m) n = 10,000 with 3, 4, 5: 2.09, 2.69, 2.02, 5 chosen).
+// The environment can override them for tuning.
 struct CostModel {
   double gather_bw;     // bytes/s of neighbour-row gathers in a dense step
   double step_fixed;    // s of fixed cost per dense step

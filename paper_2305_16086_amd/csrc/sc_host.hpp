@@ -49,9 +49,9 @@ void dev_free(P*& p) {
 // k_step).  TGT+ overlaps the tails of a group with the traversal of the next on a
 // second stream, the groups alternating between kPipeSets sets of states.  A group
 // takes states (two per block) of up to kGroupBytes, but at least kMinGroup blocks where
-// the states of all sets fit kPipeBudgetBytes (BA, TGT+, ms per call with 2, 4, 8, 16
-// blocks: n = 100,000 210, 200, 190, 187; TGT n = 34,401 45.2, 36.8, 34.5, 34.6 and 36.7
-// with 32; G(n, m) n = 10,000 with 4, 8, 16, 32: 3.37, 2.89, 2.69, 2.62).
+// the states of all sets fit kPipeBudgetBytes (ms per call with 2, 4, 8, 16 and 32 blocks:
+// BA TGT+ n = 100,000 199, 187, 175, 178, 173; TGT n = 34,401 44.7, 32.1, 28.6, 28.4, 29.9;
+// G(n, m) TGT+ n = 10,000 3.86, 2.84, 2.30, 2.06, 1.98).
 constexpr int kPipeSets = 2;
 constexpr int kMinGroup = 8;
 constexpr size_t kGroupBytes = size_t(160) << 20;
