@@ -33,9 +33,9 @@ GOLDEN = os.path.join(ROOT, "tests", "golden", "ba_100k_seed1_sampled_sc.npz")
 # from the FETCH_SIZE / WRITE_SIZE counters, scaled by kernels of known traffic
 # (profiles/hbm_ba100k_k_step.md); valid only for the
 # kernel sources they were taken on (first 16 hex digits of the SHA-256 of the files in order)
-PROP_TRAFFIC_BYTES = 2733679290
+PROP_TRAFFIC_BYTES = 2733745169
 PROP_TRAFFIC_SOURCE = (("paper_2305_16086_amd/csrc/kernels_tgt.hip",
-                        "paper_2305_16086_amd/csrc/accumulate.hpp"), "7ea66baf6ffeeb73")
+                        "paper_2305_16086_amd/csrc/accumulate.hpp"), "581ac62cb4b7dac9")
 
 
 # Fabric bytes per single-walk step of the per-source walk kernel on R-MAT scale 22 with the
@@ -44,7 +44,7 @@ PROP_TRAFFIC_SOURCE = (("paper_2305_16086_amd/csrc/kernels_tgt.hip",
 WALK_TRAFFIC_BYTES_PER_STEP = 198.0
 WALK_TRAFFIC_SOURCE = (("paper_2305_16086_amd/csrc/kernels_sparse.hip",
                         "paper_2305_16086_amd/csrc/walk.hpp",
-                        "paper_2305_16086_amd/csrc/philox.hpp"), "37ce90cc64018fdf")
+                        "paper_2305_16086_amd/csrc/philox.hpp"), "99744ab8c189b7d3")
 
 
 def node_order_flag(sc, order):
