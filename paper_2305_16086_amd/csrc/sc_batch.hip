@@ -758,9 +758,11 @@ extern "C" int sc_batch_all_edges(sc_batch* b, double eps, const int32_t* L,
   if (!b || !o || !out) return fail(SC_EINVAL, "NULL argument");
   for (size_t gi = 0; gi < b->graphs.size(); ++gi)
     if (!out[gi]) return fail(SC_EINVAL, "NULL output pointer");
-  std::vector<int> all(b->graphs.size());
-  std::iota(all.begin(), all.end(), 0);
-  return run_dispatch(b, eps, L, *o, all, nullptr, nullptr, out, st, nullptr);
+  return sc::no_throw([&] {
+    std::vector<int> all(b->graphs.size());
+    std::iota(all.begin(), all.end(), 0);
+    return run_dispatch(b, eps, L, *o, all, nullptr, nullptr, out, st, nullptr);
+  });
 }
 
 // ---------------------------------------------------------------------- autotuner

@@ -613,8 +613,10 @@ extern "C" int sc_closure_features(sc_graph* g, int precision, float* X, double*
                                    double* lo, double* hi, void* stream) {
   if (!g || !X) return fail(SC_EINVAL, "bad arguments");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  int rc = precision == 1 ? closure_features_t<double>(g, st, X, s0, uK, lo, hi)
+  const int rc = sc::no_throw([&] {
+    return precision == 1 ? closure_features_t<double>(g, st, X, s0, uK, lo, hi)
                           : closure_features_t<float>(g, st, X, s0, uK, lo, hi);
+  });
   if (rc) return rc;
   HIP_TRY(hipStreamSynchronize(st));
   return SC_OK;
@@ -624,6 +626,8 @@ extern "C" int sc_closure_dataset(sc_graph* g, int L_ref, int precision, float* 
                                   float* w, void* stream) {
   if (!g || !X || !z || L_ref < sc::kRecSteps) return fail(SC_EINVAL, "bad arguments");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  return precision == 1 ? dataset_t<double>(g, L_ref, st, X, z, w)
-                        : dataset_t<float>(g, L_ref, st, X, z, w);
+  return sc::no_throw([&] {
+    return precision == 1 ? dataset_t<double>(g, L_ref, st, X, z, w)
+                          : dataset_t<float>(g, L_ref, st, X, z, w);
+  });
 }
